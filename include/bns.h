@@ -285,6 +285,9 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *                    sums of the current one are exchanged: 1..6 that (block size, vectors) variant whatever
  *                    the shape, 16 never; 0: when the launch has three or more rounds (tensors below 4 GiB)
  *   "fused_team"     blocks that share a channel in that kernel, if they can hold it    (1..128)
+ *   "grouped"        the single-launch kernels that take groups of adjacent channels (N x C x H x W, small planes): 2 never,
+ *                    1 whenever a group fits a block, 3..6 that block size; 0: where they are faster
+ *   "grouped_channels"  channels per group in those kernels, if they can hold them (1..64)
  *   "fused_coop"     1: launch the fused kernels with hipLaunchCooperativeKernel
  *   "fused_patch_mask"  Feature Sampling forward: by default, when one block holds a channel, the statistics of
  *                    the patch come from the vectors already in registers, under a column mask (built for the
@@ -332,8 +335,8 @@ bns_status bns_set_option(const char* name, int32_t value);
  * "last_path_forward" / "last_path_backward": 1 if this thread's last bns_forward / bns_backward took the streaming kernels, 2 if the fused one, 3 if the
  * one-launch kernel for small N x H x W x C tensors, 4 (backward, N x H x W x C) the streaming kernels with dx split
  * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx"); "last_fused_backward": which fused backward kernel that was
- * (1 plain, 2 x kept in registers, 3 pipelined); "last_fused_forward": 2 if the fused forward kernel took the
- * statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was
+ * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels); "last_fused_forward": 3 if groups of channels,
+ * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was
  * loaded, modulo 2^31 (benchmarks report launches per call from its differences).
  * -1 for an unknown name. */
 int32_t bns_get_option(const char* name);

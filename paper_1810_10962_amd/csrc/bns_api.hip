@@ -69,6 +69,8 @@ const TuningEntry kTuningTable[] = {
     {"fused_variant", &Tuning::fused_variant, 7, 0, false},
     {"fused_pipe", &Tuning::fused_pipe, 16, 0, false},
     {"fused_team", &Tuning::fused_team, 128, 0, false},
+    {"grouped", &Tuning::grouped, 6, 0, false},
+    {"grouped_channels", &Tuning::grouped_channels, 64, 0, false},
     {"fused_coop", &Tuning::fused_coop, 1, 0, false},
     {"test_spin_limit", &Tuning::test_spin_limit, 1 << 21, 0, false},
     {"test_mute_exchange", &Tuning::test_mute_exchange, 1, 0, false},

@@ -630,6 +630,23 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     const int opt_variant = g_tuning.fused_variant, opt_keep_x = g_tuning.fused_keep_x, opt_pipe = g_tuning.fused_pipe;
     const int opt_team = g_tuning.fused_team, opt_path = g_tuning.path, opt_coop = g_tuning.fused_coop;
     const int opt_masked = g_tuning.fused_patch_mask;
+    // Small planes: a block per group of channels (bns_grouped.hip), unless a kernel of this file or a part of the
+    // tensor is asked for.  Backward whenever a group fits a block, forward when planes are no whole number of vectors.
+    // Measured, us, against the kernels of this file: 64x2048x7x7 bf16 38.5 -> 10.6 and 26.3 -> 12.3 (forward, backward);
+    // 64x1024x14x14 f32 backward 39.3 -> 32.9, bf16 20.8 -> 13.5 and 25.5 -> 18.0; 32x512x13x13 f32 9.6 -> 9.0 and
+    // 13.8 -> 10.1.  Forward with whole vectors is 0.4 us slower at 128x64x8x8 and 8x512x14x14, 4 us at 64x512x28x28 bf16
+    // (a channel in one block of 50 vectors per thread), and faster only where this file's kernels need several rounds
+    // (64x1024x14x14 f32: 25.0 -> 21.0): see below.
+    const bool groups = cg == d.C && opt_variant == 0 && opt_keep_x == 0 && opt_pipe == 0 && opt_masked == 0;
+    auto grouped = [&]() {
+        const hipError_t ge = launch_grouped(d, ip, backward, io, eps, momentum, st, mix);
+        if (ge == hipSuccess) (backward ? t_last_fused_backward : t_last_fused_forward) = backward ? 4 : 3;
+        return ge;
+    };
+    if (groups && (backward || d.vec == 1 || g_tuning.grouped != 0)) {
+        const hipError_t ge = grouped();
+        if (ge != hipErrorNotSupported) return ge;
+    }
     int devid = 0;
     hipError_t e = hipGetDevice(&devid);
     if (e != hipSuccess) return e;
@@ -744,6 +761,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
             Plan p;
             if ((e = plan_for(kTwoPerUnit, &p)) != hipSuccess) return e;
             if (p.v >= 0) chosen = p;
+        }
+        // several rounds: groups of channels, if they fit, take one
+        if (groups && !backward && (chosen.v < 0 || chosen.rounds > 1)) {
+            const hipError_t ge = grouped();
+            if (ge != hipErrorNotSupported) return ge;
         }
         // (Eq. 4 has no such alternative: its streaming forward is four launches)
         if (chosen.v >= 0 && !backward && !everything && chosen.rounds > 1 && opt_path != 2 && !mix)

@@ -24,10 +24,11 @@ namespace bns {
 
 // Kernels launched by the library since it was loaded ("launch_count" option: benchmarks report launches per call).
 extern std::atomic<uint32_t> g_launch_count;
-// Which single-launch backward kernel the calling thread's last fused backward call took: 1 plain, 2 x kept in registers, 3 pipelined.
+// Which single-launch backward kernel the calling thread's last fused backward call took: 1 plain, 2 x kept in registers, 3 pipelined,
+// 4 groups of channels.
 extern thread_local int32_t t_last_fused_backward;
 // Which flavour the calling thread's last fused forward call took: 1 plain or patch elements read on their own,
-// 2 patch statistics from the registers.
+// 2 patch statistics from the registers, 3 groups of channels.
 extern thread_local int32_t t_last_fused_forward;
 
 constexpr int kMaxSplits = 64;  // upper bound on blocks that share one channel's reduction
@@ -54,6 +55,9 @@ struct Tuning {
     TuneInt fused_pipe{0};                  // backward: 1..n forces variant n of the pipelined kernel, 16: never
     TuneInt fused_team{0};                  // blocks per team of the pipelined kernel, if the channel fits (0: planner)
     TuneInt fused_patch_mask{0};            // forward, patch: statistics from the registers 1 = whenever built, 2 = never, 0 = when a block holds its channel alone
+    TuneInt grouped{0};                     // kernels that take groups of channels (small planes): 2 never, 0 when they are faster,
+                                            // 1 whenever they fit, 3.. variant 0..
+    TuneInt grouped_channels{0};            // channels per group, if that fits
     TuneInt fused_coop{0};                  // 1: launch the fused kernels with hipLaunchCooperativeKernel
     TuneInt split_statistics{0};            // 1: forward statistics always as partial sums + finalize
     TuneInt nhwc_blocks{0};                 // blocks an N x H x W x C reduction aims for (default kNhwcBlocks)
@@ -156,6 +160,10 @@ struct FusedMix {
 hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps,
                         float momentum, void* header, void* slots, size_t slot_bytes, int c0, int cg, hipStream_t st,
                         const FusedMix* mix = nullptr, bool order_streams = true);
+// The same for small planes, a block per group of channels (bns_grouped.hip): nothing crosses blocks.
+// hipErrorNotSupported: a group does not fit a block, or the other kernels are faster.
+hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
+                          hipStream_t st, const FusedMix* mix = nullptr);
 // Reads the count of waits that ran out from a workspace header (0 if the header was never set up) and clears it.
 hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 

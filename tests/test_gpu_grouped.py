@@ -1,0 +1,80 @@
+"""The single-launch kernels that take groups of channels (small planes): group sizes, runs that end in a shared vector,
+a last group of fewer channels, every block size, both directions -- each against the oracle and, where x holds
+infinities and NaNs outside S, against the streaming kernels."""
+import numpy as np
+import pytest
+
+from paper_1810_10962_amd import bns, workloads
+from paper_1810_10962_amd.workloads import BS, FS, FULL, NS, Workload
+from parity import assert_parity, oracle_reference
+
+pytestmark = pytest.mark.gpu
+
+
+def _forced(wl, inp, variant, channels):
+    opts = {"path": 2, "grouped": variant, "grouped_channels": channels}
+    try:
+        for k, v in opts.items():
+            bns.bns_set_option(k, v)
+        res = bns.run_workload(wl, inp)
+        took = (bns.bns_get_option("last_fused_forward"), bns.bns_get_option("last_fused_backward"))
+    finally:
+        for k in opts:
+            bns.bns_set_option(k, 0)
+    return res, took
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,variant,channels", [
+    ((5, 7, 2, 4), 1, 64),          # planes of one vector (bf16) or two, all channels in one group
+    ((64, 20, 7, 7), 1, 8),         # whole vectors per run; the last group has 4 channels
+    ((64, 19, 7, 7), 1, 3),         # runs that end in a shared vector; one channel left for the last group
+    ((9, 33, 3, 3), 3, 5),          # planes of nine elements: a vector spans two channels almost everywhere
+    ((40, 6, 14, 14), 5, 1),        # 512 threads, 8 vectors
+    ((100, 3, 15, 13), 6, 2),       # 512 threads, 16 vectors, more rows than one pass takes
+    ((1, 65, 5, 5), 4, 64),         # one sample
+    ((33, 130, 4, 4), 1, 0),        # the planner's own group
+])
+def test_groups_of_channels(shape, variant, channels, dtype):
+    N, C_, H, W = shape
+    modes = [dict(mode=FULL), dict(mode=BS, n_s=max(1, N // 3)), dict(mode=FS, patch_h=max(1, H - 1), patch_w=max(1, W // 2)),
+             dict(mode=FS, patch_h=1, patch_w=W, fs_per_channel=1)]
+    if N >= 4:
+        modes += [dict(mode=FS, patch_h=1, patch_w=2, n_v=2, mix_beta=0.3), dict(mode=NS, n_s=1, n_v=1)]
+    for i, mkw in enumerate(modes):
+        wl = Workload(name="grouped", N=N, C=C_, H=H, W=W, dtype=dtype, data_seed=40 + i, sampling_seed=17, layer_id=i,
+                      epoch=2, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] grouped {shape} {dtype} {mkw} variant {variant} channels {channels}", flush=True)
+        res, took = _forced(wl, inp, variant, channels)
+        assert took == (3, 4)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"grouped {shape} {dtype} {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_what_lies_outside_s_does_not_reach_the_statistics(dtype):
+    """Infinities and NaNs outside S: the statistics, and y and dx of the other elements, are those of the streaming
+    kernels (which never read x outside S for them)."""
+    wl = Workload(name="grouped_nan", N=12, C=21, H=7, W=7, dtype=dtype, mode=FS, patch_h=3, patch_w=4, data_seed=3,
+                  sampling_seed=5, layer_id=1)
+    inp = workloads.make_inputs(wl)
+    box = bns.bns_sample_index(bns.make_shape(wl.N, wl.C, wl.H, wl.W), bns.make_spec(FS, 0, 3, 4, 0, 1, 0), 5)[0]
+    outside = np.ones((wl.H, wl.W), dtype=bool)
+    outside[box[2]:box[2] + box[3], box[4]:box[4] + box[5]] = False
+    h, w = np.argwhere(outside)[0], np.argwhere(outside)[-1]
+    inp["x"][:, 0::2, h[0], h[1]] = np.nan
+    inp["x"][:, 1::4, w[0], w[1]] = np.inf
+    got, took = _forced(wl, inp, 1, 8)
+    assert took == (3, 4)
+    bns.bns_set_option("path", 1)
+    try:
+        want = bns.run_workload(wl, inp)
+    finally:
+        bns.bns_set_option("path", 0)
+    assert np.isfinite(got["save_mean"]).all() and np.isfinite(got["save_invstd"]).all()
+    for k in ("y", "dx", "dgamma", "dbeta", "save_mean", "save_invstd"):
+        assert (np.isfinite(got[k]) == np.isfinite(want[k])).all(), k
+        ok = np.isfinite(want[k])
+        # the same numbers up to the order of a few hundred 32-bit additions, and one rounding to 8 bits for bf16
+        tol = 2e-5 if dtype == "f32" or k not in ("y", "dx") else 1e-2
+        assert np.allclose(got[k][ok], want[k][ok], rtol=tol, atol=tol), k
