@@ -49,13 +49,15 @@ def default_path_kernels(wl, dirs, bns):
     """Names of the kernels one default forward + backward launches for this workload (as in the counter table)."""
     pre = "nhwc_" if wl.layout == "nhwc" else ""
     grouped = bns.bns_get_option("last_fused_forward") == 3
-    fwd = {"fused": ["grouped_forward_kernel" if grouped else "fused_forward_kernel"], "one-launch": [pre + "small_forward_kernel"],
+    fwd = {"fused": [pre + ("grouped_forward_kernel" if grouped and not pre else "fused_forward_kernel")],
+           "one-launch": [pre + "fused_forward_kernel"],
            "streaming": ([pre + "stats_partial_kernel", pre + "stats_finalize_kernel"] if wl.layout == "nhwc" else
                          ["stats_one_block_kernel"]) + [pre + "normalize_kernel"]}[dirs["forward_path"]]
     fused_bwd = {1: "fused_backward_kernel", 2: "fused_backward_kernel", 3: "fused_backward_pipe_kernel",
                  4: "grouped_backward_kernel"}
-    bwd = {"fused": [fused_bwd.get(bns.bns_get_option("last_fused_backward"), "fused_backward_kernel")],
-           "one-launch": [pre + "small_backward_kernel"],
+    bwd = {"fused": [pre + "fused_backward_kernel" if pre else
+                     fused_bwd.get(bns.bns_get_option("last_fused_backward"), "fused_backward_kernel")],
+           "one-launch": [pre + "fused_backward_kernel"],
            "streaming": [pre + "reduce_partial_kernel", pre + "reduce_finalize_kernel", pre + "dx_kernel"],
            # N x H x W x C: dx outside S written by the reduction kernel, the rows of S by a kernel of their own
            "streaming-split": ["nhwc_reduce_outside_kernel", "nhwc_reduce_finalize_kernel", "nhwc_dx_rows_kernel"],

@@ -279,7 +279,7 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *                    launches per direction); 2: only the fused single-launch kernels, which keep a
  *                    channel in registers between its reduction and its element-wise pass
  *                    (BNS_EUNSUPPORTED if a channel does not fit or the layout is N x H x W x C, which has
- *                    none); 0: whichever is faster for the shape
+ *                    none of these); 0: whichever is faster for the shape
  *   "fused_variant"  1..7: block size / registers-per-thread variant of the fused kernels
  *   "fused_pipe"     the backward kernel that holds two channels per block, loading the next one while the
  *                    sums of the current one are exchanged: 1..6 that (block size, vectors) variant whatever
@@ -303,6 +303,10 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "splits_reduce"  blocks per channel in the backward reduction                (1..64)
  *   "channel_group"  the streaming path walks the channels in groups of this many, every stage on
  *                    one group before the next                                   (1..C)
+ *   "nhwc_fused"     the single-launch N x H x W x C kernels: 1 whenever they can run, 2 never; 0: few rows, or tensors beyond
+ *                    4 MB that fit the registers about once.  Kernels whose blocks wait for each other (see Concurrency) are
+ *                    not used while the stream is being captured in this layout, nor with "path" = 1
+ *   "nhwc_fused_lanes"  128-bit accesses per row of a block's column tile in them  (1..32)
  *   "nhwc_blocks"    blocks that an N x H x W x C reduction launch aims for      (1..8192)
  *   "nhwc_ew_rows"   rows per thread in the N x H x W x C element-wise kernels   (1..2^20)
  *   "nhwc_split_dx"  1: the N x H x W x C backward writes dx on the rows outside S from its reduction kernel (Eq. 6
@@ -312,8 +316,7 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *                    (Eq. 1; Eq. 6) reads again without the non-temporal hint, so that it stays in the device's
  *                    memory-side cache: 1 all of it, 2 none; 0: as much as fits there (224 MB).  Results do not
  *                    depend on it.
- *   "nhwc_small"     2: small N x H x W x C tensors also take the streaming kernels (by default one launch
- *                    per direction does everything when a thread would walk at most 16 rows)
+ *   "nhwc_small"     2: N x H x W x C tensors of every size take the streaming kernels
  *   "norm_unroll", "dx_unroll", "reduce_unroll"   128-bit accesses per thread    (1, 2, 4)
  *   "norm_nt", "dx_nt"   non-temporal access mask + 1: bit 0 loads, bit 1 stores
  *   "reduce_nt"      the same for the backward reduction: bit 0 loads of x, bit 1 loads of dy, for the channels
@@ -332,8 +335,8 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  * launch (the stamps that tell one exchange from the next are counted in the workspace, on the device). */
 bns_status bns_set_option(const char* name, int32_t value);
 /* Current value of an option (as set, 0 = automatic); also, kept per calling thread,
- * "last_path_forward" / "last_path_backward": 1 if this thread's last bns_forward / bns_backward took the streaming kernels, 2 if the fused one, 3 if the
- * one-launch kernel for small N x H x W x C tensors, 4 (backward, N x H x W x C) the streaming kernels with dx split
+ * "last_path_forward" / "last_path_backward": 1 if this thread's last bns_forward / bns_backward took the streaming kernels, 2 if the fused one, 3 if a
+ * one-launch N x H x W x C kernel whose blocks do not wait for each other (few rows), 4 (backward, N x H x W x C) the streaming kernels with dx split
  * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx"); "last_fused_backward": which fused backward kernel that was
  * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels); "last_fused_forward": 3 if groups of channels,
  * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was

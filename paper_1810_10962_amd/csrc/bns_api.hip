@@ -25,7 +25,7 @@ std::atomic<int32_t> g_splits_stats{0};
 std::atomic<int32_t> g_splits_reduce{0};
 std::atomic<int32_t> g_channel_group{0};
 // What the calling thread's last forward / backward call launched: 1 = streaming kernels,
-// 2 = fused single-launch kernel, 3 = one-launch kernel for small N x H x W x C tensors, 4 = streaming kernels with dx
+// 2 = fused single-launch kernel, 3 = one-launch N x H x W x C kernel without waits between blocks, 4 = streaming kernels with dx
 // split between the reduction kernel (rows outside S) and a kernel for the rows of S (N x H x W x C).
 thread_local int32_t t_last_path_forward = 0;
 thread_local int32_t t_last_path_backward = 0;
@@ -78,6 +78,8 @@ const TuningEntry kTuningTable[] = {
     {"fused_patch_mask", &Tuning::fused_patch_mask, 2, 0, false},
     {"split_statistics", &Tuning::split_statistics, 1, 0, false},
     {"nhwc_blocks", &Tuning::nhwc_blocks, kNhwcBlocksMax, 0, false},
+    {"nhwc_fused", &Tuning::nhwc_fused, 2, 0, false},
+    {"nhwc_fused_lanes", &Tuning::nhwc_fused_lanes, 32, 0, false},
     {"nhwc_ew_rows", &Tuning::nhwc_ew_rows, 1 << 20, 0, false},
     {"nhwc_small", &Tuning::nhwc_small, 2, 0, false},
     {"nhwc_split_dx", &Tuning::nhwc_split_dx, 2, 0, false},
@@ -124,6 +126,47 @@ bns_status reduce_range(const Dims& d, const void* x, const void* dy, const floa
     const int splits = reduce_splits(d, cg);
     if (launch_reduce_partial(d, x, dy, save_mean, ws, splits, c0, cg, x_again, st) != hipSuccess) return BNS_EDEVICE;
     return dev(launch_reduce_finalize(d, ws, splits, c0, cg, save_invstd, dgamma, dbeta, st));
+}
+
+FusedIo forward_io(const void* x, void* y, const float* gamma, const float* beta, float* save_mean, float* save_invstd,
+                   float* running_mean, float* running_var) {
+    FusedIo io;
+    io.x = x;
+    io.out = y;
+    io.gamma = gamma;
+    io.beta = beta;
+    io.save_mean = save_mean;
+    io.save_invstd = save_invstd;
+    io.running_mean = running_mean;
+    io.running_var = running_var;
+    return io;
+}
+
+FusedIo backward_io(const void* x, const void* dy, void* dx, const float* gamma, const float* save_mean,
+                    const float* save_invstd, float* dgamma, float* dbeta) {
+    FusedIo io;
+    io.x = x;
+    io.dy = dy;
+    io.out = dx;
+    io.gamma = gamma;
+    io.save_mean = const_cast<float*>(save_mean);
+    io.save_invstd = const_cast<float*>(save_invstd);
+    io.dgamma = dgamma;
+    io.dbeta = dbeta;
+    return io;
+}
+
+// N x H x W x C: the whole direction in one launch, if the tensor is for it; *status is then the call's result.  The exchange
+// slots lie where the streaming kernels keep their partial sums.
+bool nhwc_single_launch(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
+                        void* workspace, hipStream_t st, const FusedMix* mix, bool order_streams, bns_status* status) {
+    bool solo = false;
+    const hipError_t e = launch_nhwc_fused(d, ip, backward, io, eps, momentum, workspace, partials_of(workspace),
+                                           2 * nhwc_partial_bytes(d), st, mix, order_streams, g_tuning.path != 1, &solo);
+    if (e == hipErrorNotSupported) return false;
+    (backward ? t_last_path_backward : t_last_path_forward) = solo ? 3 : 2;
+    *status = dev(e);
+    return true;
 }
 
 }  // namespace
@@ -238,12 +281,8 @@ bns_status bns_forward(const bns_shape* shape, const bns_spec* spec, uint64_t se
     Partial* ws = partials_of(workspace);
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
-        hipError_t se = hipSuccess;
-        if (launch_nhwc_small_forward(d, ip.shared, x, gamma, beta, eps, momentum, y, save_mean, save_invstd, running_mean,
-                                      running_var, st, &se)) {
-            t_last_path_forward = 3;
-            return dev(se);
-        }
+        const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
+        if (nhwc_single_launch(d, ip, false, io, eps, momentum, workspace, st, nullptr, true, &s)) return s;
         t_last_path_forward = 1;
         if (launch_nhwc_stats(d, ip.shared, x, ws, eps, momentum, save_mean, save_invstd, running_mean, running_var,
                               st) != hipSuccess)
@@ -251,15 +290,7 @@ bns_status bns_forward(const bns_shape* shape, const bns_spec* spec, uint64_t se
         return dev(launch_nhwc_normalize(d, x, gamma, beta, save_mean, save_invstd, y, st));
     }
     if (g_tuning.path != 1) {
-        FusedIo io;
-        io.x = x;
-        io.out = y;
-        io.gamma = gamma;
-        io.beta = beta;
-        io.save_mean = save_mean;
-        io.save_invstd = save_invstd;
-        io.running_mean = running_mean;
-        io.running_var = running_var;
+        const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
         const hipError_t fe = launch_fused(d, ip, false, io, eps, momentum,
                                            workspace, slots_of(workspace, d), kSlotBytes, 0, d.C, st);
         if (fe == hipSuccess) {
@@ -351,11 +382,9 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
                          uint64_t(d.N) * uint64_t(d.HW);
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
-        hipError_t se = hipSuccess;
-        if (launch_nhwc_small_backward(d, ip.shared, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, st, &se)) {
-            t_last_path_backward = 3;
-            return dev(se);
-        }
+        const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
+        if (g_tuning.nhwc_split_dx == 0 && nhwc_single_launch(d, ip, true, io, 0.f, 0.f, workspace, st, nullptr, order_streams, &s))
+            return s;
         t_last_path_backward = 1;
         // Eq. 6 outside S needs none of the sums: the reduction kernel can write dx there while it has dy in
         // registers, which leaves only the rows of S for after the sums and saves one read of dy from memory.  Only on
@@ -370,15 +399,7 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
         return dev(launch_nhwc_dx(d, ip.shared, x, dy, gamma, save_mean, save_invstd, dgamma, dbeta, dx, st));
     }
     if (g_tuning.path != 1) {
-        FusedIo io;
-        io.x = x;
-        io.dy = dy;
-        io.out = dx;
-        io.gamma = gamma;
-        io.save_mean = const_cast<float*>(save_mean);
-        io.save_invstd = const_cast<float*>(save_invstd);
-        io.dgamma = dgamma;
-        io.dbeta = dbeta;
+        const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
         const hipError_t fe = launch_fused(d, ip, true, io, 0.f, 0.f, workspace, slots_of(workspace, d),
                                            kSlotBytes, 0, d.C, st, nullptr, order_streams);
         if (fe == hipSuccess) {
@@ -487,6 +508,12 @@ bns_status bns_forward_mixed(const bns_shape* shape, const bns_spec* spec, uint6
     const IndexParams ip_s = make_index_params_mixed(*shape, *spec, seed, n_v);
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
+        FusedMix mix;
+        mix.n_v = n_v;
+        mix.mix_beta = mix_beta;
+        mix.mean_parts = save_mean_parts;
+        const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
+        if (nhwc_single_launch(d, ip_s, false, io, eps, momentum, workspace, st, &mix, true, &s)) return s;
         t_last_path_forward = 1;
         if (launch_nhwc_stats_mixed(d, ip_s.shared, n_v, x, partials_of(workspace), mix_beta, eps, momentum,
                                     save_mean, save_invstd, save_mean_parts, running_mean, running_var, st) != hipSuccess)
@@ -494,15 +521,7 @@ bns_status bns_forward_mixed(const bns_shape* shape, const bns_spec* spec, uint6
         return dev(launch_nhwc_normalize(d, x, gamma, beta, save_mean, save_invstd, y, st));
     }
     if (g_tuning.path != 1) {
-        FusedIo io;
-        io.x = x;
-        io.out = y;
-        io.gamma = gamma;
-        io.beta = beta;
-        io.save_mean = save_mean;
-        io.save_invstd = save_invstd;
-        io.running_mean = running_mean;
-        io.running_var = running_var;
+        const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
         FusedMix mix;
         mix.n_v = n_v;
         mix.mix_beta = mix_beta;
@@ -549,6 +568,12 @@ bns_status bns_backward_mixed(const bns_shape* shape, const bns_spec* spec, uint
     const IndexParams ip_s = make_index_params_mixed(*shape, *spec, seed, n_v);
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
+        FusedMix mix;
+        mix.n_v = n_v;
+        mix.mix_beta = mix_beta;
+        mix.mean_parts = const_cast<float*>(save_mean_parts);
+        const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
+        if (nhwc_single_launch(d, ip_s, true, io, 0.f, 0.f, workspace, st, &mix, true, &s)) return s;
         t_last_path_backward = 1;
         if (launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, partials_of(workspace), dgamma, dbeta, false, st) !=
             hipSuccess)
@@ -557,15 +582,7 @@ bns_status bns_backward_mixed(const bns_shape* shape, const bns_spec* spec, uint
                                         save_mean_parts, dx, st));
     }
     if (g_tuning.path != 1) {
-        FusedIo io;
-        io.x = x;
-        io.dy = dy;
-        io.out = dx;
-        io.gamma = gamma;
-        io.save_mean = const_cast<float*>(save_mean);
-        io.save_invstd = const_cast<float*>(save_invstd);
-        io.dgamma = dgamma;
-        io.dbeta = dbeta;
+        const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
         FusedMix mix;
         mix.n_v = n_v;
         mix.mix_beta = mix_beta;

@@ -621,6 +621,79 @@ hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired) {
     return hipStreamSynchronize(st);
 }
 
+namespace {
+// The current device's entry of g_dev (the caller holds g_dev_mutex).
+hipError_t current_device(DeviceInfo** out) {
+    int devid = 0;
+    hipError_t e = hipGetDevice(&devid);
+    if (e != hipSuccess) return e;
+    if (devid < 0 || devid >= 16) return hipErrorNotSupported;
+    DeviceInfo& di = g_dev[devid];
+    if (di.cus == 0) {
+        int cus = 0, coop = 0;
+        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid)) != hipSuccess) return e;
+        if ((e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, devid)) != hipSuccess) return e;
+        di.coop = coop;
+        di.cus = cus;
+    }
+    *out = &di;
+    return hipSuccess;
+}
+
+// Kernels whose blocks wait for each other must not share the device with one another: two of them, each with
+// part of its grid resident, would wait for blocks that the other keeps out.  Within a process they are therefore
+// chained across streams: when such a launch goes to another stream than the one before it, an event is
+// recorded on that earlier stream (behind the earlier launch) and the new stream waits for it.  A caller that
+// stays on one stream pays nothing.  Not while a stream is being captured (the event would belong to the
+// graph); a graph that holds such launches must not run beside other calls.
+// *chain in: the launch waits and is to be ordered; out: it is not being captured (the caller then calls chain_launched).
+hipError_t chain_behind_last(DeviceInfo& di, hipStream_t st, bool* chain) {
+    if (*chain) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        *chain = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        (void)hipGetLastError();
+    }
+    if (*chain && di.chain_active && di.chain_stream != st) {
+        if (!di.chain_event && hipEventCreateWithFlags(&di.chain_event, hipEventDisableTiming) != hipSuccess)
+            di.chain_event = nullptr;
+        // (an earlier stream that has been destroyed meanwhile refuses the record: nothing is left to wait for)
+        hipError_t e;
+        if (di.chain_event && hipEventRecord(di.chain_event, di.chain_stream) == hipSuccess &&
+            (e = hipStreamWaitEvent(st, di.chain_event, 0)) != hipSuccess)
+            return e;
+        (void)hipGetLastError();
+    }
+    return hipSuccess;
+}
+void chain_launched(DeviceInfo& di, hipStream_t st) {
+    di.chain_active = true;
+    di.chain_stream = st;
+}
+}  // namespace
+
+hipError_t device_units(int* cus) {
+    std::lock_guard<std::mutex> lock(g_dev_mutex);
+    DeviceInfo* di = nullptr;
+    const hipError_t e = current_device(&di);
+    if (e == hipSuccess) *cus = di->cus;
+    return e;
+}
+
+uint32_t next_stamp_seed() { return g_stamp.fetch_add(1u); }
+
+hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool order_streams, hipStream_t st) {
+    std::lock_guard<std::mutex> lock(g_dev_mutex);
+    DeviceInfo* di = nullptr;
+    hipError_t e = current_device(&di);
+    if (e != hipSuccess) return e;
+    bool chain = waits && order_streams;
+    if ((e = chain_behind_last(*di, st, &chain)) != hipSuccess) return e;
+    g_launch_count.fetch_add(1, std::memory_order_relaxed);
+    e = hipLaunchKernel(kernel, grid, block, params, 0, st);
+    if (e == hipSuccess && chain) chain_launched(*di, st);
+    return e;
+}
+
 // Plans and launches one fused pass over channels [c0, c0 + cg).  Returns hipErrorNotSupported
 // when the channel does not fit on chip (the caller then takes the streaming kernels).
 hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps,
@@ -647,19 +720,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         const hipError_t ge = grouped();
         if (ge != hipErrorNotSupported) return ge;
     }
-    int devid = 0;
-    hipError_t e = hipGetDevice(&devid);
-    if (e != hipSuccess) return e;
-    if (devid < 0 || devid >= 16) return hipErrorNotSupported;
     std::lock_guard<std::mutex> lock(g_dev_mutex);      // planning only; released before the launch returns
-    DeviceInfo& di = g_dev[devid];
-    if (di.cus == 0) {
-        int cus = 0, coop = 0;
-        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, devid)) != hipSuccess) return e;
-        di.coop = coop;
-        di.cus = cus;
-    }
+    DeviceInfo* dip = nullptr;
+    hipError_t e = current_device(&dip);
+    if (e != hipSuccess) return e;
+    DeviceInfo& di = *dip;
     if (!di.coop || di.cus <= 0) return hipErrorNotSupported;
 
     const uint32_t hwv = uint32_t(d.HW / d.vec);
@@ -967,35 +1032,13 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     if (!backward) t_last_fused_forward = kernel == kernel_for(d, kind, best) ? 1 : 2;
     void* params[] = {&A};
 
-    // Kernels whose blocks wait for each other must not share the device with one another: two of them, each with
-    // part of its grid resident, would wait for blocks that the other keeps out.  Within a process they are therefore
-    // chained across streams: when such a launch goes to another stream than the one before it, an event is
-    // recorded on that earlier stream (behind the earlier launch) and the new stream waits for it.  A caller that
-    // stays on one stream pays nothing.  Not while a stream is being captured (the event would belong to the
-    // graph); a graph that holds such launches must not run beside other calls.
-    bool chain = false;
-    if (bestT > 1 && order_streams) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        chain = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-        (void)hipGetLastError();
-    }
-    if (chain && di.chain_active && di.chain_stream != st) {
-        if (!di.chain_event && hipEventCreateWithFlags(&di.chain_event, hipEventDisableTiming) != hipSuccess)
-            di.chain_event = nullptr;
-        // (an earlier stream that has been destroyed meanwhile refuses the record: nothing is left to wait for)
-        if (di.chain_event && hipEventRecord(di.chain_event, di.chain_stream) == hipSuccess &&
-            (e = hipStreamWaitEvent(st, di.chain_event, 0)) != hipSuccess)
-            return e;
-        (void)hipGetLastError();
-    }
+    bool chain = bestT > 1 && order_streams;
+    if ((e = chain_behind_last(di, st, &chain)) != hipSuccess) return e;
     g_launch_count.fetch_add(1, std::memory_order_relaxed);
     if (backward) t_last_fused_backward = pipe_kernel ? 3 : (kind & 2) ? 2 : 1;
     e = opt_coop ? hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(launch_nt), params, 0, st)
                             : hipLaunchKernel(kernel, dim3(grid), dim3(launch_nt), params, 0, st);
-    if (e == hipSuccess && chain) {
-        di.chain_active = true;
-        di.chain_stream = st;
-    }
+    if (e == hipSuccess && chain) chain_launched(di, st);
     return e;
 }
 

@@ -62,6 +62,8 @@ struct Tuning {
     TuneInt split_statistics{0};            // 1: forward statistics always as partial sums + finalize
     TuneInt nhwc_blocks{0};                 // blocks an N x H x W x C reduction aims for (default kNhwcBlocks)
     TuneInt nhwc_small{0};                  // 2: never take the one-launch kernels for small N x H x W x C tensors
+    TuneInt nhwc_fused{0};                  // single-launch kernels of this layout: 1 whenever they fit, 2 never, 0 from a size on
+    TuneInt nhwc_fused_lanes{0};            // column vectors of a tile in those kernels
     TuneInt nhwc_ew_rows{0};                // rows per row lane in its element-wise kernels (default kNhwcEwRows)
     TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always, 2 never, 0 when S is at most half
     // For the library's own tests of the give-up path only; a caller has no use for them.
@@ -167,6 +169,19 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
 // Reads the count of waits that ran out from a workspace header (0 if the header was never set up) and clears it.
 hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 
+// N x H x W x C (bns_nhwc_fused.hip): one launch per direction.  hipErrorNotSupported: not for this size (or, if blocks
+// would have to wait for each other, not while capturing or without may_wait).  *solo: no block waits for another.
+hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
+                             void* header, void* slots, size_t slot_bytes, hipStream_t st, const FusedMix* mix,
+                             bool order_streams, bool may_wait, bool* solo);
+constexpr size_t kNhwcFusedBytes = size_t(4) << 20;     // larger tensors take it; up to here whole calls give the bits of the stage calls
+
+// What the single-launch kernels share (bns_fused.hip): compute units of the current device; a start for the exchange
+// stamps; a launch that is chained, across streams, behind the last one whose blocks wait for each other (waits).
+hipError_t device_units(int* cus);
+uint32_t next_stamp_seed();
+hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool order_streams, hipStream_t st);
+
 hipError_t launch_index_boxes(const IndexParams& ip, int C, bns_box* boxes, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 
@@ -180,7 +195,6 @@ constexpr int kNhwcFill = 2048;        // fewest blocks an element-wise launch a
 constexpr int kNhwcBlocksMax = 8192;   // largest value the "nhwc_blocks" override takes
 constexpr int kNhwcEwRows = 4;         // rows per row lane and block in the element-wise kernels
 constexpr int kNhwcMaxSplits = 2048;   // upper bound on blocks that share one channel's reduction
-constexpr int kNhwcSmallRows = 16;     // rows per row lane up to which one block walks all rows of its channels
 constexpr int kNhwcMaxLaneRows = 1024; // rows one thread accumulates in fp32 before the sums are combined
 size_t nhwc_partial_bytes(const Dims& d);
 hipError_t launch_nhwc_stats(const Dims& d, const bns_box& b, const void* x, Partial* partial, float eps, float momentum,
@@ -207,12 +221,5 @@ hipError_t launch_nhwc_stats_mixed(const Dims& d, const bns_box& b, int n_v, con
 hipError_t launch_nhwc_dx_mixed(const Dims& d, const bns_box& b, int n_v, float mix_beta, const void* x, const void* dy,
                                 const float* gamma, const float* invstd, const float* dgamma, const float* dbeta,
                                 const float* mean_parts, void* dx, hipStream_t st);
-// Whole forward / backward in one launch for small tensors; false (nothing launched) when the tensor is not small.
-bool launch_nhwc_small_forward(const Dims& d, const bns_box& b, const void* x, const float* gamma, const float* beta,
-                               float eps, float momentum, void* y, float* save_mean, float* save_invstd,
-                               float* running_mean, float* running_var, hipStream_t st, hipError_t* err);
-bool launch_nhwc_small_backward(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
-                                const float* mean, const float* invstd, void* dx, float* dgamma, float* dbeta,
-                                hipStream_t st, hipError_t* err);
 
 }  // namespace bns

@@ -1,0 +1,121 @@
+"""The single-launch kernels of the N x H x W x C layout: column tiles whose last vector is shared, fewer channels than a
+vector, every number of rows per thread, rows that do not fit the registers, Eq. 4 -- each against the oracle; the
+give-up path of their exchange; and that they stay out of HIP graphs."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1810_10962_amd import bns, workloads
+from paper_1810_10962_amd.workloads import BS, FS, FULL, NS, Workload
+from parity import assert_parity, oracle_reference
+
+pytestmark = pytest.mark.gpu
+
+
+def _with(opts, call):
+    try:
+        for k, v in opts.items():
+            bns.bns_set_option(k, v)
+        return call()
+    finally:
+        for k in opts:
+            bns.bns_set_option(k, 0)
+
+
+def _paths():
+    return bns.bns_get_option("last_path_forward"), bns.bns_get_option("last_path_backward")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,lanes", [
+    ((3, 3, 9, 9), 0),              # fewer channels than a vector
+    ((4, 9, 20, 20), 0),            # a vector and a channel: the second vector shares seven (three) channels with the first
+    ((4, 41, 20, 20), 5),           # a last tile of one lane is avoided
+    ((2, 150, 19, 19), 8),          # tiles of unequal width, rows at odd multiples of two bytes
+    ((7, 64, 33, 31), 4),           # many members per tile, a ragged last share of the rows
+    ((30, 520, 12, 12), 0),         # more tiles than fit a row of lanes
+    ((1, 8, 1, 70), 0),             # hardly more rows than row lanes
+])
+def test_single_launch_nhwc(shape, lanes, dtype):
+    N, C_, H, W = shape
+    modes = [dict(mode=FULL), dict(mode=BS, n_s=max(1, N // 3)), dict(mode=FS, patch_h=max(1, H // 2), patch_w=max(1, W - 3))]
+    if N >= 3:
+        modes += [dict(mode=FS, patch_h=1, patch_w=2, n_v=2, mix_beta=0.3), dict(mode=NS, n_s=1, n_v=1)]
+    for i, mkw in enumerate(modes):
+        wl = Workload(name="nhwc_fused", N=N, C=C_, H=H, W=W, dtype=dtype, layout="nhwc", data_seed=50 + i, sampling_seed=18,
+                      layer_id=i, epoch=1, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch {shape} {dtype} {mkw} lanes {lanes}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": lanes}, lambda: bns.run_workload(wl, inp))
+        assert _paths() in ((2, 2), (3, 3))                 # (3: so few rows that one block takes them all)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"nhwc fused {shape} {dtype} {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rounds", [5, 9, 17, 45])
+def test_rows_per_thread(rounds, dtype):
+    """5, 9: the next larger number of kept rows; 17: x is no longer kept; 45: rows that do not fit the registers."""
+    V = 4 if dtype == "f32" else 8
+    C_ = 128 * V                                            # 16 tiles of 8 lanes on 256 compute units: 16 members of 64 rows
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 64 * (units // 16) * (rounds - 1) + 37
+    for i, mkw in enumerate((dict(mode=FULL), dict(mode=BS, n_s=1), dict(mode=FS, patch_h=1, patch_w=5, n_v=1))):
+        wl = Workload(name="rows", N=3, C=C_, H=1, W=rows // 3, dtype=dtype, layout="nhwc", data_seed=60 + i, sampling_seed=3,
+                      layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch, {rounds} rows per thread {wl.shape} {dtype} {mkw}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
+        assert _paths() == (2, 2)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
+
+
+def test_missing_team_mate_and_what_comes_after():
+    wl = Workload(name="nhwc_give_up", N=9, C=70, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=3, data_seed=5,
+                  sampling_seed=6, layer_id=1)
+    inp = workloads.make_inputs(wl)
+    buf = bns.Buffers(wl, inp)
+    print("[gpu-case] nhwc single launch, give-up path", flush=True)
+
+    def both():
+        buf.forward()
+        buf.backward()
+        assert _paths() == (2, 2)
+        return buf.results(), bns.bns_expired_waits(buf.workspace)
+
+    bad, expired_bad = _with({"nhwc_fused": 1, "test_spin_limit": 64, "test_mute_exchange": 1}, both)
+    good, expired_good = _with({"nhwc_fused": 1}, both)
+    for k in ("y", "save_mean", "save_invstd", "dx", "dgamma", "dbeta"):
+        assert np.isnan(bad[k]).all(), f"{k}: finite values after a wait that expired"
+    for k in ("running_mean", "running_var"):
+        assert np.array_equal(bad[k], inp[k].astype(np.float32)), k
+    assert expired_bad > 0 and expired_good == 0
+    assert_parity(good, oracle_reference(wl, inp), wl, what="after the give-up run", inp=inp)
+
+
+def test_a_captured_call_takes_the_streaming_kernels():
+    wl = Workload(name="nhwc_graph", N=20, C=64, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=4, data_seed=7,
+                  sampling_seed=8, layer_id=2)
+    inp = workloads.make_inputs(wl)
+    ref = oracle_reference(wl, inp)
+    buf = bns.Buffers(wl, inp)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        buf.forward()
+        buf.backward()
+        assert _paths() == (2, 2)                           # (8 MB: single launch outside a graph)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        buf.forward()
+        buf.backward()
+    assert _paths() == (1, 1)
+    for _ in range(3):
+        buf.running_mean.copy_(torch.from_numpy(inp["running_mean"]))
+        buf.running_var.copy_(torch.from_numpy(inp["running_var"]))
+        buf.y.fill_(float("nan"))
+        buf.dx.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        assert_parity(buf.results(), ref, wl, what="replay", inp=inp)
