@@ -90,15 +90,15 @@ int stats_splits(const Dims& d, const IndexParams& ip, int cg) {
     const int32_t o = g_splits_stats.load();
     if (o > 0) return o;
     const bns_box& b = ip.shared;
-    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && d.vec > 1;
+    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
     const uint64_t pts = uint64_t(b.n_cnt) * b.h_cnt * b.w_cnt;
-    return auto_splits(cg, uint32_t(planes ? pts / d.vec : pts / 4));
+    return auto_splits(cg, uint32_t(planes ? pts / stream_vec(d) : pts / 4));
 }
 
 int reduce_splits(const Dims& d, int cg) {
     const int32_t o = g_splits_reduce.load();
     if (o > 0) return o;
-    return auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / d.vec));
+    return auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / stream_vec(d)));
 }
 
 int channel_group(const Dims& d) {

@@ -147,8 +147,68 @@ struct Vec<bf16_t, 8> {
     }
 };
 
+// The same elements in planes that are no whole number of vectors (and so may start at any element): a plane then has
+// ceil(HW / V) vectors, accessed at element alignment, and the last one is moved back so that it ends with the plane.  The
+// elements it shares with the vector before it are left out of sums (the first `skip`) and written twice with the same bits.
+struct f32_odd {
+    float v;
+};
+struct bf16_odd {
+    uint16_t bits;
+};
+template <typename T>
+struct Odd {
+    static constexpr bool value = false;
+};
+template <>
+struct Odd<f32_odd> {
+    static constexpr bool value = true;
+};
+template <>
+struct Odd<bf16_odd> {
+    static constexpr bool value = true;
+};
+// First element, within its plane, of vector i of a plane of HW elements.
+template <typename T, int V>
+__device__ __forceinline__ uint32_t plane_offset(uint32_t i, int HW) {
+    return Odd<T>::value ? min(i * V, uint32_t(HW) - V) : i * V;
+}
+
+// Elements that vector i shares with the one before it.
+template <typename T, int V>
+__device__ __forceinline__ uint32_t shared_elements(uint32_t i, int HW) {
+    return i * V - plane_offset<T, V>(i, HW);
+}
+
+template <>
+struct Vec<f32_odd, 4> {
+    float f[4];
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    typedef v4 v4e __attribute__((aligned(4)));
+    __device__ __forceinline__ void set(v4 v) { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
+    __device__ __forceinline__ void load(const f32_odd* p) { set(*reinterpret_cast<const v4e*>(p)); }
+    __device__ __forceinline__ void load_nt(const f32_odd* p) { set(__builtin_nontemporal_load(reinterpret_cast<const v4e*>(p))); }
+    __device__ __forceinline__ void store(f32_odd* p) const { *reinterpret_cast<v4e*>(p) = v4{f[0], f[1], f[2], f[3]}; }
+    __device__ __forceinline__ void store_nt(f32_odd* p) const {
+        const v4 v = {f[0], f[1], f[2], f[3]};
+        __builtin_nontemporal_store(v, reinterpret_cast<v4e*>(p));
+    }
+};
+template <>
+struct Vec<bf16_odd, 8> : Vec<bf16_t, 8> {
+    typedef u4 u4e __attribute__((aligned(2)));
+    __device__ __forceinline__ void load(const bf16_odd* p) { unpack(*reinterpret_cast<const u4e*>(p)); }
+    __device__ __forceinline__ void load_nt(const bf16_odd* p) { unpack(__builtin_nontemporal_load(reinterpret_cast<const u4e*>(p))); }
+    __device__ __forceinline__ void store(bf16_odd* p) const { *reinterpret_cast<u4e*>(p) = pack(); }
+    __device__ __forceinline__ void store_nt(bf16_odd* p) const { __builtin_nontemporal_store(pack(), reinterpret_cast<u4e*>(p)); }
+};
+
 template <typename T>
 __device__ __forceinline__ float load_scalar(const T* p);
+template <>
+__device__ __forceinline__ float load_scalar<f32_odd>(const f32_odd* p) { return p->v; }
+template <>
+__device__ __forceinline__ float load_scalar<bf16_odd>(const bf16_odd* p) { return bf16_to_f32(p->bits); }
 template <>
 __device__ __forceinline__ float load_scalar<float>(const float* p) { return *p; }
 template <>

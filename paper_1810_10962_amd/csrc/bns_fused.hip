@@ -110,7 +110,7 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
             const uint32_t i = ia + uint32_t(k) * step;
             if (i < end) {
                 const uint32_t n = fdiv(i, A.hwv_div);
-                v[k] = RV::ld(xc + n * nstride + size_t(i - n * hwv) * V);
+                v[k] = RV::ld(xc + n * nstride + plane_offset<T, V>(i - n * hwv, A.HW));
             }
         }
         float s1 = 0.f, s2 = 0.f;
@@ -201,11 +201,12 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
                 if (i < end) {
                     const uint32_t n = fdiv(i, A.hwv_div);
                     if (n >= uint32_t(b.n0) && n < uint32_t(b.n0 + b.n_cnt)) {
+                        const uint32_t skip = shared_elements<T, V>(i - n * hwv, A.HW);
                         float f[V];
                         RV::unpack(v[k], f);
 #pragma unroll
                         for (int e = 0; e < V; ++e) {
-                            const float d = f[e] - pivot;
+                            const float d = Odd<T>::value && uint32_t(e) < skip ? 0.f : f[e] - pivot;
                             s1 += d;
                             s2 = fmaf(d, d, s2);
                         }
@@ -243,12 +244,14 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const uint32_t i = id + uint32_t(k) * step;
-                if (i < end && fdiv(i, A.hwv_div) < uint32_t(A.n_v)) {
+                const uint32_t n = fdiv(i, A.hwv_div);
+                if (i < end && n < uint32_t(A.n_v)) {
+                    const uint32_t skip = shared_elements<T, V>(i - n * hwv, A.HW);
                     float f[V];
                     RV::unpack(v[k], f);
 #pragma unroll
                     for (int e = 0; e < V; ++e) {
-                        const float d = f[e] - pivot_v;
+                        const float d = Odd<T>::value && uint32_t(e) < skip ? 0.f : f[e] - pivot_v;
                         v1 += d;
                         v2 = fmaf(d, d, v2);
                     }
@@ -306,7 +309,7 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
                 RV::unpack(v[k], f);
 #pragma unroll
                 for (int e = 0; e < V; ++e) f[e] = fmaf(f[e] - mu, sc, sh);
-                RV::st(yc + n * nstride + size_t(i - n * hwv) * V, RV::pack(f));
+                RV::st(yc + n * nstride + plane_offset<T, V>(i - n * hwv, A.HW), RV::pack(f));
             }
         }
     }
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
             const uint32_t i = ia + uint32_t(k) * step;
             if (i < end) {
                 const uint32_t n = fdiv(i, A.hwv_div);
-                g[k] = RV::ld(gc + n * nstride + size_t(i - n * hwv) * V);
+                g[k] = RV::ld(gc + n * nstride + plane_offset<T, V>(i - n * hwv, A.HW));
             }
         }
         float s1 = 0.f, s2 = 0.f;
@@ -373,18 +376,20 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
                 const uint32_t i = ib + uint32_t(k) * step;
                 if (i < end) {
                     const uint32_t n = fdiv(i, A.hwv_div);
-                    xk[k] = RV::ld(xc + n * nstride + size_t(i - n * hwv) * V);
+                    xk[k] = RV::ld(xc + n * nstride + plane_offset<T, V>(i - n * hwv, A.HW));
                 }
             }
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const uint32_t i = ib + uint32_t(k) * step;
                 if (i < end) {
+                    const uint32_t skip = Odd<T>::value ? shared_elements<T, V>(i - fdiv(i, A.hwv_div) * hwv, A.HW) : 0u;
                     float fg[V], fx[V];
                     RV::unpack(g[k], fg);
                     RV::unpack(xk[k], fx);
 #pragma unroll
                     for (int e = 0; e < V; ++e) {
+                        if (Odd<T>::value && uint32_t(e) < skip) continue;
                         s1 += fg[e];
                         s2 = fmaf(fg[e], fx[e] - mu, s2);
                     }
@@ -399,18 +404,20 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
                 const uint32_t i = ib + uint32_t(k0 + u) * step;
                 if (k0 + u < KMAX && i < end) {
                     const uint32_t n = fdiv(i, A.hwv_div);
-                    xv[u] = RV::ld(xc + n * nstride + size_t(i - n * hwv) * V);
+                    xv[u] = RV::ld(xc + n * nstride + plane_offset<T, V>(i - n * hwv, A.HW));
                 }
             }
 #pragma unroll
             for (int u = 0; u < XB; ++u) {
                 const uint32_t i = ib + uint32_t(k0 + u) * step;
                 if (k0 + u < KMAX && i < end) {
+                    const uint32_t skip = Odd<T>::value ? shared_elements<T, V>(i - fdiv(i, A.hwv_div) * hwv, A.HW) : 0u;
                     float fg[V], fx[V];
                     RV::unpack(g[k0 + u < KMAX ? k0 + u : 0], fg);
                     RV::unpack(xv[u], fx);
 #pragma unroll
                     for (int e = 0; e < V; ++e) {
+                        if (Odd<T>::value && uint32_t(e) < skip) continue;
                         s1 += fg[e];
                         s2 = fmaf(fg[e], fx[e] - mu, s2);
                     }
@@ -444,8 +451,7 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
             const uint32_t i = ic + uint32_t(k) * step;
             if (i < end) {
                 const uint32_t n = fdiv(i, A.hwv_div);
-                const uint32_t off = i - n * hwv;
-                const uint32_t e0 = off * V;
+                const uint32_t e0 = plane_offset<T, V>(i - n * hwv, A.HW);
                 float f[V];
                 opaque_raw(g[k]);
                 RV::unpack(g[k], f);
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
                         opaque_raw(xk[k]);
                         RV::unpack(xk[k], fx);
                     } else {
-                        RV::unpack(RV::ld(xc + n * nstride + size_t(off) * V), fx);
+                        RV::unpack(RV::ld(xc + n * nstride + e0), fx);
                     }
                     uint32_t h = fdiv(e0, A.w_div);
                     uint32_t w = e0 - h * uint32_t(A.W);
@@ -477,7 +483,7 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
 #pragma unroll
                     for (int e = 0; e < V; ++e) f[e] *= a;
                 }
-                RV::st(dc + n * nstride + size_t(off) * V, RV::pack(f));
+                RV::st(dc + n * nstride + e0, RV::pack(f));
             }
         }
     }
@@ -542,7 +548,12 @@ const void* kernel_ptr(int kind, int variant) {
     return nullptr;
 }
 
+// Planes that this file takes with element-aligned vectors (those of 4 bf16 elements keep their 64-bit accesses here).
+inline bool fused_odd(const Dims& d) { return d.vec == 1 && odd_planes(d); }
+
 const void* kernel_for(const Dims& d, int kind, int variant) {
+    if (fused_odd(d))
+        return d.dtype == BNS_F32 ? kernel_ptr<f32_odd, 4>(kind, variant) : kernel_ptr<bf16_odd, 8>(kind, variant);
     if (d.dtype == BNS_F32) return d.vec == 4 ? kernel_ptr<float, 4>(kind, variant) : kernel_ptr<float, 1>(kind, variant);
     if (d.vec == 8) return kernel_ptr<bf16_t, 8>(kind, variant);
     if (d.vec == 4) return kernel_ptr<bf16_t, 4>(kind, variant);
@@ -584,7 +595,7 @@ struct DeviceInfo {
     TeamChoice choices[kTeamChoices];
     int cus = 0;
     int coop = 0;
-    int blocks_per_cu[8][5][kNumVariants];  // [kernel kind][type/vec combo][variant], 0 = not queried yet
+    int blocks_per_cu[8][7][kNumVariants];  // [kernel kind][type/vec combo][variant], 0 = not queried yet
     int pipe_blocks_per_cu[5][kMaxPipeVariants];
     hipEvent_t chain_event = nullptr;       // orders launches whose blocks wait for each other across streams
     hipStream_t chain_stream = nullptr;     // the stream the last such launch went to
@@ -594,6 +605,7 @@ DeviceInfo g_dev[16];
 std::mutex g_dev_mutex;   // guards g_dev: launches may come from several host threads
 
 int combo_index(const Dims& d) {
+    if (fused_odd(d)) return d.dtype == BNS_F32 ? 5 : 6;
     if (d.dtype == BNS_F32) return d.vec == 4 ? 0 : 1;
     return d.vec == 8 ? 2 : d.vec == 4 ? 3 : 4;
 }
@@ -744,7 +756,8 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     DeviceInfo& di = *dip;
     if (!di.coop || di.cus <= 0) return hipErrorNotSupported;
 
-    const uint32_t hwv = uint32_t(d.HW / d.vec);
+    const int vec = fused_odd(d) ? stream_vec(d) : d.vec;
+    const uint32_t hwv = uint32_t((d.HW + vec - 1) / vec);
     const uint32_t tot = uint32_t(d.N) * hwv;
     const int combo = combo_index(d);
     int kind = (backward ? 1 : (ip.shared.h_cnt * ip.shared.w_cnt == d.HW ? 0 : 2)) | (mix ? 4 : 0);
@@ -865,6 +878,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
             const hipError_t ge = grouped();
             if (ge != hipErrorNotSupported) return ge;
         }
+        // A channel per block of 50 vectors per thread, a sampled S, and planes that are no whole number of vectors: statistics
+        // + Eq. 1 from the streaming kernels are faster (64x256x55x55 bf16: Batch Sampling 45.9 against 43.4 us, a patch, whose
+        // elements are then read on their own, 53.6 against 47.2).
+        if (!backward && !everything && chosen.v > kTwoPerUnit && chosen.T == 1 && fused_odd(d) && opt_path != 2 && !mix)
+            return hipErrorNotSupported;
         // (Eq. 4 has no such alternative: its streaming forward is four launches)
         if (chosen.v >= 0 && !backward && !everything && chosen.rounds > 1 && opt_path != 2 && !mix)
             return hipErrorNotSupported;
@@ -1010,9 +1028,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.ip = ip;
     A.hwv_div = make_fastdiv(hwv);
     A.w_div = make_fastdiv(uint32_t(d.W));
-    A.wv_div = make_fastdiv(uint32_t(d.W / d.vec > 0 ? d.W / d.vec : 1));       // used when W is a multiple of vec
+    A.wv_div = make_fastdiv(uint32_t(d.W / vec > 0 ? d.W / vec : 1));       // used when W is a multiple of vec
     A.patch_stage = 0;
-    A.rows_whole = d.W % d.vec == 0;
+    A.rows_whole = d.W % vec == 0;
     A.chw_div = make_fastdiv(uint32_t(d.C) * uint32_t(d.HW));       // C * HW < 2^31 (limits of bns_shape)
     A.C = d.C;
     A.W = d.W;

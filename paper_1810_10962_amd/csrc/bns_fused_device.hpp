@@ -83,6 +83,20 @@ struct RawVec<bf16_t, 8> {
     }
 };
 
+// Planes that are no whole number of vectors (see f32_odd): the same packed vectors, accessed at element alignment.
+template <>
+struct RawVec<f32_odd, 4> : RawVec<float, 4> {
+    typedef raw_t elem_t __attribute__((aligned(4)));
+    static __device__ __forceinline__ raw_t ld(const f32_odd* p) { return __builtin_nontemporal_load(reinterpret_cast<const elem_t*>(p)); }
+    static __device__ __forceinline__ void st(f32_odd* p, raw_t r) { __builtin_nontemporal_store(r, reinterpret_cast<elem_t*>(p)); }
+};
+template <>
+struct RawVec<bf16_odd, 8> : RawVec<bf16_t, 8> {
+    typedef raw_t elem_t __attribute__((aligned(2)));
+    static __device__ __forceinline__ raw_t ld(const bf16_odd* p) { return __builtin_nontemporal_load(reinterpret_cast<const elem_t*>(p)); }
+    static __device__ __forceinline__ void st(bf16_odd* p, raw_t r) { __builtin_nontemporal_store(r, reinterpret_cast<elem_t*>(p)); }
+};
+
 constexpr int kMaxTeam = 1024;            // members of a team (T)
 constexpr uint32_t kSpinLimit = 1u << 21; // polls before a missing team-mate is given up on (default)
 

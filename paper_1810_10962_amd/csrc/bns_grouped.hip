@@ -464,7 +464,15 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // Planes that are a whole number of vectors run well in the kernels of bns_fused.hip too: those keep the calls whose
     // few channels would fill only part of the device with large blocks (backward, us: 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12
     // bf16 8.5 against 8.9).
-    if (opt == 0 && unit == 1 && (d.C + best_g - 1) / best_g < 128 && best_v >= 2) return hipErrorNotSupported;
+    const int blocks = (d.C + best_g - 1) / best_g;
+    if (opt == 0 && unit == 1 && blocks < 128 && best_v >= 2) return hipErrorNotSupported;
+    // ... and those that would leave most of a last round of one block per compute unit empty (61x288x28x28 bf16 backward: 288
+    // blocks, the step 40.8 against 41.7 us).
+    if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > 256 && blocks % 256 != 0 && blocks % 256 < 128) return hipErrorNotSupported;
+    // Calls that take 5 us whatever they do: working out the columns costs more there than it saves (forward, us: 8x224x5x5 f32
+    // 4.8 against 5.4, 37x96x9x9 bf16 5.7 against 6.3; backward, 6x144x7x7 bf16 5.0 against 5.4).
+    const int64_t bytes = int64_t(d.N) * d.C * d.HW * (V == 8 ? 2 : 4);
+    if (opt == 0 && bytes < (backward ? (V == 8 ? 300000 : 0) : 1000000) && !mix) return hipErrorNotSupported;
     const GroupVariant gv = kGroupVariants[best_v];
     const uint32_t lanes = uint32_t((long(best_g) * d.HW + V - 1) / V);
     GroupArgs A;

@@ -31,6 +31,14 @@ extern thread_local int32_t t_last_fused_backward;
 // 2 patch statistics from the registers, 3 groups of channels.
 extern thread_local int32_t t_last_fused_forward;
 
+// Streaming kernels: planes that are no whole number of full-width vectors but hold at least one (see f32_odd in
+// bns_device.hpp), and the elements per access the streaming kernels take.
+inline bool odd_planes(const Dims& d) {
+    const int full = d.dtype == BNS_F32 ? 4 : 8;
+    return d.HW % full != 0 && d.HW >= full;
+}
+inline int stream_vec(const Dims& d) { return odd_planes(d) ? (d.dtype == BNS_F32 ? 4 : 8) : d.vec; }
+
 constexpr int kMaxSplits = 64;  // upper bound on blocks that share one channel's reduction
 
 

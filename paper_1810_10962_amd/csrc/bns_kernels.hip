@@ -50,29 +50,31 @@ __global__ __launch_bounds__(kBlock) void stats_partial_planes_kernel(
     uint32_t j = j0 + threadIdx.x;
     for (; j + 3u * kBlock < j1; j += 4u * kBlock) {
         Vec<T, V> v[4];
+        uint32_t skip[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t ju = j + u * kBlock;
-            const uint32_t n = fdiv(ju, hwv_div);
-            const T* p = base + n * nstride + size_t(ju - n * hwv) * V;
+            const uint32_t n = fdiv(ju, hwv_div), i = ju - n * hwv, off = plane_offset<T, V>(i, HW);
+            const T* p = base + n * nstride + off;
+            skip[u] = i * V - off;
             if (KEEP) v[u].load(p); else v[u].load_nt(p);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                const float dlt = v[u].f[i] - pivot;
+                const float dlt = Odd<T>::value && uint32_t(i) < skip[u] ? 0.f : v[u].f[i] - pivot;
                 s1[u & 1] += dlt;
                 s2[u & 1] = fmaf(dlt, dlt, s2[u & 1]);
             }
     }
     for (; j < j1; j += kBlock) {
-        const uint32_t n = fdiv(j, hwv_div);
+        const uint32_t n = fdiv(j, hwv_div), first = (j - n * hwv) * V, off = plane_offset<T, V>(j - n * hwv, HW);
         Vec<T, V> v;
-        v.load(base + n * nstride + size_t(j - n * hwv) * V);
+        v.load(base + n * nstride + off);
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-            const float dlt = v.f[i] - pivot;
+            const float dlt = Odd<T>::value && uint32_t(i) < first - off ? 0.f : v.f[i] - pivot;
             s1[0] += dlt;
             s2[0] = fmaf(dlt, dlt, s2[0]);
         }
@@ -148,12 +150,14 @@ __global__ __launch_bounds__(kOneBlock) void stats_one_block_kernel(
         constexpr int U = 8;                                   // all of a thread's loads in flight at once
         for (uint32_t j0 = threadIdx.x; j0 < tot; j0 += U * kOneBlock) {
             Vec<T, V> v[U];
+            uint32_t skip[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t j = j0 + u * kOneBlock;
                 if (j < tot) {
-                    const uint32_t n = fdiv(j, hwv_div);
-                    v[u].load(base + n * nstride + size_t(j - n * hwv) * V);   // (few points, read again by Eq. 1: plain)
+                    const uint32_t n = fdiv(j, hwv_div), i = j - n * hwv, off = plane_offset<T, V>(i, HW);
+                    skip[u] = i * V - off;
+                    v[u].load(base + n * nstride + off);                       // (few points, read again by Eq. 1: plain)
                 }
             }
 #pragma unroll
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(kOneBlock) void stats_one_block_kernel(
                 if (j < tot) {
 #pragma unroll
                     for (int i = 0; i < V; ++i) {
-                        const float dlt = v[u].f[i] - pivot;
+                        const float dlt = Odd<T>::value && uint32_t(i) < skip[u] ? 0.f : v[u].f[i] - pivot;
                         s1 += dlt;
                         s2 = fmaf(dlt, dlt, s2);
                     }
@@ -306,6 +310,14 @@ __global__ __launch_bounds__(kBlock) void stats_finalize_mixed_kernel(
 // ===========================================================================
 // Forward normalise + affine over every element (Eq. 1)
 // ===========================================================================
+// Vector vi of a sample's run of planes -> its first element.
+template <typename T, int V>
+__device__ __forceinline__ size_t run_offset(uint32_t vi, const FastDiv& hwv_div, int HW) {
+    if (!Odd<T>::value) return size_t(vi) * V;
+    const uint32_t c = fdiv(vi, hwv_div);
+    return size_t(c) * HW + plane_offset<T, V>(vi - c * hwv_div.d, HW);
+}
+
 // grid = (ceil(cg * HW / V / (kBlock * U)), N).  Block (bx, n) handles kBlock * U
 // consecutive vectors of the contiguous run [c0, c0 + cg) x HW of sample n.
 template <typename T, int V, int U, int NT>
@@ -319,6 +331,7 @@ __global__ __launch_bounds__(kBlock) void normalize_kernel(
     const T* xr = x + run0;
     T* yr = y + run0;
     const uint32_t v0 = blockIdx.x * uint32_t(kBlock * U) + threadIdx.x;
+    auto at = [&](uint32_t vi) { return run_offset<T, V>(vi, hwv_div, HW); };
 
     Vec<T, V> v[U];
     float mu[U], sc[U], sh[U];
@@ -326,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void normalize_kernel(
     for (int u = 0; u < U; ++u) {
         const uint32_t vi = v0 + u * kBlock;
         if (vi < run_vectors) {
-            if (NT & 1) v[u].load_nt(xr + size_t(vi) * V); else v[u].load(xr + size_t(vi) * V);
+            if (NT & 1) v[u].load_nt(xr + at(vi)); else v[u].load(xr + at(vi));
         }
     }
 #pragma unroll
@@ -348,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void normalize_kernel(
         if (vi < run_vectors) {
 #pragma unroll
             for (int i = 0; i < V; ++i) v[u].f[i] = fmaf(v[u].f[i] - mu[u], sc[u], sh[u]);
-            if (NT & 2) v[u].store_nt(yr + size_t(vi) * V); else v[u].store(yr + size_t(vi) * V);
+            if (NT & 2) v[u].store_nt(yr + at(vi)); else v[u].store(yr + at(vi));
         }
     }
 }
@@ -383,11 +396,13 @@ __global__ __launch_bounds__(kBlock) void reduce_partial_kernel(
         uint32_t j = j0 + threadIdx.x;
         for (; j + uint32_t(U - 1) * kBlock < j1; j += uint32_t(U) * kBlock) {
             Vec<T, V> g[U], v[U];
+            uint32_t skip[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t ju = j + u * kBlock;
-                const uint32_t n = fdiv(ju, hwv_div);
-                const size_t off = cbase + n * nstride + size_t(ju - n * hwv) * V;
+                const uint32_t n = fdiv(ju, hwv_div), i = ju - n * hwv, po = plane_offset<T, V>(i, HW);
+                const size_t off = cbase + n * nstride + po;
+                skip[u] = i * V - po;
                 if (M & 2) g[u].load_nt(dy + off); else g[u].load(dy + off);
                 if (M & 1) v[u].load_nt(x + off); else v[u].load(x + off);
             }
@@ -395,18 +410,20 @@ __global__ __launch_bounds__(kBlock) void reduce_partial_kernel(
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int i = 0; i < V; ++i) {
+                    if (Odd<T>::value && uint32_t(i) < skip[u]) continue;
                     s1[u] += g[u].f[i];
                     s2[u] = fmaf(g[u].f[i], v[u].f[i] - mu, s2[u]);
                 }
         }
         for (; j < j1; j += kBlock) {
-            const uint32_t n = fdiv(j, hwv_div);
-            const size_t off = cbase + n * nstride + size_t(j - n * hwv) * V;
+            const uint32_t n = fdiv(j, hwv_div), first = (j - n * hwv) * V, po = plane_offset<T, V>(j - n * hwv, HW);
+            const size_t off = cbase + n * nstride + po;
             Vec<T, V> g, v;
             g.load(dy + off);
             v.load(x + off);
 #pragma unroll
             for (int i = 0; i < V; ++i) {
+                if (Odd<T>::value && uint32_t(i) < first - po) continue;
                 s1[0] += g.f[i];
                 s2[0] = fmaf(g.f[i], v.f[i] - mu, s2[0]);
             }
@@ -469,13 +486,14 @@ __global__ __launch_bounds__(kBlock) void dx_kernel(
     T* dr = dx + run0;
     const uint32_t v0 = blockIdx.x * uint32_t(kBlock * U) + threadIdx.x;
     const uint32_t hwv = hwv_div.d;
+    auto at = [&](uint32_t vi) { return run_offset<T, V>(vi, hwv_div, HW); };
 
     Vec<T, V> g[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t vi = v0 + u * kBlock;
         if (vi < run_vectors) {
-            if (NT & 1) g[u].load_nt(gr + size_t(vi) * V); else g[u].load(gr + size_t(vi) * V);
+            if (NT & 1) g[u].load_nt(gr + at(vi)); else g[u].load(gr + at(vi));
         }
     }
 #pragma unroll
@@ -484,7 +502,7 @@ __global__ __launch_bounds__(kBlock) void dx_kernel(
         if (vi >= run_vectors) continue;
         const uint32_t cl = fdiv(vi, hwv_div);
         const int c = c0 + int(cl);
-        const uint32_t e0 = (vi - cl * hwv) * V;                  // first element, within its plane
+        const uint32_t e0 = plane_offset<T, V>(vi - cl * hwv, HW);   // first element, within its plane
         const bns_box b = virt ? bns_box{0, sets.n_v, 0, HW / W, 0, W} : box_of_channel(ip, c);
         const float r = invstd[c];
         const float a = gamma[c] * r;
@@ -493,7 +511,7 @@ __global__ __launch_bounds__(kBlock) void dx_kernel(
                              e0 < uint32_t(b.h0 + b.h_cnt) * W;
         if (touches) {
             Vec<T, V> xv;
-            if (NT & 1) xv.load_nt(xr + size_t(vi) * V); else xv.load(xr + size_t(vi) * V);
+            if (NT & 1) xv.load_nt(xr + at(vi)); else xv.load(xr + at(vi));
             const float mu = centre[c];
             const float k1 = a * wgt * dbeta[c];
             const float k2 = a * wgt * dgamma[c] * r;
@@ -514,7 +532,7 @@ __global__ __launch_bounds__(kBlock) void dx_kernel(
 #pragma unroll
             for (int i = 0; i < V; ++i) g[u].f[i] *= a;
         }
-        if (NT & 2) g[u].store_nt(dr + size_t(vi) * V); else g[u].store(dr + size_t(vi) * V);
+        if (NT & 2) g[u].store_nt(dr + at(vi)); else g[u].store(dr + at(vi));
     }
 }
 
@@ -579,6 +597,7 @@ hipError_t dispatch_unroll_nt(int U, int NT, F&& f) {
 
 template <typename F>
 hipError_t dispatch(const Dims& d, F&& f) {
+    if (odd_planes(d)) return d.dtype == BNS_F32 ? f(f32_odd(), VecTag<4>()) : f(bf16_odd(), VecTag<8>());
     if (d.dtype == BNS_F32) {
         if (d.vec == 4) return f(float(), VecTag<4>());
         return f(float(), VecTag<1>());
@@ -606,16 +625,16 @@ int auto_splits(int cg, uint32_t vectors_per_channel) {
 hipError_t launch_stats_partial(const Dims& d, const IndexParams& ip, const void* x, Partial* partial,
                                 int splits, int c0, int cg, hipStream_t st) {
     const bns_box& b = ip.shared;
-    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && d.vec > 1;
+    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
     const dim3 grid(uint32_t(cg) * uint32_t(splits));
     if (planes) {
         return dispatch(d, [&](auto t, auto vt) {
             using T = decltype(t);
             constexpr int V = decltype(vt)::value;
-            const uint32_t hwv = uint32_t(d.HW / V);
+            const uint32_t hwv = ceil_div(uint32_t(d.HW), V);
             const uint32_t tot = uint32_t(b.n_cnt) * hwv;
             const uint32_t per_block = ceil_div(tot, uint32_t(splits));
-            if (keep_for_next_pass(size_t(tot) * V * sizeof(T) * size_t(cg)))
+            if (keep_for_next_pass(size_t(b.n_cnt) * d.HW * sizeof(T) * size_t(cg)))
                 BNS_LAUNCH((stats_partial_planes_kernel<T, V, true>), grid, dim3(kBlock), 0, st,
                            static_cast<const T*>(x), partial, ip, d.C, d.HW, make_fastdiv(hwv), c0, splits,
                            per_block);
@@ -646,11 +665,11 @@ bool launch_stats_one_block(const Dims& d, const IndexParams& ip, const void* x,
                             float momentum, float* save_mean, float* save_invstd, float* running_mean,
                             float* running_var, hipStream_t st, hipError_t* err) {
     const bns_box& b = ip.shared;
-    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && d.vec > 1;
+    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
     const uint64_t pts = uint64_t(b.n_cnt) * b.h_cnt * b.w_cnt;
-    const uint64_t accesses = planes ? pts / d.vec : pts;
+    const uint64_t accesses = planes ? pts / stream_vec(d) : pts;
     if (accesses > uint64_t(kOneBlock) * 16 || cg < 64) return false;     // <= 16 accesses per thread; enough blocks
-    const uint32_t hwv = uint32_t(d.HW / d.vec);
+    const uint32_t hwv = ceil_div(uint32_t(d.HW), uint32_t(stream_vec(d)));
     const uint32_t patch = uint32_t(b.h_cnt) * uint32_t(b.w_cnt);
     const dim3 grid{uint32_t(cg)}, blk{uint32_t(kOneBlock)};
     *err = dispatch(d, [&](auto t, auto vt) {
@@ -712,7 +731,7 @@ hipError_t launch_normalize(const Dims& d, const void* x, const float* gamma, co
         return dispatch_unroll_nt(tuned(g_tuning.norm_unroll, d.dtype == BNS_F32 ? 1 : 2), tuned_nt(g_tuning.norm_nt, 3), [&](auto ut, auto nt) {
             constexpr int U = decltype(ut)::value;
             constexpr int NT = decltype(nt)::value;
-            const uint32_t hwv = uint32_t(d.HW / V);
+            const uint32_t hwv = ceil_div(uint32_t(d.HW), V);
             const uint32_t run_vectors = uint32_t(cg) * hwv;
             const dim3 grid(ceil_div(run_vectors, kBlock * U), uint32_t(d.N));
             BNS_LAUNCH((normalize_kernel<T, V, U, NT>), grid, dim3(kBlock), 0, st, static_cast<const T*>(x),
@@ -739,7 +758,7 @@ hipError_t launch_reduce_partial(const Dims& d, const void* x, const void* dy, c
         return dispatch_unroll_nt(tuned(g_tuning.reduce_unroll, 2), tuned_nt(g_tuning.reduce_nt, keep == 2 ? 0 : keep == 1 ? 1 : 3), [&](auto ut, auto nt) {
             constexpr int U = decltype(ut)::value;
             constexpr int NT = decltype(nt)::value;
-            const uint32_t hwv = uint32_t(d.HW / V);
+            const uint32_t hwv = ceil_div(uint32_t(d.HW), V);
             const uint32_t tot = uint32_t(d.N) * hwv;
             const uint32_t per_block = ceil_div(tot, uint32_t(splits));
             const dim3 grid(uint32_t(cg) * uint32_t(splits));
@@ -777,7 +796,7 @@ hipError_t launch_dx(const Dims& d, const IndexParams& ip, const void* x, const 
         return dispatch_unroll_nt(tuned(g_tuning.dx_unroll, d.dtype == BNS_F32 ? 1 : 2), tuned_nt(g_tuning.dx_nt, 3), [&](auto ut, auto nt) {
             constexpr int U = decltype(ut)::value;
             constexpr int NT = decltype(nt)::value;
-            const uint32_t hwv = uint32_t(d.HW / V);
+            const uint32_t hwv = ceil_div(uint32_t(d.HW), V);
             const uint32_t run_vectors = uint32_t(cg) * hwv;
             const dim3 grid(ceil_div(run_vectors, kBlock * U), uint32_t(d.N));
             BNS_LAUNCH((dx_kernel<T, V, U, NT>), grid, dim3(kBlock), 0, st, static_cast<const T*>(x),

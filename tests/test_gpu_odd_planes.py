@@ -1,0 +1,40 @@
+"""Planes that are no whole number of vectors, in the streaming kernels and in the single-launch kernels of every block
+size: planes of a vector and a few elements, one row, long odd planes; the last vector of a plane is shared with the one
+before it and must count once."""
+import pytest
+
+from paper_1810_10962_amd import bns, workloads
+from paper_1810_10962_amd.workloads import BS, FS, FULL, NS, Workload
+from parity import assert_parity, oracle_reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(5, 6, 3, 3), (7, 5, 1, 11), (3, 9, 5, 3), (12, 20, 2, 6), (9, 70, 13, 15), (20, 3, 45, 47),
+                                   (2, 65, 31, 1), (33, 40, 10, 10)], ids=lambda s: "x".join(map(str, s)))
+def test_odd_planes(shape, dtype):
+    N, C_, H, W = shape
+    modes = [dict(mode=FULL), dict(mode=BS, n_s=max(1, N // 2)), dict(mode=FS, patch_h=max(1, H // 2), patch_w=max(1, W - 1)),
+             dict(mode=FS, patch_h=1, patch_w=1, fs_per_channel=1)]
+    if N >= 3:
+        modes.append(dict(mode=NS, n_s=1, n_v=2, mix_beta=0.4))
+    for i, mkw in enumerate(modes):
+        wl = Workload(name="odd", N=N, C=C_, H=H, W=W, dtype=dtype, data_seed=70 + i, sampling_seed=19, layer_id=i, epoch=3, **mkw)
+        inp = workloads.make_inputs(wl)
+        ref = oracle_reference(wl, inp)
+        for opts in ({"path": 1}, {"path": 1, "split_statistics": 1, "splits_reduce": 3, "norm_unroll": 4, "dx_unroll": 4},
+                     {"grouped": 2}, {"path": 2, "fused_variant": 2}, {"path": 2, "fused_variant": 4},
+                     {"path": 2, "fused_variant": 4, "fused_keep_x": 1}, {"path": 2, "fused_variant": 7}):
+            print(f"[gpu-case] odd planes {shape} {dtype} {mkw} {opts}", flush=True)
+            try:
+                for k, v in opts.items():
+                    bns.bns_set_option(k, v)
+                res = bns.run_workload(wl, inp)
+            except bns.BnsError as e:               # a variant that is not built for Eq. 4
+                assert e.status == bns.BNS_EUNSUPPORTED and opts.get("path") == 2 and "n_v" in mkw
+                continue
+            finally:
+                for k in opts:
+                    bns.bns_set_option(k, 0)
+            assert_parity(res, ref, wl, what=f"odd {shape} {dtype} {mkw} {opts}", inp=inp)
