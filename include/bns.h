@@ -41,6 +41,8 @@
  *            results of that channel are NaN -- never a wrong finite value -- the
  *            moving averages keep their old values, the kernel ends normally, and
  *            bns_expired_waits() reports it, so nobody has to scan tensors.
+ *            The N x H x W x C calls whose blocks would wait for each other take
+ *            the streaming kernels while their stream is being captured.
  * Aliasing   Outputs must not overlap inputs or each other (x is needed again
  *            by the backward pass; dx is written while dy is read).  The host
  *            checks the tensors (y against x; dx against x and dy) and returns
@@ -58,7 +60,9 @@
  *            BNS_EDEVICE when the HIP runtime reports a launch failure.
  *            Nothing is thrown across the boundary.
  * Determinism No floating-point atomics: per-channel sums are combined in a
- *            fixed order, so results are bit-identical from run to run.
+ *            fixed order, so results are bit-identical from run to run (of the
+ *            same kernels: an N x H x W x C call inside a capture can take
+ *            others than outside, see Concurrency, and differ in the last bits).
  */
 #ifndef BNS_H
 #define BNS_H
