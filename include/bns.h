@@ -177,10 +177,10 @@ bns_status bns_backward(const bns_shape* shape, const bns_spec* spec, uint64_t s
 /* bns_backward for callers that cannot hand over a workspace they allocated: code recorded into a HIP graph
  * whose buffers are fixed before the scratch size is known, tight serving or training loops, harnesses that
  * forbid hipMalloc.  Same arguments, results (bit for bit) and errors as bns_backward, without `workspace`:
- * the partial sums and exchange slots live in an array of 4 MiB + 256 bytes built into the library's device code, one copy
+ * the partial sums and exchange slots live in an array of 5 MiB + 256 bytes built into the library's device code, one copy
  * per GPU, held from the first use of the library on that GPU until the process ends.  The call allocates
- * and frees nothing.  BNS_EWORKSPACE if bns_workspace_bytes(shape, spec) exceeds that size (N x C x H x W: more than
- * 3840 channels).  All such calls on one GPU share the one array, which keeps what the last call left in it
+ * and frees nothing.  BNS_EWORKSPACE if bns_workspace_bytes(shape, spec) exceeds that size (N x H x W x C) or
+ * 4 MiB + 256 bytes of it (N x C x H x W: more than 3840 channels).  All such calls on one GPU share the one array, which keeps what the last call left in it
  * (nothing in it has to start at zero): they must be ordered on one stream, like calls that share a
  * workspace; calls that overlap on a GPU race.  The first call on each GPU looks the array's address up and
  * should be made outside stream capture. */

@@ -16,7 +16,8 @@ thread_local int32_t bns::t_last_fused_backward = 0;
 thread_local int32_t bns::t_last_fused_forward = 0;
 
 // Built-in scratch memory of bns_backward_builtin_workspace (see there).
-constexpr size_t kBuiltinWorkspaceBytes = (size_t(4) << 20) + bns::kHeaderBytes;    // 3840 channels
+// N x C x H x W: 3840 channels; N x H x W x C: 4 MiB of partial sums behind the slots.
+constexpr size_t kBuiltinWorkspaceBytes = bns::kBuiltinNchwBytes + bns::kSlotBytes;
 static __device__ __align__(256) unsigned char scratch[kBuiltinWorkspaceBytes];
 
 namespace {
@@ -34,18 +35,18 @@ inline size_t elem_bytes(const Dims& d) { return d.dtype == BNS_F32 ? 4 : 2; }
 inline size_t tensor_bytes(const Dims& d) { return size_t(d.N) * d.C * d.HW * elem_bytes(d); }
 inline size_t partial_bytes(const Dims& d) { return (size_t(d.C) * kMaxSplits * sizeof(Partial) + 255) & ~size_t(255); }
 inline bool nhwc(const Dims& d) { return d.layout == BNS_NHWC; }
-// Workspace layout: [header][sums S][sums V][slots] (N x H x W x C: no slots).  The header comes first so that
-// bns_expired_waits finds it without knowing the shape.
-inline size_t workspace_need(const Dims& d) {
-    if (nhwc(d)) return kHeaderBytes + 2 * nhwc_partial_bytes(d);
-    return kHeaderBytes + 2 * partial_bytes(d) + kSlotBytes;
+inline WorkspaceLayout layout_of(const Dims& d) {
+    return workspace_layout(d, nhwc(d) ? nhwc_partial_bytes(d) : partial_bytes(d));
 }
-inline Partial* partials_of(void* workspace) {
-    return reinterpret_cast<Partial*>(static_cast<char*>(workspace) + kHeaderBytes);
+inline size_t workspace_need(const Dims& d) { return layout_of(d).total; }
+inline Partial* partials_of(void* workspace, const Dims& d) {
+    return reinterpret_cast<Partial*>(static_cast<char*>(workspace) + layout_of(d).sums);
 }
-inline void* slots_of(void* workspace, const Dims& d) {
-    return static_cast<char*>(workspace) + kHeaderBytes + 2 * partial_bytes(d);
+inline Partial* virtual_partials_of(void* workspace, const Dims& d) {      // Eq. 4
+    const WorkspaceLayout w = layout_of(d);
+    return reinterpret_cast<Partial*>(static_cast<char*>(workspace) + w.sums + w.sum_bytes);
 }
+inline void* slots_of(void* workspace) { return static_cast<char*>(workspace) + kHeaderBytes; }
 // N x H x W x C: one location set for all channels
 inline bns_status check_layout(const Dims& d, const bns_spec* sp) {
     return (nhwc(d) && sp->mode == BNS_FS && sp->fs_per_channel) ? BNS_EUNSUPPORTED : BNS_OK;
@@ -156,13 +157,12 @@ FusedIo backward_io(const void* x, const void* dy, void* dx, const float* gamma,
     return io;
 }
 
-// N x H x W x C: the whole direction in one launch, if the tensor is for it; *status is then the call's result.  The exchange
-// slots lie where the streaming kernels keep their partial sums.
+// N x H x W x C: the whole direction in one launch, if the tensor is for it; *status is then the call's result.
 bool nhwc_single_launch(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                         void* workspace, hipStream_t st, const FusedMix* mix, bool order_streams, bns_status* status) {
     bool solo = false;
-    const hipError_t e = launch_nhwc_fused(d, ip, backward, io, eps, momentum, workspace, partials_of(workspace),
-                                           2 * nhwc_partial_bytes(d), st, mix, order_streams, g_tuning.path != 1, &solo);
+    const hipError_t e = launch_nhwc_fused(d, ip, backward, io, eps, momentum, workspace, slots_of(workspace),
+                                           layout_of(d).slot_bytes, st, mix, order_streams, g_tuning.path != 1, &solo);
     if (e == hipErrorNotSupported) return false;
     (backward ? t_last_path_backward : t_last_path_forward) = solo ? 3 : 2;
     *status = dev(e);
@@ -227,10 +227,10 @@ bns_status bns_forward_stats(const bns_shape* shape, const bns_spec* spec, uint6
     if (workspace_bytes < workspace_need(d)) return BNS_EWORKSPACE;
     const IndexParams ip = make_index_params(*shape, *spec, seed);
     if (nhwc(d))
-        return dev(launch_nhwc_stats(d, ip.shared, x, partials_of(workspace), eps, momentum, save_mean,
+        return dev(launch_nhwc_stats(d, ip.shared, x, partials_of(workspace, d), eps, momentum, save_mean,
                                      save_invstd, running_mean, running_var, static_cast<hipStream_t>(stream)));
     return stats_range(d, ip, x, eps, momentum, save_mean, save_invstd, running_mean, running_var,
-                       partials_of(workspace), 0, d.C, static_cast<hipStream_t>(stream));
+                       partials_of(workspace, d), 0, d.C, static_cast<hipStream_t>(stream));
 }
 
 bns_status bns_forward_normalize(const bns_shape* shape, const void* x, const float* gamma, const float* beta,
@@ -278,7 +278,7 @@ bns_status bns_forward(const bns_shape* shape, const bns_spec* spec, uint64_t se
     if (workspace_bytes < workspace_need(d)) return BNS_EWORKSPACE;
     const IndexParams ip = make_index_params(*shape, *spec, seed);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Partial* ws = partials_of(workspace);
+    Partial* ws = partials_of(workspace, d);
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
         const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
@@ -292,7 +292,7 @@ bns_status bns_forward(const bns_shape* shape, const bns_spec* spec, uint64_t se
     if (g_tuning.path != 1) {
         const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
         const hipError_t fe = launch_fused(d, ip, false, io, eps, momentum,
-                                           workspace, slots_of(workspace, d), kSlotBytes, 0, d.C, st);
+                                           workspace, slots_of(workspace), layout_of(d).slot_bytes, 0, d.C, st);
         if (fe == hipSuccess) {
             t_last_path_forward = 2;
             return BNS_OK;
@@ -322,10 +322,10 @@ bns_status bns_backward_reduce(const bns_shape* shape, const void* x, const void
     if (!aligned16(x) || !aligned16(dy) || !aligned16(workspace)) return BNS_EINVAL;
     if (workspace_bytes < workspace_need(d)) return BNS_EWORKSPACE;
     if (nhwc(d))
-        return dev(launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, partials_of(workspace), dgamma, dbeta, false,
+        return dev(launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, partials_of(workspace, d), dgamma, dbeta, false,
                                       static_cast<hipStream_t>(stream)));
     // (the location set is not known here: dy is taken to be what the dx pass reads again)
-    return reduce_range(d, x, dy, save_mean, save_invstd, dgamma, dbeta, partials_of(workspace), 0, d.C, false,
+    return reduce_range(d, x, dy, save_mean, save_invstd, dgamma, dbeta, partials_of(workspace, d), 0, d.C, false,
                         static_cast<hipStream_t>(stream));
 }
 
@@ -376,7 +376,7 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
     if (workspace_bytes < workspace_need(d)) return BNS_EWORKSPACE;
     const IndexParams ip = make_index_params(*shape, *spec, seed);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Partial* ws = partials_of(workspace);
+    Partial* ws = partials_of(workspace, d);
     // the dx pass reads x on the points of S only: worth keeping in cache when that is most of the tensor
     const bool x_again = 2u * uint64_t(ip.shared.n_cnt) * uint64_t(ip.shared.h_cnt) * uint64_t(ip.shared.w_cnt) >=
                          uint64_t(d.N) * uint64_t(d.HW);
@@ -400,8 +400,8 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
     }
     if (g_tuning.path != 1) {
         const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
-        const hipError_t fe = launch_fused(d, ip, true, io, 0.f, 0.f, workspace, slots_of(workspace, d),
-                                           kSlotBytes, 0, d.C, st, nullptr, order_streams);
+        const hipError_t fe = launch_fused(d, ip, true, io, 0.f, 0.f, workspace, slots_of(workspace),
+                                           layout_of(d).slot_bytes, 0, d.C, st, nullptr, order_streams);
         if (fe == hipSuccess) {
             t_last_path_backward = 2;
             return BNS_OK;
@@ -456,7 +456,7 @@ bns_status bns_backward_builtin_workspace(const bns_shape* shape, const bns_spec
     Dims d;
     const bns_status s = backward_check(shape, spec, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, &d);
     if (s != BNS_OK) return s;
-    if (workspace_need(d) > kBuiltinWorkspaceBytes) return BNS_EWORKSPACE;     // too many channels for the built-in scratch
+    if (workspace_need(d) > (nhwc(d) ? kBuiltinWorkspaceBytes : kBuiltinNchwBytes)) return BNS_EWORKSPACE;     // too many channels
     void* ws = nullptr;
     const bns_status ws_status = builtin_workspace(&ws);
     if (ws_status != BNS_OK) return ws_status;
@@ -515,7 +515,7 @@ bns_status bns_forward_mixed(const bns_shape* shape, const bns_spec* spec, uint6
         const FusedIo io = forward_io(x, y, gamma, beta, save_mean, save_invstd, running_mean, running_var);
         if (nhwc_single_launch(d, ip_s, false, io, eps, momentum, workspace, st, &mix, true, &s)) return s;
         t_last_path_forward = 1;
-        if (launch_nhwc_stats_mixed(d, ip_s.shared, n_v, x, partials_of(workspace), mix_beta, eps, momentum,
+        if (launch_nhwc_stats_mixed(d, ip_s.shared, n_v, x, partials_of(workspace, d), mix_beta, eps, momentum,
                                     save_mean, save_invstd, save_mean_parts, running_mean, running_var, st) != hipSuccess)
             return BNS_EDEVICE;
         return dev(launch_nhwc_normalize(d, x, gamma, beta, save_mean, save_invstd, y, st));
@@ -527,7 +527,7 @@ bns_status bns_forward_mixed(const bns_shape* shape, const bns_spec* spec, uint6
         mix.mix_beta = mix_beta;
         mix.mean_parts = save_mean_parts;
         const hipError_t fe = launch_fused(d, ip_s, false, io, eps, momentum,
-                                           workspace, slots_of(workspace, d), kSlotBytes, 0, d.C, st,
+                                           workspace, slots_of(workspace), layout_of(d).slot_bytes, 0, d.C, st,
                                            &mix);
         if (fe == hipSuccess) {
             t_last_path_forward = 2;
@@ -538,8 +538,8 @@ bns_status bns_forward_mixed(const bns_shape* shape, const bns_spec* spec, uint6
     }
     t_last_path_forward = 1;
     const IndexParams ip_v = make_index_params_virtual(*shape, n_v);
-    Partial* ws_s = partials_of(workspace);
-    Partial* ws_v = reinterpret_cast<Partial*>(reinterpret_cast<char*>(partials_of(workspace)) + partial_bytes(d));
+    Partial* ws_s = partials_of(workspace, d);
+    Partial* ws_v = virtual_partials_of(workspace, d);
     const int splits_s = stats_splits(d, ip_s, d.C);
     const int splits_v = stats_splits(d, ip_v, d.C);
     if (launch_stats_partial(d, ip_s, x, ws_s, splits_s, 0, d.C, st) != hipSuccess) return BNS_EDEVICE;
@@ -575,7 +575,7 @@ bns_status bns_backward_mixed(const bns_shape* shape, const bns_spec* spec, uint
         const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
         if (nhwc_single_launch(d, ip_s, true, io, 0.f, 0.f, workspace, st, &mix, true, &s)) return s;
         t_last_path_backward = 1;
-        if (launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, partials_of(workspace), dgamma, dbeta, false, st) !=
+        if (launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, partials_of(workspace, d), dgamma, dbeta, false, st) !=
             hipSuccess)
             return BNS_EDEVICE;
         return dev(launch_nhwc_dx_mixed(d, ip_s.shared, n_v, mix_beta, x, dy, gamma, save_invstd, dgamma, dbeta,
@@ -587,8 +587,8 @@ bns_status bns_backward_mixed(const bns_shape* shape, const bns_spec* spec, uint
         mix.n_v = n_v;
         mix.mix_beta = mix_beta;
         mix.mean_parts = const_cast<float*>(save_mean_parts);
-        const hipError_t fe = launch_fused(d, ip_s, true, io, 0.f, 0.f, workspace, slots_of(workspace, d),
-                                           kSlotBytes, 0, d.C, st, &mix);
+        const hipError_t fe = launch_fused(d, ip_s, true, io, 0.f, 0.f, workspace, slots_of(workspace),
+                                           layout_of(d).slot_bytes, 0, d.C, st, &mix);
         if (fe == hipSuccess) {
             t_last_path_backward = 2;
             return BNS_OK;
@@ -597,7 +597,7 @@ bns_status bns_backward_mixed(const bns_shape* shape, const bns_spec* spec, uint
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
     }
     t_last_path_backward = 1;
-    s = reduce_range(d, x, dy, save_mean, save_invstd, dgamma, dbeta, partials_of(workspace), 0, d.C, false, st);
+    s = reduce_range(d, x, dy, save_mean, save_invstd, dgamma, dbeta, partials_of(workspace, d), 0, d.C, false, st);
     if (s != BNS_OK) return s;
     const bns_box& b = ip_s.shared;
     DxSets sets;

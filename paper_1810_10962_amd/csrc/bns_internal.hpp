@@ -9,6 +9,7 @@
 
 #include "bns_index.hpp"
 #include "bns_validate.hpp"
+#include "bns_workspace.hpp"
 
 // Kernel launch whose status the following hipGetLastError() reports: the thread's last-error state may
 // still hold a failure of some earlier, unrelated runtime call (the caller's, the framework's), which must
@@ -156,8 +157,6 @@ struct FusedIo {
     float* dgamma = nullptr;
     float* dbeta = nullptr;
 };
-constexpr size_t kSlotBytes = 256 * 1024;   // stamped exchange slots of the fused kernels
-constexpr size_t kHeaderBytes = 256;        // in front of everything else in a workspace
 // hipErrorNotSupported: the channel does not fit on chip (take the streaming kernels instead).
 // mix != nullptr: "VDN + sampling" (Eq. 4); `ip` then describes the sampled real set.
 struct FusedMix {

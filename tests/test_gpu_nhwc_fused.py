@@ -92,6 +92,36 @@ def test_missing_team_mate_and_what_comes_after():
     assert_parity(good, oracle_reference(wl, inp), wl, what="after the give-up run", inp=inp)
 
 
+def test_sums_left_by_the_streaming_kernels_are_not_taken_for_a_team_mates():
+    """The exchange takes any slot word that carries the launch's stamp.  Streaming calls on constant tensors leave zeros
+    as partial sums in the workspace; the next stamp is then set to zero, which is what those words would carry
+    if they lay in the slots."""
+    wl = Workload(name="nhwc_left_over", N=9, C=70, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=3, data_seed=5,
+                  sampling_seed=6, layer_id=1)
+    inp = workloads.make_inputs(wl)
+    flat = dict(inp, x=np.full_like(inp["x"], 2.0), dy=np.zeros_like(inp["dy"]))
+    buf, left = bns.Buffers(wl, inp), bns.Buffers(wl, flat)
+    left.workspace = buf.workspace
+    header = torch.tensor([0x626E7301 << 32, 0], dtype=torch.int64, device="cuda").view(torch.uint8)     # magic | stamp 0, counts 0
+    print("[gpu-case] nhwc single launch after streaming calls in the same workspace", flush=True)
+
+    def streaming():
+        buf.workspace.fill_(0xA5)                           # (no zeros, and no stamps used before, in the slots themselves)
+        left.forward()
+        left.backward()
+        assert _paths() == (1, 1)
+        buf.workspace[:16].copy_(header)
+
+    _with({"nhwc_fused": 2}, streaming)
+    _with({"nhwc_fused": 1}, buf.forward)
+    assert _paths()[0] == 2
+    _with({"nhwc_fused": 2}, streaming)
+    _with({"nhwc_fused": 1}, buf.backward)
+    assert _paths()[1] == 2
+    assert bns.bns_expired_waits(buf.workspace) == 0
+    assert_parity(buf.results(), oracle_reference(wl, inp), wl, what="after streaming calls", inp=inp)
+
+
 def test_a_captured_call_takes_the_streaming_kernels():
     wl = Workload(name="nhwc_graph", N=20, C=64, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=4, data_seed=7,
                   sampling_seed=8, layer_id=2)

@@ -90,6 +90,19 @@ def test_index_sweep_under_sanitizers_equals_the_oracle(index_harness, tmp_path)
     assert len(modes_seen) == 9
 
 
+def test_partial_sums_never_lie_in_exchange_slots(tmp_path):
+    """Offsets of a workspace's regions, for one shape and between shapes that use the same memory in turn."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not found")
+    exe = str(tmp_path / "workspace_harness")
+    _run([gxx, "-std=c++17", "-O1", "-g", "-Wall", "-Werror", *SAN, os.path.join(CHECKS, "workspace_harness.cpp"), "-o", exe])
+    assert _run([exe], env=ENV).split() == ["shapes", "200000"]
+    from paper_1810_10962_amd import bns
+    for layout in ("nchw", "nhwc"):             # the library's own sizes: header, slots of 1 MiB, sums
+        assert bns.bns_workspace_bytes(bns.make_shape(1, 8, 1, 1, layout=layout), bns.make_spec(bns.BNS_FULL)) > 256 + (1 << 20)
+
+
 def test_entry_points_reject_bad_arguments_under_sanitizers(tmp_path):
     hipcc = next((c for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
     clang = "/opt/rocm/lib/llvm/bin/clang++"
