@@ -182,7 +182,8 @@ bns_status bns_backward(const bns_shape* shape, const bns_spec* spec, uint64_t s
  * and frees nothing.  BNS_EWORKSPACE if bns_workspace_bytes(shape, spec) exceeds that size (N x H x W x C) or
  * 4 MiB + 256 bytes of it (N x C x H x W: more than 3840 channels).  All such calls on one GPU share the one array, which keeps what the last call left in it
  * (nothing in it has to start at zero): they must be ordered on one stream, like calls that share a
- * workspace; calls that overlap on a GPU race.  The first call on each GPU looks the array's address up and
+ * workspace; calls that overlap on a GPU race.  Against the other calls of the library they are ordered like any call
+ * (see Concurrency).  The first call on each GPU looks the array's address up and
  * should be made outside stream capture. */
 bns_status bns_backward_builtin_workspace(const bns_shape* shape, const bns_spec* spec, uint64_t seed,
                                           const void* x, const void* dy, const float* gamma,

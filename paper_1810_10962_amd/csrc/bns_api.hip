@@ -159,10 +159,10 @@ FusedIo backward_io(const void* x, const void* dy, void* dx, const float* gamma,
 
 // N x H x W x C: the whole direction in one launch, if the tensor is for it; *status is then the call's result.
 bool nhwc_single_launch(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
-                        void* workspace, hipStream_t st, const FusedMix* mix, bool order_streams, bns_status* status) {
+                        void* workspace, hipStream_t st, const FusedMix* mix, bool may_create_event, bns_status* status) {
     bool solo = false;
     const hipError_t e = launch_nhwc_fused(d, ip, backward, io, eps, momentum, workspace, slots_of(workspace),
-                                           layout_of(d).slot_bytes, st, mix, order_streams, g_tuning.path != 1, &solo);
+                                           layout_of(d).slot_bytes, st, mix, may_create_event, g_tuning.path != 1, &solo);
     if (e == hipErrorNotSupported) return false;
     (backward ? t_last_path_backward : t_last_path_forward) = solo ? 3 : 2;
     *status = dev(e);
@@ -368,7 +368,7 @@ bns_status backward_check(const bns_shape* shape, const bns_spec* spec, const vo
 bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t seed, const void* x, const void* dy,
                          const float* gamma, const float* save_mean, const float* save_invstd, void* dx,
                          float* dgamma, float* dbeta, void* workspace, size_t workspace_bytes, void* stream,
-                         bool order_streams) {
+                         bool may_create_event) {
     Dims d;
     bns_status s = backward_check(shape, spec, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, &d);
     if (s != BNS_OK) return s;
@@ -383,7 +383,7 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
         const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
-        if (g_tuning.nhwc_split_dx == 0 && nhwc_single_launch(d, ip, true, io, 0.f, 0.f, workspace, st, nullptr, order_streams, &s))
+        if (g_tuning.nhwc_split_dx == 0 && nhwc_single_launch(d, ip, true, io, 0.f, 0.f, workspace, st, nullptr, may_create_event, &s))
             return s;
         t_last_path_backward = 1;
         // Eq. 6 outside S needs none of the sums: the reduction kernel can write dx there while it has dy in
@@ -401,7 +401,7 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
     if (g_tuning.path != 1) {
         const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
         const hipError_t fe = launch_fused(d, ip, true, io, 0.f, 0.f, workspace, slots_of(workspace),
-                                           layout_of(d).slot_bytes, 0, d.C, st, nullptr, order_streams);
+                                           layout_of(d).slot_bytes, 0, d.C, st, nullptr, may_create_event);
         if (fe == hipSuccess) {
             t_last_path_backward = 2;
             return BNS_OK;
@@ -460,7 +460,7 @@ bns_status bns_backward_builtin_workspace(const bns_shape* shape, const bns_spec
     void* ws = nullptr;
     const bns_status ws_status = builtin_workspace(&ws);
     if (ws_status != BNS_OK) return ws_status;
-    // (no event between streams here: creating one allocates, and these calls are ordered by the caller anyway)
+    // (no event is created here: that allocates)
     return backward_impl(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, ws,
                          kBuiltinWorkspaceBytes, stream, false);
 }

@@ -682,18 +682,24 @@ TeamChoice& choice_slot(DeviceInfo& di, int32_t tag, uint32_t tot, int32_t cg) {
 // part of its grid resident, would wait for blocks that the other keeps out.  Within a process they are therefore
 // chained across streams: when such a launch goes to another stream than the one before it, an event is
 // recorded on that earlier stream (behind the earlier launch) and the new stream waits for it.  A caller that
-// stays on one stream pays nothing.  Not while a stream is being captured (the event would belong to the
+// stays on one stream records nothing.  Not while a stream is being captured (the event would belong to the
 // graph); a graph that holds such launches must not run beside other calls.
-// *chain in: the launch waits and is to be ordered; out: it is not being captured (the caller then calls chain_launched).
-hipError_t chain_behind_last(DeviceInfo& di, hipStream_t st, bool* chain) {
+// The event is made by the first such call that may allocate (may_create).  A call that may not (on the built-in scratch)
+// then finds it if there is anything to wait for: until one of the others has run, the only launches to be behind are of
+// its own kind, which the caller orders.
+// *chain in: the launch waits; out: it is not being captured (the caller then calls chain_launched).
+hipError_t chain_behind_last(DeviceInfo& di, hipStream_t st, bool may_create, bool* chain) {
     if (*chain) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         *chain = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
         (void)hipGetLastError();
     }
-    if (*chain && di.chain_active && di.chain_stream != st) {
-        if (!di.chain_event && hipEventCreateWithFlags(&di.chain_event, hipEventDisableTiming) != hipSuccess)
-            di.chain_event = nullptr;
+    if (!*chain) return hipSuccess;
+    if (!di.chain_event && may_create && hipEventCreateWithFlags(&di.chain_event, hipEventDisableTiming) != hipSuccess) {
+        di.chain_event = nullptr;
+        (void)hipGetLastError();
+    }
+    if (di.chain_active && di.chain_stream != st) {
         // (an earlier stream that has been destroyed meanwhile refuses the record: nothing is left to wait for)
         hipError_t e;
         if (di.chain_event && hipEventRecord(di.chain_event, di.chain_stream) == hipSuccess &&
@@ -719,13 +725,14 @@ hipError_t device_units(int* cus) {
 
 uint32_t next_stamp_seed() { return g_stamp.fetch_add(1u); }
 
-hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool order_streams, hipStream_t st) {
+hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool may_create_event,
+                          hipStream_t st) {
     std::lock_guard<std::mutex> lock(g_dev_mutex);
     DeviceInfo* di = nullptr;
     hipError_t e = current_device(&di);
     if (e != hipSuccess) return e;
-    bool chain = waits && order_streams;
-    if ((e = chain_behind_last(*di, st, &chain)) != hipSuccess) return e;
+    bool chain = waits;
+    if ((e = chain_behind_last(*di, st, may_create_event, &chain)) != hipSuccess) return e;
     g_launch_count.fetch_add(1, std::memory_order_relaxed);
     e = hipLaunchKernel(kernel, grid, block, params, 0, st);
     if (e == hipSuccess && chain) chain_launched(*di, st);
@@ -736,7 +743,7 @@ hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** para
 // when the channel does not fit on chip (the caller then takes the streaming kernels).
 hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps,
                         float momentum, void* header, void* slots, size_t slot_bytes, int c0, int cg, hipStream_t st,
-                        const FusedMix* mix, bool order_streams) {
+                        const FusedMix* mix, bool may_create_event) {
     // One read of each option per call: a concurrent bns_set_option cannot change a choice half way through.
     const int opt_variant = g_tuning.fused_variant, opt_keep_x = g_tuning.fused_keep_x, opt_pipe = g_tuning.fused_pipe;
     const int opt_team = g_tuning.fused_team, opt_path = g_tuning.path, opt_coop = g_tuning.fused_coop;
@@ -1105,8 +1112,8 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     if (!backward) t_last_fused_forward = kernel == kernel_for(d, kind, best) ? 1 : 2;
     void* params[] = {&A};
 
-    bool chain = bestT > 1 && order_streams;
-    if ((e = chain_behind_last(di, st, &chain)) != hipSuccess) return e;
+    bool chain = bestT > 1;
+    if ((e = chain_behind_last(di, st, may_create_event, &chain)) != hipSuccess) return e;
     g_launch_count.fetch_add(1, std::memory_order_relaxed);
     if (backward) t_last_fused_backward = pipe_kernel ? 3 : (kind & 2) ? 2 : 1;
     e = opt_coop ? hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(launch_nt), params, 0, st)

@@ -165,10 +165,10 @@ struct FusedMix {
     float* mean_parts = nullptr;     // [E_v per channel][E_s per channel]: forward writes, backward reads
 };
 // header: the first kHeaderBytes of the workspace (launch counter, count of waits that ran out).
-// order_streams: chain launches whose blocks wait for each other across streams with an event (see there).
+// may_create_event: the call may make the event that chains, across streams, launches whose blocks wait for each other.
 hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps,
                         float momentum, void* header, void* slots, size_t slot_bytes, int c0, int cg, hipStream_t st,
-                        const FusedMix* mix = nullptr, bool order_streams = true);
+                        const FusedMix* mix = nullptr, bool may_create_event = true);
 // The same for small planes, a block per group of channels (bns_grouped.hip): nothing crosses blocks.
 // hipErrorNotSupported: a group does not fit a block, or the other kernels are faster.
 hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
@@ -180,7 +180,7 @@ hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 // would have to wait for each other, not while capturing or without may_wait).  *solo: no block waits for another.
 hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                              void* header, void* slots, size_t slot_bytes, hipStream_t st, const FusedMix* mix,
-                             bool order_streams, bool may_wait, bool* solo);
+                             bool may_create_event, bool may_wait, bool* solo);
 // Taken by tensors of few rows and by large ones; the others keep the streaming kernels, and with them the bits of the stage
 // calls for whole calls (16x64x32x32 f32: 13.0 / 14.7 us against 9.8 / 10.3 in one launch).
 constexpr size_t kNhwcFusedBytes = size_t(4) << 20;
@@ -190,7 +190,8 @@ constexpr uint32_t kNhwcFewRows = 8192;
 // stamps; a launch that is chained, across streams, behind the last one whose blocks wait for each other (waits).
 hipError_t device_units(int* cus);
 uint32_t next_stamp_seed();
-hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool order_streams, hipStream_t st);
+hipError_t launch_waiting(const void* kernel, dim3 grid, dim3 block, void** params, bool waits, bool may_create_event,
+                          hipStream_t st);
 
 hipError_t launch_index_boxes(const IndexParams& ip, int C, bns_box* boxes, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);

@@ -714,7 +714,7 @@ const void* row_kernel(int variant, bool backward, bool mixed) {
 
 hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                              void* header, void* slots, size_t slot_bytes, hipStream_t st, const FusedMix* mix,
-                             bool order_streams, bool may_wait, bool* solo) {
+                             bool may_create_event, bool may_wait, bool* solo) {
     const bns_box& b = ip.shared;
     const int full = d.dtype == BNS_F32 ? 4 : 8, V = d.C < full ? 1 : full, opt = g_tuning.nhwc_fused;
     if (opt == 2 || g_tuning.nhwc_small == 2) return hipErrorNotSupported;
@@ -844,7 +844,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
                                               : row_kernel<bf16_t, 1>(variant, backward, mixed);
     *solo = T == 1;
     void* params[] = {&A};
-    return launch_waiting(kernel, dim3(uint32_t(tiles) * uint32_t(T)), dim3(kRowThreads), params, T > 1, order_streams, st);
+    return launch_waiting(kernel, dim3(uint32_t(tiles) * uint32_t(T)), dim3(kRowThreads), params, T > 1, may_create_event, st);
 }
 
 }  // namespace bns

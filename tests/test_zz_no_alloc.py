@@ -21,6 +21,10 @@ CASES = [
     (Workload(name="noalloc_c", N=16, C=64, H=20, W=20, mode=FS, patch_h=6, patch_w=6, dtype="bf16", data_seed=13,
               sampling_seed=7),
      Workload(name="noalloc_d", N=5, C=7, H=7, W=7, mode=BS, n_s=2, dtype="bf16", data_seed=14, sampling_seed=8)),
+    # N x H x W x C: blocks that wait for each other, then a tensor of few rows
+    (Workload(name="noalloc_e", N=24, C=96, H=28, W=28, mode=BS, n_s=3, layout="nhwc", data_seed=15, sampling_seed=9),
+     Workload(name="noalloc_f", N=5, C=40, H=7, W=7, mode=FS, patch_h=3, patch_w=4, layout="nhwc", data_seed=16,
+              sampling_seed=10)),
 ]
 
 
@@ -35,6 +39,8 @@ def _one_call(wl):
     print(f"[gpu-case] bns_backward_builtin_workspace {wl.name} {wl.shape} {wl.dtype} mode={wl.mode}", flush=True)
     bns.bns_backward_builtin_workspace(b.shape, b.spec, b.seed, b.x, b.dy, b.gamma, b.save_mean, b.save_invstd,
                                        b.dx, b.dgamma, b.dbeta)
+    if wl.name == "noalloc_e" and bns.bns_get_option("path") == 0:
+        assert bns.bns_get_option("last_path_backward") == 2
     got = b.results()
     for name in ("dx", "dgamma", "dbeta"):
         assert np.array_equal(got[name], want[name]), f"{wl.name} {name}: differs from bns_backward"
@@ -52,6 +58,57 @@ def test_builtin_workspace_matches_bns_backward_twice_in_a_row(case, path):
         _one_call(second)
     finally:
         bns.bns_set_option("path", 0)
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_builtin_workspace_beside_other_calls_on_other_streams(layout):
+    """Threads with single-launch calls on streams of their own, one of them on the built-in scratch: kernels whose blocks
+    wait for each other never share the device, so every result is right and no wait runs out."""
+    import threading
+    results, errors = {}, []
+
+    def worker(k):
+        try:
+            wl = Workload(name=f"beside{k}", N=32, C=96, H=28, W=28, mode=(BS, FS)[k % 2], n_s=4, patch_h=7, patch_w=7, layout=layout,
+                          dtype=("f32", "bf16")[(k // 2) % 2], data_seed=80 + k, sampling_seed=90 + k, layer_id=k, epoch=2)
+            inp = make_inputs(wl)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                b = bns.Buffers(wl, inp)
+                for _ in range(8):
+                    b.forward()
+                    assert bns.bns_get_option("last_path_forward") == 2
+                    if k == 0:
+                        bns.bns_backward_builtin_workspace(b.shape, b.spec, b.seed, b.x, b.dy, b.gamma, b.save_mean, b.save_invstd,
+                                                           b.dx, b.dgamma, b.dbeta)
+                    else:
+                        b.backward()
+                    assert bns.bns_get_option("last_path_backward") == 2
+                res = b.results()
+                expired = bns.bns_expired_waits(b.workspace) + (bns.bns_expired_waits(None, stream_of=b.x) if k == 0 else 0)
+            results[k] = (wl, inp, res, expired)
+        except Exception as e:          # noqa: BLE001  (reported below, in the main thread)
+            errors.append((k, repr(e)))
+
+    print(f"[gpu-case] built-in scratch beside other streams, {layout}", flush=True)
+    options = {"test_spin_limit": 1 << 16, "nhwc_fused": 1, "fused_variant": 3}      # (a wait that ran out would cost tens of milliseconds)
+    try:
+        for name, v in options.items():
+            bns.bns_set_option(name, v)
+        threads = [threading.Thread(target=worker, args=(k,)) for k in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        for name in options:
+            bns.bns_set_option(name, 0)
+    assert not errors, errors
+    assert len(results) == 4
+    for k, (wl, inp, res, expired) in sorted(results.items()):
+        assert expired == 0, f"thread {k}: {expired} waits ran out"
+        ref = oracle_reference(wl, inp)
+        ref.pop("running_mean"), ref.pop("running_var")          # eight iterations went into them
+        assert_parity({n: v for n, v in res.items() if n in ref}, ref, wl, what=f"beside {k} {wl}", inp=inp)
 
 
 def test_builtin_workspace_rejects_what_does_not_fit():
