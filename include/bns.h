@@ -42,7 +42,10 @@
  *            moving averages keep their old values, the kernel ends normally, and
  *            bns_expired_waits() reports it, so nobody has to scan tensors.
  *            The N x H x W x C calls whose blocks would wait for each other take
- *            the streaming kernels while their stream is being captured.
+ *            the streaming kernels while their stream is being captured; and so do
+ *            calls of either layout while the stream that carried the last such
+ *            kernel is being captured and is not their own (they cannot be ordered
+ *            behind it without touching that capture).
  * Aliasing   Outputs must not overlap inputs or each other (x is needed again
  *            by the backward pass; dx is written while dy is read).  The host
  *            checks the tensors (y against x; dx against x and dy) and returns
@@ -61,8 +64,8 @@
  *            Nothing is thrown across the boundary.
  * Determinism No floating-point atomics: per-channel sums are combined in a
  *            fixed order, so results are bit-identical from run to run (of the
- *            same kernels: an N x H x W x C call inside a capture can take
- *            others than outside, see Concurrency, and differ in the last bits).
+ *            same kernels: a call inside or beside a capture can take others
+ *            than outside, see Concurrency, and differ in the last bits).
  */
 #ifndef BNS_H
 #define BNS_H

@@ -683,7 +683,7 @@ TeamChoice& choice_slot(DeviceInfo& di, int32_t tag, uint32_t tot, int32_t cg) {
 // chained across streams: when such a launch goes to another stream than the one before it, an event is
 // recorded on that earlier stream (behind the earlier launch) and the new stream waits for it.  A caller that
 // stays on one stream records nothing.  Not while a stream is being captured (the event would belong to the
-// graph); a graph that holds such launches must not run beside other calls.
+// graph); a graph that holds such launches must not run beside other calls.  hipErrorNotSupported: no order can be had.
 // The event is made by the first such call that may allocate (may_create).  A call that may not (on the built-in scratch)
 // then finds it if there is anything to wait for: until one of the others has run, the only launches to be behind are of
 // its own kind, which the caller orders.
@@ -700,6 +700,13 @@ hipError_t chain_behind_last(DeviceInfo& di, hipStream_t st, bool may_create, bo
         (void)hipGetLastError();
     }
     if (di.chain_active && di.chain_stream != st) {
+        // The earlier stream is being captured now: a record there would go into that graph, and the new stream with it.
+        // The call takes kernels that do not wait.
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        const hipError_t known = hipStreamIsCapturing(di.chain_stream, &cap);
+        (void)hipGetLastError();
+        if (known == hipErrorStreamCaptureImplicit || (known == hipSuccess && cap != hipStreamCaptureStatusNone))
+            return hipErrorNotSupported;
         // (an earlier stream that has been destroyed meanwhile refuses the record: nothing is left to wait for)
         hipError_t e;
         if (di.chain_event && hipEventRecord(di.chain_event, di.chain_stream) == hipSuccess &&

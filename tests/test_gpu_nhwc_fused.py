@@ -149,3 +149,47 @@ def test_a_captured_call_takes_the_streaming_kernels():
         torch.cuda.synchronize()
         graph.replay()
         assert_parity(buf.results(), ref, wl, what="replay", inp=inp)
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_a_call_beside_a_capture_leaves_the_capture_alone(layout):
+    """A stream that carried a kernel whose blocks wait is captured; a call on another stream meanwhile cannot be ordered behind
+    that kernel without recording on the captured stream.  It takes the streaming kernels, runs at once, and the graph
+    holds what was captured."""
+    wl = Workload(name="beside_capture", N=32, C=96, H=28, W=28, dtype="f32", layout=layout, mode=BS, n_s=4, data_seed=9,
+                  sampling_seed=11, layer_id=3)
+    inp = workloads.make_inputs(wl)
+    ref = oracle_reference(wl, inp)
+    a, b = bns.Buffers(wl, inp), bns.Buffers(wl, inp)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print(f"[gpu-case] a call beside a capture, {layout}", flush=True)
+
+    def capture():
+        with torch.cuda.stream(side):
+            a.forward()
+            a.backward()
+        assert _paths() == (2, 2)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            a.forward()
+            with torch.cuda.stream(other):
+                b.forward()
+                b.backward()
+            beside = _paths()
+            a.backward()
+        return beside
+
+    beside = _with({"fused_variant": 3}, capture)
+    assert beside == (1, 1)
+    other.synchronize()
+    assert_parity(b.results(), ref, wl, what="beside the capture", inp=inp)
+    for _ in range(3):
+        a.running_mean.copy_(torch.from_numpy(inp["running_mean"]))
+        a.running_var.copy_(torch.from_numpy(inp["running_var"]))
+        a.y.fill_(float("nan"))
+        a.dx.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        assert_parity(a.results(), ref, wl, what="replay", inp=inp)
