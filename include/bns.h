@@ -329,12 +329,13 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "norm_nt", "dx_nt"   non-temporal access mask + 1: bit 0 loads, bit 1 stores
  *   "reduce_nt"      the same for the backward reduction: bit 0 loads of x, bit 1 loads of dy, for the channels
  *                    that "cache_reuse" keeps (the others are loaded non-temporally)
- * Two more exist for the library's own tests only; they make results wrong on purpose and a caller has no
+ * Three more exist for the library's own tests only; they make results wrong on purpose and a caller has no
  * use for them:
  *   "test_spin_limit"    polls a block of a fused kernel waits for a team-mate's sums before it gives up
  *                    (1..2^21, the default)
  *   "test_mute_exchange" 1: no block publishes its sums, so every such wait runs out -- the two together let
  *                    a test reach the give-up path (NaN sums, the kernel ends normally) from the host
+ *   "test_mute_channel"  c + 1: no block of an N x H x W x C kernel publishes its sums of channel c
  * The options are atomics: setting one while another thread launches work is defined (that call sees the old
  * or the new value), but the launch choices of calls in flight are then anyone's guess -- set them first.
  * Notes on the fused kernels: blocks of a team exchange partial sums through the workspace and wait

@@ -75,6 +75,7 @@ const TuningEntry kTuningTable[] = {
     {"fused_coop", &Tuning::fused_coop, 1, 0, false},
     {"test_spin_limit", &Tuning::test_spin_limit, 1 << 21, 0, false},
     {"test_mute_exchange", &Tuning::test_mute_exchange, 1, 0, false},
+    {"test_mute_channel", &Tuning::test_mute_channel, 1 << 24, 0, false},
     {"fused_keep_x", &Tuning::fused_keep_x, 2, 0, false},
     {"fused_patch_mask", &Tuning::fused_patch_mask, 2, 0, false},
     {"split_statistics", &Tuning::split_statistics, 1, 0, false},

@@ -78,6 +78,7 @@ struct Tuning {
     // For the library's own tests of the give-up path only; a caller has no use for them.
     TuneInt test_spin_limit{0};             // polls a team member waits for a team-mate before giving up (default 2^21)
     TuneInt test_mute_exchange{0};          // 1: no member publishes its sums, so every wait runs out
+    TuneInt test_mute_channel{0};           // c + 1: no member publishes channel c (N x H x W x C)
 };
 extern Tuning g_tuning;
 inline int tuned(int v, int dflt) { return v > 0 ? v : dflt; }

@@ -47,6 +47,7 @@ struct RowArgs {
     int32_t TY;             // row lanes
     int32_t rounds;         // rows per thread
     int32_t keep_x;         // backward: x is read again where it lies in S, leave it in the memory-side cache
+    int32_t mute_channel;   // 1 + a channel that no member publishes (host-forced give-up, for tests of that path); 0: none
 };
 
 struct RowLane {
@@ -133,7 +134,7 @@ __device__ __forceinline__ void put_word(unsigned long long* p, uint32_t stamp, 
 
 // Waits until the N words that `at(i)` names carry the stamp; bounded like poll_pair.  False if the wait ran out.
 template <int N, typename At>
-__device__ __forceinline__ bool poll_words(const FusedArgs& F, uint32_t stamp, At&& at, uint32_t (&payload)[N], uint32_t* lost) {
+__device__ __forceinline__ bool poll_words(const FusedArgs& F, uint32_t stamp, At&& at, uint32_t (&payload)[N]) {
     uint32_t limit = F.spin_limit;
     for (uint32_t spin = 0; spin < limit; ++spin) {
         unsigned long long w[N];
@@ -151,19 +152,20 @@ __device__ __forceinline__ bool poll_words(const FusedArgs& F, uint32_t stamp, A
         __builtin_amdgcn_s_sleep(2);
     }
     __hip_atomic_fetch_add(&F.hdr->expired, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *lost = 1u;
     return false;
 }
 
 // This member's pair of channel t: published by thread t.
 __device__ __forceinline__ void tile_publish(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, double s1, double s2) {
     if (A.f.T == 1 || int(threadIdx.x) >= l.width || A.f.mute) return;
+    if (A.mute_channel == l.tile * int(A.ct_div.d) + int(threadIdx.x) + 1) return;
     unsigned long long* mine = pair_slot(A, l, set, l.j, int(threadIdx.x));
     put_word(mine, stamp, __float_as_uint(float(s1)));
     put_word(mine + 1, stamp, __float_as_uint(float(s2)));
 }
 
-// Adds the pairs of members first, first + step, ... of channel ch, B of them polled at a time; NaN if a wait ran out.
+// Adds the pairs of members first, first + step, ... of channel ch, B of them polled at a time.  If a wait ran out: NaN, and
+// lost[ch] is set (lost = null: the caller does not ask).
 template <int B>
 __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, int ch, int first, int step,
                                             uint32_t* lost, double& s1, double& s2) {
@@ -172,9 +174,10 @@ __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, 
         uint32_t w[2 * B];
         const bool ok = poll_words<2 * B>(A.f, stamp, [&](int i) {
             return pair_slot(A, l, set, min(m0 + (i / 2) * step, A.f.T - 1), ch) + (i & 1);
-        }, w, lost);
+        }, w);
         if (!ok) {
             s1 = s2 = __builtin_nan("");
+            if (lost) lost[ch] = 1u;
             return;
         }
 #pragma unroll
@@ -187,7 +190,7 @@ __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, 
 }
 
 // Totals over the members, by thread t < CT.  Every sum is taken in a fixed order, so all members get the same bits.
-// A wait that runs out leaves NaN and sets *lost.
+// A wait that runs out leaves NaN in that channel and sets its word of lost.
 __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, double* part, uint32_t* lost,
                                              double& s1, double& s2) {
     if (A.f.T == 1) return;
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
     __shared__ double part[2 * kRowThreads];
     __shared__ float piv[(MIXED ? 2 : 1) * kRowMaxTile];
     __shared__ float4 consts[kRowMaxTile];
-    __shared__ uint32_t words[3], lost;
+    __shared__ uint32_t words[3], lost[kRowMaxTile];
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
     const size_t C = size_t(F.C);
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             for (int e = 0; e < V; ++e) piv[kRowMaxTile + l.local + e] = coarse(p[e] / float(rows));
         }
     }
-    if (threadIdx.x == 0) lost = 0u;
+    if (threadIdx.x < uint32_t(kRowMaxTile)) lost[threadIdx.x] = 0u;
     stamp_accept(F, state, words);
     __syncthreads();
     const uint32_t stamp = read_stamp(F, words);
@@ -382,8 +385,8 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
         if (l.j == 0 && F.running_mean) rm = F.running_mean[c];
         if (l.j == 0 && F.running_var) rv = F.running_var[c];
     }
-    tile_collect(A, l, stamp, 0, part, &lost, s1, s2);
-    if (MIXED) tile_collect(A, l, stamp, 1, part, &lost, u1, u2);
+    tile_collect(A, l, stamp, 0, part, lost, s1, s2);
+    if (MIXED) tile_collect(A, l, stamp, 1, part, lost, u1, u2);
     if (leads) {
         const double m1 = s1 / F.s;
         double mean = double(piv[threadIdx.x]) + m1;
@@ -408,8 +411,8 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             F.save_mean[c] = mu;
             F.save_invstd[c] = r;
             const double al = double(F.momentum);
-            // (a wait for a team-mate that ran out leaves NaN statistics; the moving averages then stay as they are)
-            const bool arrived = F.T == 1 || static_cast<volatile uint32_t&>(lost) == 0u;
+            // (a wait for a team-mate that ran out leaves NaN statistics in its channel, whose moving averages then stay as they are)
+            const bool arrived = F.T == 1 || static_cast<volatile uint32_t*>(lost)[threadIdx.x] == 0u;
             if (F.running_mean && arrived) F.running_mean[c] = float((1.0 - al) * double(rm) + al * mean);
             if (F.running_var && arrived) F.running_var[c] = float((1.0 - al) * double(rv) + al * var);
         }
@@ -462,7 +465,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
     __shared__ float lds[2 * kRowThreads * V];
     __shared__ double part[2 * kRowThreads];
     __shared__ float4 consts[(MIXED ? 2 : 1) * kRowMaxTile];
-    __shared__ uint32_t words[3], lost;
+    __shared__ uint32_t words[3];
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
     const size_t C = size_t(F.C);
@@ -474,7 +477,6 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
     float mu[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) mu[e] = F.save_mean[l.col + e];
-    if (threadIdx.x == 0) lost = 0u;
 
     double a[V], q[V];
 #pragma unroll
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
         centre = MIXED ? F.mean_parts[F.C + c] : F.save_mean[c];
         if (MIXED) e_v = F.mean_parts[c];
     }
-    tile_collect(A, l, stamp, 0, part, &lost, s1, s2);
+    tile_collect(A, l, stamp, 0, part, nullptr, s1, s2);
     if (leads) {
         const float dbeta = float(s1);
         const float dgamma = float(s2 * double(r));
@@ -812,6 +814,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     const int spin = g_tuning.test_spin_limit;
     F.spin_limit = spin > 0 ? uint32_t(spin) : kSpinLimit;
     F.mute = g_tuning.test_mute_exchange;
+    A.mute_channel = g_tuning.test_mute_channel;
     F.eps = eps;
     F.momentum = momentum;
     F.s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);

@@ -92,6 +92,30 @@ def test_missing_team_mate_and_what_comes_after():
     assert_parity(good, oracle_reference(wl, inp), wl, what="after the give-up run", inp=inp)
 
 
+def test_a_wait_that_runs_out_concerns_its_channel_only():
+    """One channel of a tile is not published: its results are NaN and its moving averages stay, every other channel of
+    the tile is right, its moving averages (Eq. 8) included."""
+    wl = Workload(name="nhwc_one_channel", N=9, C=70, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=3, data_seed=5,
+                  sampling_seed=6, layer_id=1)
+    inp = workloads.make_inputs(wl)
+    buf = bns.Buffers(wl, inp)
+    print("[gpu-case] nhwc single launch, one channel not published", flush=True)
+    _with({"nhwc_fused": 1, "test_spin_limit": 64, "test_mute_channel": 6}, buf.forward)
+    assert _paths()[0] == 2
+    got, ref = buf.results(), oracle_reference(wl, inp)
+    assert bns.bns_expired_waits(buf.workspace) > 0
+    rest = np.arange(wl.C) != 5
+    for k in ("y", "save_mean", "save_invstd"):
+        bad = np.moveaxis(got[k], 1, 0)[5] if k == "y" else got[k][5]
+        assert np.isnan(bad).all(), k
+    for k in ("running_mean", "running_var"):
+        assert got[k][5] == inp[k][5], k
+        # one fp32 rounding of each term of Eq. 8 and of the statistic itself
+        np.testing.assert_allclose(got[k][rest], ref[k][rest], rtol=1e-5, atol=1e-6, err_msg=k)
+    y, want = got["y"][:, rest], ref["y"][:, rest]
+    assert np.abs(y - want).max() <= 1e-5 * np.abs(want).max()
+
+
 def test_sums_left_by_the_streaming_kernels_are_not_taken_for_a_team_mates():
     """The exchange takes any slot word that carries the launch's stamp.  Streaming calls on constant tensors leave zeros
     as partial sums in the workspace; the next stamp is then set to zero, which is what those words would carry
