@@ -1063,9 +1063,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.T = bestT;
     A.num_teams = best_blocks / bestT;
     if (A.num_teams > cg) A.num_teams = cg;
-    // (four sets of slots for Eq. 4: thousands of 64-thread blocks would not fit them; fewer teams then take more rounds)
-    if (mix && size_t(A.num_teams) * bestT * 4 * 2 * sizeof(unsigned long long) > slot_bytes)
-        A.num_teams = int(slot_bytes / (size_t(bestT) * 4 * 2 * sizeof(unsigned long long)));
+    // A team of one exchanges nothing and needs no slots.  The others: two sets of a pair per block, four in the forward pass
+    // of Eq. 4; thousands of 64-thread blocks can be more than the slots of a tensor of many channels hold, and fewer teams
+    // then take more rounds.
+    const size_t slots_per_team = bestT == 1 ? 0 : size_t(bestT) * (mix && !backward ? 4 : 2) * 2 * sizeof(unsigned long long);
+    if (mix && size_t(A.num_teams) * slots_per_team > slot_bytes) A.num_teams = int(slot_bytes / slots_per_team);
     if (A.num_teams < 1) return hipErrorNotSupported;
     A.tot = tot;
     const uint32_t rounds = uint32_t((cg + A.num_teams - 1) / A.num_teams);
@@ -1096,7 +1098,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.inv_s = float(1.0 / A.s);
 
     const int grid = A.num_teams * bestT;
-    if (size_t(grid) * (mix ? 4 : 2) * 2 * sizeof(unsigned long long) > slot_bytes) return hipErrorNotSupported;
+    if (size_t(A.num_teams) * slots_per_team > slot_bytes) return hipErrorNotSupported;
     {
         const uint64_t chunks = (uint64_t(tot) + launch_nt - 1) / launch_nt;
         if ((chunks + bestT - 1) / bestT > uint64_t(launch_k)) return hipErrorNotSupported;

@@ -758,3 +758,23 @@ def test_copy_reference():
         bns.bns_copy_reference(dst, src[:n])
         torch.cuda.synchronize()
         assert torch.equal(dst, src[:n])
+
+
+@pytest.mark.parametrize("shape", [(8, 3840, 8, 8), (4, 6000, 8, 8)], ids=["teams", "blocks_of_their_own"])
+def test_eq_4_with_more_64_thread_blocks_than_four_slot_sets_hold(shape):
+    """The forward pass of Eq. 4 takes four sets of exchange slots.  Two blocks per channel at 3840 channels: 480 KiB of them
+    where the workspace has 256 KiB, so that the channels are done in two rounds.  A block per channel at 6000 channels
+    exchanges nothing and takes no slots."""
+    N, C_, H, W = shape
+    wl = Workload(name="mixed_slots", N=N, C=C_, H=H, W=W, mode=BS, n_s=2, n_v=2, mix_beta=0.5, data_seed=21, sampling_seed=22,
+                  layer_id=3)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] Eq. 4 with 64-thread blocks {shape}", flush=True)
+    try:
+        bns.bns_set_option("path", 2)
+        bns.bns_set_option("fused_variant", 1)
+        res = bns.run_workload(wl, inp)
+    finally:
+        bns.bns_set_option("path", 0)
+        bns.bns_set_option("fused_variant", 0)
+    assert_parity(res, oracle_reference(wl, inp), wl, what=f"Eq. 4, 64-thread blocks {shape}", inp=inp)
