@@ -560,8 +560,9 @@ const void* kernel_ptr(int kind, int variant) {
 // Planes that this file takes with element-aligned vectors (those of 4 bf16 elements keep their 64-bit accesses here).
 inline bool fused_odd(const Dims& d) { return d.vec == 1 && odd_planes(d); }
 
-const void* kernel_for(const Dims& d, int kind, int variant) {
-    if (fused_odd(d))
+// odd: with element-aligned vectors (see launch_fused)
+const void* kernel_for(const Dims& d, bool odd, int kind, int variant) {
+    if (odd)
         return d.dtype == BNS_F32 ? kernel_ptr<f32_odd, 4>(kind, variant) : kernel_ptr<bf16_odd, 8>(kind, variant);
     if (d.dtype == BNS_F32) return d.vec == 4 ? kernel_ptr<float, 4>(kind, variant) : kernel_ptr<float, 1>(kind, variant);
     if (d.vec == 8) return kernel_ptr<bf16_t, 8>(kind, variant);
@@ -613,8 +614,8 @@ struct DeviceInfo {
 DeviceInfo g_dev[16];
 std::mutex g_dev_mutex;   // guards g_dev: launches may come from several host threads
 
-int combo_index(const Dims& d) {
-    if (fused_odd(d)) return d.dtype == BNS_F32 ? 5 : 6;
+int combo_index(const Dims& d, bool odd) {
+    if (odd) return d.dtype == BNS_F32 ? 5 : 6;
     if (d.dtype == BNS_F32) return d.vec == 4 ? 0 : 1;
     return d.vec == 8 ? 2 : d.vec == 4 ? 3 : 4;
 }
@@ -779,10 +780,22 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     DeviceInfo& di = *dip;
     if (!di.coop || di.cus <= 0) return hipErrorNotSupported;
 
-    const int vec = fused_odd(d) ? stream_vec(d) : d.vec;
+    // Planes that are no whole number of vectors: element-aligned vectors, except in channels of up to 2048 elements, which
+    // hardly fill the threads of a block with one element each.  What a vector costs there -- its offset within the plane, the
+    // elements it shares -- is more than the accesses it saves: medians over the tensors of a sweep, vectors against elements,
+    // 0.88 of the speed backward (30x16x9x9 bf16, a patch, 7.2 against 5.6 us) and 0.97 forward (4x226x5x5 bf16 5.2 against 4.5 us);
+    // forward with a patch, whose elements are read on their own, 1.03.  Eq. 4 has no kernels with one element per access.
+    // Whole planes in fp32 with more channels than (512, 8) blocks of vectors fit at once: up to 4096 elements, whose (512, 8) blocks
+    // of elements need fewer registers (2x1188x43x42 backward 14.2 against 19.1 us, 8x656x21x21 forward 8.5 against 9.4; where those do
+    // not fit at once either, forward, vectors: 11x1549x17x17 12.1 against 27.6).
+    const int64_t channel = int64_t(d.N) * d.HW;
+    const bool whole = ip.shared.h_cnt * ip.shared.w_cnt == d.HW;
+    const bool crowded = d.dtype == BNS_F32 && whole && cg > 2 * di.cus && (backward || cg <= 3 * di.cus);
+    const bool odd = fused_odd(d) && (mix || opt_variant != 0 || (!backward && !whole) || channel > (crowded ? 4096 : 2048));
+    const int vec = odd ? stream_vec(d) : d.vec;
     const uint32_t hwv = uint32_t((d.HW + vec - 1) / vec);
     const uint32_t tot = uint32_t(d.N) * hwv;
-    const int combo = combo_index(d);
+    const int combo = combo_index(d, odd);
     int kind = (backward ? 1 : (ip.shared.h_cnt * ip.shared.w_cnt == d.HW ? 0 : 2)) | (mix ? 4 : 0);
 
     // Choice of variant and team size, from sweeps on MI355X (64x256x56x56 fp32/bf16, 128x64x32x32,
@@ -804,10 +817,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         const Variant& va = kVariants[v];
         out->v = -1;
         int& bpc = di.blocks_per_cu[kind][combo][v];
-        if (bpc == 0 && kernel_for(d, kind, v) == nullptr) bpc = -1;        // flavour not built for this variant
+        if (bpc == 0 && kernel_for(d, odd, kind, v) == nullptr) bpc = -1;        // flavour not built for this variant
         if (bpc == 0) {
             int nb = 0;
-            const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel_for(d, kind, v), va.nt, 0);
+            const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel_for(d, odd, kind, v), va.nt, 0);
             if (oe != hipSuccess) return oe;
             bpc = nb > 0 ? nb : -1;
         }
@@ -833,11 +846,12 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         if (Tmin > blocks || Tmin > kMaxTeam) return hipSuccess;
         long bestT = 0, best_cost = 0, best_rounds = 0;
         // widen only while every thread still keeps >= 4 vectors: below that the exchange costs more
-        // than the extra blocks bring
+        // than the extra blocks bring (element-aligned vectors, which take longer: >= 2; 50x16x19x19 f32 backward 9.3 -> 8.7)
         long Thi = 2 * Tmin;
         if (long(cg) * Tmin < blocks) {
             Thi = blocks / cg;
-            if (Thi > chunks / 4) Thi = chunks / 4;
+            const long least = odd ? 2 : 4;
+            if (Thi > chunks / least) Thi = chunks / least;
             if (Thi < Tmin) Thi = Tmin;
         }
         for (long T = Tmin; T <= Thi && T <= kMaxTeam && T <= blocks; ++T) {
@@ -875,8 +889,42 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         }
         return hipSuccess;
     };
+    // Planes with element-aligned vectors.  Blocks of 64 to 256 threads only where one holds its channel: teams of them, which
+    // the rule above likes for their single round, are the slowest choice here (forward, us: 7x128x61x61 f32 18.7 against 10.6
+    // with (512, 8), 4x1600x25x25 bf16 34.2 against 9.5 with a (256, 4) block per channel, more rounds or not); then (512, 8), if
+    // the channels take one round or a block holds its channel, then (512, 16).
+    // Backward: x is kept, whatever S is, and (512, 8) is the kernel (us, against the rule above: 14x16x103x102 f32 11.0 against
+    // 13.8, 2x100x39x39 f32 5.7 against 7.3), except that a (256, 4) block that holds its channel is taken when the (512, 8) blocks need
+    // several rounds (3x1024x29x29 bf16 9.9 against 11.0).
+    // 400 tensors drawn afresh, groups of channels and one-element kernels as chosen, against one-element kernels throughout: forward
+    // 1.33 times the speed (geometric mean), 9 more than 3 % slower (worst 74x16x9x9 f32 7.6 against 6.9), backward 1.33, 15 (worst
+    // 17x528x15x14 f32 12.1 against 10.7); the two together never more than 6 % slower.
+    auto odd_plan = [&](Plan* out) -> hipError_t {
+        hipError_t pe;
+        Plan p;
+        out->v = -1;
+        if (backward) {
+            if (opt_keep_x == 2 || channel <= 2048) return hipSuccess;
+            const int plain = kind;
+            kind |= 2;
+            Plan small;
+            if ((pe = plan_for(2, &small)) != hipSuccess || (pe = plan_for(3, &p)) != hipSuccess) return pe;
+            if (small.v >= 0 && small.T == 1 && (p.v < 0 || p.rounds > 1)) *out = small;
+            else if (p.v >= 0) *out = p;
+            else kind = plain;
+            return hipSuccess;
+        }
+        for (int v = 0; v <= 4 && out->v < 0; ++v) {
+            if ((pe = plan_for(v, &p)) != hipSuccess) return pe;
+            if (p.v >= 0 && (p.T == 1 || (v >= 3 && p.rounds == 1))) *out = p;
+        }
+        return hipSuccess;
+    };
     Plan chosen;
-    if (opt_variant > 0) {
+    if (odd && opt_variant == 0 && (e = odd_plan(&chosen)) != hipSuccess) return e;
+    if (chosen.v >= 0) {
+        // taken
+    } else if (opt_variant > 0) {
         if (backward && opt_keep_x == 1) {        // both forced: the keep-x flavour of that variant, if built
             kind |= 2;
             if ((e = plan_for(opt_variant - 1, &chosen)) != hipSuccess) return e;
@@ -904,7 +952,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         // A channel per block of 50 vectors per thread, a sampled S, and planes that are no whole number of vectors: statistics
         // + Eq. 1 from the streaming kernels are faster (64x256x55x55 bf16: Batch Sampling 45.9 against 43.4 us, a patch, whose
         // elements are then read on their own, 53.6 against 47.2).
-        if (!backward && !everything && chosen.v > kTwoPerUnit && chosen.T == 1 && fused_odd(d) && opt_path != 2 && !mix)
+        if (!backward && !everything && chosen.v > kTwoPerUnit && chosen.T == 1 && odd && opt_path != 2 && !mix)
             return hipErrorNotSupported;
         // (Eq. 4 has no such alternative: its streaming forward is four launches)
         if (chosen.v >= 0 && !backward && !everything && chosen.rounds > 1 && opt_path != 2 && !mix)
@@ -1103,7 +1151,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         const uint64_t chunks = (uint64_t(tot) + launch_nt - 1) / launch_nt;
         if ((chunks + bestT - 1) / bestT > uint64_t(launch_k)) return hipErrorNotSupported;
     }
-    const void* kernel = pipe_kernel ? pipe_kernel : kernel_for(d, kind, best);
+    const void* kernel = pipe_kernel ? pipe_kernel : kernel_for(d, odd, kind, best);
     // A patch, and the block holds its channel alone: nothing happens while the vectors arrive that separately
     // read patch elements could run ahead for, so the statistics come from the registers
     // (64x256x56x56 bf16, 14x14 patch: forward 49.4 -> 42.8 us; full BN on the same tensor 41.5).
@@ -1118,7 +1166,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
             A.patch_stage = (bestT == 1 && slots <= uint64_t(kStageSlots)) ? 1 : 0;
         }
     }
-    if (!backward) t_last_fused_forward = kernel == kernel_for(d, kind, best) ? 1 : 2;
+    if (!backward) t_last_fused_forward = kernel == kernel_for(d, odd, kind, best) ? 1 : 2;
     void* params[] = {&A};
 
     bool chain = bestT > 1;

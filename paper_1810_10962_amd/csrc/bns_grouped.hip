@@ -461,11 +461,10 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // A run of more than half a block's threads leaves the others without work (3x700x33x33 f32: 273 of 512 threads, forward
     // 11.4 us against 8.6 with one element per access).
     if (opt == 0 && (G * d.HW + V - 1) / V > 256) return hipErrorNotSupported;
-    // Planes that are a whole number of vectors run well in the kernels of bns_fused.hip too: those keep the calls whose
-    // few channels would fill only part of the device with large blocks (backward, us: 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12
-    // bf16 8.5 against 8.9).
+    // Few channels would fill only part of the device with large blocks; the kernels of bns_fused.hip share a channel (backward, us:
+    // 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12 bf16 8.5 against 8.9, 102x64x23x23 bf16 11.0 against 19.3).
     const int blocks = (d.C + best_g - 1) / best_g;
-    if (opt == 0 && unit == 1 && blocks < 128 && best_v >= 2) return hipErrorNotSupported;
+    if (opt == 0 && blocks < 128 && best_v >= 2) return hipErrorNotSupported;
     // ... and those that would leave most of a last round of one block per compute unit empty (61x288x28x28 bf16 backward: 288
     // blocks, the step 40.8 against 41.7 us).
     if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > 256 && blocks % 256 != 0 && blocks % 256 < 128) return hipErrorNotSupported;

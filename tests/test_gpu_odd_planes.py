@@ -1,6 +1,6 @@
 """Planes that are no whole number of vectors, in the streaming kernels and in the single-launch kernels of every block
 size: planes of a vector and a few elements, one row, long odd planes; the last vector of a plane is shared with the one
-before it and must count once."""
+before it and must count once.  And the kernels that such planes get by default, on both sides of each line of the rule."""
 import pytest
 
 from paper_1810_10962_amd import bns, workloads
@@ -38,3 +38,27 @@ def test_odd_planes(shape, dtype):
                 for k in opts:
                     bns.bns_set_option(k, 0)
             assert_parity(res, ref, wl, what=f"odd {shape} {dtype} {mkw} {opts}", inp=inp)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    (1, 5, 45, 45),                 # 2025 elements per channel: one element per access
+    (1, 5, 29, 71),                 # 2059: vectors, one block
+    (1, 1100, 47, 47),              # more channels than (512, 8) blocks fit at once
+    (7, 20, 61, 61),                # teams of (512, 8) blocks
+    (2, 600, 67, 67),               # several rounds of them
+    (2, 530, 45, 45),               # fp32: 4050 elements per channel, more channels than blocks of vectors at once
+    (12, 3, 101, 99),               # few channels: the default's share of a block in bf16
+], ids=lambda s: "x".join(map(str, s)))
+def test_default_kernels_for_odd_planes(shape, dtype):
+    N, C_, H, W = shape
+    modes = [dict(mode=FULL), dict(mode=BS, n_s=max(1, N // 2)), dict(mode=FS, patch_h=max(1, H // 3), patch_w=max(1, W // 2))]
+    if N >= 3:
+        modes.append(dict(mode=FS, patch_h=2, patch_w=3, n_v=2, mix_beta=0.4))
+    for i, mkw in enumerate(modes):
+        wl = Workload(name="odd_default", N=N, C=C_, H=H, W=W, dtype=dtype, data_seed=75 + i, sampling_seed=20, layer_id=i, epoch=1,
+                      **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] odd planes, default kernels {shape} {dtype} {mkw}", flush=True)
+        res = bns.run_workload(wl, inp)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"odd, default {shape} {dtype} {mkw}", inp=inp)
