@@ -100,7 +100,7 @@ int stats_splits(const Dims& d, const IndexParams& ip, int cg) {
 int reduce_splits(const Dims& d, int cg) {
     const int32_t o = g_splits_reduce.load();
     if (o > 0) return o;
-    return auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / stream_vec(d)));
+    return auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / access_vec(d, odd_reduce(d))));
 }
 
 int channel_group(const Dims& d) {

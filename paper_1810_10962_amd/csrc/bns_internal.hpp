@@ -38,7 +38,22 @@ inline bool odd_planes(const Dims& d) {
     const int full = d.dtype == BNS_F32 ? 4 : 8;
     return d.HW % full != 0 && d.HW >= full;
 }
-inline int stream_vec(const Dims& d) { return odd_planes(d) ? (d.dtype == BNS_F32 ? 4 : 8) : d.vec; }
+inline int access_vec(const Dims& d, bool odd) { return odd ? (d.dtype == BNS_F32 ? 4 : 8) : d.vec; }
+inline int stream_vec(const Dims& d) { return access_vec(d, odd_planes(d)); }
+// Where they do not pay, planes keep accesses of d.vec elements.  Normalise, reduce and dx: tensors that take the launch and little
+// else, where the vector's place in its plane is worked out for nothing (4x400x7x7 bf16: normalise 2.8 against 3.4 us, dx 3.2
+// against 4.2).  Normalise and dx with single elements lose beyond about 2 MB (13x256x19x18 bf16 4.5 against 3.8 us), with the 64-bit
+// accesses of bf16 beyond about 8 MB (49x1024x10x10 6.4 against 5.5; 63x1024x6x6, 4.6 MB, 3.9 against 4.6); reduce, which
+// stores nothing, with single elements later: bf16 between 24 and 104 MB (32x512x27x27 14.0 against 14.9, 64x256x57x57 49.9 against 45.8),
+// fp32 at about 4 MB (29x100x13x15, 2.3 MB, 7.0 against 7.8; 3x1312x17x17, 4.6 MB, 7.8 against 7.8).
+inline size_t tensor_size(const Dims& d) { return size_t(d.N) * size_t(d.C) * size_t(d.HW) * (d.dtype == BNS_F32 ? 4 : 2); }
+inline bool odd_passes(const Dims& d) { return odd_planes(d) && tensor_size(d) >= (size_t(d.vec == 1 ? 2 : 8) << 20); }
+inline bool odd_reduce(const Dims& d) {
+    return odd_planes(d) && tensor_size(d) >= (size_t(d.vec == 4 ? 8 : d.dtype == BNS_F32 ? 4 : 32) << 20);
+}
+// Statistics of a channel in one block of 1024 threads: with 64-bit accesses two blocks share a compute unit, with 128-bit ones
+// of bf16 one (100x1312x6x6, 4 samples: 8.3 against 14.2 us); single elements are slower than either.
+inline bool odd_one_block(const Dims& d) { return odd_planes(d) && d.vec == 1; }
 
 constexpr int kMaxSplits = 64;  // upper bound on blocks that share one channel's reduction
 

@@ -595,9 +595,10 @@ hipError_t dispatch_unroll_nt(int U, int NT, F&& f) {
     }
 }
 
+// odd: element-aligned vectors (see odd_planes)
 template <typename F>
-hipError_t dispatch(const Dims& d, F&& f) {
-    if (odd_planes(d)) return d.dtype == BNS_F32 ? f(f32_odd(), VecTag<4>()) : f(bf16_odd(), VecTag<8>());
+hipError_t dispatch(const Dims& d, bool odd, F&& f) {
+    if (odd) return d.dtype == BNS_F32 ? f(f32_odd(), VecTag<4>()) : f(bf16_odd(), VecTag<8>());
     if (d.dtype == BNS_F32) {
         if (d.vec == 4) return f(float(), VecTag<4>());
         return f(float(), VecTag<1>());
@@ -628,7 +629,7 @@ hipError_t launch_stats_partial(const Dims& d, const IndexParams& ip, const void
     const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
     const dim3 grid(uint32_t(cg) * uint32_t(splits));
     if (planes) {
-        return dispatch(d, [&](auto t, auto vt) {
+        return dispatch(d, odd_planes(d), [&](auto t, auto vt) {
             using T = decltype(t);
             constexpr int V = decltype(vt)::value;
             const uint32_t hwv = ceil_div(uint32_t(d.HW), V);
@@ -665,14 +666,14 @@ bool launch_stats_one_block(const Dims& d, const IndexParams& ip, const void* x,
                             float momentum, float* save_mean, float* save_invstd, float* running_mean,
                             float* running_var, hipStream_t st, hipError_t* err) {
     const bns_box& b = ip.shared;
-    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
+    const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && access_vec(d, odd_one_block(d)) > 1;
     const uint64_t pts = uint64_t(b.n_cnt) * b.h_cnt * b.w_cnt;
-    const uint64_t accesses = planes ? pts / stream_vec(d) : pts;
+    const uint64_t accesses = planes ? pts / access_vec(d, odd_one_block(d)) : pts;
     if (accesses > uint64_t(kOneBlock) * 16 || cg < 64) return false;     // <= 16 accesses per thread; enough blocks
-    const uint32_t hwv = ceil_div(uint32_t(d.HW), uint32_t(stream_vec(d)));
+    const uint32_t hwv = ceil_div(uint32_t(d.HW), uint32_t(access_vec(d, odd_one_block(d))));
     const uint32_t patch = uint32_t(b.h_cnt) * uint32_t(b.w_cnt);
     const dim3 grid{uint32_t(cg)}, blk{uint32_t(kOneBlock)};
-    *err = dispatch(d, [&](auto t, auto vt) {
+    *err = dispatch(d, odd_one_block(d), [&](auto t, auto vt) {
         using T = decltype(t);
         constexpr int V = decltype(vt)::value;
         if (planes)
@@ -725,7 +726,7 @@ hipError_t launch_stats_finalize_mixed(const Dims& d, const IndexParams& ip_s, c
 hipError_t launch_normalize(const Dims& d, const void* x, const float* gamma, const float* beta,
                             const float* mean, const float* invstd, void* y, int c0, int cg, hipStream_t st,
                             float var_eps) {
-    return dispatch(d, [&](auto t, auto vt) {
+    return dispatch(d, odd_passes(d), [&](auto t, auto vt) {
         using T = decltype(t);
         constexpr int V = decltype(vt)::value;
         return dispatch_unroll_nt(tuned(g_tuning.norm_unroll, d.dtype == BNS_F32 ? 1 : 2), tuned_nt(g_tuning.norm_nt, 3), [&](auto ut, auto nt) {
@@ -752,7 +753,7 @@ hipError_t launch_reduce_partial(const Dims& d, const void* x, const void* dy, c
     const size_t fit = kKeepBytes / (per_channel * (both ? 2 : 1));
     const int keep_channels = reuse == 2 ? 0 : reuse == 1 ? cg : int(std::min<size_t>(size_t(cg), fit));
     const int keep = keep_channels == 0 ? 0 : both ? 2 : 1;
-    return dispatch(d, [&](auto t, auto vt) {
+    return dispatch(d, odd_reduce(d), [&](auto t, auto vt) {
         using T = decltype(t);
         constexpr int V = decltype(vt)::value;
         return dispatch_unroll_nt(tuned(g_tuning.reduce_unroll, 2), tuned_nt(g_tuning.reduce_nt, keep == 2 ? 0 : keep == 1 ? 1 : 3), [&](auto ut, auto nt) {
@@ -790,7 +791,7 @@ hipError_t launch_dx(const Dims& d, const IndexParams& ip, const void* x, const 
         sets.w_s = float(1.0 / s);
         sets.centre_s = mean;
     }
-    return dispatch(d, [&](auto t, auto vt) {
+    return dispatch(d, odd_passes(d), [&](auto t, auto vt) {
         using T = decltype(t);
         constexpr int V = decltype(vt)::value;
         return dispatch_unroll_nt(tuned(g_tuning.dx_unroll, d.dtype == BNS_F32 ? 1 : 2), tuned_nt(g_tuning.dx_nt, 3), [&](auto ut, auto nt) {

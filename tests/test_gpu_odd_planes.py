@@ -62,3 +62,43 @@ def test_default_kernels_for_odd_planes(shape, dtype):
         print(f"[gpu-case] odd planes, default kernels {shape} {dtype} {mkw}", flush=True)
         res = bns.run_workload(wl, inp)
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"odd, default {shape} {dtype} {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("shape,dtype", [
+    ((3, 100, 41, 42), "f32"),      # 2.07 MB, below the line of the streaming passes: one element per access
+    ((3, 100, 43, 45), "f32"),      # 2.3 MB: vectors
+    ((5, 100, 45, 47), "bf16"),     # 2.1 MB, vectors of eight
+    ((9, 139, 58, 58), "bf16"),     # 8.4 MB and planes of 420.5 vectors: eight elements, below the line (64-bit accesses) four
+    ((9, 138, 58, 58), "bf16"),
+    ((60, 95, 3, 63), "f32"),       # 4.3 MB, vectors in the reduction, too; 47.25 of them per plane
+], ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else s)
+def test_odd_planes_in_the_streaming_kernels(shape, dtype):
+    N, C_, H, W = shape
+    for i, mkw in enumerate((dict(mode=FULL), dict(mode=BS, n_s=max(1, N // 3)), dict(mode=FS, patch_h=H // 2, patch_w=W // 2),
+                             dict(mode=FS, patch_h=2, patch_w=2, n_v=1, mix_beta=0.3))):
+        wl = Workload(name="odd_streaming", N=N, C=C_, H=H, W=W, dtype=dtype, data_seed=80 + i, sampling_seed=21, layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        ref = oracle_reference(wl, inp)
+        for opts in ({"path": 1}, {"path": 1, "split_statistics": 1, "splits_reduce": 3, "norm_unroll": 4, "dx_unroll": 4}):
+            print(f"[gpu-case] odd planes, streaming {shape} {dtype} {mkw} {opts}", flush=True)
+            try:
+                for k, v in opts.items():
+                    bns.bns_set_option(k, v)
+                res = bns.run_workload(wl, inp)
+            finally:
+                for k in opts:
+                    bns.bns_set_option(k, 0)
+            assert_parity(res, ref, wl, what=f"odd, streaming {shape} {dtype} {mkw} {opts}", inp=inp)
+
+
+def test_odd_planes_in_the_bf16_reduction():
+    """34 MB: the sums of Eq. 5 from vectors of eight elements."""
+    wl = Workload(name="odd_reduce", N=17, C=100, H=99, W=101, dtype="bf16", mode=BS, n_s=4, data_seed=86, sampling_seed=22, layer_id=5)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] odd planes, streaming reduction {wl.shape} bf16", flush=True)
+    bns.bns_set_option("path", 1)
+    try:
+        res = bns.run_workload(wl, inp)
+    finally:
+        bns.bns_set_option("path", 0)
+    assert_parity(res, oracle_reference(wl, inp), wl, what="odd, bf16 reduction", inp=inp)
