@@ -12,7 +12,8 @@
 // a persistent grid's shallower queue of loads.  Measured against the streaming kernels (three launches per direction), us
 // forward / backward, Batch Sampling: 50x150x19x19 f32 13.8 / 15.5 against 17.7 / 25.4 (one element per access there);
 // 64x512x14x14 bf16 14.7 / 15.9 against 19.1 / 25.6; 64x256x28x28 f32 24.1 / 32.5 against 31.8 / 40.8; 64x256x56x56 bf16
-// 45.5 / 65.9 against 49.2 / 74.6, full BN 48.3 / 79.3 against 60.9 / 90.3.
+// 45.9 / 65.7 against 48.4 / 72.2 (the step of the benchmark 115 against 118; in its loops of one direction the forward gains nothing,
+// 50.8 against 50.7), full BN 48.1 / 78.3 against 59.5 / 88.0.
 //
 // Columns that are no whole number of vectors: the last vector of a row is moved back so that it ends with the row.  The
 // channels it shares with the vector before it are computed twice, with the same bits.
@@ -686,8 +687,8 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
 constexpr int kRowKeeps[] = {4, 8, 16, 40};     // (the last: see most_rows)
 constexpr int kNumRowKeeps = sizeof(kRowKeeps) / sizeof(kRowKeeps[0]);
 // Rows per thread up to which a block takes every row of its columns (13x29x7x10 bf16, 8 rows: 10.7 / 12.7 us against 10.0 /
-// 8.7 streaming; 28x64x6x6 f32, 8 rows: 8.1 / 10.2 against 11.9 / 11.0).
-constexpr int row_solo(int V, bool backward) { return V == 8 ? (backward ? 4 : 5) : 8; }
+// 8.7 streaming; 28x64x6x6 f32, 8 rows: forward 8.1 against 11.9; backward 52x349x4x4 f32, 7 rows, 12.7 against 10.5).
+constexpr int row_solo(int V, bool backward) { return V == 8 ? (backward ? 4 : 5) : (backward ? 4 : 8); }
 // What the registers hold beside the sums (Eq. 4 forward walks the rows twice).
 constexpr int most_rows(int V, bool backward, bool mixed) {
     return backward ? (V == 8 ? 28 : 40) : mixed ? 20 : (V == 8 ? 36 : 40);
@@ -776,16 +777,35 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     const int rounds = (groups + T - 1) / T;
     // Beyond what the registers hold, rows are read twice, and the streaming kernels' short blocks do that faster; where the line
     // lies (us, streaming against this, forward / backward, 64x256xHxW): f32 40x40 (50 rows per thread), Batch Sampling
-    // 44.4 / 72.3 against 44.2 / 58.7, a patch 47.4 / 72.7 against 48.4 / 58.8; 56x56 (98 rows) 77 / 134 against 84 / 134.
-    // Full BN forward reads everything twice there: 103 against 89, 128 samples 202 against 187.
-    const bool everything = b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W;
+    // 44.0 / 71.2 against 43.8 / 58.5, a patch 47.1 / 71.1 against 47.6 / 58.9; 56x56 (98 rows) 76 / 130 against 83 / 130.
+    // Full BN forward reads everything twice there, up to where little of it is left in the memory-side cache: f32 128 samples (196
+    // rows) 196 against 187, 160 (245) 245 against 240, 192 (294) 295 against 296, 256 (392) 391 against 411; bf16 the same
+    // rows, 320 samples 251 against 245, 512 398 against 410.
+    // A last tile with idle lanes costs their share of the bandwidth: 41x80x80x80 f32 (20 of 24 lanes, 49 rows) forward 41.6
+    // against 45.1, 100x96x60x60 bf16 (12 of 16, 44 rows) backward 60.5 against 77.0, 60x80x64x64 f32 backward 67.7 against 73.9, full BN
+    // forward 45.8 against 40.4 with 46 rows, 78x80x70x70 64.9 against 69.8 with 72.
+    const bool everything = b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W, idle = CV * 10 < tiles * TX * 9;
     const int most = most_rows(V, backward, mix != nullptr);
-    if (opt != 1 && T > 1 && rounds > (backward ? 64 : everything && !mix ? 1 << 30 : make_rowset(d, b).contiguous ? most + most * 2 / 5 : most))
-        return hipErrorNotSupported;
+    // Rows that begin on no 64 bytes are slower the second time, too: 91x92x56x56 f32, a patch, 53 rows, backward 76.5 against 100.6
+    // (where streaming has to take narrower accesses for want of whole vectors, this is still the faster).
+    const bool split_lines = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 != 0 && d.C % V == 0;
+    const int limit = !backward && everything && !mix                         ? (idle ? most + most * 2 / 5 : 256)
+                      : idle || split_lines                                   ? most
+                      : backward                                              ? 64
+                      : make_rowset(d, b).contiguous                          ? most + most * 2 / 5
+                                                                              : most;
+    if (opt != 1 && T > 1 && rounds > limit) return hipErrorNotSupported;
+    // Ragged bf16 rows of small tensors: streaming takes single elements, and that is enough (13x137x7x7 backward 9.4 against 11.1 us,
+    // 21x58x12x12 forward 9.8 against 11.2; 12x26x25x25, 390 KB, 9.9 / 11.2 against 10.5 / 10.1).
+    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 400000) return hipErrorNotSupported;
     // bf16 rows that do not begin on cache lines: tiles of one and the same line are read by different blocks (12x432x73x70, us:
-    // 42 / 52 against 35 / 48 streaming; 60x336x38x38 40 / 52 against 33 / 53; below 16 rows per thread this is the faster).
+    // 42 / 52 against 35 / 48 streaming; 60x336x38x38 40 / 52 against 33 / 53; below 16 rows per thread this is the faster, forward
+    // with rows that begin on no 64 bytes below 10: 27x272x37x40, 12 rows, 25.0 against 21.7, 10x176x68x68, 8 rows, 20.5 against 22.7).
+    // Full BN forward, which streaming reads twice as well, until it reads rows again itself (4x1736x84x84 70.7 against 65.5).
     const size_t pitch = size_t(d.C) * 2;
-    if (opt != 1 && T > 1 && rounds > 16 && V == 8 && d.C % V == 0 && !(everything && !backward) && pitch % (backward ? 64 : 128) != 0)
+    const int lines = backward || pitch % 64 == 0 ? 16 : 10;
+    if (opt != 1 && T > 1 && rounds > lines && V == 8 && d.C % V == 0 && !(everything && !backward && rounds <= most) &&
+        pitch % (backward ? 64 : 128) != 0)
         return hipErrorNotSupported;
     int variant = 0;
     while (variant + 1 < kNumRowKeeps && kRowKeeps[variant] < rounds) ++variant;

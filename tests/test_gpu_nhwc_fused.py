@@ -69,6 +69,24 @@ def test_rows_per_thread(rounds, dtype):
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
 
 
+@pytest.mark.parametrize("shape,dtype,want", [
+    ((13, 137, 7, 7), "bf16", (3, 1)),          # ragged rows, 175 KB: not in waiting kernels
+    ((30, 137, 12, 12), "bf16", (2, 2)),        # the same rows, 1.2 MB
+    ((52, 349, 4, 4), "f32", (3, 2)),           # seven rows per thread: one block takes them forward, a team backward
+    ((4, 349, 4, 4), "f32", (3, 3)),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_default_choice_on_both_sides_of_its_lines(shape, dtype, want):
+    N, C_, H, W = shape
+    for i, mkw in enumerate((dict(mode=FULL), dict(mode=BS, n_s=2), dict(mode=FS, patch_h=2, patch_w=3))):
+        wl = Workload(name="nhwc_default", N=N, C=C_, H=H, W=W, dtype=dtype, layout="nhwc", data_seed=65 + i, sampling_seed=4,
+                      layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc default kernels {shape} {dtype} {mkw}", flush=True)
+        res = bns.run_workload(wl, inp)
+        assert _paths() == want
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"nhwc default {shape} {dtype} {mkw}", inp=inp)
+
+
 def test_missing_team_mate_and_what_comes_after():
     wl = Workload(name="nhwc_give_up", N=9, C=70, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=3, data_seed=5,
                   sampling_seed=6, layer_id=1)
