@@ -764,8 +764,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     // (a channel in one block of 50 vectors per thread), and faster only where this file's kernels need several rounds
     // (64x1024x14x14 f32: 25.0 -> 21.0): see below.
     const bool groups = cg == d.C && opt_variant == 0 && opt_keep_x == 0 && opt_pipe == 0 && opt_masked == 0;
+    int cus = 0;                                        // (asked for before the lock is taken: device_units takes it, too)
+    hipError_t e = device_units(&cus);
+    if (e != hipSuccess) return e;
     auto grouped = [&]() {
-        const hipError_t ge = launch_grouped(d, ip, backward, io, eps, momentum, st, mix);
+        const hipError_t ge = launch_grouped(d, ip, backward, io, eps, momentum, st, cus, mix);
         if (ge == hipSuccess) (backward ? t_last_fused_backward : t_last_fused_forward) = backward ? 4 : 3;
         return ge;
     };
@@ -775,8 +778,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     }
     std::lock_guard<std::mutex> lock(g_dev_mutex);      // planning only; released before the launch returns
     DeviceInfo* dip = nullptr;
-    hipError_t e = current_device(&dip);
-    if (e != hipSuccess) return e;
+    if ((e = current_device(&dip)) != hipSuccess) return e;
     DeviceInfo& di = *dip;
     if (!di.coop || di.cus <= 0) return hipErrorNotSupported;
 
@@ -944,8 +946,12 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
             if ((e = plan_for(kTwoPerUnit, &p)) != hipSuccess) return e;
             if (p.v >= 0) chosen = p;
         }
-        // several rounds: groups of channels, if they fit, take one
-        if (groups && !backward && (chosen.v < 0 || chosen.rounds > 1)) {
+        // several rounds: groups of channels, if they fit, take one or two.  (Not full BN in bf16 whose channels fill their block: that
+        // streams as well, 128x1024x16x16 28.0 against 32.8 us, 128x2048x8x8 16.0 against 17.0; a half-filled block does not,
+        // 64x1024x16x16 20.5 against 15.0.)
+        const bool filled = chosen.v >= 0 && chosen.T == 1 && everything && d.vec == 8 &&
+                            8 * uint64_t(tot) >= 7 * uint64_t(kVariants[chosen.v].nt) * uint64_t(kVariants[chosen.v].kmax);
+        if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1)) {
             const hipError_t ge = grouped();
             if (ge != hipErrorNotSupported) return ge;
         }

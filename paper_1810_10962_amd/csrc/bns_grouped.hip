@@ -434,17 +434,17 @@ void launch_any(int variant, bool backward, bool mixed, const GroupArgs& A, dim3
 }  // namespace
 
 hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
-                          hipStream_t st, const FusedMix* mix) {
+                          hipStream_t st, int cus, const FusedMix* mix) {
     const int V = d.dtype == BNS_F32 ? 4 : 8;
     const int opt = g_tuning.grouped, opt_g = g_tuning.grouped_channels;
-    if (d.HW < V || opt == 2) return hipErrorNotSupported;
+    if (d.HW < V || opt == 2 || cus <= 0) return hipErrorNotSupported;
     // Channels per group: about one block per compute unit (64x2048x7x7 bf16, forward + backward: groups of 8, 256 blocks,
     // 23 us; of 4, 28 us; of 2, 29 us; 64x512x7x7: groups of 2, 256 blocks, 15.4 us; of 8, 18.5 us), whole vectors per run
     // (multiples of `unit` channels) if that leaves as many blocks, fewer when the rows of a group would not fit the
     // largest block.  Block: the smallest that holds the group.
     const int unit = d.HW % V == 0 ? 1 : d.HW % (V / 2) == 0 ? 2 : (V == 8 && d.HW % 2 == 0) ? 4 : V;
     const int64_t room = int64_t(kGroupVariants[kNumGroupVariants - 1].nt) * kGroupVariants[kNumGroupVariants - 1].k;
-    int64_t G = opt_g > 0 ? opt_g : (d.C + 255) / 256;
+    int64_t G = opt_g > 0 ? opt_g : (d.C + cus - 1) / cus;
     G = std::min<int64_t>({G, room * V / (int64_t(d.HW) * d.N), kGroupMaxChannels, d.C});
     int best_v = -1;
     for (; G >= 1 && best_v < 0; --G) {
@@ -464,12 +464,22 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // Few channels would fill only part of the device with large blocks; the kernels of bns_fused.hip share a channel (backward, us:
     // 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12 bf16 8.5 against 8.9, 102x64x23x23 bf16 11.0 against 19.3).
     const int blocks = (d.C + best_g - 1) / best_g;
-    if (opt == 0 && blocks < 128 && best_v >= 2) return hipErrorNotSupported;
+    if (opt == 0 && blocks < cus / 2 && best_v >= 2) return hipErrorNotSupported;
     // ... and those that would leave most of a last round of one block per compute unit empty (61x288x28x28 bf16 backward: 288
     // blocks, the step 40.8 against 41.7 us).
-    if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > 256 && blocks % 256 != 0 && blocks % 256 < 128) return hipErrorNotSupported;
+    if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > cus && blocks % cus != 0 && blocks % cus < cus / 2) return hipErrorNotSupported;
+    // Forward, planes of whole vectors: beyond two rounds of blocks, of which one holds a compute unit and neither loads while it
+    // stores nor the other way round, the other kernels are ahead (Batch Sampling, us: 96x1024x20x20 bf16, 1024 blocks, 38.1 against
+    // 46.2, 128x2048x14x14 f32, 2048 blocks, 77.9 against 97.4; with two rounds 64x2048x14x14 bf16 31.3 against 25.3).
+    if (opt == 0 && !backward && d.vec > 1 && blocks > 2 * cus) return hipErrorNotSupported;
+    // Backward, planes of whole full-width vectors that begin on cache lines (fp32) or any (bf16): from the second round on the pipelined
+    // kernel is ahead (128x1024x16x16, us: bf16 39.1 against 42.5, f32 74.3 against 80.0; 96x1024x20x20 bf16 57.5 against 62.0; otherwise
+    // not: 64x2048x14x14 bf16 48.5 against 34.9, f32 74.1 against 67.9).
+    const bool lines = V == 8 || d.HW * 4 % 128 == 0;
+    if (opt == 0 && backward && d.vec == V && lines && !mix && blocks > cus) return hipErrorNotSupported;
     // Calls that take 5 us whatever they do: working out the columns costs more there than it saves (forward, us: 8x224x5x5 f32
-    // 4.8 against 5.4, 37x96x9x9 bf16 5.7 against 6.3; backward, 6x144x7x7 bf16 5.0 against 5.4).
+    // 4.8 against 5.4, 37x96x9x9 bf16 5.7 against 6.3; backward, 6x144x7x7 bf16 5.0 against 5.4).  Just above the lines the median gain is
+    // nil: forward, 1.0 to 1.3 MB, 1.00 (30 tensors), backward, bf16, 0.3 to 0.5 MB, 1.06 (66); fp32 below 0.1 MB 1.03 (54).
     const int64_t bytes = int64_t(d.N) * d.C * d.HW * (V == 8 ? 2 : 4);
     if (opt == 0 && bytes < (backward ? (V == 8 ? 300000 : 0) : 1000000) && !mix) return hipErrorNotSupported;
     const GroupVariant gv = kGroupVariants[best_v];

@@ -186,9 +186,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
                         float momentum, void* header, void* slots, size_t slot_bytes, int c0, int cg, hipStream_t st,
                         const FusedMix* mix = nullptr, bool may_create_event = true);
 // The same for small planes, a block per group of channels (bns_grouped.hip): nothing crosses blocks.
-// hipErrorNotSupported: a group does not fit a block, or the other kernels are faster.
+// hipErrorNotSupported: a group does not fit a block, or the other kernels are faster.  cus: compute units of the device.
 hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
-                          hipStream_t st, const FusedMix* mix = nullptr);
+                          hipStream_t st, int cus, const FusedMix* mix = nullptr);
 // Reads the count of waits that ran out from a workspace header (0 if the header was never set up) and clears it.
 hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 

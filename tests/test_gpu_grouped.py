@@ -3,6 +3,7 @@ a last group of fewer channels, every block size, both directions -- each agains
 infinities and NaNs outside S, against the streaming kernels."""
 import numpy as np
 import pytest
+import torch
 
 from paper_1810_10962_amd import bns, workloads
 from paper_1810_10962_amd.workloads import BS, FS, FULL, NS, Workload
@@ -78,3 +79,29 @@ def test_what_lies_outside_s_does_not_reach_the_statistics(dtype):
         # the same numbers up to the order of a few hundred 32-bit additions, and one rounding to 8 bits for bf16
         tol = 2e-5 if dtype == "f32" or k not in ("y", "dx") else 1e-2
         assert np.allclose(got[k][ok], want[k][ok], rtol=tol, atol=tol), k
+
+
+def test_default_choice_where_the_other_kernels_take_several_rounds():
+    """Forward, planes of whole vectors: the planner turns to groups of channels when a channel per block means several
+    rounds, and keeps to the other kernels when the groups would, too."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    for C_, N, want in ((4 * units, 64, 3), (4 * units, 96, 1)):        # groups of four channels; of one, four rounds of blocks
+        side = 14 if want == 3 else 20
+        wl = Workload(name="grouped_rounds", N=N, C=C_, H=side, W=side, dtype="bf16", mode=BS, n_s=8, data_seed=44, sampling_seed=9,
+                      layer_id=2)
+        x = torch.randn(N, C_, side, side, device="cuda").to(torch.bfloat16)
+        shape, spec = bns.make_shape(N, C_, side, side, "bf16"), bns.make_spec(BS, 8, 0, 0, 0, 2, 0)
+        vec = [torch.rand(C_, device="cuda") for _ in range(6)]
+        y = torch.empty_like(x)
+        ws = torch.empty(bns.bns_workspace_bytes(shape, spec), dtype=torch.uint8, device="cuda")
+        print(f"[gpu-case] grouped or not, {wl.shape}", flush=True)
+        bns.bns_forward(shape, spec, 9, x, vec[0], vec[1], 1e-5, 0.1, y, vec[2], vec[3], vec[4], vec[5], ws)
+        path, kind = bns.bns_get_option("last_path_forward"), bns.bns_get_option("last_fused_forward")
+        assert (path, kind) == (2, 3) if want == 3 else path == 1
+        n0 = int(bns.bns_sample_index(shape, spec, 9)[0][0])
+        s = x[n0:n0 + 8].double()
+        mean, var = s.mean(dim=(0, 2, 3)), s.var(dim=(0, 2, 3), unbiased=False)
+        assert torch.allclose(vec[2].double(), mean, rtol=0, atol=1e-5)     # 1600 and more terms of size one: some 1e-6 in 32 bits
+        want_y = (x.double() - mean[None, :, None, None]) * (vec[0].double() / torch.sqrt(var + 1e-5))[None, :, None, None]
+        want_y += vec[1].double()[None, :, None, None]
+        assert float((y.double() - want_y).abs().max()) <= 2 ** -8 * float(want_y.abs().max()) + 1e-3    # one rounding to 8 bits
