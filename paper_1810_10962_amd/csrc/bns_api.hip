@@ -384,7 +384,7 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
     if (nhwc(d)) {
         if (g_tuning.path == 2) return BNS_EUNSUPPORTED;
         const FusedIo io = backward_io(x, dy, dx, gamma, save_mean, save_invstd, dgamma, dbeta);
-        if (g_tuning.nhwc_split_dx == 0 && nhwc_single_launch(d, ip, true, io, 0.f, 0.f, workspace, st, nullptr, may_create_event, &s))
+        if (g_tuning.nhwc_split_dx != 1 && nhwc_single_launch(d, ip, true, io, 0.f, 0.f, workspace, st, nullptr, may_create_event, &s))
             return s;
         t_last_path_backward = 1;
         // Eq. 6 outside S needs none of the sums: the reduction kernel can write dx there while it has dy in

@@ -85,11 +85,11 @@ struct Tuning {
     TuneInt fused_coop{0};                  // 1: launch the fused kernels with hipLaunchCooperativeKernel
     TuneInt split_statistics{0};            // 1: forward statistics always as partial sums + finalize
     TuneInt nhwc_blocks{0};                 // blocks an N x H x W x C reduction aims for (default kNhwcBlocks)
-    TuneInt nhwc_small{0};                  // 2: never take the one-launch kernels for small N x H x W x C tensors
+    TuneInt nhwc_small{0};                  // 2: streaming kernels for N x H x W x C tensors of every size (as nhwc_fused = 2)
     TuneInt nhwc_fused{0};                  // single-launch kernels of this layout: 1 whenever they fit, 2 never, 0 from a size on
     TuneInt nhwc_fused_lanes{0};            // column vectors of a tile in those kernels
     TuneInt nhwc_ew_rows{0};                // rows per row lane in its element-wise kernels (default kNhwcEwRows)
-    TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always, 2 never, 0 when S is at most half
+    TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always; 0, 2 never
     // For the library's own tests of the give-up path only; a caller has no use for them.
     TuneInt test_spin_limit{0};             // polls a team member waits for a team-mate before giving up (default 2^21)
     TuneInt test_mute_exchange{0};          // 1: no member publishes its sums, so every wait runs out

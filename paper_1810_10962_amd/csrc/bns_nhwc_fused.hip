@@ -1,8 +1,8 @@
 // Single-launch kernels for the N x H x W x C layout: the statistics (or the sums of Eq. 5) and the element-wise pass of
 // one direction in one kernel, with as much of the tensor as fits kept in registers in between.
 //
-// The tensor is a matrix of M = N*H*W rows by C columns.  A block of 512 threads owns a tile of CT columns (whole rows up
-// to 512 channels) and one of T shares of the rows: thread (ty, tx) holds V channels of the rows (k * T + j) * TY + ty, so
+// The tensor is a matrix of M = N*H*W rows by C columns.  A block of 512 threads owns a tile of CT <= 128 columns
+// and one of T shares of the rows: thread (ty, tx) holds V channels of the rows (k * T + j) * TY + ty, so
 // that the device as a whole walks the tensor front to back.  The first K
 // of a thread's rows stay in registers; what does not fit is read again in the second phase, from the memory-side cache if
 // it fits there.  The T blocks of a tile exchange their column sums once, through the stamped slots of the other single-launch
@@ -725,7 +725,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     int cus = 0;
     hipError_t e = device_units(&cus);
     if (e != hipSuccess) return e;
-    // Column tiles of up to 512 channels, and never a last tile narrower than a vector.
+    // Column tiles of up to 128 channels, and never a last tile narrower than a vector.
     const int CV = (d.C + V - 1) / V;
     const size_t bytes = size_t(M) * size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2);
     auto lanes_for = [&](int lanes) {

@@ -235,6 +235,24 @@ def test_backward_with_dx_split_by_the_branches_of_eq_6(shape, mkw, dtype, kerne
         assert (split[k] == whole[k]).all(), f"{k}: split and one-kernel dx differ"
 
 
+def test_split_dx_never_is_the_default(kernel_choice):
+    """The value 2 of "nhwc_split_dx" takes the kernels that 0 takes: the same bits, from the same number of launches."""
+    wl = Workload(name="split_dx_never", N=20, C=64, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=4, data_seed=33,
+                  sampling_seed=34, layer_id=2)
+    inp = workloads.make_inputs(wl)
+    res, took = [], []
+    for value in (0, 2):
+        bns.bns_set_option("nhwc_split_dx", value)
+        try:
+            res.append(bns.run_workload(wl, inp))
+            took.append((bns.bns_get_option("last_path_forward"), bns.bns_get_option("last_path_backward")))
+        finally:
+            bns.bns_set_option("nhwc_split_dx", 0)
+    assert took[0] == took[1] == ((2, 2) if kernel_choice == "auto" else (1, 1))
+    for k in res[0]:
+        assert (res[0][k] == res[1][k]).all(), k
+
+
 def test_same_results_as_the_other_layout():
     """Both layouts compute the same function of the logical tensor: equal index, results equal up to rounding order."""
     wl = workloads.WORKLOADS["vdn"].replace(N=12, C=40)
