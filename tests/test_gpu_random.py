@@ -113,6 +113,8 @@ OVERRIDES = {
     "nhwc_ew_rows": [0, 1, 2, 9, 64, 5000, 1 << 20], "nhwc_small": [0, 2], "nhwc_split_dx": [0, 1, 2], "fused_variant": [0, 0, 1, 2, 3, 4, 5, 6, 7],
     "fused_keep_x": [0, 1, 2], "fused_patch_mask": [0, 1, 2], "fused_coop": [0, 1], "path": [0, 0, 1, 2],
     "fused_pipe": [0, 0, 1, 2, 3, 4, 5, 6, 16], "fused_team": [0, 0, 1, 2, 3, 5, 8, 16, 128],
+    "grouped": [0, 1, 2, 3, 4, 5, 6], "grouped_channels": [0, 1, 3, 64], "nhwc_fused": [0, 1, 1, 2],
+    "nhwc_fused_lanes": [0, 1, 2, 5, 17, 32],
 }
 
 
