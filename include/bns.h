@@ -202,7 +202,10 @@ bns_status bns_backward_builtin_workspace(const bns_shape* shape, const bns_spec
 bns_status bns_expired_waits(void* workspace, size_t workspace_bytes, void* stream, int32_t* expired /* HOST */);
 
 /* The stages that the two calls above are made of, for callers that want to place
- * other work between them (and for per-kernel timing).  Same conventions.
+ * other work between them (and for per-kernel timing).  Same conventions.  A whole call
+ * that took the streaming kernels ("last_path_forward" / "last_path_backward" = 1) carries the bits of its
+ * stages; the single-launch kernels sum in another order and can differ from them in the last bits.  In
+ * N x H x W x C these are the default up to 8192 rows (N*H*W) and, as far as they are the faster side, beyond 4 MB.
  *
  * bns_forward_stats     Eq. 3 + Eq. 8: statistics of x over S and running averages.
  * bns_forward_normalize Eq. 1: y from x and the saved statistics, all points.
