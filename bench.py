@@ -333,7 +333,8 @@ def main():
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                     achieved_by_counters=round(traffic / dom_s / 1e9, 1) if traffic else None,
                     frac_by_counters=round(traffic / dom_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                    stale=traffic is None, counters_measured_at_commit=traffic_table.get("measured_at_commit"),
+                    stale=traffic is None, counters_measured_at_commit=traffic_table.get("measured_at_commit_of", {}).get(
+                        wl.name, traffic_table.get("measured_at_commit")),
                     algorithmic_bytes_per_launch=int(dom_bytes), algorithmic_bytes_note=dom_note,
                     effective_two_pass={"bytes_per_launch": int(two_pass_bytes),
                                         "GBs": round(two_pass_bytes / dom_s / 1e9, 1),
