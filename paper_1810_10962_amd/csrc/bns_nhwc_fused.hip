@@ -3,10 +3,10 @@
 //
 // The tensor is a matrix of M = N*H*W rows by C columns.  A block of 512 threads owns a tile of CT <= 128 columns
 // and one of T shares of the rows: thread (ty, tx) holds V channels of the rows (k * T + j) * TY + ty, so
-// that the device as a whole walks the tensor front to back.  The first K
-// of a thread's rows stay in registers; what does not fit is read again in the second phase, from the memory-side cache if
-// it fits there (64x256x56x56 bf16 through the L2s, by counters: backward 370 MB, 308 are the least; forward 210, 206).  The T blocks of a tile exchange their column sums once, through the stamped slots of the other single-launch
-// kernels (bns_fused_device.hpp); with T = 1 nothing crosses blocks.
+// that the device as a whole walks the tensor front to back.  The first K of a thread's rows stay in registers; what does not
+// fit is read again in the second phase, from the memory-side cache if it fits there (64x256x56x56 bf16 through the L2s, by
+// counters: backward 370 MB, 308 are the least; forward 210, 206).  The T blocks of a tile exchange their column sums once,
+// through the stamped slots of the other single-launch kernels (bns_fused_device.hpp); with T = 1 nothing crosses blocks.
 //
 // Bound by memory, by the exchange (about 3 us between the last load and the first store) and, where rows are read twice, by
 // a persistent grid's shallower queue of loads.  Measured against the streaming kernels (three launches per direction), us
