@@ -310,8 +310,9 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "split_statistics"  1: the streaming forward statistics always run as partial sums + finalize
  *                    (by default one 1024-thread block per channel does both when a channel has few
  *                    sampled points)
- *   "splits_stats"   blocks per channel in the statistics reduction (implies split_statistics) (1..64)
- *   "splits_reduce"  blocks per channel in the backward reduction                (1..64)
+ *   "splits_stats"   blocks per channel in the statistics reduction (implies split_statistics) (1..64; with
+ *                    3073 to 3840 channels 48 at most are used)
+ *   "splits_reduce"  blocks per channel in the backward reduction                (1..64; as above)
  *   "channel_group"  the streaming path walks the channels in groups of this many, every stage on
  *                    one group before the next                                   (1..C)
  *   "nhwc_fused"     the single-launch N x H x W x C kernels: 1 whenever they can run, 2 never; 0: few rows, or tensors beyond

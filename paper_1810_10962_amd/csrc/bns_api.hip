@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "../../include/bns.h"
@@ -33,10 +34,10 @@ thread_local int32_t t_last_path_backward = 0;
 
 inline size_t elem_bytes(const Dims& d) { return d.dtype == BNS_F32 ? 4 : 2; }
 inline size_t tensor_bytes(const Dims& d) { return size_t(d.N) * d.C * d.HW * elem_bytes(d); }
-inline size_t partial_bytes(const Dims& d) { return (size_t(d.C) * kMaxSplits * sizeof(Partial) + 255) & ~size_t(255); }
+inline size_t partial_bytes(const Dims& d) { return (size_t(d.C) * most_splits(d.C) * sizeof(Partial) + 255) & ~size_t(255); }
 inline bool nhwc(const Dims& d) { return d.layout == BNS_NHWC; }
 inline WorkspaceLayout layout_of(const Dims& d) {
-    return workspace_layout(d, nhwc(d) ? nhwc_partial_bytes(d) : partial_bytes(d));
+    return workspace_layout(nhwc(d) ? nhwc_partial_bytes(d) : partial_bytes(d));
 }
 inline size_t workspace_need(const Dims& d) { return layout_of(d).total; }
 inline Partial* partials_of(void* workspace, const Dims& d) {
@@ -90,17 +91,17 @@ const TuningEntry kTuningTable[] = {
 
 int stats_splits(const Dims& d, const IndexParams& ip, int cg) {
     const int32_t o = g_splits_stats.load();
-    if (o > 0) return o;
+    if (o > 0) return std::min(o, most_splits(d.C));
     const bns_box& b = ip.shared;
     const bool planes = !ip.per_channel && b.h_cnt == d.H && b.w_cnt == d.W && stream_vec(d) > 1;
     const uint64_t pts = uint64_t(b.n_cnt) * b.h_cnt * b.w_cnt;
-    return auto_splits(cg, uint32_t(planes ? pts / stream_vec(d) : pts / 4));
+    return std::min(auto_splits(cg, uint32_t(planes ? pts / stream_vec(d) : pts / 4)), most_splits(d.C));
 }
 
 int reduce_splits(const Dims& d, int cg) {
     const int32_t o = g_splits_reduce.load();
-    if (o > 0) return o;
-    return auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / access_vec(d, odd_reduce(d))));
+    if (o > 0) return std::min(o, most_splits(d.C));
+    return std::min(auto_splits(cg, uint32_t(uint64_t(d.N) * d.HW / access_vec(d, odd_reduce(d)))), most_splits(d.C));
 }
 
 int channel_group(const Dims& d) {

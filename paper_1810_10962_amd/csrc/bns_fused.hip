@@ -1118,10 +1118,8 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.num_teams = best_blocks / bestT;
     if (A.num_teams > cg) A.num_teams = cg;
     // A team of one exchanges nothing and needs no slots.  The others: two sets of a pair per block, four in the forward pass
-    // of Eq. 4; thousands of 64-thread blocks can be more than the slots of a tensor of many channels hold, and fewer teams
-    // then take more rounds.
+    // of Eq. 4.
     const size_t slots_per_team = bestT == 1 ? 0 : size_t(bestT) * (mix && !backward ? 4 : 2) * 2 * sizeof(unsigned long long);
-    if (mix && size_t(A.num_teams) * slots_per_team > slot_bytes) A.num_teams = int(slot_bytes / slots_per_team);
     if (A.num_teams < 1) return hipErrorNotSupported;
     A.tot = tot;
     const uint32_t rounds = uint32_t((cg + A.num_teams - 1) / A.num_teams);

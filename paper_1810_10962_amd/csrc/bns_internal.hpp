@@ -55,8 +55,6 @@ inline bool odd_reduce(const Dims& d) {
 // of bf16 one (100x1312x6x6, 4 samples: 8.3 against 14.2 us); single elements are slower than either.
 inline bool odd_one_block(const Dims& d) { return odd_planes(d) && d.vec == 1; }
 
-constexpr int kMaxSplits = 64;  // upper bound on blocks that share one channel's reduction
-
 
 // Launch-shape choices; 0 = the default for the storage type (see tuned()).  The benchmark
 // can override them through bns_set_option.  Defaults come from sweeps on MI355X at

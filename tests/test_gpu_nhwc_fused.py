@@ -164,6 +164,41 @@ def test_sums_left_by_the_streaming_kernels_are_not_taken_for_a_team_mates():
     assert_parity(buf.results(), oracle_reference(wl, inp), wl, what="after streaming calls", inp=inp)
 
 
+def test_sums_of_many_channels_in_the_other_layout_are_not_taken_for_a_team_mates():
+    """As above for the widest exchange (452 KiB of slots), after N x C x H x W calls of 3840 channels, whose workspace has the
+    least room for slots."""
+    wl = Workload(name="nhwc_wide", N=9, C=256, H=40, W=40, dtype="bf16", layout="nhwc", mode=BS, n_s=3, data_seed=7,
+                  sampling_seed=8, layer_id=1)
+    before = Workload(name="nchw_many", N=9, C=3840, H=8, W=8, dtype="f32", mode=BS, n_s=3, data_seed=9, sampling_seed=10)
+    inp, flat = workloads.make_inputs(wl), workloads.make_inputs(before)
+    flat.update(x=np.full_like(flat["x"], 2.0), dy=np.zeros_like(flat["dy"]))
+    buf, left = bns.Buffers(wl, inp), bns.Buffers(before, flat)
+    assert left.workspace.numel() >= buf.workspace.numel()
+    buf.workspace = left.workspace
+    header = torch.tensor([0x626E7301 << 32, 0], dtype=torch.int64, device="cuda").view(torch.uint8)
+    print("[gpu-case] nhwc single launch after nchw streaming calls of 3840 channels in the same workspace", flush=True)
+
+    def streaming():
+        buf.workspace.fill_(0xA5)
+        left.forward()
+        left.backward()
+        assert _paths() == (1, 1)
+        buf.workspace[:16].copy_(header)
+
+    many, wide = {"path": 1, "splits_stats": 64, "splits_reduce": 64}, {"nhwc_fused": 1, "nhwc_fused_lanes": 16}
+    _with(many, streaming)
+    _with(wide, buf.forward)
+    assert _paths()[0] == 2
+    _with(many, streaming)
+    _with(wide, buf.backward)
+    assert _paths()[1] == 2
+    assert bns.bns_expired_waits(buf.workspace) == 0
+    assert_parity(buf.results(), oracle_reference(wl, inp), wl, what="after streaming calls", inp=inp)
+    res = _with(many, lambda: bns.run_workload(before, workloads.make_inputs(before)))        # blocks per channel bounded
+    assert_parity(res, oracle_reference(before, workloads.make_inputs(before)), before, what="3840 channels, 64 splits",
+                  inp=workloads.make_inputs(before))
+
+
 def test_a_captured_call_takes_the_streaming_kernels():
     wl = Workload(name="nhwc_graph", N=20, C=64, H=40, W=40, dtype="f32", layout="nhwc", mode=BS, n_s=4, data_seed=7,
                   sampling_seed=8, layer_id=2)

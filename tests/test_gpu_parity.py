@@ -762,9 +762,9 @@ def test_copy_reference():
 
 @pytest.mark.parametrize("shape", [(8, 3840, 8, 8), (4, 6000, 8, 8)], ids=["teams", "blocks_of_their_own"])
 def test_eq_4_with_more_64_thread_blocks_than_four_slot_sets_hold(shape):
-    """The forward pass of Eq. 4 takes four sets of exchange slots.  Two blocks per channel at 3840 channels: 480 KiB of them
-    where the workspace has 256 KiB, so that the channels are done in two rounds.  A block per channel at 6000 channels
-    exchanges nothing and takes no slots."""
+    """The forward pass of Eq. 4 takes four sets of exchange slots.  Two blocks per channel at 3840 channels: 480 KiB of them,
+    more than the N x C x H x W kernels take otherwise.  A block per channel at 6000 channels exchanges nothing and takes no
+    slots."""
     N, C_, H, W = shape
     wl = Workload(name="mixed_slots", N=N, C=C_, H=H, W=W, mode=BS, n_s=2, n_v=2, mix_beta=0.5, data_seed=21, sampling_seed=22,
                   layer_id=3)
