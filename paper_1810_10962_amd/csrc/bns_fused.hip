@@ -259,7 +259,9 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
             }
         }
         if (!kStampFirst && it == 0) stamp_accept(A, stamp_request(A), words);
-        block_allsum2<NT>(s1, s2, red);
+        double d1, d2;                                          // (planes with element-aligned vectors only)
+        if constexpr (Odd<T>::value) block_allsum2_wide<NT>(s1, s2, red, d1, d2);
+        else block_allsum2<NT>(s1, s2, red);
         if (NT == kWave) __syncthreads();                       // (one wave: block_allsum2 has no barrier of its own)
         double t1, t2, u1 = 0.0, u2 = 0.0;
         bool arrived;
@@ -268,13 +270,19 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
             // (130x128x28x28 f32, 7x7 patch + 2 virtual samples: 27.3 -> 25.7 us)
             team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it, s1, s2);
             __syncthreads();                                    // red[] is read by every thread of the first sum
-            block_allsum2<NT>(v1, v2, red);
+            double w1, w2;
+            if constexpr (Odd<T>::value) block_allsum2_wide<NT>(v1, v2, red, w1, w2);
+            else block_allsum2<NT>(v1, v2, red);
             team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it + 1u, v1, v2);
             arrived = team_collect<NT, 4>(A, words, team * A.T, 2u * it, s1, s2, t1, t2, team_lds, bc);
             __syncthreads();                                    // bc[] is read by every thread
             arrived &= team_collect<NT, 4>(A, words, team * A.T, 2u * it + 1u, v1, v2, u1, u2, team_lds, bc);
         } else {
             arrived = team_allsum2<NT>(A, words, team * A.T, j, it, s1, s2, t1, t2, team_lds, bc);
+        }
+        if (Odd<T>::value && !MIXED && A.T == 1) {            // (Eq. 4: no registers for them)
+            t1 = d1;
+            t2 = d2;
         }
 
         // Eq. 3 (every thread computes the same values from the same totals)
@@ -435,10 +443,16 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
         }
         }
         if (!kStampFirst && it == 0) stamp_accept(A, stamp_request(A), words);
-        block_allsum2<NT>(s1, s2, red);
+        double d1, d2;                                          // (planes with element-aligned vectors only)
+        if constexpr (Odd<T>::value) block_allsum2_wide<NT>(s1, s2, red, d1, d2);
+        else block_allsum2<NT>(s1, s2, red);
         if (NT == kWave) __syncthreads();
         double t1, t2;
         team_allsum2<NT>(A, words, team * A.T, j, it, s1, s2, t1, t2, team_lds, bc);
+        if (Odd<T>::value && A.T == 1) {
+            t1 = d1;
+            t2 = d2;
+        }
 
         const float dbeta = float(t1);
         const float dgamma = float(t2 * double(r));

@@ -197,6 +197,38 @@ __device__ __forceinline__ void block_allsum2(float& a, float& b, float* red) {
     }
 }
 
+// The same with the waves' sums added in fp64; (a, b) = the totals rounded to fp32, (da, db) = as they are.  For planes that are no
+// whole number of vectors: vectors let fewer and larger blocks share a channel than single elements did, so fewer sums meet in
+// the fp64 sum over the team, and the fp32 chain over the waves was felt (error of the mean against 64 bits: 3x16x91x91, a
+// 45x45 patch, 2.8e-8 with single elements, 6.0e-8 with fp32 here, 3.7e-8 now; 9x848x23x23, Batch Sampling, 1.5e-7, 1.2e-7,
+// 5.1e-8; at most 2 % of the time).
+template <int NT>
+__device__ __forceinline__ void block_allsum2_wide(float& a, float& b, float* red, double& da, double& db) {
+    a = wave_sum(a);
+    b = wave_sum(b);
+    da = double(a);
+    db = double(b);
+    constexpr int nw = NT / kWave;
+    if (nw > 1) {
+        const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+        __syncthreads();                       // red[] may still be read from the previous use
+        if (lane == 0) {
+            red[wave] = a;
+            red[nw + wave] = b;
+        }
+        __syncthreads();
+        da = double(red[0]);
+        db = double(red[nw]);
+#pragma unroll
+        for (int w = 1; w < nw; ++w) {
+            da += double(red[w]);
+            db += double(red[nw + w]);
+        }
+        a = float(da);
+        b = float(db);
+    }
+}
+
 // First stamp of this launch, the same value in every block (see TeamHeader).  In two steps, by thread 0 of every
 // block of the grid: stamp_request issues the load of the header word; stamp_accept, placed behind the first
 // channel's loads so that the round trip passes behind them, checks the word and leaves the stamp in the LDS word

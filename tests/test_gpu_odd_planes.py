@@ -1,6 +1,7 @@
 """Planes that are no whole number of vectors, in the streaming kernels and in the single-launch kernels of every block
 size: planes of a vector and a few elements, one row, long odd planes; the last vector of a plane is shared with the one
 before it and must count once.  And the kernels that such planes get by default, on both sides of each line of the rule."""
+import numpy as np
 import pytest
 
 from paper_1810_10962_amd import bns, workloads
@@ -102,3 +103,24 @@ def test_odd_planes_in_the_bf16_reduction():
     finally:
         bns.bns_set_option("path", 0)
     assert_parity(res, oracle_reference(wl, inp), wl, what="odd, bf16 reduction", inp=inp)
+
+
+@pytest.mark.parametrize("shape,mkw", [((57, 144, 31, 31), dict(mode=FS, patch_h=7, patch_w=7)),
+                                       ((9, 848, 23, 23), dict(mode=BS, n_s=2))], ids=["streaming_statistics", "single_launch"])
+def test_odd_planes_lose_no_precision_by_fewer_blocks(shape, mkw):
+    """Error of the mean over all channels.  One rounding to fp32 is 3.4e-8 of a value (2^-24 / sqrt(3)); the sums within a wave
+    add about as much again.  Adding the waves in fp32 made it 1.4e-7 and 1.2e-7."""
+    N, C_, H, W = shape
+    wl = Workload(name="odd_mean", N=N, C=C_, H=H, W=W, dtype="f32", data_seed=90, sampling_seed=23, layer_id=6, **mkw)
+    inp = workloads.make_inputs(wl)
+    rng = np.random.default_rng(91)
+    mu, sigma = rng.uniform(-1, 1, (1, C_, 1, 1)), rng.uniform(0.5, 2, (1, C_, 1, 1))
+    inp["x"] = (rng.standard_normal(shape) * sigma + mu).astype(inp["x"].dtype)
+    ref = oracle_reference(wl, inp)
+    print(f"[gpu-case] odd planes, error of the mean {shape} {mkw}", flush=True)
+    res = bns.run_workload(wl, inp)
+    assert_parity(res, ref, wl, what=f"odd, mean {shape}", inp=inp)
+    got, want = res["save_mean"].astype(np.float64), ref["save_mean"]
+    error = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"error of the mean {error:.2e}", flush=True)
+    assert error < 8e-8
