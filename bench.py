@@ -48,13 +48,14 @@ def load_traffic():
 def default_path_kernels(wl, dirs, bns):
     """Names of the kernels one default forward + backward launches for this workload (as in the counter table)."""
     pre = "nhwc_" if wl.layout == "nhwc" else ""
-    grouped = bns.bns_get_option("last_fused_forward") == 3
-    fwd = {"fused": [pre + ("grouped_forward_kernel" if grouped and not pre else "fused_forward_kernel")],
+    fused_fwd = {3: "grouped_forward_kernel", 4: "resident_forward_kernel"}
+    fwd = {"fused": [pre + "fused_forward_kernel" if pre else
+                     fused_fwd.get(bns.bns_get_option("last_fused_forward"), "fused_forward_kernel")],
            "one-launch": [pre + "fused_forward_kernel"],
            "streaming": ([pre + "stats_partial_kernel", pre + "stats_finalize_kernel"] if wl.layout == "nhwc" else
                          ["stats_one_block_kernel"]) + [pre + "normalize_kernel"]}[dirs["forward_path"]]
     fused_bwd = {1: "fused_backward_kernel", 2: "fused_backward_kernel", 3: "fused_backward_pipe_kernel",
-                 4: "grouped_backward_kernel"}
+                 4: "grouped_backward_kernel", 5: "resident_backward_kernel"}
     bwd = {"fused": [pre + "fused_backward_kernel" if pre else
                      fused_bwd.get(bns.bns_get_option("last_fused_backward"), "fused_backward_kernel")],
            "one-launch": [pre + "fused_backward_kernel"],

@@ -299,6 +299,8 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "grouped"        the single-launch kernels that take groups of adjacent channels (N x C x H x W, small planes): 2 never,
  *                    1 whenever a group fits a block, 3..6 that block size; 0: where they are faster
  *   "grouped_channels"  channels per group in those kernels, if they can hold them (1..64)
+ *   "resident"       the single-launch kernels of one block per compute unit (N x C x H x W, large tensors): 2 never, 1 whenever a
+ *                    channel fits, 3 / 4 backward with dy alone / with x beside it on chip; 0: where they are faster
  *   "fused_coop"     1: launch the fused kernels with hipLaunchCooperativeKernel
  *   "fused_patch_mask"  Feature Sampling forward: by default, when one block holds a channel, the statistics of
  *                    the patch come from the vectors already in registers, under a column mask (built for the
@@ -351,7 +353,8 @@ bns_status bns_set_option(const char* name, int32_t value);
  * "last_path_forward" / "last_path_backward": 1 if this thread's last bns_forward / bns_backward took the streaming kernels, 2 if the fused one, 3 if a
  * one-launch N x H x W x C kernel whose blocks do not wait for each other (few rows), 4 (backward, N x H x W x C) the streaming kernels with dx split
  * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx"); "last_fused_backward": which fused backward kernel that was
- * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels); "last_fused_forward": 3 if groups of channels,
+ * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels, 5 one block per compute unit); "last_fused_forward": 3 if groups of
+ * channels, 4 if one block per compute unit,
  * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was
  * loaded, modulo 2^31 (benchmarks report launches per call from its differences).
  * -1 for an unknown name. */

@@ -73,6 +73,7 @@ const TuningEntry kTuningTable[] = {
     {"fused_team", &Tuning::fused_team, 128, 0, false},
     {"grouped", &Tuning::grouped, 6, 0, false},
     {"grouped_channels", &Tuning::grouped_channels, 64, 0, false},
+    {"resident", &Tuning::resident, 4, 0, false},
     {"fused_coop", &Tuning::fused_coop, 1, 0, false},
     {"test_spin_limit", &Tuning::test_spin_limit, 1 << 21, 0, false},
     {"test_mute_exchange", &Tuning::test_mute_exchange, 1, 0, false},

@@ -790,6 +790,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         const hipError_t ge = grouped();
         if (ge != hipErrorNotSupported) return ge;
     }
+    if (groups && opt_team == 0 && opt_coop == 0) {
+        const hipError_t re = launch_resident(d, ip, backward, io, eps, momentum, header, slots, slot_bytes, st, cus, mix,
+                                              may_create_event);
+        if (re != hipErrorNotSupported) return re;
+    }
     std::lock_guard<std::mutex> lock(g_dev_mutex);      // planning only; released before the launch returns
     DeviceInfo* dip = nullptr;
     if ((e = current_device(&dip)) != hipSuccess) return e;

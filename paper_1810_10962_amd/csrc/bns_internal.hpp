@@ -26,10 +26,10 @@ namespace bns {
 // Kernels launched by the library since it was loaded ("launch_count" option: benchmarks report launches per call).
 extern std::atomic<uint32_t> g_launch_count;
 // Which single-launch backward kernel the calling thread's last fused backward call took: 1 plain, 2 x kept in registers, 3 pipelined,
-// 4 groups of channels.
+// 4 groups of channels, 5 one block per compute unit.
 extern thread_local int32_t t_last_fused_backward;
 // Which flavour the calling thread's last fused forward call took: 1 plain or patch elements read on their own,
-// 2 patch statistics from the registers, 3 groups of channels.
+// 2 patch statistics from the registers, 3 groups of channels, 4 one block per compute unit.
 extern thread_local int32_t t_last_fused_forward;
 
 // Streaming kernels: planes that are no whole number of full-width vectors but hold at least one (see f32_odd in
@@ -80,6 +80,8 @@ struct Tuning {
     TuneInt grouped{0};                     // kernels that take groups of channels (small planes): 2 never, 0 when they are faster,
                                             // 1 whenever they fit, 3.. variant 0..
     TuneInt grouped_channels{0};            // channels per group, if that fits
+    TuneInt resident{0};                    // kernels of one block per compute unit (large tensors): 2 never, 1 whenever they fit, 3 and 4 with all / half
+                                            // of the registers for one tensor, 0 where they are faster
     TuneInt fused_coop{0};                  // 1: launch the fused kernels with hipLaunchCooperativeKernel
     TuneInt split_statistics{0};            // 1: forward statistics always as partial sums + finalize
     TuneInt nhwc_blocks{0};                 // blocks an N x H x W x C reduction aims for (default kNhwcBlocks)
@@ -187,6 +189,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
 // hipErrorNotSupported: a group does not fit a block, or the other kernels are faster.  cus: compute units of the device.
 hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                           hipStream_t st, int cus, const FusedMix* mix = nullptr);
+// The same for large tensors, one block per compute unit (bns_resident.hip).
+hipError_t launch_resident(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
+                           void* header, void* slots, size_t slot_bytes, hipStream_t st, int cus, const FusedMix* mix,
+                           bool may_create_event);
 // Reads the count of waits that ran out from a workspace header (0 if the header was never set up) and clears it.
 hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 
