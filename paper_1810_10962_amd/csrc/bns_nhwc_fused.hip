@@ -3,17 +3,17 @@
 //
 // The tensor is a matrix of M = N*H*W rows by C columns.  A block of 512 threads owns a tile of CT <= 128 columns
 // and one of T shares of the rows: thread (ty, tx) holds V channels of the rows (k * T + j) * TY + ty, so
-// that the device as a whole walks the tensor front to back.  The first K of a thread's rows stay in registers; what does not
-// fit is read again in the second phase, from the memory-side cache if it fits there (64x256x56x56 bf16 through the L2s, by
-// counters: backward 370 MB, 308 are the least; forward 210, 206).  The T blocks of a tile exchange their column sums once,
-// through the stamped slots of the other single-launch kernels (bns_fused_device.hpp); with T = 1 nothing crosses blocks.
+// that the device as a whole walks the tensor front to back.  The first K of a thread's rows stay in registers, the next L in LDS;
+// what does not fit is read again in the second phase, from the memory-side cache if it fits there.  The T blocks of a tile exchange
+// their column sums once, through the stamped slots of the other single-launch kernels (bns_fused_device.hpp); with T = 1 nothing
+// crosses blocks.
 //
-// Bound by memory, by the exchange (about 3 us between the last load and the first store) and, where rows are read twice, by
-// a persistent grid's shallower queue of loads.  Measured against the streaming kernels (three launches per direction), us
-// forward / backward, Batch Sampling: 50x150x19x19 f32 13.8 / 15.5 against 17.7 / 25.4 (one element per access there);
-// 64x512x14x14 bf16 14.7 / 15.9 against 19.1 / 25.6; 64x256x28x28 f32 24.1 / 32.5 against 31.8 / 40.8; 64x256x56x56 bf16
-// 45.9 / 65.7 against 48.4 / 72.2 (the step of the benchmark 115 against 118; in its loops of one direction the forward gains nothing,
-// 50.8 against 50.7), full BN 48.1 / 78.3 against 59.5 / 88.0.
+// Bound by memory, by the exchange (about 1.5 us after the last block of a tile has its sums, which takes up to 3 more) and, in small
+// tensors, by a chain of latencies: by stamps on the device, 50x150x19x19 f32 forward spends 2 us until the average block runs, 3 on
+// its loads, 1.3 on its sums, 6 waiting for the last block and the exchange, 1 on its stores.  Measured against the streaming
+// kernels (three launches per direction), us forward / backward, Batch Sampling: 64x256x40x40 f32 44.1 / 69.7 against 39.1 / 53.2;
+// 64x256x56x56 bf16 47.6 / 71.1 against 42.3 / 57.8 (45.5 / 65.7 when loads had conditions around them and rows beyond the registers were
+// read twice), full BN 59.4 / 86.3 against 44.0 / 70.4; 67x512x11x11 f32 15.7 / 21.1 against 11.2 / 13.3.
 //
 // Columns that are no whole number of vectors: the last vector of a row is moved back so that it ends with the row.  The
 // channels it shares with the vector before it are computed twice, with the same bits.
@@ -47,6 +47,7 @@ struct RowArgs {
     int32_t CV;             // column vectors of a row
     int32_t TY;             // row lanes
     int32_t rounds;         // rows per thread
+    uint32_t pitch;         // bytes of a row
     int32_t keep_x;         // backward: x is read again where it lies in S, leave it in the memory-side cache
     int32_t mute_channel;   // 1 + a channel that no member publishes (host-forced give-up, for tests of that path); 0: none
 };
@@ -89,45 +90,93 @@ __device__ __forceinline__ bool in_set(const RowArgs& A, int set, uint32_t row) 
     return A.S.contiguous ? row - A.s_lo < A.S.rows : row_in(A.B, row);
 }
 
+// Sums over i < n of p[i * CT] and of the same kRowThreads further, four loads in flight, in a fixed order.  (A loop: in a kernel that
+// runs for a few microseconds, instructions that are fetched once cost more than they save.)
+__device__ __forceinline__ void add_strided(const double* p, int CT, int n, double& s1, double& s2) {
+    s1 = s2 = 0.0;
+#pragma unroll 1
+    for (int i0 = 0; i0 < n; i0 += 4) {
+        double v[4], w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int at = min(i0 + u, n - 1) * CT;
+            v[u] = p[at];
+            w[u] = p[kRowThreads + at];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            s1 += i0 + u < n ? v[u] : 0.0;
+            s2 += i0 + u < n ? w[u] : 0.0;
+        }
+    }
+}
+
 // Column sums of the block, by thread t < CT for channel t of the tile: per-thread sums through LDS, added in fp64 in a
-// fixed order (first over the row lanes q, q + Q, ..., then over q).
+// fixed order (first over the row lanes q, q + Q, ..., then over q).  What it costs is a chain of LDS round trips, so a vector's sums
+// are written side by side (128-bit writes without bank conflicts), loads are requested several at a time, and no more than
+// kSumGroups threads share a channel, whose sums one thread then adds (2x512x14x14 f32, 16 channels, 128 row lanes: 1.5 us with
+// 32 groups added one after the other).
+constexpr int kSumGroups = 8;
 template <int V>
 __device__ __forceinline__ void tile_sums(const RowArgs& A, const RowLane& l, const double (&a)[V], const double (&q)[V], float* lds,
                                           double* part, double& s1, double& s2) {
+    typedef float vec_t __attribute__((ext_vector_type(V < 4 ? 1 : 4)));
+    constexpr int kWidth = V < 4 ? 1 : 4;
     const int CT = int(A.ct_div.d);
     __syncthreads();                                        // lds and part may still be read from the previous use
     if (l.live) {
+        vec_t* va = reinterpret_cast<vec_t*>(lds + l.ty * CT + l.tx * V);
+        vec_t* vq = reinterpret_cast<vec_t*>(lds + (A.TY + l.ty) * CT + l.tx * V);
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            lds[l.ty * CT + l.local + e] = float(a[e]);
-            lds[(A.TY + l.ty) * CT + l.local + e] = float(q[e]);
+        for (int e = 0; e < V; e += kWidth) {
+            vec_t wa, wq;
+#pragma unroll
+            for (int i = 0; i < kWidth; ++i) {
+                wa[i] = float(a[e + i]);
+                wq[i] = float(q[e + i]);
+            }
+            va[e / kWidth] = wa;
+            vq[e / kWidth] = wq;
         }
     }
     __syncthreads();
-    const int g = int(fdiv(threadIdx.x, A.ct_div)), ch = int(threadIdx.x) - g * CT, Q = kRowThreads / CT;
+    const int g = int(fdiv(threadIdx.x, A.ct_div)), ch = int(threadIdx.x) - g * CT, Q = min(kRowThreads / CT, kSumGroups);
+    // where channel ch lies in a row lane's sums: the last vector of a row may have been moved back
+    const int vec = min(ch / V, (l.width - 1) / V), first = min(vec * V, A.f.C - V - l.tile * CT);
+    const float* at = lds + vec * V + (ch - first);
     s1 = s2 = 0.0;
     if (g < Q && ch < l.width) {
-        for (int r = g; r < A.TY; r += Q) {
-            s1 += double(lds[r * CT + ch]);
-            s2 += double(lds[(A.TY + r) * CT + ch]);
+#pragma unroll 1
+        for (int r0 = g; r0 < A.TY; r0 += 4 * Q) {
+            float u1[4], u2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = min(r0 + u * Q, A.TY - 1);
+                u1[u] = at[r * CT];
+                u2[u] = at[(A.TY + r) * CT];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                s1 += r0 + u * Q < A.TY ? double(u1[u]) : 0.0;
+                s2 += r0 + u * Q < A.TY ? double(u2[u]) : 0.0;
+            }
         }
         part[g * CT + ch] = s1;
         part[kRowThreads + g * CT + ch] = s2;
     }
     __syncthreads();
     if (int(threadIdx.x) < l.width) {
-        for (int i = 1; i < Q; ++i) {
-            s1 += part[i * CT + ch];
-            s2 += part[kRowThreads + i * CT + ch];
-        }
+        add_strided(part + ch, CT, Q, s1, s2);
     }
 }
 
 // Exchange of the column sums between the T members of a tile: every member reads all T pairs of every channel.  Words are
-// stamped as in the other single-launch kernels.  Slots: [set][tile][member][channel], so a member's pairs are written side by side.
-__device__ __forceinline__ unsigned long long* pair_slot(const RowArgs& A, const RowLane& l, int set, int member, int ch) {
+// stamped as in the other single-launch kernels.  Slots: [set][tile][member][first or second sum][channel]: the lanes of a wave that
+// reads a member's sums, one channel each, take whole cache lines.  (Every such read goes past the L2, and T members read T * CT pairs:
+// with the two words of a pair side by side each line was fetched twice, 36 MB in the exchange of 50x150x19x19 f32.)
+__device__ __forceinline__ unsigned long long* sum_slot(const RowArgs& A, const RowLane& l, int set, int member, int which, int ch) {
     const size_t tile = size_t(set * A.f.num_teams + l.tile), T = size_t(A.f.T), CT = A.ct_div.d;
-    return A.f.slots + 2 * ((tile * T + size_t(member)) * CT + size_t(ch));
+    return A.f.slots + ((tile * T + size_t(member)) * 2 + size_t(which)) * CT + size_t(ch);
 }
 __device__ __forceinline__ void put_word(unsigned long long* p, uint32_t stamp, uint32_t payload) {
     __hip_atomic_store(p, (static_cast<unsigned long long>(stamp) << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -160,9 +209,8 @@ __device__ __forceinline__ bool poll_words(const FusedArgs& F, uint32_t stamp, A
 __device__ __forceinline__ void tile_publish(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, double s1, double s2) {
     if (A.f.T == 1 || int(threadIdx.x) >= l.width || A.f.mute) return;
     if (A.mute_channel == l.tile * int(A.ct_div.d) + int(threadIdx.x) + 1) return;
-    unsigned long long* mine = pair_slot(A, l, set, l.j, int(threadIdx.x));
-    put_word(mine, stamp, __float_as_uint(float(s1)));
-    put_word(mine + 1, stamp, __float_as_uint(float(s2)));
+    put_word(sum_slot(A, l, set, l.j, 0, int(threadIdx.x)), stamp, __float_as_uint(float(s1)));
+    put_word(sum_slot(A, l, set, l.j, 1, int(threadIdx.x)), stamp, __float_as_uint(float(s2)));
 }
 
 // Adds the pairs of members first, first + step, ... of channel ch, B of them polled at a time.  If a wait ran out: NaN, and
@@ -174,7 +222,7 @@ __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, 
     for (int m0 = first; m0 < A.f.T; m0 += B * step) {
         uint32_t w[2 * B];
         const bool ok = poll_words<2 * B>(A.f, stamp, [&](int i) {
-            return pair_slot(A, l, set, min(m0 + (i / 2) * step, A.f.T - 1), ch) + (i & 1);
+            return sum_slot(A, l, set, min(m0 + (i / 2) * step, A.f.T - 1), i & 1, ch);
         }, w);
         if (!ok) {
             s1 = s2 = __builtin_nan("");
@@ -199,18 +247,35 @@ __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l,
     const int g = int(fdiv(threadIdx.x, A.ct_div)), ch = int(threadIdx.x) - g * CT, Q = kRowThreads / CT;
     __syncthreads();                                        // part may still be read
     if (g < Q && ch < l.width) {
-        add_members<kRowPoll>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
+        // (words are requested for every member at once, and none twice: the polls of all blocks share one path)
+        if (T <= 2 * Q) add_members<2>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
+        else add_members<kRowPoll>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
         part[g * CT + ch] = s1;
         part[kRowThreads + g * CT + ch] = s2;
     }
     __syncthreads();
     if (int(threadIdx.x) < l.width) {
-        for (int i = 1; i < Q && i < T; ++i) {
-            s1 += part[i * CT + ch];
-            s2 += part[kRowThreads + i * CT + ch];
-        }
+        add_strided(part + ch, CT, min(Q, T), s1, s2);
     }
 }
+
+template <typename P>
+__device__ __forceinline__ P* at_byte(P* base, uint32_t off) {      // (pointer arithmetic: the access stays a global one)
+    typedef typename std::conditional<std::is_const<P>::value, const char, char>::type byte_t;
+    return reinterpret_cast<P*>(reinterpret_cast<byte_t*>(base) + off);
+}
+
+// A thread's way down the rows: the next row, and its byte offset from the tensor's first element, column included.
+// (ANEW: each phase walks anew instead of keeping one offset per row alive, where there are many)
+template <bool ANEW>
+struct RowWalk {
+    uint32_t row, off;
+    __device__ __forceinline__ void next(uint32_t step, uint32_t hop) {
+        if (ANEW) asm volatile("" : "+v"(row), "+v"(off));
+        row += step;
+        off += hop;
+    }
+};
 
 template <typename T, int V, bool NT>
 __device__ __forceinline__ typename RawVec<T, V>::raw_t row_load(const T* p) {
@@ -226,41 +291,64 @@ __device__ __forceinline__ void row_store(T* p, typename RawVec<T, V>::raw_t r) 
     __builtin_nontemporal_store(r, reinterpret_cast<elem_t*>(p));
 }
 
-// Forward: Eq. 3 (Eq. 4 if MIXED), Eq. 8, Eq. 1.
-template <typename T, int V, int K, bool MIXED>
+// Forward: Eq. 3 (Eq. 4 if MIXED), Eq. 8, Eq. 1.  A thread keeps K rows in registers and L in LDS; rows beyond are read again.
+// Beyond 16 rows loads are unconditional (past the end the last row is read) and run kAhead rows ahead of the sums: a condition around a load
+// makes every later wait one for all loads, and a thread that issues all of them first finds most of its rows there before it
+// adds the first one up.
+template <typename T, int V, int K, int L, bool MIXED>
 __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowArgs A) {
     typedef RawVec<T, V> RV;
-    __shared__ float lds[2 * kRowThreads * V];
+    typedef typename RV::raw_t raw_t;
+    __shared__ raw_t park[L > 0 ? L * kRowThreads : 1];
+    __shared__ float __attribute__((aligned(16))) lds[2 * kRowThreads * V];
     __shared__ double part[2 * kRowThreads];
     __shared__ float piv[(MIXED ? 2 : 1) * kRowMaxTile];
     __shared__ float4 consts[kRowMaxTile];
     __shared__ uint32_t words[3], lost[kRowMaxTile];
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
-    const size_t C = size_t(F.C);
-    const T* x = static_cast<const T*>(F.x) + l.col;
-    T* y = static_cast<T*>(F.out) + l.col;
+    const T* x = static_cast<const T*>(F.x);
+    T* y = static_cast<T*>(F.out);
     const unsigned long long state = stamp_request(F);
-    const uint32_t step = uint32_t(F.T) * uint32_t(A.TY), last = A.M - 1u;
+    const uint32_t step = uint32_t(F.T) * uint32_t(A.TY), hop = step * A.pitch;
+    const uint32_t column = uint32_t(l.col) * uint32_t(sizeof(T)), last = (A.M - 1u) * A.pitch + column;
+    typedef RowWalk<(K > 16)> Walk;
+    auto walk_from = [&](int k) {
+        const uint32_t row = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty)) + uint32_t(k) * step;
+        return Walk{row, row * A.pitch + column};
+    };
 
     // The pivot of a channel is the mean of its first few sampled rows (see coarse), read by the first row lane.
-    typename RV::raw_t pv[kPivotRows], pw[MIXED ? kPivotRows : 1];
+    raw_t pv[kPivotRows], pw[MIXED ? kPivotRows : 1];
     if (l.ty == 0) {
 #pragma unroll
         for (int i = 0; i < kPivotRows; ++i) {
             const uint32_t row = sampled_row(A.S, min(uint32_t(i), A.S.pivot_rows - 1u));
-            pv[i] = row_load<T, V, false>(x + size_t(row) * C);
-            if constexpr (MIXED) pw[i] = row_load<T, V, false>(x + size_t(min(uint32_t(i), A.virtual_rows - 1u)) * C);
+            pv[i] = row_load<T, V, false>(at_byte(x, row * A.pitch + column));
+            if constexpr (MIXED) pw[i] = row_load<T, V, false>(at_byte(x, min(uint32_t(i), A.virtual_rows - 1u) * A.pitch + column));
         }
     }
-    typename RV::raw_t v[K];
-    auto keep_rows = [&]() {
-        const uint32_t ra = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty));
+    constexpr int kAhead = K < 16 ? K : 16;
+    constexpr bool kTight = K <= kAhead;                    // all loads come before the first sum: only those that are needed
+    raw_t v[K], u[L > 0 ? L : 1];
+    Walk wl = walk_from(K);                              // of the loads
+    if constexpr (L > 0) {
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k < A.rounds) v[k] = row_load<T, V, true>(x + size_t(min(ra + uint32_t(k) * step, last)) * C);
+        for (int k = 0; k < L; ++k) {
+            u[k] = row_load<T, V, true>(at_byte(x, min(wl.off, last)));
+            wl.next(step, hop);
+        }
+    }
+    wl = walk_from(0);
+    auto load = [&](int k) {
+        v[k] = row_load<T, V, true>(at_byte(x, min(wl.off, last)));
+        wl.next(step, hop);
     };
-    if (K <= 16) keep_rows();
+    if constexpr (L == 0) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (!kTight || k < A.rounds) load(k);
+    }
     if (l.ty == 0 && l.live) {
         float p[V], f[V];
 #pragma unroll
@@ -302,54 +390,68 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             a[e] = q[e] = 0.0;
             p[e] = piv[set * kRowMaxTile + l.local + e];
         }
-        // four rows at a time: their differences are added in fp32, the sum goes into the fp64 accumulator
-        auto add4 = [&](const typename RV::raw_t (&w)[4], uint32_t row) {
-            bool m[4];
+        // Up to four rows of the walk are added in fp32, their sum goes into the fp64 accumulator.
+        auto add = [&](auto rows, Walk& w, auto&& row_of) {
+            constexpr int R = decltype(rows)::value;
+            bool in[R], any = false;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t ru = row + uint32_t(u) * step;
-                m[u] = ru < A.M && in_set(A, set, ru);
+            for (int i = 0; i < R; ++i) {
+                in[i] = w.row < A.M && in_set(A, set, w.row);
+                any |= in[i];
+                w.next(step, hop);
             }
-            if (m[0] | m[1] | m[2] | m[3]) {
-                float d[4][V];
+            if (any) {
+                float fa[V], fq[V];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    RV::unpack(w[u], d[u]);
+                for (int e = 0; e < V; ++e) fa[e] = fq[e] = 0.f;
 #pragma unroll
-                    for (int e = 0; e < V; ++e) d[u][e] = m[u] ? d[u][e] - p[e] : 0.f;
+                for (int i = 0; i < R; ++i) {
+                    float f[V];
+                    RV::unpack(row_of(i), f);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const float d = in[i] ? f[e] - p[e] : 0.f;
+                        fa[e] += d;
+                        fq[e] = fmaf(d, d, fq[e]);
+                    }
                 }
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
-                    a[e] += double((d[0][e] + d[1][e]) + (d[2][e] + d[3][e]));
-                    q[e] += double(fmaf(d[3][e], d[3][e], fmaf(d[2][e], d[2][e], fmaf(d[1][e], d[1][e], d[0][e] * d[0][e]))));
+                    a[e] += double(fa[e]);
+                    q[e] += double(fq[e]);
                 }
             }
+            if constexpr (!kTight) {                        // (the sums keep pace with the loads, or the registers run out)
+#pragma unroll
+                for (int e = 0; e < V; ++e) asm volatile("" : "+v"(a[e]), "+v"(q[e]));
+            }
         };
-        const uint32_t rb = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty));
-        // Rows that are not kept are read for the statistics if they are in S: two batches of eight in flight.  Those of the
-        // first set come before the rows that are kept, while the registers are free.
+        typedef std::integral_constant<int, 4> four;
+        // Rows that are not kept are read for the statistics if they are in S: two batches of eight in flight.
         auto passing = [&]() {
-            auto batch = [&](typename RV::raw_t(&w)[8], int k) {
+            const uint32_t rb = walk_from(0).row;
+            auto batch = [&](raw_t(&w)[8], int k) {
                 bool any = false;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const uint32_t row = rb + uint32_t(k + u) * step;
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t row = rb + uint32_t(k + i) * step;
                     any |= row < A.M && in_set(A, set, row);
                 }
                 if (any) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) w[u] = row_load<T, V, false>(x + size_t(min(rb + uint32_t(k + u) * step, last)) * C);
+                    for (int i = 0; i < 8; ++i)
+                        w[i] = row_load<T, V, false>(at_byte(x, min((rb + uint32_t(k + i) * step) * A.pitch + column, last)));
                 }
                 return any;
             };
-            auto add8 = [&](const typename RV::raw_t(&w)[8], int k) {
-                const typename RV::raw_t lo[4] = {w[0], w[1], w[2], w[3]}, hi[4] = {w[4], w[5], w[6], w[7]};
-                add4(lo, rb + uint32_t(k) * step);
-                add4(hi, rb + uint32_t(k + 4) * step);
+            auto add8 = [&](const raw_t(&w)[8], int k) {
+                Walk at = walk_from(k);
+                add(four(), at, [&](int i) { return w[i]; });
+                add(four(), at, [&](int i) { return w[4 + i]; });
             };
-            typename RV::raw_t w0[8], w1[8];
-            bool any0 = batch(w0, K), any1 = false;
-            for (int k = K; k < A.rounds; k += 16) {
+            raw_t w0[8], w1[8];
+            bool any0 = batch(w0, K + L), any1 = false;
+            for (int k = K + L; k < A.rounds; k += 16) {
                 if (k + 8 < A.rounds) any1 = batch(w1, k + 8);
                 if (any0) add8(w0, k);
                 if (k + 8 >= A.rounds) break;
@@ -357,13 +459,37 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
                 if (any1) add8(w1, k + 8);
             }
         };
-        if (K > 16 && A.rounds > K) passing();
-        if (K > 16 && set == 0) keep_rows();
+        if (L > 0 && A.rounds > K + L) passing();
+        if constexpr (L > 0) {
+            if (set == 0) {
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) load(k);
+            }
+            static_assert(L % 2 == 0, "pairs of rows");
+            Walk w = walk_from(K);
+#pragma unroll
+            for (int k = 0; k < L; k += 2) {
+                if (set == 0) {
+                    park[k * kRowThreads + threadIdx.x] = u[k];
+                    park[(k + 1) * kRowThreads + threadIdx.x] = u[k + 1];
+                }
+                add(std::integral_constant<int, 2>(), w, [&](int i) { return set == 0 ? u[k + i] : park[(k + i) * kRowThreads + threadIdx.x]; });
+            }
+        }
+        Walk w = walk_from(0);
 #pragma unroll
         for (int k = 0; k < K; k += 4) {
-            if (k < A.rounds) {
-                const typename RV::raw_t w[4] = {v[k], v[k + 1], v[k + 2], v[k + 3]};
-                add4(w, rb + uint32_t(k) * step);
+            if (set == 0) {
+#pragma unroll
+                for (int i = k + kAhead; i < k + kAhead + 4 && i < K; ++i) load(i);
+            }
+            if (!kTight || k < A.rounds) {
+                static_assert(K % 4 == 0, "four rows at a time");
+                if constexpr (!kTight) {
+#pragma unroll
+                    for (int i = k; i < k + 4; ++i) opaque_raw(v[i]);
+                }
+                add(four(), w, [&](int i) { return v[k + i]; });
             }
         }
         double t1, t2;
@@ -429,120 +555,166 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             sc[e] = k4.y;
             sh[e] = k4.z;
         }
-        const uint32_t rc = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty));
-        auto finish = [&](const typename RV::raw_t& w, uint32_t row) {
+        auto finish = [&](const raw_t& w, const Walk& at) {
             float f[V];
             RV::unpack(w, f);
 #pragma unroll
             for (int e = 0; e < V; ++e) f[e] = fmaf(f[e] - mu[e], sc[e], sh[e]);
-            if (row < A.M) row_store<T, V>(y + size_t(row) * C, RV::pack(f));
+            if (at.row < A.M) row_store<T, V>(at_byte(y, at.off), RV::pack(f));
         };
+        Walk w = walk_from(0);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (k < A.rounds) {
+            if (!kTight || k < A.rounds) {
                 opaque_raw(v[k]);
-                finish(v[k], rc + uint32_t(k) * step);
+                finish(v[k], w);
+                w.next(step, hop);
             }
         }
-        if (K > 16) {
-            for (int k = K; k < A.rounds; k += kRowBatch) {
-                typename RV::raw_t w[kRowBatch];
-                const uint32_t row = rc + uint32_t(k) * step;
+        if constexpr (L > 0) {
 #pragma unroll
-                for (int u = 0; u < kRowBatch; ++u) w[u] = row_load<T, V, true>(x + size_t(min(row + uint32_t(u) * step, last)) * C);
+            for (int k = 0; k < L; ++k) {
+                finish(park[k * kRowThreads + threadIdx.x], w);
+                w.next(step, hop);
+            }
+            for (int k = K + L; k < A.rounds; k += kRowBatch) {
+                raw_t r[kRowBatch];
+                Walk wr = w;
 #pragma unroll
-                for (int u = 0; u < kRowBatch; ++u) finish(w[u], row + uint32_t(u) * step);
+                for (int i = 0; i < kRowBatch; ++i) {
+                    r[i] = row_load<T, V, true>(at_byte(x, min(wr.off, last)));
+                    wr.next(step, hop);
+                }
+#pragma unroll
+                for (int i = 0; i < kRowBatch; ++i) {
+                    finish(r[i], w);
+                    w.next(step, hop);
+                }
             }
         }
     }
     team_done(F, l.j, stamp);
 }
 
-// Backward: the sums of Eq. 5, Eq. 6.  dy stays in registers; x of the rows of S is read again (KEEPX: stays, too).
-template <typename T, int V, int K, bool KEEPX, bool MIXED>
+// Backward: the sums of Eq. 5, Eq. 6.  dy stays in registers (K rows) and LDS (L rows); x of the rows of S is read again (KEEPX:
+// stays, too).  Loads as in the forward kernel.
+template <typename T, int V, int K, int L, bool KEEPX, bool MIXED>
 __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(RowArgs A) {
     typedef RawVec<T, V> RV;
     typedef typename RV::raw_t raw_t;
-    __shared__ float lds[2 * kRowThreads * V];
+    __shared__ raw_t park[L > 0 ? L * kRowThreads : 1];
+    __shared__ float __attribute__((aligned(16))) lds[2 * kRowThreads * V];
     __shared__ double part[2 * kRowThreads];
     __shared__ float4 consts[(MIXED ? 2 : 1) * kRowMaxTile];
     __shared__ uint32_t words[3];
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
-    const size_t C = size_t(F.C);
-    const T* x = static_cast<const T*>(F.x) + l.col;
-    const T* dy = static_cast<const T*>(F.dy) + l.col;
-    T* dx = static_cast<T*>(F.out) + l.col;
+    const T* x = static_cast<const T*>(F.x);
+    const T* dy = static_cast<const T*>(F.dy);
+    T* dx = static_cast<T*>(F.out);
     const unsigned long long state = stamp_request(F);
-    const uint32_t step = uint32_t(F.T) * uint32_t(A.TY), last = A.M - 1u;
+    const uint32_t step = uint32_t(F.T) * uint32_t(A.TY), hop = step * A.pitch;
+    const uint32_t column = uint32_t(l.col) * uint32_t(sizeof(T)), last = (A.M - 1u) * A.pitch + column;
+    typedef RowWalk<(K > 16)> Walk;
+    auto walk_from = [&](int k) {
+        const uint32_t row = uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty) + uint32_t(k) * step;
+        return Walk{row, row * A.pitch + column};
+    };
     float mu[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) mu[e] = F.save_mean[l.col + e];
 
     double a[V], q[V];
+    float fa[V], fq[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) a[e] = q[e] = 0.0;
-    // four rows at a time, rows k .. k + 3 of the thread: added in fp32, the sum goes into the fp64 accumulator.  Rows past the
-    // end (copies of the last one, or never loaded) are dropped.
+    for (int e = 0; e < V; ++e) {
+        a[e] = q[e] = 0.0;
+        fa[e] = fq[e] = 0.f;
+    }
+    // Up to four rows are added in fp32 (add), their sum goes into the fp64 accumulator (flush).  Rows past the end, copies of
+    // the last one, are dropped.
     const uint32_t block0 = uint32_t(l.j) * uint32_t(A.TY);
-    auto add4 = [&](const raw_t(&wg)[4], const raw_t(&wx)[4], int k) {
-        float p[4][V], t[4][V];
+    auto add = [&](const raw_t& wg, const raw_t& wx, uint32_t row, int k) {
+        float g[V], t[V];
+        RV::unpack(wg, g);
+        RV::unpack(wx, t);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float fx[V];
-            RV::unpack(wg[u], p[u]);
-            RV::unpack(wx[u], fx);
+        for (int e = 0; e < V; ++e) t[e] -= mu[e];
+        if (block0 + uint32_t(k) * step + uint32_t(A.TY) > A.M) {           // (the same for the whole block)
 #pragma unroll
-            for (int e = 0; e < V; ++e) t[u][e] = fx[e] - mu[e];
-        }
-        if (block0 + uint32_t(k + 3) * step + uint32_t(A.TY) > A.M) {       // (the same for the whole block)
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (block0 + uint32_t(l.ty) + uint32_t(k + u) * step >= A.M) {
-#pragma unroll
-                    for (int e = 0; e < V; ++e) p[u][e] = t[u][e] = 0.f;
-                }
+            for (int e = 0; e < V; ++e) {
+                g[e] = row < A.M ? g[e] : 0.f;
+                t[e] = row < A.M ? t[e] : 0.f;
+            }
         }
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-            a[e] += double((p[0][e] + p[1][e]) + (p[2][e] + p[3][e]));
-            q[e] += double(fmaf(p[1][e], t[1][e], p[0][e] * t[0][e]) + fmaf(p[3][e], t[3][e], p[2][e] * t[2][e]));
+            fa[e] += g[e];
+            fq[e] = fmaf(g[e], t[e], fq[e]);
+        }
+    };
+    auto flush = [&]() {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            a[e] += double(fa[e]);
+            q[e] += double(fq[e]);
+            fa[e] = fq[e] = 0.f;
+            asm volatile("" : "+v"(a[e]), "+v"(q[e]));
         }
     };
     raw_t g[K], xk[KEEPX ? K : 1];
-    const uint32_t r0 = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty));
-    constexpr int XB = K < 8 ? K : 8;                       // rows of x in flight beside those of dy
     if constexpr (KEEPX) {
+        static_assert(K <= 16, "all loads come before the first sum: only those that are needed");
+        Walk wl = walk_from(0), w = wl;
+        auto load = [&](int k) {
+            const uint32_t off = min(wl.off, last);
+            g[k] = row_load<T, V, true>(at_byte(dy, off));
+            xk[k] = row_load<T, V, true>(at_byte(x, off));
+            wl.next(step, hop);
+        };
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (k < A.rounds) {
-                const size_t off = size_t(min(r0 + uint32_t(k) * step, last)) * C;
-                g[k] = row_load<T, V, true>(dy + off);
-                xk[k] = row_load<T, V, true>(x + off);
-            }
+            if (k < A.rounds) load(k);
 #pragma unroll
-        for (int k = 0; k < K; k += 4)
+        for (int k = 0; k < K; k += 4) {
             if (k < A.rounds) {
-                const raw_t wg[4] = {g[k], g[k + 1], g[k + 2], g[k + 3]}, wx[4] = {xk[k], xk[k + 1], xk[k + 2], xk[k + 3]};
-                add4(wg, wx, k);
+#pragma unroll
+                for (int i = k; i < k + 4; ++i) {
+                    opaque_raw(xk[i]);
+                    add(g[i], xk[i], w.row, i);
+                    w.next(step, hop);
+                }
+                flush();
             }
+        }
     } else {
         auto first_pass = [&](auto plain) {
             constexpr bool kNt = !decltype(plain)::value;
             // Rows that are not kept come first, while the registers are free: dy is left in the memory-side cache.
             auto batch = [&](raw_t(&wg)[4], raw_t(&wx)[4], int k) {
+                Walk w = walk_from(k);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const size_t off = size_t(min(r0 + uint32_t(k + u) * step, last)) * C;
-                    wg[u] = row_load<T, V, false>(dy + off);
-                    wx[u] = row_load<T, V, kNt>(x + off);
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t off = min(w.off, last);
+                    wg[i] = row_load<T, V, false>(at_byte(dy, off));
+                    wx[i] = row_load<T, V, kNt>(at_byte(x, off));
+                    w.next(step, hop);
                 }
             };
-            if (K < A.rounds) {
+            auto add4 = [&](const raw_t(&wg)[4], const raw_t(&wx)[4], int k) {
+                Walk w = walk_from(k);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    add(wg[i], wx[i], w.row, k + i);
+                    w.next(step, hop);
+                }
+                flush();
+            };
+            if (K + L < A.rounds) {
                 raw_t g0[4], x0[4], g1[4], x1[4], g2[4], x2[4];     // three batches in flight
-                batch(g0, x0, K);
-                if (K + 4 < A.rounds) batch(g1, x1, K + 4);
-                for (int k = K;; k += 12) {
+                batch(g0, x0, K + L);
+                if (K + L + 4 < A.rounds) batch(g1, x1, K + L + 4);
+                for (int k = K + L;; k += 12) {
                     if (k + 8 < A.rounds) batch(g2, x2, k + 8);
                     add4(g0, x0, k);
                     if (k + 4 >= A.rounds) break;
@@ -554,25 +726,45 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
                     if (k + 12 >= A.rounds) break;
                 }
             }
+            // The rows of LDS, then those of the registers: two rows of both tensors at a time, two such pairs in flight.
+            static_assert(L % 2 == 0, "pairs of rows");
+            Walk wl = walk_from(K), w = wl;
+            raw_t d0[2], d1[2], x0[2], x1[2];
+            auto request = [&](int k, raw_t(&d)[2], raw_t(&xb)[2]) {        // k: rows of LDS first, L of them
+                if (k == L) wl = walk_from(0);
 #pragma unroll
-            for (int k0 = 0; k0 < K; k0 += XB) {
-                raw_t xv[XB];
-                const uint32_t ra = opaque(r0);
-#pragma unroll
-                for (int u = 0; u < XB; ++u)
-                    if (k0 + u < K && k0 + u < A.rounds)
-                        g[k0 + u] = row_load<T, V, true>(dy + size_t(min(ra + uint32_t(k0 + u) * step, last)) * C);
-#pragma unroll
-                for (int u = 0; u < XB; ++u)
-                    if (k0 + u < K && k0 + u < A.rounds)
-                        xv[u] = row_load<T, V, kNt>(x + size_t(min(ra + uint32_t(k0 + u) * step, last)) * C);
-#pragma unroll
-                for (int u = 0; u < XB; u += 4)
-                    if (k0 + u < K && k0 + u < A.rounds) {
-                        const raw_t wg[4] = {g[k0 + u], g[k0 + u + 1], g[k0 + u + 2], g[k0 + u + 3]};
-                        const raw_t wx[4] = {xv[u], xv[u + 1], xv[u + 2], xv[u + 3]};
-                        add4(wg, wx, k0 + u);
+                for (int i = 0; i < 2; ++i)
+                    if (k + i < L + K) {
+                        const uint32_t off = min(wl.off, last);
+                        if (k < L) d[i] = row_load<T, V, true>(at_byte(dy, off));
+                        else g[k + i - L] = row_load<T, V, true>(at_byte(dy, off));
+                        xb[i] = row_load<T, V, kNt>(at_byte(x, off));
+                        wl.next(step, hop);
                     }
+            };
+            auto take = [&](int k, raw_t(&d)[2], raw_t(&xb)[2]) {
+                if (k == L) w = walk_from(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (k + i < L + K) {
+                        opaque_raw(xb[i]);
+                        if (k < L) {
+                            park[(k + i) * kRowThreads + threadIdx.x] = d[i];
+                            add(d[i], xb[i], w.row, K + k + i);
+                        } else {
+                            add(g[k + i - L], xb[i], w.row, k + i - L);
+                        }
+                        w.next(step, hop);
+                    }
+                if (k % 4 == 2 || k + 2 >= L + K) flush();
+            };
+            request(0, d0, x0);
+#pragma unroll
+            for (int k = 0; k < L + K; k += 4) {
+                if (k + 2 < L + K) request(k + 2, d1, x1);
+                take(k, d0, x0);
+                if (k + 4 < L + K) request(k + 4, d0, x0);
+                if (k + 2 < L + K) take(k + 2, d1, x1);
             }
         };
         if (A.keep_x) first_pass(std::true_type());
@@ -615,11 +807,10 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
             k2[e] = kc.z;
             ce[e] = kc.w;
         }
-        const uint32_t rc = opaque(uint32_t(l.j) * uint32_t(A.TY) + uint32_t(l.ty));
-        auto finish = [&](raw_t gr, raw_t xr, bool sampled, uint32_t row) {
+        auto finish = [&](const raw_t& gr, const raw_t& xr, bool sampled, const Walk& at) {
             float f[V];
             RV::unpack(gr, f);
-            if (MIXED && row < A.virtual_rows) {
+            if (MIXED && at.row < A.virtual_rows) {
                 float fx[V];
                 RV::unpack(xr, fx);
 #pragma unroll
@@ -636,78 +827,102 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
 #pragma unroll
                 for (int e = 0; e < V; ++e) f[e] *= ar[e];
             }
-            if (row < A.M) row_store<T, V>(dx + size_t(row) * C, RV::pack(f));
+            if (at.row < A.M) row_store<T, V>(at_byte(dx, at.off), RV::pack(f));
         };
         auto sampled_here = [&](uint32_t row) { return row < A.M && ((MIXED && row < A.virtual_rows) || in_set(A, 0, row)); };
+        Walk w = walk_from(0);
         // x of the rows of S is requested four rows at a time
 #pragma unroll
-        for (int k0 = 0; k0 < K; k0 += 4) {
-            if (k0 < A.rounds) {
-                bool sampled[4];
-                raw_t xr[4];
+        for (int k0 = 0; k0 < K + L; k0 += 4) {
+            if (K <= 16 && k0 >= A.rounds) break;
+            bool sampled[4];
+            raw_t xr[4];
+            Walk wx = w;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t row = rc + uint32_t(k0 + u) * step;
-                    sampled[u] = sampled_here(row);
+            for (int i = 0; i < 4; ++i)
+                if (k0 + i < K + L) {
+                    sampled[i] = sampled_here(wx.row);
                     if constexpr (KEEPX) {
-                        opaque_raw(xk[k0 + u]);
-                        xr[u] = xk[k0 + u];
-                    } else if (sampled[u]) {
-                        xr[u] = row_load<T, V, true>(x + size_t(row) * C);
+                        opaque_raw(xk[k0 + i]);
+                        xr[i] = xk[k0 + i];
+                    } else if (sampled[i]) {
+                        xr[i] = row_load<T, V, true>(at_byte(x, wx.off));
                     }
+                    wx.next(step, hop);
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    opaque_raw(g[k0 + u]);
-                    finish(g[k0 + u], xr[u], sampled[u], rc + uint32_t(k0 + u) * step);
+            for (int i = 0; i < 4; ++i)
+                if (k0 + i < K + L) {
+                    if (k0 + i < K) {
+                        opaque_raw(g[k0 + i < K ? k0 + i : 0]);
+                        finish(g[k0 + i < K ? k0 + i : 0], xr[i], sampled[i], w);
+                    } else {
+                        finish(park[(k0 + i - K) * kRowThreads + threadIdx.x], xr[i], sampled[i], w);
+                    }
+                    w.next(step, hop);
                 }
-            }
         }
         if constexpr (!KEEPX) {
-            for (int k = K; k < A.rounds; k += kRowBatch) {
-                raw_t w[kRowBatch], xr[kRowBatch];
+            for (int k = K + L; k < A.rounds; k += kRowBatch) {
+                raw_t r[kRowBatch], xr[kRowBatch];
                 bool sampled[kRowBatch];
-                const uint32_t row = rc + uint32_t(k) * step;
+                Walk wr = w;
 #pragma unroll
-                for (int u = 0; u < kRowBatch; ++u) {
-                    const uint32_t ru = row + uint32_t(u) * step;
-                    w[u] = row_load<T, V, true>(dy + size_t(min(ru, last)) * C);
-                    sampled[u] = sampled_here(ru);
-                    if (sampled[u]) xr[u] = row_load<T, V, true>(x + size_t(ru) * C);
+                for (int i = 0; i < kRowBatch; ++i) {
+                    r[i] = row_load<T, V, true>(at_byte(dy, min(wr.off, last)));
+                    sampled[i] = sampled_here(wr.row);
+                    if (sampled[i]) xr[i] = row_load<T, V, true>(at_byte(x, wr.off));
+                    wr.next(step, hop);
                 }
 #pragma unroll
-                for (int u = 0; u < kRowBatch; ++u) finish(w[u], xr[u], sampled[u], row + uint32_t(u) * step);
+                for (int i = 0; i < kRowBatch; ++i) {
+                    finish(r[i], xr[i], sampled[i], w);
+                    w.next(step, hop);
+                }
             }
         }
     }
     team_done(F, l.j, stamp);
 }
 
-// Rows kept in registers per thread.  Backward keeps x beside dy up to 16 rows.
-constexpr int kRowKeeps[] = {4, 8, 16, 40};     // (the last: see most_rows)
+// Rows kept per thread: in registers, and in LDS by the largest variant.  Backward keeps x beside dy up to 16 rows.
+constexpr int kRowKeeps[] = {4, 8, 16, 24, 64};     // (the last: see most_rows)
 constexpr int kNumRowKeeps = sizeof(kRowKeeps) / sizeof(kRowKeeps[0]);
+constexpr int kRowPark = 14;                        // 112 of the 160 KiB
 // Rows per thread up to which a block takes every row of its columns (13x29x7x10 bf16, 8 rows: 10.7 / 12.7 us against 10.0 /
 // 8.7 streaming; 28x64x6x6 f32, 8 rows: forward 8.1 against 11.9; backward 52x349x4x4 f32, 7 rows, 12.7 against 10.5).
 constexpr int row_solo(int V, bool backward) { return V == 8 ? (backward ? 4 : 5) : (backward ? 4 : 8); }
 // What the registers hold beside the sums (Eq. 4 forward walks the rows twice).
-constexpr int most_rows(int V, bool backward, bool mixed) {
-    return backward ? (V == 8 ? 28 : 40) : mixed ? 20 : (V == 8 ? 36 : 40);
+constexpr int reg_rows(int V, bool backward, bool mixed) {
+    return backward ? (V == 8 ? 35 : 40) : mixed ? 20 : (V == 8 ? 36 : 40);
 }
+constexpr int most_rows(int V, bool backward, bool mixed) { return reg_rows(V, backward, mixed) + kRowPark; }
 
 template <typename T, int V>
 const void* row_kernel(int variant, bool backward, bool mixed) {
-#define BNS_ROW_CASE(I, KF, KM, K, KX)                                                                                         \
-    case I:                                                                                                             \
-        if (backward)                                                                                                   \
-            return mixed ? reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, KX, true>)                \
-                         : reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, KX, false>);              \
-        return mixed ? reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, KM, true>)                         \
-                     : reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, KF, false>);
+#define BNS_ROW_CASE(I, K)                                                                                      \
+    case I:                                                                                                     \
+        if (backward)                                                                                           \
+            return mixed ? reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, 0, true, true>)   \
+                         : reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, 0, true, false>); \
+        return mixed ? reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, K, 0, true>)              \
+                     : reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, K, 0, false>);
     switch (variant) {
-        BNS_ROW_CASE(0, 4, 4, 4, true)
-        BNS_ROW_CASE(1, 8, 8, 8, true)
-        BNS_ROW_CASE(2, 16, 16, 16, true)
-        BNS_ROW_CASE(3, most_rows(V, false, false), most_rows(V, false, true), most_rows(V, true, false), false)
+        BNS_ROW_CASE(0, 4)
+        BNS_ROW_CASE(1, 8)
+        BNS_ROW_CASE(2, 16)
+        case 3:
+            if (backward && !mixed) return reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, 24, 0, false, false>);
+            if (!backward && !mixed) return reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, 24, 0, false>);
+            [[fallthrough]];
+        case 4:
+            if (backward)
+                return mixed ? reinterpret_cast<const void*>(
+                                   &nhwc_fused_backward_kernel<T, V, reg_rows(V, true, true), kRowPark, false, true>)
+                             : reinterpret_cast<const void*>(
+                                   &nhwc_fused_backward_kernel<T, V, reg_rows(V, true, false), kRowPark, false, false>);
+            return mixed ? reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, reg_rows(V, false, true), kRowPark, true>)
+                         : reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, reg_rows(V, false, false), kRowPark, false>);
     }
 #undef BNS_ROW_CASE
     return nullptr;
@@ -738,21 +953,22 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     int TX = lanes_for(want > 0 ? want : 4), T = 1, groups = groups_for(TX);   // rows TY at a time
     // Few rows: every block takes all rows of a narrow tile, and nothing crosses blocks.
     if (groups > row_solo(V, backward) || (opt == 1 && may_wait && M > 64u)) {
-        if (opt != 1 && bytes <= kNhwcFusedBytes && M > kNhwcFewRows) return hipErrorNotSupported;
+        if (opt != 1 && bytes <= kNhwcFusedBytes && bytes > kNhwcSmallBytes && M > kNhwcFewRows) return hipErrorNotSupported;
         // Width of a tile: 128 or 256 bytes where rows begin at multiples of 64 (a tile that shares its cache lines with the
         // next one costs a third: 63x160x44x44 f32 backward, us: 8 lanes 44, 9 lanes 82, 16 lanes 48), else 8 to 16 lanes, rather
         // more (12x432x73x70 bf16, 864 bytes per row: 9 lanes 56, 14 lanes 47); and what leaves few lanes, threads and compute
-        // units without work, with a price on the T * CT pairs of sums that every member reads (128x64x32x32 f32 forward:
-        // 128 members x 32 channels 17.6, 256 x 64 20.8).
+        // units without work, with a price on the T * CT pairs of sums that every member reads, about 1.1 us for 4096 (128x64x32x32
+        // f32 forward: 128 members x 32 channels 17.6, 256 x 64 20.8; 50x150x19x19 f32: 85 x 52 13.5 / 14.9, 51 x 32 12.5 / 13.9).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
         double best = 0.0;
         for (int lanes = want > 0 ? want : 8; lanes <= (want > 0 ? want : 16); lanes += aligned ? 8 : 1) {
             const int tx = lanes_for(lanes), g = groups_for(tx), count = (CV + tx - 1) / tx;
             const int t = std::min((g + 3) / 4, std::max(1, cus / count));
+            // what a narrower tile, idle lanes, threads or compute units cost is a share of the time at the memory; us
             const double width = aligned ? ((tx > 8) == (V == 4) ? 1.0 : 0.97) : 1.0 + 0.02 * (tx - 8);
-            const double pairs = double(t) * tx * V / 4096.0;
-            const double score = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads *
-                                 std::min(1.0, double(count * t) / cus) * width * std::max(0.1, 1.0 - 0.08 * std::max(0.0, pairs - 1.0));
+            const double use = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads *
+                               std::min(1.0, double(count * t) / cus) * width;
+            const double score = 1.0 / (6.0 + double(bytes) * (backward ? 3 : 2) / 6.2e6 / use + 1.1 * double(t) * tx * V / 4096.0);
             if (score > best) {
                 best = score;
                 TX = tx;
@@ -775,37 +991,45 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     }
     if (T > 1 && size_t(sets) * tiles * size_t(TX * V) * size_t(T) * 16 > slot_bytes) return hipErrorNotSupported;
     const int rounds = (groups + T - 1) / T;
-    // Beyond what the registers hold, rows are read twice, and the streaming kernels' short blocks do that faster; where the line
-    // lies (us, streaming against this, forward / backward, 64x256xHxW): f32 40x40 (50 rows per thread), Batch Sampling
-    // 44.0 / 71.2 against 43.8 / 58.5, a patch 47.1 / 71.1 against 47.6 / 58.9; 56x56 (98 rows) 76 / 130 against 83 / 130.
+    // Beyond what a block holds, rows are read twice, and the streaming kernels' short blocks do that faster; where the line
+    // lies (us, streaming against this, forward / backward, 64x256xHxH): f32 44x44 (61 rows per thread), Batch Sampling 54.6 / 82.7 against
+    // 50.3 / 66.9, a patch 54.9 / 82.2 against 51.7 / 67.9; 48x48 (72) 59.3 / 96.5 against 60.6 / 83.9, 58.3 / 96.0 against 62.8 / 83.0; 56x56 (98)
+    // 76.6 / 127.7 against 83.4 / 119.1; 128 samples of it (196) 145 / 256 against 165 / 250; bf16 64x64 (64) 57.4 / 89.3 against 54.2 / 83.2, a
+    // patch 57.9 / 90.2 against 62.2 / 94.5, 60x60 (57) 56.3 / 81.2 against 50.6 / 71.4; 72x72 (81) 69.9 / 109.9 against 68.0 / 109.1; 80x80 (100) 82.8 /
+    // 132.2 against 84.3 / 138.2.
     // Full BN forward reads everything twice there, up to where little of it is left in the memory-side cache: f32 128 samples (196
-    // rows) 196 against 187, 160 (245) 245 against 240, 192 (294) 295 against 296, 256 (392) 391 against 411; bf16 the same
+    // rows) 201 against 179, 160 (245) 245 against 240, 192 (294) 295 against 296, 256 (392) 391 against 411; bf16 the same
     // rows, 320 samples 251 against 245, 512 398 against 410.
     // A last tile with idle lanes costs their share of the bandwidth: 41x80x80x80 f32 (20 of 24 lanes, 49 rows) forward 41.6
-    // against 45.1, 100x96x60x60 bf16 (12 of 16, 44 rows) backward 60.5 against 77.0, 60x80x64x64 f32 backward 67.7 against 73.9, full BN
+    // against 45.1, 26x80x100x101 (48) backward 69.9 against 74.4, 100x96x60x60 bf16 (12 of 16, 44 rows) backward 60.5 against 77.0, full BN
     // forward 45.8 against 40.4 with 46 rows, 78x80x70x70 64.9 against 69.8 with 72.
     const bool everything = b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W, idle = CV * 10 < tiles * TX * 9;
-    const int most = most_rows(V, backward, mix != nullptr);
+    const int most = most_rows(V, backward, mix != nullptr), regs = reg_rows(V, backward, mix != nullptr);
     // Rows that begin on no 64 bytes are slower the second time, too: 91x92x56x56 f32, a patch, 53 rows, backward 76.5 against 100.6
-    // (where streaming has to take narrower accesses for want of whole vectors, this is still the faster).
+    // full BN forward, 56 rows, 57.8 against 73.9 (where streaming has to take narrower accesses for want of whole vectors, this is
+    // still the faster).
     const bool split_lines = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 != 0 && d.C % V == 0;
-    const int limit = !backward && everything && !mix                         ? (idle ? most + most * 2 / 5 : 256)
-                      : idle || split_lines                                   ? most
-                      : backward                                              ? 64
-                      : make_rowset(d, b).contiguous                          ? most + most * 2 / 5
-                                                                              : most;
+    const int limit = !backward && everything && !mix                         ? (idle ? regs + regs * 2 / 5 : split_lines ? regs : 256)
+                      : idle || split_lines                                   ? regs
+                      : mix                                                   ? most
+                      : backward                                              ? (V == 8 ? 81 : 128)
+                      : make_rowset(d, b).contiguous                          ? (V == 8 ? 81 : 66)
+                                                                              : (V == 8 ? 58 : 62);
     if (opt != 1 && T > 1 && rounds > limit) return hipErrorNotSupported;
-    // Ragged bf16 rows of small tensors: streaming takes single elements, and that is enough (13x137x7x7 backward 9.4 against 11.1 us,
-    // 21x58x12x12 forward 9.8 against 11.2; 12x26x25x25, 390 KB, 9.9 / 11.2 against 10.5 / 10.1).
-    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 400000) return hipErrorNotSupported;
-    // bf16 rows that do not begin on cache lines: tiles of one and the same line are read by different blocks (12x432x73x70, us:
-    // 42 / 52 against 35 / 48 streaming; 60x336x38x38 40 / 52 against 33 / 53; below 16 rows per thread this is the faster, forward
-    // with rows that begin on no 64 bytes below 10: 27x272x37x40, 12 rows, 25.0 against 21.7, 10x176x68x68, 8 rows, 20.5 against 22.7).
+    // Ragged bf16 rows of the smallest tensors: streaming takes single elements, and that is enough (13x137x7x7, 175 KB, backward 9.4
+    // against 10.3 us; 37x143x5x5, 265 KB, 11.6 / 11.2 against 9.4 / 9.8).
+    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 180000) return hipErrorNotSupported;
+    // bf16 rows that do not begin on cache lines: tiles of one and the same line are read by different blocks (us, streaming against this:
+    // 12x432x73x70, 52 rows per thread, 34.7 / 45.7 against 37.8 / 50.9; 60x336x38x38, 28 rows, 38.4 / 53.7 against 41.0 / 54.1; 75x1296x15x16, 25 rows,
+    // 34.1 / 44.6 against 34.2 / 39.5; 27x272x37x40, 12 rows, 23.7 / 31.5 against 22.7 / 22.9).
     // Full BN forward, which streaming reads twice as well, until it reads rows again itself (4x1736x84x84 70.7 against 65.5).
     const size_t pitch = size_t(d.C) * 2;
-    const int lines = backward || pitch % 64 == 0 ? 16 : 10;
+    const int lines = backward ? 26 : 16;
     if (opt != 1 && T > 1 && rounds > lines && V == 8 && d.C % V == 0 && !(everything && !backward && rounds <= most) &&
         pitch % (backward ? 64 : 128) != 0)
+        return hipErrorNotSupported;
+    // (byte offsets are 32-bit, those of rows past the end included)
+    if ((uint64_t(std::max(rounds, most + kRowBatch) + kRowBatch) * uint64_t(T) * uint64_t(TY) + uint64_t(TY)) * uint64_t(d.C) * (d.dtype == BNS_F32 ? 4u : 2u) >= (uint64_t(1) << 32))
         return hipErrorNotSupported;
     int variant = 0;
     while (variant + 1 < kNumRowKeeps && kRowKeeps[variant] < rounds) ++variant;
@@ -859,6 +1083,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     A.CV = CV;
     A.TY = TY;
     A.rounds = rounds;
+    A.pitch = uint32_t(d.C) * (d.dtype == BNS_F32 ? 4u : 2u);
     A.keep_x = bytes <= kKeepBytes;
     const bool mixed = mix != nullptr;
     const void* kernel = V == 8               ? row_kernel<bf16_t, 8>(variant, backward, mixed)

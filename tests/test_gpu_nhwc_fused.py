@@ -270,3 +270,20 @@ def test_a_call_beside_a_capture_leaves_the_capture_alone(layout):
         torch.cuda.synchronize()
         graph.replay()
         assert_parity(a.results(), ref, wl, what="replay", inp=inp)
+
+
+@pytest.mark.parametrize("dtype,rounds", [("f32", 24), ("f32", 25), ("f32", 54), ("f32", 55), ("bf16", 25), ("bf16", 49), ("bf16", 50), ("bf16", 51)])
+def test_rows_in_registers_and_lds(dtype, rounds):
+    """The last number of rows that a variant holds and the first that it does not: registers alone (24), registers and LDS (backward 54
+    in fp32, 49 in bf16; forward 54 and 50), a row that is read again."""
+    V = 4 if dtype == "f32" else 8
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 64 * (units // 16) * (rounds - 1) + 37
+    for i, mkw in enumerate((dict(mode=FULL), dict(mode=BS, n_s=1))):
+        wl = Workload(name="rows_lds", N=3, C=128 * V, H=1, W=rows // 3, dtype=dtype, layout="nhwc", data_seed=64 + i, sampling_seed=4,
+                      layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch, {rounds} rows per thread {wl.shape} {dtype} {mkw}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
+        assert _paths() == (2, 2)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
