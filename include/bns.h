@@ -206,6 +206,8 @@ bns_status bns_expired_waits(void* workspace, size_t workspace_bytes, void* stre
  * that took the streaming kernels ("last_path_forward" / "last_path_backward" = 1) carries the bits of its
  * stages; the single-launch kernels sum in another order and can differ from them in the last bits.  In
  * N x H x W x C these are the default up to 8192 rows (N*H*W) and, as far as they are the faster side, beyond 4 MB.
+ * Beyond them bns_backward of that layout may write part of dx while it sums ("last_path_backward" = 4, "nhwc_split_ordered"), in an
+ * order of its own, too (with "path" = 1 or "nhwc_split_dx" = 2 it does not).
  *
  * bns_forward_stats     Eq. 3 + Eq. 8: statistics of x over S and running averages.
  * bns_forward_normalize Eq. 1: y from x and the saved statistics, all points.
@@ -323,9 +325,12 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "nhwc_fused_lanes"  128-bit accesses per row of a block's column tile in them  (1..32)
  *   "nhwc_blocks"    blocks that an N x H x W x C reduction launch aims for      (1..8192)
  *   "nhwc_ew_rows"   rows per thread in the N x H x W x C element-wise kernels   (1..2^20)
- *   "nhwc_split_dx"  1: the N x H x W x C backward writes dx on the rows outside S from its reduction kernel (Eq. 6
- *                    needs no sum there) and the rows of S from a kernel of their own; by default (and with 2)
- *                    the reduction is followed by one dx kernel over all rows, which is faster on this device
+ *   "nhwc_split_dx"  the N x H x W x C backward writes dx on the rows outside S from its reduction kernel (Eq. 6
+ *                    needs no sum there) and the rows of S from a kernel of their own: 1 always, with the bits of the stage calls;
+ *                    2 never; 0: see "nhwc_split_ordered"
+ *   "nhwc_split_ordered"  with "nhwc_split_dx" = 0 and "path" other than 1, bns_backward does so front to back, which adds the rows in another
+ *                    order: 1 whenever it can (16-byte accesses), 2 never; 0: S at most a quarter of the rows, tensors from 16 MB
+ *                    whose channels fill the lanes, where the single launch does not run
  *   "cache_reuse"    streaming kernels: a first pass (statistics; the sums of Eq. 5) loads what the pass after it
  *                    (Eq. 1; Eq. 6) reads again without the non-temporal hint, so that it stays in the device's
  *                    memory-side cache: 1 all of it, 2 none; 0: as much as fits there (224 MB).  Results do not
@@ -352,7 +357,7 @@ bns_status bns_set_option(const char* name, int32_t value);
 /* Current value of an option (as set, 0 = automatic); also, kept per calling thread,
  * "last_path_forward" / "last_path_backward": 1 if this thread's last bns_forward / bns_backward took the streaming kernels, 2 if the fused one, 3 if a
  * one-launch N x H x W x C kernel whose blocks do not wait for each other (few rows), 4 (backward, N x H x W x C) the streaming kernels with dx split
- * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx"); "last_fused_backward": which fused backward kernel that was
+ * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx", "nhwc_split_ordered"); "last_fused_backward": which fused backward kernel that was
  * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels, 5 one block per compute unit); "last_fused_forward": 3 if groups of
  * channels, 4 if one block per compute unit,
  * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was

@@ -86,6 +86,7 @@ const TuningEntry kTuningTable[] = {
     {"nhwc_fused_lanes", &Tuning::nhwc_fused_lanes, 32, 0, false},
     {"nhwc_ew_rows", &Tuning::nhwc_ew_rows, 1 << 20, 0, false},
     {"nhwc_small", &Tuning::nhwc_small, 2, 0, false},
+    {"nhwc_split_ordered", &Tuning::nhwc_split_ordered, 2, 0, false},
     {"nhwc_split_dx", &Tuning::nhwc_split_dx, 2, 0, false},
     {"cache_reuse", &Tuning::cache_reuse, 2, 0, false},
 };
@@ -390,12 +391,14 @@ bns_status backward_impl(const bns_shape* shape, const bns_spec* spec, uint64_t 
             return s;
         t_last_path_backward = 1;
         // Eq. 6 outside S needs none of the sums: the reduction kernel can write dx there while it has dy in
-        // registers, which leaves only the rows of S for after the sums and saves one read of dy from memory.  Only on
-        // request: the dx pass finds most of dy in the memory-side cache, and that second read costs less than the
-        // slower kernel that the split makes of the reduction (measured up to 128 x 256 x 56 x 56).
-        if (g_tuning.nhwc_split_dx == 1) {
+        // registers, which leaves only the rows of S for after the sums and saves one read of dy from memory.  By default where
+        // that kernel can go through the rows front to back and the rule of nhwc_split_ordered holds; in shares, with the
+        // bits of the stage calls, only on request: it is the slower side ("path" = 1 asks for those bits, too).
+        const bool split = g_tuning.nhwc_split_dx == 1;
+        const bool ordered = !split && g_tuning.nhwc_split_dx == 0 && g_tuning.path != 1 && nhwc_split_ordered(d, ip.shared);
+        if (split || ordered) {
             t_last_path_backward = 4;
-            return dev(launch_nhwc_backward_split(d, ip.shared, x, dy, gamma, save_mean, save_invstd, ws, dgamma, dbeta, dx, st));
+            return dev(launch_nhwc_backward_split(d, ip.shared, x, dy, gamma, save_mean, save_invstd, ws, dgamma, dbeta, dx, ordered, st));
         }
         if (launch_nhwc_reduce(d, x, dy, save_mean, save_invstd, ws, dgamma, dbeta, x_again, st) != hipSuccess)
             return BNS_EDEVICE;

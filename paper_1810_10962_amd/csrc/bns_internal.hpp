@@ -89,6 +89,7 @@ struct Tuning {
     TuneInt nhwc_fused{0};                  // single-launch kernels of this layout: 1 whenever they fit, 2 never, 0 from a size on
     TuneInt nhwc_fused_lanes{0};            // column vectors of a tile in those kernels
     TuneInt nhwc_ew_rows{0};                // rows per row lane in its element-wise kernels (default kNhwcEwRows)
+    TuneInt nhwc_split_ordered{0};          // that kernel front to back (beyond the single launch): 1 whenever it can run, 2 never
     TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always; 0, 2 never
     // For the library's own tests of the give-up path only; a caller has no use for them.
     TuneInt test_spin_limit{0};             // polls a team member waits for a team-mate before giving up (default 2^21)
@@ -240,9 +241,10 @@ hipError_t launch_nhwc_reduce(const Dims& d, const void* x, const void* dy, cons
                               Partial* partial, float* dgamma, float* dbeta, bool x_again, hipStream_t st);
 // Backward with dx split by the two branches of Eq. 6: the reduction kernel also writes dx outside S, a second
 // element-wise kernel takes the rows of S after the sums ((3 + 2r) e bytes per element instead of (4 + r) e).
+bool nhwc_split_ordered(const Dims& d, const bns_box& b);
 hipError_t launch_nhwc_backward_split(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
                                       const float* mean, const float* invstd, Partial* partial, float* dgamma,
-                                      float* dbeta, void* dx, hipStream_t st);
+                                      float* dbeta, void* dx, bool ordered, hipStream_t st);
 hipError_t launch_nhwc_dx(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
                           const float* mean, const float* invstd, const float* dgamma, const float* dbeta, void* dx,
                           hipStream_t st);

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "bns_device.hpp"
+#include "bns_fused_device.hpp"
 #include "bns_internal.hpp"
 #include "bns_nhwc_device.hpp"
 
@@ -316,6 +317,108 @@ __global__ __launch_bounds__(kBlock) void nhwc_reduce_outside_kernel(const T* __
                                                                      const float* __restrict__ invstd, RowBox B) {
     __shared__ float lds[2 * kBlock * V];
     reduce_partial_body<T, V, true, 0>(x, dy, mean, partial, t, M, dx, gamma, invstd, B, lds, 0u);
+}
+
+// Sums and dx outside S as above for 16-byte vectors, front to back: block k takes the chunks k, k + splits, ... of
+// kSplitRows rows per row lane, so that the whole launch reads and writes one window that moves through the tensors, as a flat
+// copy does.  Loads alone do not mind blocks that each walk a share of their own; with stores between them that costs a
+// fifth of the rate (128x256x56x56 f32, the whole backward pass: shares 255 us, front to back 231; 4.9 and 6.0 TB/s).
+// The loads of the next chunk are issued before this one is added up and stored, and neither loads nor stores hang on a
+// condition, which would make each wait one for everything in flight: a row past the end is loaded as the last one and left out of
+// the sums, and rows that must not be written (those, and the rows of S) are stored to an offset beyond the buffer, which
+// the address check drops.  Rows are added in pairs in fp32, pairs in fp64, as in reduce_partial_body.
+// CONTIG: S is one run of rows.  (Chunks that touch S loaded without the non-temporal hint, for nhwc_dx_rows_kernel to find them in
+// the memory-side cache, cost more than they gave: the choice between the two loads is a branch in the loop, 246 us.)
+constexpr int kSplitRows = 4;
+
+template <typename T, int V, bool CONTIG>
+__global__ __launch_bounds__(kBlock, 2) void nhwc_reduce_outside_ordered_kernel(
+    const T* __restrict__ x, const T* __restrict__ dy, const float* __restrict__ mean, Partial* __restrict__ partial, Tiling t,
+    uint32_t M, T* __restrict__ dx, const float* __restrict__ gamma, const float* __restrict__ invstd, RowBox B, uint32_t s_lo,
+    uint32_t s_rows) {
+    typedef RawVec<T, V> RV;
+    typedef typename RV::raw_t raw_t;
+    typedef uint32_t store_t __attribute__((ext_vector_type(4)));
+    __shared__ float lds[2 * kBlock * V];
+    Lane l = lane_of(t);
+    const uint32_t tiles = gridDim.x / uint32_t(t.splits);              // the tiles of a chunk side by side
+    l.k = int(blockIdx.x / tiles);
+    l.cv = int((blockIdx.x - uint32_t(l.k) * tiles) << t.log2_tx) + l.tx;
+    l.live = l.cv < t.CV;
+    const uint32_t TY = uint32_t(l.TY), step = uint32_t(kSplitRows) * TY, chunks = (M + step - 1u) / step, G = uint32_t(t.splits);
+    const uint32_t pitch = uint32_t(t.C) * uint32_t(sizeof(T));
+    // (lanes past the last channel vector repeat it and store nothing)
+    const uint32_t cv = uint32_t(l.live ? l.cv : t.CV - 1), col = cv * uint32_t(V * sizeof(T));
+    float mu[V], sc[V], a[V], q[V];
+    double A[V], Q[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        mu[e] = mean[cv * V + e];
+        sc[e] = gamma[cv * V + e] * invstd[cv * V + e];                 // a = gamma r
+        A[e] = Q[e] = 0.0;
+    }
+    raw_t g[2][kSplitRows], v[2][kSplitRows];
+    auto load = [&](int at, uint32_t chunk) {
+        const uint32_t r0 = min(chunk, chunks - 1u) * step, rows = min(step, M - r0);
+        const char* xb = reinterpret_cast<const char*>(x + size_t(r0) * t.C);
+        const char* gb = reinterpret_cast<const char*>(dy + size_t(r0) * t.C);
+#pragma unroll
+        for (int u = 0; u < kSplitRows; ++u) {
+            const uint32_t off = min(uint32_t(l.ty) + uint32_t(u) * TY, rows - 1u) * pitch + col;
+            g[at][u] = __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(gb + off));
+            v[at][u] = __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(xb + off));
+        }
+    };
+    auto add = [&](int at, uint32_t chunk) {
+        if (chunk >= chunks) return;
+        const uint32_t r0 = chunk * step, rows = min(step, M - r0);
+        const auto out = __builtin_amdgcn_make_buffer_rsrc(dx + size_t(r0) * t.C, 0, int(rows * pitch), 0x00027000);
+        float p1[V], p2[V];
+#pragma unroll
+        for (int u = 0; u < kSplitRows; ++u) {
+            const uint32_t r = uint32_t(l.ty) + uint32_t(u) * TY, row = r0 + r;
+            const bool live = r < rows;
+            float fg[V], fx[V];
+            RV::unpack(g[at][u], fg);
+            RV::unpack(v[at][u], fx);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const float d = live ? fx[e] - mu[e] : 0.f, h = live ? fg[e] : 0.f;
+                if (u % 2 == 0) {
+                    p1[e] = h;
+                    p2[e] = h * d;
+                } else {
+                    A[e] += double(p1[e] + h);
+                    Q[e] += double(fmaf(h, d, p2[e]));
+                }
+                fg[e] *= sc[e];
+            }
+            const bool in = CONTIG ? row - s_lo < s_rows : row_in(B, row);
+            const uint32_t off = live && l.live && !in ? r * pitch + col : 0x7FFFFFF0u;
+            union {
+                raw_t raw;
+                store_t words;
+            } w;
+            w.raw = RV::pack(fg);
+            __builtin_amdgcn_raw_buffer_store_b128(w.words, out, int(off), 0, 2);        // 2: non-temporal
+        }
+    };
+    uint32_t i = uint32_t(l.k);
+    load(0, i);
+    for (; i < chunks; i += 2u * G) {
+        load(1, i + G);
+        __builtin_amdgcn_sched_barrier(0);
+        add(0, i);
+        load(0, i + 2u * G);
+        __builtin_amdgcn_sched_barrier(0);
+        add(1, i + G);
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        a[e] = float(A[e]);
+        q[e] = float(Q[e]);
+    }
+    write_partials<V>(a, q, lds, t, l, partial);
 }
 
 // Finalize kernels: a block takes kFinCh neighbouring channels; thread (ch, kl) adds the partials
@@ -822,23 +925,50 @@ hipError_t launch_nhwc_reduce(const Dims& d, const void* x, const void* dy, cons
     });
 }
 
+// Does a whole backward call that the single launch does not take use the reduction that writes dx outside S front to back?  It can
+// where accesses are 16 bytes and a chunk's offsets stay below 2^30.  It is the faster side (us, streaming against this)
+//   * where S is small, since the rows of S are read again and those outside are not: 128x256x56x56 f32 a patch of 1/16 248 / 224,
+//     Batch Sampling 1/8 251 / 231, 3/4 289 / 294; bf16 1/8 129 / 121, 1/4 132 / 126, 1/2 140 / 139;
+//   * where few column lanes idle: 120x1024x24x24 f32 179 / 152, 100x480x45x45 (120 of 128 lanes) 248 / 235, 40x200x70x70 (50 of 64)
+//     103.0 / 105.4, 100x328x45x45 (82 of 128) 194 / 206;
+//   * beyond a few launches' worth of bytes: 32x256x28x28 f32 (26 MB) 25.0 / 24.4, 6x128x28x28 (2.4 MB) 11.8 / 12.9.
+bool nhwc_split_ordered(const Dims& d, const bns_box& b) {
+    const int opt = g_tuning.nhwc_split_ordered;
+    const size_t size = d.dtype == BNS_F32 ? 4 : 2, pitch = size_t(d.C) * size, M = size_t(d.N) * size_t(d.HW);
+    if (opt == 2 || column_vec(d) * size != 16 || pitch * size_t(kBlock * kSplitRows) >= (size_t(1) << 30)) return false;
+    if (opt == 1) return true;
+    const Tiling t = make_tiling(d, uint32_t(M));
+    const size_t lanes = size_t((t.CV + (1 << t.log2_tx) - 1) >> t.log2_tx) << t.log2_tx;
+    return 4 * size_t(b.n_cnt) * size_t(b.h_cnt) * size_t(b.w_cnt) <= M && 8 * size_t(t.CV) >= 7 * lanes && M * pitch >= size_t(16) << 20;
+}
+
 // The whole backward pass with dx split by Eq. 6's two branches: sums + dx outside S, finalize, dx on S.
 hipError_t launch_nhwc_backward_split(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
                                       const float* mean, const float* invstd, Partial* partial, float* dgamma,
-                                      float* dbeta, void* dx, hipStream_t st) {
+                                      float* dbeta, void* dx, bool ordered, hipStream_t st) {
     const uint32_t M = uint32_t(d.N) * uint32_t(d.HW);
-    const Tiling t = make_tiling(d, M);      // the tiling of launch_nhwc_reduce: same partials, same sums, bit for bit
+    const Tiling t = make_tiling(d, M);      // the tiling of launch_nhwc_reduce: same partials, same sums, bit for bit (not `ordered`)
     if (!fits_region(d, t)) return hipErrorInvalidValue;
     const RowBox B = make_rowbox(d, b);
     const RowSet S = make_rowset(d, b);
     const Tiling ts = make_tiling(d, S.rows, 0, true);
+    const uint32_t s_lo = (uint32_t(b.n0) * uint32_t(d.H) + uint32_t(b.h0)) * uint32_t(d.W) + uint32_t(b.w0);
     const double s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
     return dispatch_nhwc(d, [&](auto ty, auto vt) {
         using T = decltype(ty);
         constexpr int V = decltype(vt)::value;
-        BNS_LAUNCH((nhwc_reduce_outside_kernel<T, V>), dim3(grid_of(t)), dim3(kBlock), 0, st,
-                   static_cast<const T*>(x), static_cast<const T*>(dy), mean, partial, t, M, static_cast<T*>(dx), gamma,
-                   invstd, B);
+        const T* xp = static_cast<const T*>(x);
+        const T* gp = static_cast<const T*>(dy);
+        T* op = static_cast<T*>(dx);
+        const dim3 grid(grid_of(t)), block(kBlock);
+        if constexpr (V * sizeof(T) == 16) {
+            if (ordered) {
+                auto kernel = S.contiguous ? &nhwc_reduce_outside_ordered_kernel<T, V, true> : &nhwc_reduce_outside_ordered_kernel<T, V, false>;
+                BNS_LAUNCH((*kernel), grid, block, 0, st, xp, gp, mean, partial, t, M, op, gamma, invstd, B, s_lo, S.rows);
+            }
+        }
+        if (!ordered)
+            BNS_LAUNCH((nhwc_reduce_outside_kernel<T, V>), grid, block, 0, st, xp, gp, mean, partial, t, M, op, gamma, invstd, B);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         BNS_LAUNCH(nhwc_reduce_finalize_kernel, dim3(ceil_div_u(uint32_t(d.C), kFinCh)), dim3(kBlock), 0, st,
