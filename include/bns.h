@@ -334,7 +334,7 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *   "cache_reuse"    streaming kernels: a first pass (statistics; the sums of Eq. 5) loads what the pass after it
  *                    (Eq. 1; Eq. 6) reads again without the non-temporal hint, so that it stays in the device's
  *                    memory-side cache: 1 all of it, 2 none; 0: as much as fits there (224 MB).  Results do not
- *                    depend on it.
+ *                    depend on it (nor does the "nhwc_split_ordered" backward, which loads by a rule of its own).
  *   "nhwc_small"     2: N x H x W x C tensors of every size take the streaming kernels, as with "nhwc_fused" = 2
  *   "norm_unroll", "dx_unroll", "reduce_unroll"   128-bit accesses per thread    (1, 2, 4)
  *   "norm_nt", "dx_nt"   non-temporal access mask + 1: bit 0 loads, bit 1 stores

@@ -327,11 +327,11 @@ __global__ __launch_bounds__(kBlock) void nhwc_reduce_outside_kernel(const T* __
 // condition, which would make each wait one for everything in flight: a row past the end is loaded as the last one and left out of
 // the sums, and rows that must not be written (those, and the rows of S) are stored to an offset beyond the buffer, which
 // the address check drops.  Rows are added in pairs in fp32, pairs in fp64, as in reduce_partial_body.
-// CONTIG: S is one run of rows.  (Chunks that touch S loaded without the non-temporal hint, for nhwc_dx_rows_kernel to find them in
-// the memory-side cache, cost more than they gave: the choice between the two loads is a branch in the loop, 246 us.)
+// CONTIG: S is one run of rows.  KEEP: the chunks that hold it come last and are loaded without the non-temporal hint, so that
+// nhwc_dx_rows_kernel finds them in the memory-side cache.
 constexpr int kSplitRows = 4;
 
-template <typename T, int V, bool CONTIG>
+template <typename T, int V, bool CONTIG, bool KEEP>
 __global__ __launch_bounds__(kBlock, 2) void nhwc_reduce_outside_ordered_kernel(
     const T* __restrict__ x, const T* __restrict__ dy, const float* __restrict__ mean, Partial* __restrict__ partial, Tiling t,
     uint32_t M, T* __restrict__ dx, const float* __restrict__ gamma, const float* __restrict__ invstd, RowBox B, uint32_t s_lo,
@@ -358,19 +358,20 @@ __global__ __launch_bounds__(kBlock, 2) void nhwc_reduce_outside_ordered_kernel(
         A[e] = Q[e] = 0.0;
     }
     raw_t g[2][kSplitRows], v[2][kSplitRows];
-    auto load = [&](int at, uint32_t chunk) {
-        const uint32_t r0 = min(chunk, chunks - 1u) * step, rows = min(step, M - r0);
+    auto load = [&](int at, uint32_t chunk, auto kept) __attribute__((always_inline)) {
+        const uint32_t r0 = chunk * step, rows = min(step, M - r0);
         const char* xb = reinterpret_cast<const char*>(x + size_t(r0) * t.C);
         const char* gb = reinterpret_cast<const char*>(dy + size_t(r0) * t.C);
 #pragma unroll
         for (int u = 0; u < kSplitRows; ++u) {
             const uint32_t off = min(uint32_t(l.ty) + uint32_t(u) * TY, rows - 1u) * pitch + col;
-            g[at][u] = __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(gb + off));
-            v[at][u] = __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(xb + off));
+            const raw_t* pg = reinterpret_cast<const raw_t*>(gb + off);
+            const raw_t* px = reinterpret_cast<const raw_t*>(xb + off);
+            g[at][u] = decltype(kept)::value ? *pg : __builtin_nontemporal_load(pg);
+            v[at][u] = decltype(kept)::value ? *px : __builtin_nontemporal_load(px);
         }
     };
-    auto add = [&](int at, uint32_t chunk) {
-        if (chunk >= chunks) return;
+    auto add = [&](int at, uint32_t chunk) __attribute__((always_inline)) {
         const uint32_t r0 = chunk * step, rows = min(step, M - r0);
         const auto out = __builtin_amdgcn_make_buffer_rsrc(dx + size_t(r0) * t.C, 0, int(rows * pitch), 0x00027000);
         float p1[V], p2[V];
@@ -403,15 +404,27 @@ __global__ __launch_bounds__(kBlock, 2) void nhwc_reduce_outside_ordered_kernel(
             __builtin_amdgcn_raw_buffer_store_b128(w.words, out, int(off), 0, 2);        // 2: non-temporal
         }
     };
-    uint32_t i = uint32_t(l.k);
-    load(0, i);
-    for (; i < chunks; i += 2u * G) {
-        load(1, i + G);
-        __builtin_amdgcn_sched_barrier(0);
-        add(0, i);
-        load(0, i + 2u * G);
-        __builtin_amdgcn_sched_barrier(0);
-        add(1, i + G);
+    // The chunks chunk_of(i), i = first, first + G, ... below count.
+    auto walk = [&](uint32_t first, uint32_t count, auto kept, auto&& chunk_of) __attribute__((always_inline)) {
+        if (first >= count) return;
+        auto next = [&](uint32_t i) { return chunk_of(min(i, count - 1u)); };
+        load(0, next(first), kept);
+        for (uint32_t i = first; i < count; i += 2u * G) {
+            load(1, next(i + G), kept);
+            __builtin_amdgcn_sched_barrier(0);
+            add(0, next(i));
+            load(0, next(i + 2u * G), kept);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + G < count) add(1, next(i + G));
+        }
+    };
+    const uint32_t k = uint32_t(l.k);
+    if constexpr (KEEP) {
+        const uint32_t c0 = s_lo / step, held = (s_lo + s_rows - 1u) / step + 1u - c0, rest = chunks - held;
+        walk(k, rest, std::false_type(), [&](uint32_t i) { return i < c0 ? i : i + held; });
+        walk((k + G - rest % G) % G, held, std::true_type(), [&](uint32_t i) { return c0 + i; });      // (those with a chunk less first)
+    } else {
+        walk(k, chunks, std::false_type(), [&](uint32_t i) { return i; });
     }
 #pragma unroll
     for (int e = 0; e < V; ++e) {
@@ -928,8 +941,8 @@ hipError_t launch_nhwc_reduce(const Dims& d, const void* x, const void* dy, cons
 // Does a whole backward call that the single launch does not take use the reduction that writes dx outside S front to back?  It can
 // where accesses are 16 bytes and a chunk's offsets stay below 2^30.  It is the faster side (us, streaming against this)
 //   * where S is small, since the rows of S are read again and those outside are not: 128x256x56x56 f32 a patch of 1/16 248 / 224,
-//     Batch Sampling 1/8 251 / 231, 3/4 289 / 294; bf16 1/8 129 / 121, 1/4 132 / 126, 1/2 140 / 139;
-//   * where few column lanes idle: 120x1024x24x24 f32 179 / 152, 100x480x45x45 (120 of 128 lanes) 248 / 235, 40x200x70x70 (50 of 64)
+//     Batch Sampling 1/8 251 / 223, 1/4 258 / 241, 3/4 289 / 294; bf16 1/8 129 / 117, 1/4 132 / 122, 1/2 140 / 139;
+//   * where few column lanes idle: 120x1024x24x24 f32 179 / 152, 100x480x45x45 (120 of 128 lanes) 247 / 230, 40x200x70x70 (50 of 64)
 //     103.0 / 105.4, 100x328x45x45 (82 of 128) 194 / 206;
 //   * beyond a few launches' worth of bytes: 32x256x28x28 f32 (26 MB) 25.0 / 24.4, 6x128x28x28 (2.4 MB) 11.8 / 12.9.
 bool nhwc_split_ordered(const Dims& d, const bns_box& b) {
@@ -963,7 +976,13 @@ hipError_t launch_nhwc_backward_split(const Dims& d, const bns_box& b, const voi
         const dim3 grid(grid_of(t)), block(kBlock);
         if constexpr (V * sizeof(T) == 16) {
             if (ordered) {
-                auto kernel = S.contiguous ? &nhwc_reduce_outside_ordered_kernel<T, V, true> : &nhwc_reduce_outside_ordered_kernel<T, V, false>;
+                // (a walk of its own for the rows of S costs a drained pipeline: a single sample of 128, 196 chunks for 512 blocks, 218 us
+                // against 214; sixteen, six chunks per block, 223 against 232.  Not the "cache_reuse" option: the order of the sums depends on it)
+                const uint32_t held = S.rows / (uint32_t(kSplitRows) * uint32_t(kBlock >> t.log2_tx));
+                const bool keep = 2 * size_t(S.rows) * size_t(d.C) * sizeof(T) <= kKeepBytes && held >= 2u * uint32_t(t.splits);
+                auto kernel = !S.contiguous ? &nhwc_reduce_outside_ordered_kernel<T, V, false, false>
+                              : keep        ? &nhwc_reduce_outside_ordered_kernel<T, V, true, true>
+                                            : &nhwc_reduce_outside_ordered_kernel<T, V, true, false>;
                 BNS_LAUNCH((*kernel), grid, block, 0, st, xp, gp, mean, partial, t, M, op, gamma, invstd, B, s_lo, S.rows);
             }
         }
