@@ -241,10 +241,11 @@ hipError_t launch_nhwc_reduce(const Dims& d, const void* x, const void* dy, cons
                               Partial* partial, float* dgamma, float* dbeta, bool x_again, hipStream_t st);
 // Backward with dx split by the two branches of Eq. 6: the reduction kernel also writes dx outside S, a second
 // element-wise kernel takes the rows of S after the sums ((3 + 2r) e bytes per element instead of (4 + r) e).
-bool nhwc_split_ordered(const Dims& d, const bns_box& b);
 hipError_t launch_nhwc_backward_split(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
                                       const float* mean, const float* invstd, Partial* partial, float* dgamma,
                                       float* dbeta, void* dx, bool ordered, hipStream_t st);
+// Whether bns_backward takes it `ordered` (front to back, 16-byte accesses) where the single launch does not run.
+bool nhwc_split_ordered(const Dims& d, const bns_box& b);
 hipError_t launch_nhwc_dx(const Dims& d, const bns_box& b, const void* x, const void* dy, const float* gamma,
                           const float* mean, const float* invstd, const float* dgamma, const float* dbeta, void* dx,
                           hipStream_t st);
