@@ -202,11 +202,11 @@ hipError_t read_expired_waits(void* header, hipStream_t st, int32_t* expired);
 hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                              void* header, void* slots, size_t slot_bytes, hipStream_t st, const FusedMix* mix,
                              bool may_create_event, bool may_wait, bool* solo);
-// Taken by tensors of few rows, by small and by large ones.  The band between, the last 32 KiB up to 4 MiB, keeps the streaming kernels for their bits, not
-// for their speed: whole calls there always gave the bits of the stage calls, and test_bit_identical_reruns_and_stage_calls holds its
-// tensor, which lies exactly at the upper limit, to that (16x64x32x32 f32: 13.0 / 14.7 us against 9.8 / 10.3 in one launch).  Below it
-// the launches of the streaming kernels are most of the time (101x16x14x14 bf16 15.5 / 14.8 us streaming, 9.1 / 8.9 in one launch).
-constexpr size_t kNhwcFusedBytes = size_t(4) << 20, kNhwcSmallBytes = kNhwcFusedBytes - (size_t(32) << 10);
+// Taken by tensors of few rows and by large ones.  What lies between, more rows than kNhwcFewRows in up to 4 MiB, keeps the streaming
+// kernels although they are the slower side (101x16x14x14 bf16 15.5 / 14.8 us against 9.1 / 8.9 in one launch, 16x64x32x32 f32 13.0 /
+// 14.7 against 9.8 / 10.3): a whole call there carries the bits of its stage calls, a captured call those of an eager one, and calls
+// on several streams overlap, none of which kernels whose blocks wait for each other can give.
+constexpr size_t kNhwcFusedBytes = size_t(4) << 20;
 constexpr uint32_t kNhwcFewRows = 8192;
 
 // What the single-launch kernels share (bns_fused.hip): compute units of the current device; a start for the exchange

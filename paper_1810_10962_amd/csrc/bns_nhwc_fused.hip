@@ -953,7 +953,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     int TX = lanes_for(want > 0 ? want : 4), T = 1, groups = groups_for(TX);   // rows TY at a time
     // Few rows: every block takes all rows of a narrow tile, and nothing crosses blocks.
     if (groups > row_solo(V, backward) || (opt == 1 && may_wait && M > 64u)) {
-        if (opt != 1 && bytes <= kNhwcFusedBytes && bytes > kNhwcSmallBytes && M > kNhwcFewRows) return hipErrorNotSupported;
+        if (opt != 1 && bytes <= kNhwcFusedBytes && M > kNhwcFewRows) return hipErrorNotSupported;
         // Width of a tile: 128 or 256 bytes where rows begin at multiples of 64 (a tile that shares its cache lines with the
         // next one costs a third: 63x160x44x44 f32 backward, us: 8 lanes 44, 9 lanes 82, 16 lanes 48), else 8 to 16 lanes, rather
         // more (12x432x73x70 bf16, 864 bytes per row: 9 lanes 56, 14 lanes 47); and what leaves few lanes, threads and compute

@@ -287,3 +287,41 @@ def test_rows_in_registers_and_lds(dtype, rounds):
         res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
         assert _paths() == (2, 2)
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(N=101, C=16, H=14, W=14, dtype="bf16"),            # 633 KB, 19796 rows
+    dict(N=43, C=24, H=14, W=14, dtype="f32"),              # 809 KB, 8428 rows
+    dict(N=33, C=10, H=16, W=16, dtype="bf16"),             # 8448 rows, columns that are no whole number of vectors
+    dict(N=16, C=63, H=32, W=32, dtype="f32"),              # 4 MiB less 64 KiB
+], ids=lambda kw: "{N}x{C}x{H}x{W}-{dtype}".format(**kw))
+def test_many_rows_in_up_to_4_mib_carry_the_bits_of_the_stage_calls(kw):
+    """More than 8192 rows, up to 4 MiB: a whole call has the bits of its stage calls, and a captured one those of an eager one."""
+    wl = Workload(name="nhwc_band", layout="nhwc", mode=FS, patch_h=5, patch_w=7, data_seed=17, sampling_seed=8, layer_id=4, **kw)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] many rows in up to 4 MiB {wl.shape} {wl.dtype}", flush=True)
+    whole = bns.run_workload(wl, inp)
+    assert _paths() == (1, 1)
+    buf = bns.Buffers(wl, inp)
+    bns.bns_forward_stats(buf.shape, buf.spec, buf.seed, buf.x, wl.eps, wl.momentum, buf.save_mean, buf.save_invstd,
+                          buf.running_mean, buf.running_var, buf.workspace)
+    bns.bns_forward_normalize(buf.shape, buf.x, buf.gamma, buf.beta, buf.save_mean, buf.save_invstd, buf.y)
+    bns.bns_backward_reduce(buf.shape, buf.x, buf.dy, buf.save_mean, buf.save_invstd, buf.dgamma, buf.dbeta, buf.workspace)
+    bns.bns_backward_dx(buf.shape, buf.spec, buf.seed, buf.x, buf.dy, buf.gamma, buf.save_mean, buf.save_invstd, buf.dgamma,
+                        buf.dbeta, buf.dx)
+    stages = buf.results()
+    buf = bns.Buffers(wl, inp)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        buf.forward()
+        buf.backward()
+    for _ in range(3):
+        buf.running_mean.copy_(torch.from_numpy(inp["running_mean"]))
+        buf.running_var.copy_(torch.from_numpy(inp["running_var"]))
+        buf.y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+    replay = buf.results()
+    for k in whole:
+        assert (whole[k] == stages[k]).all() and (whole[k] == replay[k]).all(), k
