@@ -1028,9 +1028,9 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     if (opt != 1 && T > 1 && rounds > lines && V == 8 && d.C % V == 0 && !(everything && !backward && rounds <= most) &&
         pitch % (backward ? 64 : 128) != 0)
         return hipErrorNotSupported;
-    // (byte offsets are 32-bit, those of rows past the end included)
-    if ((uint64_t(std::max(rounds, most + kRowBatch) + kRowBatch) * uint64_t(T) * uint64_t(TY) + uint64_t(TY)) * uint64_t(d.C) * (d.dtype == BNS_F32 ? 4u : 2u) >= (uint64_t(1) << 32))
-        return hipErrorNotSupported;
+    // Byte offsets are 32-bit.  Those of rows past the end may wrap: loads are clamped to the last row, so what is read lies in the
+    // tensor, and sums and stores go by the row's number.
+    if (bytes >= (size_t(1) << 32)) return hipErrorNotSupported;
     int variant = 0;
     while (variant + 1 < kNumRowKeeps && kRowKeeps[variant] < rounds) ++variant;
 

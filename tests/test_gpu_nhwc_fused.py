@@ -325,3 +325,31 @@ def test_many_rows_in_up_to_4_mib_carry_the_bits_of_the_stage_calls(kw):
     replay = buf.results()
     for k in whole:
         assert (whole[k] == stages[k]).all() and (whole[k] == replay[k]).all(), k
+
+
+@pytest.mark.parametrize("shape", [(2, 131072, 2, 2), (5, 9000000, 1, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_few_rows_of_very_many_channels(shape):
+    """Rows so long that the offsets of rows past the end, which the kernel walks over, approach (first shape) or pass (second)
+    32 bits: one launch without waits, the results of the streaming kernels."""
+    N, C_, H, W = shape
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    rand = lambda *s: torch.rand(*s, generator=gen, device="cuda")                  # noqa: E731
+    sh, sp = bns.make_shape(N, C_, H, W, "f32", "nhwc"), bns.make_spec(BS, N - 1, 0, 0, 0, 3, 0)
+    x, dy, gamma, beta = rand(N, H, W, C_) - 0.3, rand(N, H, W, C_) - 0.5, rand(C_) + 0.5, rand(C_)
+    ws = torch.empty(bns.bns_workspace_bytes(sh, sp), dtype=torch.uint8, device="cuda")
+    print(f"[gpu-case] few rows of very many channels {shape}", flush=True)
+
+    def step():
+        out = dict(y=torch.empty_like(x), dx=torch.empty_like(x), rm=torch.zeros(C_, device="cuda"), rv=torch.ones(C_, device="cuda"))
+        out.update({k: torch.empty(C_, device="cuda") for k in ("mean", "invstd", "dgamma", "dbeta")})
+        bns.bns_forward(sh, sp, 7, x, gamma, beta, 1e-3, 0.1, out["y"], out["mean"], out["invstd"], out["rm"], out["rv"], ws)
+        bns.bns_backward(sh, sp, 7, x, dy, gamma, out["mean"], out["invstd"], out["dx"], out["dgamma"], out["dbeta"], ws)
+        return out
+
+    got = step()
+    assert _paths() == (3, 3)
+    want = _with({"nhwc_fused": 2}, step)
+    assert _paths() == (1, 1)
+    for k in got:
+        assert torch.allclose(got[k], want[k], rtol=1e-5, atol=1e-5 * float(want[k].abs().max())), k
