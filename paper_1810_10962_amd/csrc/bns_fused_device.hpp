@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bns_device.hpp"
 #include "bns_internal.hpp"
 
@@ -392,6 +394,12 @@ __device__ __forceinline__ bool team_allsum2(const FusedArgs& A, uint32_t* words
                                              double* bc) {
     team_publish(A, read_stamp(A, words), team_first_block, j, it, a, b);
     return team_collect<NT>(A, words, team_first_block, it, a, b, ta, tb, team_lds, bc);
+}
+
+template <typename P>
+__device__ __forceinline__ P* at_byte(P* base, uint32_t off) {      // (pointer arithmetic: the access stays a global one)
+    typedef typename std::conditional<std::is_const<P>::value, const char, char>::type byte_t;
+    return reinterpret_cast<P*>(reinterpret_cast<byte_t*>(base) + off);
 }
 
 // Returns v unchanged but opaque to the optimiser.  Each phase of a fused kernel derives its

@@ -26,6 +26,7 @@
 #include "bns_fused_device.hpp"
 #include "bns_internal.hpp"
 #include "bns_nhwc_device.hpp"
+#include "bns_nhwc_rows.hpp"
 
 namespace bns {
 
@@ -174,9 +175,10 @@ __device__ __forceinline__ void tile_sums(const RowArgs& A, const RowLane& l, co
 // stamped as in the other single-launch kernels.  Slots: [set][tile][member][first or second sum][channel]: the lanes of a wave that
 // reads a member's sums, one channel each, take whole cache lines.  (Every such read goes past the L2, and T members read T * CT pairs:
 // with the two words of a pair side by side each line was fetched twice, 36 MB in the exchange of 50x150x19x19 f32.)
+// (32-bit offsets: beside a full register file, sixteen 64-bit addresses went through scratch memory)
 __device__ __forceinline__ unsigned long long* sum_slot(const RowArgs& A, const RowLane& l, int set, int member, int which, int ch) {
-    const size_t tile = size_t(set * A.f.num_teams + l.tile), T = size_t(A.f.T), CT = A.ct_div.d;
-    return A.f.slots + ((tile * T + size_t(member)) * 2 + size_t(which)) * CT + size_t(ch);
+    const uint32_t tile = uint32_t(set * A.f.num_teams + l.tile), T = uint32_t(A.f.T), CT = A.ct_div.d;
+    return at_byte(A.f.slots, (((tile * T + uint32_t(member)) * 2u + uint32_t(which)) * CT + uint32_t(ch)) * 8u);
 }
 __device__ __forceinline__ void put_word(unsigned long long* p, uint32_t stamp, uint32_t payload) {
     __hip_atomic_store(p, (static_cast<unsigned long long>(stamp) << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -240,6 +242,7 @@ __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, 
 
 // Totals over the members, by thread t < CT.  Every sum is taken in a fixed order, so all members get the same bits.
 // A wait that runs out leaves NaN in that channel and sets its word of lost.
+template <int B>
 __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, double* part, uint32_t* lost,
                                              double& s1, double& s2) {
     if (A.f.T == 1) return;
@@ -249,7 +252,7 @@ __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l,
     if (g < Q && ch < l.width) {
         // (words are requested for every member at once, and none twice: the polls of all blocks share one path)
         if (T <= 2 * Q) add_members<2>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
-        else add_members<kRowPoll>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
+        else add_members<B>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
         part[g * CT + ch] = s1;
         part[kRowThreads + g * CT + ch] = s2;
     }
@@ -257,12 +260,6 @@ __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l,
     if (int(threadIdx.x) < l.width) {
         add_strided(part + ch, CT, min(Q, T), s1, s2);
     }
-}
-
-template <typename P>
-__device__ __forceinline__ P* at_byte(P* base, uint32_t off) {      // (pointer arithmetic: the access stays a global one)
-    typedef typename std::conditional<std::is_const<P>::value, const char, char>::type byte_t;
-    return reinterpret_cast<P*>(reinterpret_cast<byte_t*>(base) + off);
 }
 
 // A thread's way down the rows: the next row, and its byte offset from the tensor's first element, column included.
@@ -294,8 +291,8 @@ __device__ __forceinline__ void row_store(T* p, typename RawVec<T, V>::raw_t r) 
 // Forward: Eq. 3 (Eq. 4 if MIXED), Eq. 8, Eq. 1.  A thread keeps K rows in registers and L in LDS; rows beyond are read again.
 // Beyond 16 rows loads are unconditional (past the end the last row is read) and run kAhead rows ahead of the sums: a condition around a load
 // makes every later wait one for all loads, and a thread that issues all of them first finds most of its rows there before it
-// adds the first one up.
-template <typename T, int V, int K, int L, bool MIXED>
+// adds the first one up.  FIRST: all loads come first all the same (see rows_first).
+template <typename T, int V, int K, int L, bool MIXED, bool FIRST>
 __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowArgs A) {
     typedef RawVec<T, V> RV;
     typedef typename RV::raw_t raw_t;
@@ -328,7 +325,9 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             if constexpr (MIXED) pw[i] = row_load<T, V, false>(at_byte(x, min(uint32_t(i), A.virtual_rows - 1u) * A.pitch + column));
         }
     }
-    constexpr int kAhead = K < 16 ? K : 16;
+    constexpr int kAhead = FIRST || K < kRowKeepX ? K : kRowKeepX;
+    constexpr bool kAgain = L > 0 || (FIRST && K > kRowKeepX);         // takes more rows than it holds, too
+    constexpr int kPoll = K + L > 52 ? kRowPoll / 2 : kRowPoll;        // (the registers are full)
     constexpr bool kTight = K <= kAhead;                    // all loads come before the first sum: only those that are needed
     raw_t v[K], u[L > 0 ? L : 1];
     Walk wl = walk_from(K);                              // of the loads
@@ -344,7 +343,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
         v[k] = row_load<T, V, true>(at_byte(x, min(wl.off, last)));
         wl.next(step, hop);
     };
-    if constexpr (L == 0) {
+    if constexpr (!kAgain) {
 #pragma unroll
         for (int k = 0; k < kAhead; ++k)
             if (!kTight || k < A.rounds) load(k);
@@ -459,7 +458,14 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
                 if (any1) add8(w1, k + 8);
             }
         };
-        if (L > 0 && A.rounds > K + L) passing();
+        if (kAgain && A.rounds > K + L) passing();
+        if constexpr (kAgain && L == 0) {
+            if (set == 0) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (k < A.rounds) load(k);
+            }
+        }
         if constexpr (L > 0) {
             if (set == 0) {
 #pragma unroll
@@ -512,8 +518,8 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
         if (l.j == 0 && F.running_mean) rm = F.running_mean[c];
         if (l.j == 0 && F.running_var) rv = F.running_var[c];
     }
-    tile_collect(A, l, stamp, 0, part, lost, s1, s2);
-    if (MIXED) tile_collect(A, l, stamp, 1, part, lost, u1, u2);
+    tile_collect<kPoll>(A, l, stamp, 0, part, lost, s1, s2);
+    if (MIXED) tile_collect<kPoll>(A, l, stamp, 1, part, lost, u1, u2);
     if (leads) {
         const double m1 = s1 / F.s;
         double mean = double(piv[threadIdx.x]) + m1;
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
                 w.next(step, hop);
             }
         }
-        if constexpr (L > 0) {
+        if constexpr (kAgain) {
 #pragma unroll
             for (int k = 0; k < L; ++k) {
                 finish(park[k * kRowThreads + threadIdx.x], w);
@@ -635,22 +641,18 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
     // the last one, are dropped.
     const uint32_t block0 = uint32_t(l.j) * uint32_t(A.TY);
     auto add = [&](const raw_t& wg, const raw_t& wx, uint32_t row, int k) {
+        const bool whole = block0 + uint32_t(k) * step + uint32_t(A.TY) <= A.M;            // (the same for the whole block)
         float g[V], t[V];
         RV::unpack(wg, g);
         RV::unpack(wx, t);
 #pragma unroll
-        for (int e = 0; e < V; ++e) t[e] -= mu[e];
-        if (block0 + uint32_t(k) * step + uint32_t(A.TY) > A.M) {           // (the same for the whole block)
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                g[e] = row < A.M ? g[e] : 0.f;
-                t[e] = row < A.M ? t[e] : 0.f;
-            }
-        }
-#pragma unroll
         for (int e = 0; e < V; ++e) {
-            fa[e] += g[e];
-            fq[e] = fmaf(g[e], t[e], fq[e]);
+            const float h = whole || row < A.M ? g[e] : 0.f, d = whole || row < A.M ? t[e] - mu[e] : 0.f;
+            fa[e] += h;
+            fq[e] = fmaf(h, d, fq[e]);
+            // (two channels at a time: with all eight of a bf16 vector unpacked at once 35 + 14 rows went through 48 bytes of scratch
+            // memory; 16x512x1xW, 49 rows per thread, 1.00 -> 1.05 of the speed of 28 rows and no LDS)
+            if (V == 8 && e % 2 == 1) asm volatile("" : "+v"(fa[e - e % 2]), "+v"(fq[e - e % 2]), "+v"(fa[e]), "+v"(fq[e]));
         }
     };
     auto flush = [&]() {
@@ -784,7 +786,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
         centre = MIXED ? F.mean_parts[F.C + c] : F.save_mean[c];
         if (MIXED) e_v = F.mean_parts[c];
     }
-    tile_collect(A, l, stamp, 0, part, nullptr, s1, s2);
+    tile_collect<kRowPoll>(A, l, stamp, 0, part, nullptr, s1, s2);
     if (leads) {
         const float dbeta = float(s1);
         const float dgamma = float(s2 * double(r));
@@ -885,46 +887,42 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
     team_done(F, l.j, stamp);
 }
 
-// Rows kept per thread: in registers, and in LDS by the largest variant.  Backward keeps x beside dy up to 16 rows.
-constexpr int kRowKeeps[] = {4, 8, 16, 24, 64};     // (the last: see most_rows)
-constexpr int kNumRowKeeps = sizeof(kRowKeeps) / sizeof(kRowKeeps[0]);
-constexpr int kRowPark = 14;                        // 112 of the 160 KiB
 // Rows per thread up to which a block takes every row of its columns (13x29x7x10 bf16, 8 rows: 10.7 / 12.7 us against 10.0 /
 // 8.7 streaming; 28x64x6x6 f32, 8 rows: forward 8.1 against 11.9; backward 52x349x4x4 f32, 7 rows, 12.7 against 10.5).
 constexpr int row_solo(int V, bool backward) { return V == 8 ? (backward ? 4 : 5) : (backward ? 4 : 8); }
-// What the registers hold beside the sums (Eq. 4 forward walks the rows twice).
-constexpr int reg_rows(int V, bool backward, bool mixed) {
-    return backward ? (V == 8 ? 35 : 40) : mixed ? 20 : (V == 8 ? 36 : 40);
+
+template <typename T, int V, int I, bool MIXED, bool FIRST>
+const void* row_forward() {
+    constexpr RowsHeld h = rows_held(V, false, MIXED, I);
+    return reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, h.regs, FIRST ? 0 : h.park, MIXED, FIRST && (h.regs > kRowKeepX)>);
 }
-constexpr int most_rows(int V, bool backward, bool mixed) { return reg_rows(V, backward, mixed) + kRowPark; }
+template <typename T, int V, int I, bool MIXED>
+const void* row_backward() {
+    constexpr RowsHeld h = rows_held(V, true, MIXED, I);
+    return reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, h.regs, h.park, (h.regs <= kRowKeepX), MIXED>);
+}
 
 template <typename T, int V>
-const void* row_kernel(int variant, bool backward, bool mixed) {
-#define BNS_ROW_CASE(I, K)                                                                                      \
-    case I:                                                                                                     \
-        if (backward)                                                                                           \
-            return mixed ? reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, 0, true, true>)   \
-                         : reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, K, 0, true, false>); \
-        return mixed ? reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, K, 0, true>)              \
-                     : reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, K, 0, false>);
+const void* row_kernel(int variant, bool backward, bool mixed, bool first) {
+#define BNS_ROW_CASE(I)                                                                             \
+    case I:                                                                                         \
+        return backward ? (mixed ? row_backward<T, V, I, true>() : row_backward<T, V, I, false>())   \
+               : mixed  ? row_forward<T, V, I, true, false>()                                        \
+               : first  ? row_forward<T, V, I, false, (V > 1)>()                                     \
+                        : row_forward<T, V, I, false, false>();
     switch (variant) {
-        BNS_ROW_CASE(0, 4)
-        BNS_ROW_CASE(1, 8)
-        BNS_ROW_CASE(2, 16)
-        case 3:
-            if (backward && !mixed) return reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, 24, 0, false, false>);
-            if (!backward && !mixed) return reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, 24, 0, false>);
-            [[fallthrough]];
-        case 4:
-            if (backward)
-                return mixed ? reinterpret_cast<const void*>(
-                                   &nhwc_fused_backward_kernel<T, V, reg_rows(V, true, true), kRowPark, false, true>)
-                             : reinterpret_cast<const void*>(
-                                   &nhwc_fused_backward_kernel<T, V, reg_rows(V, true, false), kRowPark, false, false>);
-            return mixed ? reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, reg_rows(V, false, true), kRowPark, true>)
-                         : reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, reg_rows(V, false, false), kRowPark, false>);
+        BNS_ROW_CASE(0)
+        BNS_ROW_CASE(1)
+        BNS_ROW_CASE(2)
+        BNS_ROW_CASE(3)
+        BNS_ROW_CASE(4)
+        BNS_ROW_CASE(5)
+        BNS_ROW_CASE(6)
+        BNS_ROW_CASE(7)
+        BNS_ROW_CASE(8)
     }
 #undef BNS_ROW_CASE
+    static_assert(kRowVariants == 9, "one case each");
     return nullptr;
 }
 
@@ -1004,7 +1002,7 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     // against 45.1, 26x80x100x101 (48) backward 69.9 against 74.4, 100x96x60x60 bf16 (12 of 16, 44 rows) backward 60.5 against 77.0, full BN
     // forward 45.8 against 40.4 with 46 rows, 78x80x70x70 64.9 against 69.8 with 72.
     const bool everything = b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W, idle = CV * 10 < tiles * TX * 9;
-    const int most = most_rows(V, backward, mix != nullptr), regs = reg_rows(V, backward, mix != nullptr);
+    const int most = rows_most(V, backward, mix != nullptr), regs = rows_in_registers(V, backward, mix != nullptr, false);
     // Rows that begin on no 64 bytes are slower the second time, too: 91x92x56x56 f32, a patch, 53 rows, backward 76.5 against 100.6
     // full BN forward, 56 rows, 57.8 against 73.9 (where streaming has to take narrower accesses for want of whole vectors, this is
     // still the faster).
@@ -1031,8 +1029,6 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     // Byte offsets are 32-bit.  Those of rows past the end may wrap: loads are clamped to the last row, so what is read lies in the
     // tensor, and sums and stores go by the row's number.
     if (bytes >= (size_t(1) << 32)) return hipErrorNotSupported;
-    int variant = 0;
-    while (variant + 1 < kNumRowKeeps && kRowKeeps[variant] < rounds) ++variant;
 
     RowArgs A;
     FusedArgs& F = A.f;
@@ -1085,11 +1081,12 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     A.rounds = rounds;
     A.pitch = uint32_t(d.C) * (d.dtype == BNS_F32 ? 4u : 2u);
     A.keep_x = bytes <= kKeepBytes;
-    const bool mixed = mix != nullptr;
-    const void* kernel = V == 8               ? row_kernel<bf16_t, 8>(variant, backward, mixed)
-                         : V == 4             ? row_kernel<float, 4>(variant, backward, mixed)
-                         : d.dtype == BNS_F32 ? row_kernel<float, 1>(variant, backward, mixed)
-                                              : row_kernel<bf16_t, 1>(variant, backward, mixed);
+    const bool mixed = mix != nullptr, first = rows_first(rounds, V, backward, mixed, long(A.pitch));
+    const int variant = row_variant(rounds, V, backward, mixed);
+    const void* kernel = V == 8               ? row_kernel<bf16_t, 8>(variant, backward, mixed, first)
+                         : V == 4             ? row_kernel<float, 4>(variant, backward, mixed, first)
+                         : d.dtype == BNS_F32 ? row_kernel<float, 1>(variant, backward, mixed, first)
+                                              : row_kernel<bf16_t, 1>(variant, backward, mixed, first);
     *solo = T == 1;
     void* params[] = {&A};
     return launch_waiting(kernel, dim3(uint32_t(tiles) * uint32_t(T)), dim3(kRowThreads), params, T > 1, may_create_event, st);

@@ -1,0 +1,52 @@
+// Rows per thread that the single-launch N x H x W x C kernels hold (bns_nhwc_fused.hip): plain C++ without HIP headers, so that a host
+// compiler can check it alone.
+#pragma once
+
+namespace bns {
+
+// Rows in registers and, behind them, in LDS.
+struct RowsHeld {
+    int regs, park;
+};
+
+constexpr int kRowKeepX = 16;       // rows up to which a thread's loads all come first; backward holds x beside dy
+constexpr int kRowPark = 14;        // 112 of the 160 KiB of LDS
+// What the registers hold beside the sums, without scratch memory (Eq. 4 forward walks the rows twice, with more in flight where there are
+// rows in LDS, too).
+constexpr int rows_in_registers(int V, bool backward, bool mixed, bool parks) {
+    return backward ? (V == 8 ? 35 : 40) : mixed ? (V == 8 && parks ? 16 : 20) : (V == 8 ? 36 : 40);
+}
+constexpr int rows_most(int V, bool backward, bool mixed) { return rows_in_registers(V, backward, mixed, true) + kRowPark; }
+
+// Variants: steps of four rows beyond 16, the last of up to eight.  Rows that a variant holds and a thread has not are loaded (the last row again and again)
+// and dropped all the same, which costs nearly what a row costs: with 24 and 49 (54) rows only, bf16 x 512 backward with 26
+// rows per thread ran at 0.83, f32 x 256 at 0.81 of the speed of a kernel with a condition around every load, now at 1.07
+// and 1.00; forward 0.93 and 0.92, now 1.09 and 1.07.
+constexpr int kRowVariants = 9;
+constexpr RowsHeld rows_held(int V, bool backward, bool mixed, int variant) {
+    const int steps[] = {4, 8, 16, 20, 24, 28, 32};
+    const bool parks = variant == kRowVariants - 1;
+    const int all = rows_in_registers(V, backward, mixed, parks);
+    if (V > 1 || variant < 3) {
+        if (variant < 7) return RowsHeld{steps[variant] < all ? steps[variant] : all, 0};
+    }
+    return RowsHeld{all, parks ? kRowPark : 0};             // (fewer of them for single elements)
+}
+// The smallest variant that holds them.
+constexpr int row_variant(int rounds, int V, bool backward, bool mixed) {
+    int v = 0;
+    while (v + 1 < kRowVariants && rows_held(V, backward, mixed, v).regs + rows_held(V, backward, mixed, v).park < rounds) ++v;
+    return v;
+}
+
+// Forward: whether all loads of a thread come before its first sum beyond 16 rows, too, each under a condition.  Where rows begin on
+// no 64 bytes, the blocks of neighbouring tiles read the same lines, and they meet in the L2 when both request everything at once, not
+// when each goes at the pace of its sums (us, paced against this: f32 16x150x1xW, 24 rows per thread, 34.4 / 32.1, 44 rows 61.0 / 55.8; 79
+// channels, 24 rows, 39.0 / 35.9; bf16 x 431, 28 rows, 43.3 / 41.5).  Rows beyond the registers are then read twice; LDS holds them
+// better in bf16 (431 channels, 44 rows, 1.18 of the speed of the paced kernel without it against 1.14, 50 rows 1.25 against 1.16).  Where
+// rows are aligned the pace is worth 7 % and more.
+constexpr bool rows_first(int rounds, int V, bool backward, bool mixed, long pitch) {
+    return !backward && !mixed && V > 1 && rounds > kRowKeepX && pitch % 64 != 0 && (V == 4 || rounds <= rows_in_registers(V, false, false, false));
+}
+
+}  // namespace bns

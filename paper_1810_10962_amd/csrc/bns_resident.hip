@@ -129,12 +129,6 @@ struct Walker {
     }
 };
 
-template <typename P>
-__device__ __forceinline__ P* at_byte(P* base, uint32_t off) {      // (pointer arithmetic: the access stays a global one)
-    typedef typename std::conditional<std::is_const<P>::value, const char, char>::type byte_t;
-    return reinterpret_cast<P*>(reinterpret_cast<byte_t*>(base) + off);
-}
-
 // d if bit e of m is set, else 0 (a NaN that is masked out must not reach a sum).
 __device__ __forceinline__ float masked(float d, uint32_t m, int e) {
     return __uint_as_float(__float_as_uint(d) & uint32_t(__builtin_amdgcn_sbfe(int(m), e, 1)));

@@ -353,3 +353,22 @@ def test_few_rows_of_very_many_channels(shape):
     assert _paths() == (1, 1)
     for k in got:
         assert torch.allclose(got[k], want[k], rtol=1e-5, atol=1e-5 * float(want[k].abs().max())), k
+
+
+@pytest.mark.parametrize("dtype,rounds,ragged", [
+    ("f32", 20, False), ("f32", 28, True), ("f32", 33, False), ("f32", 41, True),         # 41, ragged: a row that is read again
+    ("bf16", 17, True), ("bf16", 29, False), ("bf16", 36, True), ("bf16", 37, True),      # 36: the last with all loads first, 37: LDS
+])
+def test_rows_between_the_steps(dtype, rounds, ragged):
+    """Every step of the rows that registers hold beyond 16, rows that begin on no 64 bytes (forward requests all of them first), Eq. 4."""
+    V = 4 if dtype == "f32" else 8
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 64 * (units // 16) * (rounds - 1) + 37
+    for i, mkw in enumerate((dict(mode=BS, n_s=1), dict(mode=FS, patch_h=1, patch_w=rows // 7, n_v=1, mix_beta=0.4))):
+        wl = Workload(name="rows_steps", N=3, C=128 * V - (3 if ragged else 0), H=1, W=rows // 3, dtype=dtype, layout="nhwc", data_seed=74 + i,
+                      sampling_seed=5, layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch, {rounds} rows per thread {wl.shape} {dtype} {mkw}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
+        assert _paths() == (2, 2)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
