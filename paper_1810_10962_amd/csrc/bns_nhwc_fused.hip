@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "bns_device.hpp"
@@ -953,22 +954,27 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     if (groups > row_solo(V, backward) || (opt == 1 && may_wait && M > 64u)) {
         if (opt != 1 && bytes <= kNhwcFusedBytes && M > kNhwcFewRows) return hipErrorNotSupported;
         // Width of a tile: 128 or 256 bytes where rows begin at multiples of 64 (a tile that shares its cache lines with the
-        // next one costs a third: 63x160x44x44 f32 backward, us: 8 lanes 44, 9 lanes 82, 16 lanes 48), else 8 to 16 lanes, rather
-        // more (12x432x73x70 bf16, 864 bytes per row: 9 lanes 56, 14 lanes 47); and what leaves few lanes, threads and compute
-        // units without work, with a price on the T * CT pairs of sums that every member reads, about 1.1 us for 4096 (128x64x32x32
-        // f32 forward: 128 members x 32 channels 17.6, 256 x 64 20.8; 50x150x19x19 f32: 85 x 52 13.5 / 14.9, 51 x 32 12.5 / 13.9).
+        // next one costs a third: 63x160x44x44 f32 backward, us: 8 lanes 44, 9 lanes 82, 16 lanes 48), else 8 to 16 lanes; and what
+        // leaves few lanes, threads and compute units without work, with a price on the T * CT pairs of sums that every member
+        // reads (128x64x32x32 f32 forward: 128 members x 32 channels 17.6, 256 x 64 20.8; 50x150x19x19 f32: 85 x 52 13.5 / 14.9, 51 x
+        // 32 12.5 / 13.9).  The times below are estimates, us, of what depends on the width.  Rows that begin on no 64 bytes: fitted to
+        // 1800 passes over tensors of 0.2 to 130 MB, each timed with two to five widths; the tile it picks takes 1.01 of the time of the best
+        // of them, at most 1.2 (prices as for aligned rows: 1.03, 1.5).  A line shared between tiles costs as much as 115 bytes of one's own (13x293x67x67 f32
+        // forward, 8 lanes 61.9, 16 lanes 48.0); idle compute units cost less than their share, since small tensors do not fill
+        // the memory's queues; 1024 pairs are polled in one go (25x382x8x8 bf16 forward, 8 members x 72 channels 9.2, 13 x 128 10.6).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
         double best = 0.0;
         for (int lanes = want > 0 ? want : 8; lanes <= (want > 0 ? want : 16); lanes += aligned ? 8 : 1) {
             const int tx = lanes_for(lanes), g = groups_for(tx), count = (CV + tx - 1) / tx;
             const int t = std::min((g + 3) / 4, std::max(1, cus / count));
-            // what a narrower tile, idle lanes, threads or compute units cost is a share of the time at the memory; us
-            const double width = aligned ? ((tx > 8) == (V == 4) ? 1.0 : 0.97) : 1.0 + 0.02 * (tx - 8);
-            const double use = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads *
-                               std::min(1.0, double(count * t) / cus) * width;
-            const double score = 1.0 / (6.0 + double(bytes) * (backward ? 3 : 2) / 6.2e6 / use + 1.1 * double(t) * tx * V / 4096.0);
-            if (score > best) {
-                best = score;
+            // what a narrower tile, idle lanes, threads or compute units cost is a share of the time at the memory
+            const double use = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads * std::min(1.0, double(count * t) / cus);
+            const double moved = double(bytes) * (backward ? 3 : 2), pairs = double(t) * tx * V / 4096.0;
+            const double time = aligned ? moved / 6.2e6 / use / ((tx > 8) == (V == 4) ? 1.0 : 0.97) + 1.1 * pairs
+                                        : moved / 6.9e6 / std::sqrt(use * std::sqrt(use)) * (count > 1 ? 1.0 + 7.2 / tx : 1.0) *
+                                                  (tx % 8 == 0 ? 1.0 : 1.07) + 2.1 * pairs + (pairs > 0.25 ? 0.7 : 0.0);
+            if (tx * V <= kRowMaxTile && (best == 0.0 || time < best)) {
+                best = time;
                 TX = tx;
                 groups = g;
                 T = t;
