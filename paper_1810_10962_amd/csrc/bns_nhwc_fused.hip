@@ -1013,22 +1013,31 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     // full BN forward, 56 rows, 57.8 against 73.9 (where streaming has to take narrower accesses for want of whole vectors, this is
     // still the faster).
     const bool split_lines = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 != 0 && d.C % V == 0;
-    const int limit = !backward && everything && !mix                         ? (idle ? regs + regs * 2 / 5 : split_lines ? regs : 256)
-                      : idle || split_lines                                   ? regs
-                      : mix                                                   ? most
-                      : backward                                              ? (V == 8 ? 81 : 128)
-                      : make_rowset(d, b).contiguous                          ? (V == 8 ? 81 : 66)
-                                                                              : (V == 8 ? 58 : 62);
+    // Where streaming takes single elements the line lies further out: Eq. 4 backward 112x407x25x25 f32, 58 rows, 177.2 against 115.1, 19x659x53x53 bf16, 70 rows,
+    // 157.5 against 82.3; backward with idle lanes 32x393x40x40 f32 116.2 against 76.8, 16x431x1xW bf16, 66 to 81 rows, twice the time; bf16 rows of
+    // whole vectors 1.02 (66 rows) to 1.05 (81) the other way, 132 and 660 channels (64-bit accesses) forward, a patch, 44 to 60 rows, 1.1.
+    const bool single = d.C % 4 != 0;
+    const int limit = !backward && everything && !mix                         ? (idle && !single ? regs + regs * 2 / 5 : split_lines ? regs : 256)
+                      : (idle && !single) || split_lines                      ? regs
+                      : mix && (!backward || !single)                         ? (backward ? 64 : 34)
+                      : backward                                              ? (V != 8 ? 128 : d.C % V == 0 ? 64 : 81)
+                      : make_rowset(d, b).contiguous                          ? (V != 8 ? 66 : d.C % 8 == 4 ? 50 : 81)
+                                                                              : (V != 8 ? 62 : d.C % 8 == 4 ? regs : 58);
     if (opt != 1 && T > 1 && rounds > limit) return hipErrorNotSupported;
-    // Ragged bf16 rows of the smallest tensors: streaming takes single elements, and that is enough (13x137x7x7, 175 KB, backward 9.4
-    // against 10.3 us; 37x143x5x5, 265 KB, 11.6 / 11.2 against 9.4 / 9.8).
-    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 180000) return hipErrorNotSupported;
+    // Ragged bf16 rows of small tensors: streaming takes single elements, and that is enough (3x107x18x18, 208 KB, backward 8.0 against 14.2
+    // us, 5x230x11x11, 278 KB, 9.1 / 8.2 against 9.5 / 9.3, 4x190x16x16, 389 KB, 8.8 / 8.0 against 9.6 / 9.6; 18x122x10x10, 439 KB, 10.8 / 9.9
+    // against 9.6 / 9.1).
+    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 400000) return hipErrorNotSupported;
     // bf16 rows that do not begin on cache lines: tiles of one and the same line are read by different blocks (us, streaming against this:
     // 12x432x73x70, 52 rows per thread, 34.7 / 45.7 against 37.8 / 50.9; 60x336x38x38, 28 rows, 38.4 / 53.7 against 41.0 / 54.1; 75x1296x15x16, 25 rows,
     // 34.1 / 44.6 against 34.2 / 39.5; 27x272x37x40, 12 rows, 23.7 / 31.5 against 22.7 / 22.9).
     // Full BN forward, which streaming reads twice as well, until it reads rows again itself (4x1736x84x84 70.7 against 65.5).
     const size_t pitch = size_t(d.C) * 2;
-    const int lines = backward ? 26 : 16;
+    // Backward, S part of the rows, the line also lies where streaming's column lanes are nearly all at work and rows are short (17 to 26 rows per
+    // thread, 16x120x1xW (15 of 16 lanes) 32.9 / 34.2 to 42.5 / 43.5, 248 (31 of 32) 35.4 / 35.2 to 44.6 / 46.9; 336 (42 of 64) 41.7 / 33.6, 600
+    // (75 of 128) 53.2 / 41.1, 72 (9 of 16) 49.4 / 35.7).
+    const bool whole_lanes = CV <= 32 && CV % 16 != 0 && 10 * CV >= 9 * ((CV + 15) / 16 * 16);
+    const int lines = !backward || (whole_lanes && !everything) ? 16 : 26;
     if (opt != 1 && T > 1 && rounds > lines && V == 8 && d.C % V == 0 && !(everything && !backward && rounds <= most) &&
         pitch % (backward ? 64 : 128) != 0)
         return hipErrorNotSupported;
