@@ -19,20 +19,17 @@
 // Sums: a few vectors at a time in fp32, everything beyond in fp64 (only the pair that crosses blocks is rounded to fp32).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
 #include "bns_device.hpp"
 #include "bns_fused_device.hpp"
 #include "bns_internal.hpp"
+#include "bns_resident_plan.hpp"
 
 namespace bns {
 
 namespace {
 
-constexpr int kResThreads = 512;
 constexpr int kResWaves = kResThreads / kWave;
 constexpr int kPark = 17;           // vectors of x per thread that LDS holds (and a place for those that are not kept): 144 of the 160 KiB
-constexpr int kResMaxTeam = 256;
 
 struct ResidentArgs {
     FusedArgs f;
@@ -459,78 +456,29 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
     team_done(F, j, read_stamp(F, words));
 }
 
-constexpr int kBigVectors = 49;     // 64x56x56 in bf16, half of it in fp32, is 49 vectors for each of 512 threads
-constexpr int kPairVectors = 25;    // of x and of dy
-
 template <typename T, int V, int PATCH>
 const void* resident_ptr(bool backward, bool keep_x, bool mixed) {
-    if (!backward) return reinterpret_cast<const void*>(&resident_forward_kernel<T, V, kBigVectors, PATCH>);
-    return mixed    ? reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kPairVectors, PATCH, true, true>)
-           : keep_x ? reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kPairVectors, PATCH, true, false>)
-                    : reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kBigVectors, PATCH, false, false>);
+    constexpr bool f32 = V == 4, odd = Odd<T>::value, general = PATCH == kPatch;
+    constexpr int kForward = resident_vectors(f32, odd, general, false, false), kBig = resident_vectors(f32, odd, general, true, false),
+                  kPair = resident_vectors(f32, odd, general, true, true);
+    if (!backward) return reinterpret_cast<const void*>(&resident_forward_kernel<T, V, kForward, PATCH>);
+    return mixed    ? reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kPair, PATCH, true, true>)
+           : keep_x ? reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kPair, PATCH, true, false>)
+                    : reinterpret_cast<const void*>(&resident_backward_kernel<T, V, kBig, PATCH, false, false>);
 }
 
-const void* resident_kernel(const Dims& d, bool odd, bool patch, bool backward, bool keep_x, bool mixed) {
-#define BNS_RESIDENT(T, V)                                                                                  \
-    return !patch         ? resident_ptr<T, V, kWholePlanes>(backward, keep_x, mixed)                        \
-           : d.W % V == 0 ? resident_ptr<T, V, Odd<T>::value ? kPatch : kPatchRows>(backward, keep_x, mixed) \
-                          : resident_ptr<T, V, kPatch>(backward, keep_x, mixed);
+const void* resident_kernel(const Dims& d, const ResidentChoice& c, bool backward, bool mixed) {
+    const bool x = c.keep_x, rows = c.patch && !c.general;
     if (d.dtype == BNS_F32) {
-        if (odd) { BNS_RESIDENT(f32_odd, 4) }
-        BNS_RESIDENT(float, 4)
+        if (c.odd) return c.patch ? resident_ptr<f32_odd, 4, kPatch>(backward, x, mixed) : resident_ptr<f32_odd, 4, kWholePlanes>(backward, x, mixed);
+        return rows      ? resident_ptr<float, 4, kPatchRows>(backward, x, mixed)
+               : c.patch ? resident_ptr<float, 4, kPatch>(backward, x, mixed)
+                         : resident_ptr<float, 4, kWholePlanes>(backward, x, mixed);
     }
-    if (odd) { BNS_RESIDENT(bf16_odd, 8) }
-    BNS_RESIDENT(bf16_t, 8)
-#undef BNS_RESIDENT
-}
-
-// Teams for a kernel of K vectors per thread: the fewest rounds that blocks of K vectors allow; in a single round, as many
-// blocks as there are compute units, or as leave each thread something to do.
-struct ResidentPlan {
-    int64_t T = 0, teams = 0, rounds = 0;
-    double used = 0.0;      // share of a block's registers in use
-    double fill = 0.0;      // the same over the device and all rounds
-};
-ResidentPlan resident_plan(int64_t chunks, int64_t C, int K, int cus) {
-    ResidentPlan p;
-    const int64_t least = (chunks + K - 1) / K, most = std::min<int64_t>(cus, kResMaxTeam);
-    if (least > most) return p;
-    p.T = cus / least >= C ? std::max(least, std::min<int64_t>({cus / C, (chunks + 3) / 4, most})) : least;
-    p.teams = std::min<int64_t>(cus / p.T, C);
-    p.rounds = (C + p.teams - 1) / p.teams;
-    p.used = double(chunks) / double(p.T * K);
-    p.fill = double(chunks) * double(C) / (double(cus) * K * double(p.rounds));
-    return p;
-}
-
-// Where these kernels are the faster ones: where the registers are well used, which is what fewer rounds, hence fewer pauses for an
-// exchange, come from.  Against the other single-launch kernels (times in us, theirs / these):
-//   forward: 64x256x56x56 bf16, one round, Batch Sampling 36.7 / 34.5, a patch 39.7 / 37.0, everything 38.9 / 36.4; 45x48x105x105 f32 (0.91
-//     of the registers) 42.9 / 40.9, but 42x64x90x90 (0.85) 35.9 / 37.7.  Two rounds against the streaming kernels: everything
-//     64x64x112x112 f32 82.4 / 77.7, Batch Sampling 64x256x56x56 f32 71.9 / 75.6, so only where all of x is read twice there.  A patch
-//     whose rows are no whole number of vectors: 64x256x55x55 bf16 47.3 (streaming) / 51.2.
-//   backward, dy alone (S small): 64x256x56x56, Batch Sampling, bf16 (one round) 64.9 / 49.4, f32 (two) 114.1 / 106.1; 78x64x100x100 f32, a
-//     patch, two rounds 131.8 / 104.8; 56x240x39x39 f32 54.5 / 47.4; 44x368x43x43 f32 (0.59 of the registers) 79.5 / 75.3; three rounds
-//     28x671x46x46 109.5 / 114.4.  bf16 planes that are no whole number of vectors need too much arithmetic per vector:
-//     59x80x71x71 41.3 / 53.5.
-//   backward, x beside dy: one round 27x80x62x60 f32 28.8 / 19.9, 59x80x71x71 bf16 41.3 / 34.8, but 60x128x27x27 f32 (0.44 of a block's
-//     registers) 15.5 / 17.4; two 64x256x56x56 bf16, everything, 66.9 / 53.9, 18x512x60x60 bf16 (0.64) 46.2 / 42.0, 18x133x56x54 f32
-//     (0.28) 26.3 / 29.8; four 64x64x112x112 f32, everything, 124.0 / 118.8 (teams of
-//     16), 64x256x56x56 f32 (teams of 4) 115.5 / 119.6, 18x934x48x48 f32 (0.77) 87.2 / 90.3.
-bool forward_pays(const ResidentPlan& p, bool everything, bool general_patch) {
-    return p.T > 0 && p.fill >= 0.9 && !general_patch && (p.rounds == 1 || (p.rounds == 2 && everything));
-}
-bool big_pays(const ResidentPlan& p, const Dims& d, bool odd) {
-    if (p.T == 0 || (odd && d.dtype != BNS_F32)) return false;
-    if (p.rounds == 1) return p.used >= (d.dtype == BNS_F32 ? 0.65 : 0.75) && p.fill >= 0.5;
-    return p.rounds == 2 && p.used >= 0.7 && p.fill >= 0.55;
-}
-bool pair_pays(const ResidentPlan& p, const Dims& d, bool odd, bool general_patch) {
-    if (p.T == 0) return false;
-    if (p.rounds == 1) return p.used >= (general_patch ? 0.9 : 0.8) && p.fill >= 0.5;
-    if (general_patch && d.dtype != BNS_F32) return false;
-    if (p.rounds == 2) return p.fill >= (odd && d.dtype != BNS_F32 ? 0.8 : 0.6);
-    return p.rounds <= 4 && p.fill >= 0.94 && p.T >= 8;     // (the pipelined kernel needs teams of several dozen blocks there)
+    if (c.odd) return c.patch ? resident_ptr<bf16_odd, 8, kPatch>(backward, x, mixed) : resident_ptr<bf16_odd, 8, kWholePlanes>(backward, x, mixed);
+    return rows      ? resident_ptr<bf16_t, 8, kPatchRows>(backward, x, mixed)
+           : c.patch ? resident_ptr<bf16_t, 8, kPatch>(backward, x, mixed)
+                     : resident_ptr<bf16_t, 8, kWholePlanes>(backward, x, mixed);
 }
 
 }  // namespace
@@ -538,34 +486,15 @@ bool pair_pays(const ResidentPlan& p, const Dims& d, bool odd, bool general_patc
 hipError_t launch_resident(const Dims& d, const IndexParams& ip, bool backward, const FusedIo& io, float eps, float momentum,
                            void* header, void* slots, size_t slot_bytes, hipStream_t st, int cus, const FusedMix* mix,
                            bool may_create_event) {
-    const int opt = g_tuning.resident;
-    const int V = d.dtype == BNS_F32 ? 4 : 8;
-    const uint32_t e = d.dtype == BNS_F32 ? 4u : 2u;
-    if (opt == 2 || d.HW < V || cus <= 0 || (mix && !backward)) return hipErrorNotSupported;
-    const bool odd = d.HW % V != 0;
+    const ResidentChoice choice = resident_choice(d, ip, backward, mix != nullptr, g_tuning.resident, cus);
+    if (!choice.take) return hipErrorNotSupported;
+    const uint32_t e = d.dtype == BNS_F32 ? 4u : 2u, hwv = choice.plane_vectors;
+    const int V = choice.vector;
     const bns_box& b = ip.shared;
-    const uint32_t hwv = uint32_t((d.HW + V - 1) / V);
     const uint64_t tot = uint64_t(d.N) * hwv;
-    const int64_t chunks = int64_t((tot + kResThreads - 1) / kResThreads);
-    if (opt == 0 && chunks * d.C < int64_t(cus) * 8) return hipErrorNotSupported;         // (nothing below comes near)
-    const bool everything = !ip.per_channel && b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W;
-    const bool patch = b.h_cnt * b.w_cnt != d.HW;
-    const ResidentPlan big = resident_plan(chunks, d.C, kBigVectors, cus), pair = resident_plan(chunks, d.C, kPairVectors, cus);
-    bool keep_x = false;
-    if (opt != 0) {
-        keep_x = backward && (mix || opt == 4 || (opt == 1 && everything));
-    } else if (!backward) {
-        if (!forward_pays(big, everything, patch && d.W % V != 0)) return hipErrorNotSupported;
-    } else {
-        const bool pair_ok = pair_pays(pair, d, odd, patch && d.W % V != 0), big_ok = !everything && !mix && big_pays(big, d, odd);
-        if (!pair_ok && !big_ok) return hipErrorNotSupported;
-        keep_x = pair_ok && !(big_ok && big.rounds < pair.rounds);
-    }
-    const ResidentPlan p = keep_x ? pair : big;
-    if (p.T == 0) return hipErrorNotSupported;
-    const int K = keep_x ? kPairVectors : kBigVectors;
-    const int64_t T = p.T, teams = p.teams, rounds = p.rounds;
-    const void* kernel = resident_kernel(d, odd, patch, backward, keep_x, mix != nullptr);
+    const int64_t T = choice.plan.T, teams = choice.plan.teams, rounds = choice.plan.rounds;
+    const int K = choice.held;
+    const void* kernel = resident_kernel(d, choice, backward, mix != nullptr);
     // offsets within the tensor are 32-bit, those of vectors past the end of a channel included
     const uint64_t stride = uint64_t(d.C) * uint64_t(d.HW) * e;
     const uint64_t step = uint64_t(T) * kResThreads;
