@@ -88,6 +88,15 @@ struct Walker {
             w.c -= w.c >= A.f.wv_div.d ? A.f.wv_div.d : 0u;
         }
     }
+    // The same for loads, which need no place within the row.
+    __device__ __forceinline__ void next_load(Walk& w) const {
+        asm volatile("" : "+v"(w.nb), "+v"(w.r));
+        w.r += A.dr;
+        w.nb += A.dn;
+        const bool wrap = w.r >= A.f.hwv_div.d;
+        w.r -= wrap ? A.f.hwv_div.d : 0u;
+        w.nb += wrap ? A.stride : 0u;
+    }
     __device__ __forceinline__ uint32_t element(const Walk& w) const { return plane_offset<T, V>(w.r, A.f.HW); }
     // (all lanes past the end read the channel's first vector: one line, whatever the number of such loads)
     __device__ __forceinline__ uint32_t load_at(const Walk& w) const { return exists(w) ? store_at(w) : 0u; }
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_forward_kernel(Reside
         constexpr int kAhead = K < 20 ? K : 20, kGroup = 7; // kGroup: vectors added up in fp32
         auto load = [&](int k) {
             v[k] = RV::ld(at_byte(xc, at.load_at(wl)));
-            at.next(wl);
+            at.next_load(wl);
         };
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) load(k);
@@ -288,6 +297,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
     __shared__ raw_t park[KEEPX ? 1 : (kPark + 1) * kResThreads];
     __shared__ double red[2 * kResWaves], bc[2];
     __shared__ float team_lds[2 * kMaxTeam];
+    __shared__ float consts[2][2];
     __shared__ uint32_t words[3];
     const FusedArgs& F = A.f;
     Walker<T, V, PATCH> at(A);
@@ -310,6 +320,15 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
         double d1 = 0.0, d2 = 0.0;
         uint32_t parked = 0;
         Walk wl = w0, w = w0;                               // of the loads, of the sums
+        // What came with the mean waits in LDS, behind the barriers of the sums: held in registers, these two and the start of the walk
+        // sent 12 to 52 bytes of most of these kernels through scratch memory.
+        float* held = consts[it & 1u];                      // (a slow wave may still read those of the channel before)
+        auto keep_constants = [&]() {
+            if (threadIdx.x == 0) {
+                held[0] = r;
+                held[1] = ga;
+            }
+        };
         // The sums of one vector.
         auto add = [&](const raw_t& gv, const raw_t& xv, float& s1, float& s2) {
             float fg[V], fx[V];
@@ -326,6 +345,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
             for (int e = 0; e < V; ++e) {
                 t1 += fg[e];
                 t2 = fmaf(fg[e], fx[e] - mu, t2);
+                if (V == 8 && e % 2 == 1) asm volatile("" : "+v"(t1), "+v"(t2));
             }
             const bool ok = at.exists(w);
             s1 += ok ? t1 : 0.f;
@@ -338,11 +358,12 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
                 const uint32_t off = at.load_at(wl);
                 g[k] = RV::ld(at_byte(gc, off));
                 xk[k] = RV::ld(at_byte(xc, off));
-                at.next(wl);
+                at.next_load(wl);
             };
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) load(k);
             mu = settled(mu);
+            keep_constants();
 #pragma unroll
             for (int k0 = 0; k0 < K; k0 += kGroup) {
                 float s1 = 0.f, s2 = 0.f;
@@ -369,7 +390,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
                         const uint32_t off = at.load_at(wl);
                         g[k0 + u] = RV::ld(at_byte(gc, off));
                         xb[u] = RV::ld(at_byte(xc, off));
-                        at.next(wl);
+                        at.next_load(wl);
                     }
             };
             auto use = [&](raw_t(&xb)[XB], int k0) {
@@ -391,6 +412,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
             };
             batch(b0, 0);
             mu = settled(mu);
+            keep_constants();
 #pragma unroll
             for (int k0 = 0; k0 < K; k0 += 2 * XB) {
                 if (k0 + XB < K) batch(b1, k0 + XB);
@@ -404,8 +426,8 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
         team_publish(F, read_stamp(F, words), team * F.T, j, it, float(d1), float(d2));
         gather(F, words, team * F.T, it, d1, d2, team_lds, bc);
 
-        r = settled(r);
-        ga = settled(ga);
+        r = held[0];
+        ga = held[1];
         const float dbeta = float(d1);
         const float dgamma = float(d2 * double(r));
         if (j == 0 && threadIdx.x == 0) {
@@ -419,7 +441,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
         const float k1v = MIXED ? a * F.w_v * dbeta : 0.f, k2v = MIXED ? a * F.w_v * dgamma * r : 0.f;
         const float centre_v = MIXED ? F.mean_parts[c] : 0.f;
         parked = 0;
-        w = w0;
+        w = at.start(int(opaque(uint32_t(j))));             // (not kept, either)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             float f[V];
