@@ -321,10 +321,12 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
         uint32_t parked = 0;
         Walk wl = w0, w = w0;                               // of the loads, of the sums
         // What came with the mean waits in LDS, behind the barriers of the sums: held in registers, these two and the start of the walk
-        // sent 12 to 52 bytes of most of these kernels through scratch memory.
+        // sent 12 to 52 bytes of these kernels through scratch memory.  Not where registers suffice: with ten vectors of each tensor in
+        // flight the branch costs a pause (64x256x56x56 bf16, everything, 54.3 -> 56.5 us).
+        constexpr bool kStash = !KEEPX || (PATCH == kPatch && V == 8);
         float* held = consts[it & 1u];                      // (a slow wave may still read those of the channel before)
         auto keep_constants = [&]() {
-            if (threadIdx.x == 0) {
+            if (kStash && threadIdx.x == 0) {
                 held[0] = r;
                 held[1] = ga;
             }
@@ -345,7 +347,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
             for (int e = 0; e < V; ++e) {
                 t1 += fg[e];
                 t2 = fmaf(fg[e], fx[e] - mu, t2);
-                if (V == 8 && e % 2 == 1) asm volatile("" : "+v"(t1), "+v"(t2));
+                if (V == 8 && !KEEPX && e % 2 == 1) asm volatile("" : "+v"(t1), "+v"(t2));      // (two elements at a time: registers)
             }
             const bool ok = at.exists(w);
             s1 += ok ? t1 : 0.f;
@@ -426,8 +428,8 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
         team_publish(F, read_stamp(F, words), team * F.T, j, it, float(d1), float(d2));
         gather(F, words, team * F.T, it, d1, d2, team_lds, bc);
 
-        r = held[0];
-        ga = held[1];
+        r = kStash ? held[0] : settled(r);
+        ga = kStash ? held[1] : settled(ga);
         const float dbeta = float(d1);
         const float dgamma = float(d2 * double(r));
         if (j == 0 && threadIdx.x == 0) {
