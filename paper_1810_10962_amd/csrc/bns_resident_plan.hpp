@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 #include "bns_index.hpp"
@@ -53,6 +54,7 @@ struct ResidentChoice {
 struct ResidentLayer {
     bool f32, odd, patch, general, everything;
     int64_t plane, stride;      // vectors of a plane, bytes from a sample to the next
+    double samples, rows, columns;      // shares of the samples, and of the rows and columns of a plane, whose vectors touch S
 };
 
 // A thread's vectors lie T * 512 vectors apart.  Places of the plane that they take in turn: where a plane is 512 vectors
@@ -61,6 +63,12 @@ struct ResidentLayer {
 inline int64_t resident_places(const ResidentPlan& p, const ResidentLayer& l) {
     const int64_t step = p.T * kResThreads % l.plane;
     return step == 0 ? 1 : l.plane / std::gcd(step, l.plane);
+}
+// The largest share of a thread's vectors that touch S.
+inline double resident_dense(const ResidentPlan& p, const ResidentLayer& l) {
+    if (!l.patch) return l.samples;
+    const int64_t places = resident_places(p, l);
+    return l.samples * (places < 8 ? std::ceil(double(places) * l.rows) / double(places) : l.rows * l.columns);
 }
 // ... and with samples a multiple of 1 MiB apart as well, what the device reads at one time lies in few memory channels, unless all channels
 // of the layer are read at once (us, other kernels / these): 94x128x64x64 bf16, everything, 63.4 / 113.6, 97x128x64x64 f32 112.7 / 154.9,
@@ -87,10 +95,14 @@ inline bool resident_forward_pays(const ResidentPlan& p, const ResidentLayer& l)
 //     (0.62) 69.8 / 75.1, 30x320x80x80 bf16 (0.60) 74.0 / 77.2; three rounds 28x671x46x46 f32 109.5 / 114.4.  Patches that threads meet at few places:
 //     48x172x64x64 bf16 (one) 49.1 / 60.0, two rounds 64x48x96x96 f32 (three) 66.4 / 79.2, but one round 21x192x64x64 f32 (two) 40.7 / 36.2.  Patches whose rows are no whole number of
 //     vectors: f32 two rounds 128x128x43x45 (0.62) 81.4 / 96.1, 34x127x93x93 (0.73) 100.3 / 108.0, one 106x240x27x27 (0.73) 51.2 / 52.6, 33x192x55x55 (0.75)
-//     55.1 / 43.2, 48x96x60x61 (0.66) 46.4 / 44.1; bf16 96x48x100x100 (0.90) 65.0 / 69.4.  bf16 planes that
+//     55.1 / 43.2, 48x96x60x61 (0.66) 46.4 / 44.1; bf16 96x48x100x100 (0.90) 65.0 / 69.4.  Where more of a thread's
+//     vectors touch S than LDS holds (a third of 49) the rest is read again: 64x256x56x56 f32, Batch Sampling of 26, 32, 38 and 48 of the 64 samples,
+//     113.9 / 107.7, 114.7 / 113.5, 114.2 / 117.0, 114.5 / 123.2, a patch of half and of nine tenths of the points 118.3 / 121.9, 118.8 / 137.5;
+//     21x250x64x64 f32, two places, a patch of 28 rows 53.7 / 45.0, of 35 rows 53.5 / 55.0; bf16 64x256x56x56, 38 and 48 samples, 66.3 /
+//     59.8, 66.6 / 63.7 (x beside dy 54.1 and 53.7: the better from 32 samples on).  bf16 planes that
 //     are no whole number of vectors need too much arithmetic per vector: 59x80x71x71 41.3 / 53.5.
 inline bool resident_big_pays(const ResidentPlan& p, const ResidentLayer& l) {
-    if (p.T == 0 || (l.odd && !l.f32) || resident_aliased(p, l)) return false;
+    if (p.T == 0 || (l.odd && !l.f32) || resident_aliased(p, l) || resident_dense(p, l) > (l.f32 ? 0.5 : 0.6)) return false;
     if (l.patch && resident_places(p, l) < (p.rounds == 1 ? 2 : 4)) return false;
     if (l.general && (!l.f32 || p.fill < (p.rounds > 1 ? 0.8 : l.odd ? 0.75 : 0.6))) return false;
     if (p.rounds == 1) return p.used >= (l.f32 ? 0.65 : 0.75) && p.fill >= 0.5;
@@ -133,6 +145,9 @@ inline ResidentChoice resident_choice(const Dims& d, const IndexParams& ip, bool
     l.everything = !ip.per_channel && b.n_cnt == d.N && b.h_cnt == d.H && b.w_cnt == d.W;
     l.plane = c.plane_vectors;
     l.stride = int64_t(d.C) * d.HW * (f32 ? 4 : 2);
+    l.samples = double(b.n_cnt) / double(d.N);
+    l.rows = double(b.h_cnt) / double(d.H);
+    l.columns = c.general ? 1.0 : std::min(1.0, double(b.w_cnt + c.vector - 1) / double(d.W));
     const ResidentPlan big = resident_plan(chunks, d.C, resident_vectors(f32, c.odd, c.general, backward, false), cus);
     const ResidentPlan pair = resident_plan(chunks, d.C, resident_vectors(f32, c.odd, c.general, backward, true), cus);
     if (opt != 0) {
@@ -143,7 +158,7 @@ inline ResidentChoice resident_choice(const Dims& d, const IndexParams& ip, bool
     } else {
         const bool pair_ok = resident_pair_pays(pair, l), big_ok = !l.everything && !mixed && resident_big_pays(big, l);
         c.take = pair_ok || big_ok;
-        c.keep_x = pair_ok && !(big_ok && big.rounds < pair.rounds);
+        c.keep_x = pair_ok && !(big_ok && big.rounds < pair.rounds && resident_dense(big, l) <= (f32 ? 0.5 : 0.45));
     }
     c.plan = c.keep_x ? pair : big;
     c.held = resident_vectors(f32, c.odd, c.general, backward, c.keep_x);

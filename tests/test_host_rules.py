@@ -77,7 +77,14 @@ LAYERS = [
     (33, 192, 55, 55, 0, FS, 0, 13, 13, 0, 1, 1),           # one round of them: 55.1 / 43.2
     (106, 240, 27, 27, 0, FS, 0, 6, 6, 0, 1, 2),            # 51.2 / 52.6 with dy alone, 51.0 with x beside it
     (97, 128, 64, 64, 0, BS, 12, 0, 0, 0, 1, 0),            # samples 2 MiB apart, two rounds: 112.7 / 154.9
+    (64, 256, 56, 56, 0, BS, 32, 0, 0, 0, 1, 1),            # half of x is needed again: 114.7 / 113.5
+    (64, 256, 56, 56, 0, BS, 48, 0, 0, 0, 1, 0),            # three quarters: 114.5 / 123.2
+    (64, 256, 56, 56, 0, FS, 0, 53, 53, 0, 1, 0),           # 118.8 / 137.5
+    (21, 250, 64, 64, 0, FS, 0, 28, 28, 0, 1, 1),           # two places, less than half of the rows: 53.7 / 45.0
     # backward, x beside dy
+    (21, 250, 64, 64, 0, FS, 0, 35, 35, 0, 1, 2),           # two places, more than half: 53.5 / 50.2 (dy alone 55.0)
+    (64, 256, 56, 56, 1, BS, 32, 0, 0, 0, 1, 2),            # half of x: 65.9 / 54.5 (57.2)
+    (64, 256, 56, 56, 1, BS, 25, 0, 0, 0, 1, 1),            # 0.39: 65.3 / 52.9 (53.9)
     (94, 128, 64, 64, 1, FULL, 0, 0, 0, 0, 1, 0),           # samples 1 MiB apart, two rounds: 63.4 / 113.6
     (98, 112, 64, 64, 1, FULL, 0, 0, 0, 0, 1, 2),           # 62.5 / 49.6
     (128, 256, 32, 32, 1, BS, 1, 0, 0, 0, 1, 0),            # 39.6 / 49.1
