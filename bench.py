@@ -61,7 +61,8 @@ def default_path_kernels(wl, dirs, bns):
            "one-launch": [pre + "fused_backward_kernel"],
            "streaming": [pre + "reduce_partial_kernel", pre + "reduce_finalize_kernel", pre + "dx_kernel"],
            # N x H x W x C: dx outside S written by the reduction kernel, the rows of S by a kernel of their own
-           "streaming-split": ["nhwc_reduce_outside_kernel", "nhwc_reduce_finalize_kernel", "nhwc_dx_rows_kernel"],
+           "streaming-split": ["nhwc_reduce_outside_kernel" if bns.bns_get_option("nhwc_split_dx") == 1 else
+                               "nhwc_reduce_outside_ordered_kernel", "nhwc_reduce_finalize_kernel", "nhwc_dx_rows_kernel"],
            }[dirs["backward_path"]]
     return fwd, bwd
 

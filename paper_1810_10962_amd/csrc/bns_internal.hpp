@@ -90,7 +90,8 @@ struct Tuning {
     TuneInt nhwc_fused_lanes{0};            // column vectors of a tile in those kernels
     TuneInt nhwc_ew_rows{0};                // rows per row lane in its element-wise kernels (default kNhwcEwRows)
     TuneInt nhwc_split_ordered{0};          // that kernel front to back (beyond the single launch): 1 whenever it can run, 2 never
-    TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always; 0, 2 never
+    TuneInt nhwc_split_dx{0};               // backward writes dx outside S from the reduction kernel: 1 always (bits of the stage calls), 2 never, 0 as
+                                            // nhwc_split_ordered says
     // For the library's own tests of the give-up path only; a caller has no use for them.
     TuneInt test_spin_limit{0};             // polls a team member waits for a team-mate before giving up (default 2^21)
     TuneInt test_mute_exchange{0};          // 1: no member publishes its sums, so every wait runs out

@@ -114,7 +114,7 @@ OVERRIDES = {
     "fused_keep_x": [0, 1, 2], "fused_patch_mask": [0, 1, 2], "fused_coop": [0, 1], "path": [0, 0, 1, 2],
     "fused_pipe": [0, 0, 1, 2, 3, 4, 5, 6, 16], "fused_team": [0, 0, 1, 2, 3, 5, 8, 16, 128],
     "grouped": [0, 1, 2, 3, 4, 5, 6], "grouped_channels": [0, 1, 3, 64], "nhwc_fused": [0, 1, 1, 2],
-    "nhwc_fused_lanes": [0, 1, 2, 5, 17, 32],
+    "nhwc_fused_lanes": [0, 1, 2, 5, 17, 32], "resident": [0, 1, 2, 3, 4], "nhwc_split_ordered": [0, 1, 1, 2],
 }
 
 

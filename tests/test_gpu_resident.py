@@ -110,3 +110,23 @@ def test_a_team_mate_that_never_publishes_ends_in_nan():
             bns.bns_set_option(k, 0)
     assert np.isnan(res["dbeta"]).all() and np.isnan(res["dgamma"]).all()
     assert bns.bns_expired_waits(b.workspace) > 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_team_mate_that_never_publishes_leaves_the_moving_averages_alone(dtype):
+    wl = Workload(name="resident_mute_forward", N=90, C=6, H=56, W=56, dtype=dtype, mode=BS, n_s=4, data_seed=8, sampling_seed=1)
+    inp = workloads.make_inputs(wl)
+    opts = {"path": 2, "resident": 1, "test_mute_exchange": 1, "test_spin_limit": 64}
+    b = bns.Buffers(wl, inp)
+    try:
+        for k, v in opts.items():
+            bns.bns_set_option(k, v)
+        b.forward()
+        res = b.results()
+        assert bns.bns_get_option("last_fused_forward") == 4
+    finally:
+        for k in opts:
+            bns.bns_set_option(k, 0)
+    assert np.isnan(res["save_mean"]).all() and np.isnan(res["save_invstd"]).all() and np.isnan(res["y"]).all()
+    assert (res["running_mean"] == inp["running_mean"]).all() and (res["running_var"] == inp["running_var"]).all()
+    assert bns.bns_expired_waits(b.workspace) > 0
