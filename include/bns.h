@@ -329,8 +329,9 @@ bns_status bns_copy_reference(void* dst, const void* src, size_t bytes, void* st
  *                    needs no sum there) and the rows of S from a kernel of their own: 1 always, with the bits of the stage calls;
  *                    2 never; 0: see "nhwc_split_ordered"
  *   "nhwc_split_ordered"  with "nhwc_split_dx" = 0 and "path" other than 1, bns_backward does so front to back, which adds the rows in another
- *                    order: 1 whenever it can (16-byte accesses), 2 never; 0: S at most a quarter of the rows, tensors from 16 MB
- *                    whose channels fill the lanes, where the single launch does not run
+ *                    order: 1 whenever it can (16-byte accesses), 2 never; 0: where it is the faster side (S at most a
+ *                    quarter of the rows, tensors from 16 MB whose channels fill one, two, four or eight column tiles)
+ *                    and the single launch does not run
  *   "cache_reuse"    streaming kernels: a first pass (statistics; the sums of Eq. 5) loads what the pass after it
  *                    (Eq. 1; Eq. 6) reads again without the non-temporal hint, so that it stays in the device's
  *                    memory-side cache: 1 all of it, 2 none; 0: as much as fits there (224 MB).  Results do not

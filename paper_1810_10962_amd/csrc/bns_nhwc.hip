@@ -944,15 +944,25 @@ hipError_t launch_nhwc_reduce(const Dims& d, const void* x, const void* dy, cons
 //     Batch Sampling 1/8 251 / 223, 1/4 258 / 241, 3/4 289 / 294; bf16 1/8 129 / 117, 1/4 132 / 122, 1/2 140 / 139;
 //   * where few column lanes idle: 120x1024x24x24 f32 179 / 152, 100x480x45x45 (120 of 128 lanes) 247 / 230, 40x200x70x70 (50 of 64)
 //     103.0 / 105.4, 100x328x45x45 (82 of 128) 194 / 206;
-//   * beyond a few launches' worth of bytes: 32x256x28x28 f32 (26 MB) 25.0 / 24.4, 6x128x28x28 (2.4 MB) 11.8 / 12.9.
+//   * beyond a few launches' worth of bytes: 32x256x28x28 f32 (26 MB) 25.0 / 24.4, 6x128x28x28 (2.4 MB) 11.8 / 12.9;
+//   * where rows are whole segments of 64 bytes in one, two, four or eight column tiles: the blocks of a tile write their share of a row
+//     long after the other tiles' blocks wrote theirs.  Of 2673 further layers drawn so (C up to 3200, 16-420 MB, S up to 1/4, 7/8 of the
+//     lanes) it is 1.08 times as fast in the mean and none loses 5 %; of 1799 in five to seven tiles 591 do, 99x1480x18x18 f32 Batch
+//     Sampling 143.5 / 158.9, 6x1152x99x99 f32 180 / 207, except where S is contiguous and no lane idles (f32, three, five, six tiles: 1.03,
+//     115 layers, one; bf16, three: 1.01, five of 117);
+//   * rows that start anywhere only where S is contiguous and there are at most two tiles (1.03, 129 layers, none): a patch
+//     22x1128x45x45 f32 147 / 175.
 bool nhwc_split_ordered(const Dims& d, const bns_box& b) {
     const int opt = g_tuning.nhwc_split_ordered;
     const size_t size = d.dtype == BNS_F32 ? 4 : 2, pitch = size_t(d.C) * size, M = size_t(d.N) * size_t(d.HW);
     if (opt == 2 || column_vec(d) * size != 16 || pitch * size_t(kBlock * kSplitRows) >= (size_t(1) << 30)) return false;
     if (opt == 1) return true;
+    const RowSet S = make_rowset(d, b);
     const Tiling t = make_tiling(d, uint32_t(M));
-    const size_t lanes = size_t((t.CV + (1 << t.log2_tx) - 1) >> t.log2_tx) << t.log2_tx;
-    return 4 * size_t(b.n_cnt) * size_t(b.h_cnt) * size_t(b.w_cnt) <= M && 8 * size_t(t.CV) >= 7 * lanes && M * pitch >= size_t(16) << 20;
+    const size_t tiles = size_t((t.CV + (1 << t.log2_tx) - 1) >> t.log2_tx), lanes = tiles << t.log2_tx;
+    if (4 * size_t(S.rows) > M || 8 * size_t(t.CV) < 7 * lanes || M * pitch < size_t(16) << 20) return false;
+    if (pitch % 64) return tiles <= 2 && S.contiguous;
+    return tiles <= 2 || tiles == 4 || tiles == 8 || (tiles <= 6 && d.dtype == BNS_F32 && S.contiguous && 100 * size_t(t.CV) >= 97 * lanes);
 }
 
 // The whole backward pass with dx split by Eq. 6's two branches: sums + dx outside S, finalize, dx on S.

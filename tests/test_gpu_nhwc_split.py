@@ -67,3 +67,25 @@ def test_rule_of_the_default(kw, want):
     assert _run(wl, inp, nhwc_fused=2)[1] == want
     assert _run(wl, inp, nhwc_fused=2, nhwc_split_ordered=2)[1] == 1 and _run(wl, inp, nhwc_fused=2, nhwc_split_dx=2)[1] == 1
     assert _run(wl, inp, path=1)[1] == 1
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(C=1024, dtype="f32", mode=BS, n_s=8), 4),                             # four column tiles of 64 lanes
+    (dict(C=1024, dtype="f32", mode=FS, patch_h=7, patch_w=7), 4),
+    (dict(C=768, dtype="f32", mode=BS, n_s=8), 4),                              # three, no lane idle, S contiguous
+    (dict(C=768, dtype="f32", mode=FS, patch_h=7, patch_w=7), 1),
+    (dict(C=736, dtype="f32", mode=BS, n_s=8), 1),                              # 184 of 192 lanes
+    (dict(C=1536, dtype="bf16", mode=BS, n_s=8), 1),
+    (dict(C=2048, dtype="f32", mode=FS, patch_h=7, patch_w=7), 4),              # eight
+    (dict(C=1792, dtype="f32", mode=FS, patch_h=7, patch_w=7), 1),              # seven
+    (dict(C=484, dtype="f32", mode=BS, n_s=8), 4),                              # two, rows that start anywhere
+    (dict(C=484, dtype="f32", mode=FS, patch_h=7, patch_w=7), 1),
+    (dict(C=764, dtype="f32", mode=BS, n_s=8), 1),                              # three of them
+], ids=str)
+def test_rule_of_column_tiles_and_segments(kw, want):
+    wl = Workload(name="split_tiles", N=64, H=14, W=14, layout="nhwc", data_seed=7, sampling_seed=8, layer_id=1, **kw)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] tiles {kw}", flush=True)
+    res, path = _run(wl, inp, nhwc_fused=2)
+    assert path == want
+    assert_parity(res, oracle_reference(wl, inp), wl, what=f"tiles {kw}", inp=inp)
