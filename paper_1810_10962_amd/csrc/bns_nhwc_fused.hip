@@ -11,9 +11,10 @@
 // Bound by memory, by the exchange (about 1.5 us after the last block of a tile has its sums, which takes up to 3 more) and, in small
 // tensors, by a chain of latencies: by stamps on the device, 50x150x19x19 f32 forward spends 2 us until the average block runs, 3 on
 // its loads, 1.3 on its sums, 6 waiting for the last block and the exchange, 1 on its stores.  Measured against the streaming
-// kernels (three launches per direction), us forward / backward, Batch Sampling: 64x256x40x40 f32 44.1 / 69.7 against 39.1 / 53.2;
-// 64x256x56x56 bf16 47.6 / 71.1 against 42.3 / 57.8 (45.5 / 65.7 when loads had conditions around them and rows beyond the registers were
-// read twice), full BN 59.4 / 86.3 against 44.0 / 70.4; 67x512x11x11 f32 15.7 / 21.1 against 11.2 / 13.3.
+// kernels (three launches per direction), us forward / backward, Batch Sampling: 64x256x40x40 f32 43.9 / 70.1 against 40.4 / 55.4;
+// 64x256x56x56 bf16 47.6 / 71.2 against 42.5 / 57.4 (45.5 / 65.7 when loads had conditions around them and rows beyond the registers were
+// read twice), full BN 58.5 / 85.8 against 44.7 / 65.9 (backward 70.4 while it spilled registers); 67x512x11x11 f32 16.2 / 21.0 against
+// 11.5 / 13.7.
 //
 // Columns that are no whole number of vectors: the last vector of a row is moved back so that it ends with the row.  The
 // channels it shares with the vector before it are computed twice, with the same bits.
