@@ -959,8 +959,8 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
         // leaves few lanes, threads and compute units without work, with a price on the T * CT pairs of sums that every member
         // reads (128x64x32x32 f32 forward: 128 members x 32 channels 17.6, 256 x 64 20.8; 50x150x19x19 f32: 85 x 52 13.5 / 14.9, 51 x
         // 32 12.5 / 13.9).  The times below are estimates, us, of what depends on the width.  Rows that begin on no 64 bytes: fitted to
-        // 1800 passes over tensors of 0.2 to 130 MB, each timed with two to five widths; the tile it picks takes 1.01 of the time of the best
-        // of them, at most 1.2 (prices as for aligned rows: 1.03, 1.5).  A line shared between tiles costs as much as 115 bytes of one's own (13x293x67x67 f32
+        // 1800 passes over tensors of 0.2 to 130 MB, each timed with two to five widths; over 4100 further ones, with all of them, the tile it picks takes
+        // 1.02 of the time of the best, 117 times more than 1.1, at most 1.42 (prices as for aligned rows, over the 1800: 1.03, 1.5).  A line shared between tiles costs as much as 115 bytes of one's own (13x293x67x67 f32
         // forward, 8 lanes 61.9, 16 lanes 48.0); idle compute units cost less than their share, since small tensors do not fill
         // the memory's queues; 1024 pairs are polled in one go (25x382x8x8 bf16 forward, 8 members x 72 channels 9.2, 13 x 128 10.6).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
