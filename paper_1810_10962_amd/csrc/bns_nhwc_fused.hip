@@ -11,7 +11,7 @@
 // Bound by memory, by the exchange (about 1.5 us after the last block of a tile has its sums, which takes up to 3 more) and, in small
 // tensors, by a chain of latencies: by stamps on the device, 50x150x19x19 f32 forward spends 2 us until the average block runs, 3 on
 // its loads, 1.3 on its sums, 6 waiting for the last block and the exchange, 1 on its stores.  Measured against the streaming
-// kernels (three launches per direction), us forward / backward, Batch Sampling: 64x256x40x40 f32 43.9 / 70.1 against 40.4 / 55.4;
+// kernels (three launches per direction), us forward / backward, Batch Sampling: 64x256x40x40 f32 43.9 / 70.1 against 39.1 / 55.4;
 // 64x256x56x56 bf16 47.6 / 71.2 against 42.5 / 57.4 (45.5 / 65.7 when loads had conditions around them and rows beyond the registers were
 // read twice), full BN 58.5 / 85.8 against 44.7 / 65.9 (backward 70.4 while it spilled registers); 67x512x11x11 f32 16.2 / 21.0 against
 // 11.5 / 13.7.
@@ -244,7 +244,6 @@ __device__ __forceinline__ void add_members(const RowArgs& A, const RowLane& l, 
 
 // Totals over the members, by thread t < CT.  Every sum is taken in a fixed order, so all members get the same bits.
 // A wait that runs out leaves NaN in that channel and sets its word of lost.
-template <int B>
 __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l, uint32_t stamp, int set, double* part, uint32_t* lost,
                                              double& s1, double& s2) {
     if (A.f.T == 1) return;
@@ -254,7 +253,7 @@ __device__ __forceinline__ void tile_collect(const RowArgs& A, const RowLane& l,
     if (g < Q && ch < l.width) {
         // (words are requested for every member at once, and none twice: the polls of all blocks share one path)
         if (T <= 2 * Q) add_members<2>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
-        else add_members<B>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
+        else add_members<kRowPoll>(A, l, stamp, set, ch, g, Q, lost, s1, s2);
         part[g * CT + ch] = s1;
         part[kRowThreads + g * CT + ch] = s2;
     }
@@ -329,7 +328,9 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
     }
     constexpr int kAhead = FIRST || K < kRowKeepX ? K : kRowKeepX;
     constexpr bool kAgain = L > 0 || (FIRST && K > kRowKeepX);         // takes more rows than it holds, too
-    constexpr int kPoll = K + L > 52 ? kRowPoll / 2 : kRowPoll;        // (the registers are full)
+    // The registers are full: what a channel needs waits in LDS for its sums.  (Half as many polls at a time instead: 64x256x40x40 f32 40.3
+    // against 39.1 us, 56x56 full BN 81.6 against 80.2.)
+    constexpr bool kStow = K + L > 52;
     constexpr bool kTight = K <= kAhead;                    // all loads come before the first sum: only those that are needed
     raw_t v[K], u[L > 0 ? L : 1];
     Walk wl = walk_from(K);                              // of the loads
@@ -382,6 +383,15 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
     const uint32_t stamp = read_stamp(F, words);
 
     double s1 = 0.0, s2 = 0.0, u1 = 0.0, u2 = 0.0;          // thread t < CT: the sums of channel t
+    float ga = 0.f, be = 0.f, rm = 0.f, rv = 0.f;
+    const int c = l.tile * int(A.ct_div.d) + int(threadIdx.x);
+    const bool leads = int(threadIdx.x) < l.width;
+    auto channel = [&]() {
+        ga = F.gamma[c];
+        be = F.beta[c];
+        if (l.j == 0 && F.running_mean) rm = F.running_mean[c];
+        if (l.j == 0 && F.running_var) rv = F.running_var[c];
+    };
 #pragma unroll
     for (int set = 0; set < (MIXED ? 2 : 1); ++set) {
         double a[V], q[V];
@@ -501,6 +511,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             }
         }
         double t1, t2;
+        if (kStow && set == 0 && leads) channel();
         tile_sums<V>(A, l, a, q, lds, part, t1, t2);
         tile_publish(A, l, stamp, set, t1, t2);
         if (set == 0) {
@@ -511,18 +522,20 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             u2 = t2;
         }
     }
-    float ga = 0.f, be = 0.f, rm = 0.f, rv = 0.f;
-    const int c = l.tile * int(A.ct_div.d) + int(threadIdx.x);
-    const bool leads = int(threadIdx.x) < l.width;
     if (leads) {
-        ga = F.gamma[c];
-        be = F.beta[c];
-        if (l.j == 0 && F.running_mean) rm = F.running_mean[c];
-        if (l.j == 0 && F.running_var) rv = F.running_var[c];
+        if (kStow) consts[threadIdx.x] = float4{ga, be, rm, rv};
+        else channel();
     }
-    tile_collect<kPoll>(A, l, stamp, 0, part, lost, s1, s2);
-    if (MIXED) tile_collect<kPoll>(A, l, stamp, 1, part, lost, u1, u2);
+    tile_collect(A, l, stamp, 0, part, lost, s1, s2);
+    if (MIXED) tile_collect(A, l, stamp, 1, part, lost, u1, u2);
     if (leads) {
+        if (kStow) {
+            const float4 w = consts[threadIdx.x];
+            ga = w.x;
+            be = w.y;
+            rm = w.z;
+            rv = w.w;
+        }
         const double m1 = s1 / F.s;
         double mean = double(piv[threadIdx.x]) + m1;
         double var = s2 / F.s - m1 * m1;
@@ -788,7 +801,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
         centre = MIXED ? F.mean_parts[F.C + c] : F.save_mean[c];
         if (MIXED) e_v = F.mean_parts[c];
     }
-    tile_collect<kRowPoll>(A, l, stamp, 0, part, nullptr, s1, s2);
+    tile_collect(A, l, stamp, 0, part, nullptr, s1, s2);
     if (leads) {
         const float dbeta = float(s1);
         const float dgamma = float(s2 * double(r));
