@@ -1040,8 +1040,11 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     if (opt != 1 && T > 1 && rounds > limit) return hipErrorNotSupported;
     // Ragged bf16 rows of small tensors: streaming takes single elements, and that is enough (3x107x18x18, 208 KB, backward 8.0 against 14.2
     // us, 5x230x11x11, 278 KB, 9.1 / 8.2 against 9.5 / 9.3, 4x190x16x16, 389 KB, 8.8 / 8.0 against 9.6 / 9.6; 18x122x10x10, 439 KB, 10.8 / 9.9
-    // against 9.6 / 9.1).
-    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < 400000) return hipErrorNotSupported;
+    // against 9.6 / 9.1).  Of 200 drawn layers of 180 to 400 KB this launch took 1.04 of streaming's time forward and 1.11 backward; but 0.94
+    // in full BN forward, 0.97 in Eq. 4 forward, and 0.87 (60 layers) where streaming has 64-bit accesses, which save it little: 8x28x23x23 (237 KB) 11.0
+    // / 10.5 against 8.3 / 8.3.  (Below: 13x137x7x7, 175 KB, backward 9.4 against 10.3, 37x143x5x5, 265 KB, 11.6 / 11.2 against 9.4 / 9.8.)
+    const bool elements = single && (backward || (!everything && !mix));
+    if (opt != 1 && T > 1 && V == 8 && d.C % V != 0 && bytes < (elements ? 400000u : 180000u)) return hipErrorNotSupported;
     // bf16 rows that do not begin on cache lines: tiles of one and the same line are read by different blocks (us, streaming against this:
     // 12x432x73x70, 52 rows per thread, 34.7 / 45.7 against 37.8 / 50.9; 60x336x38x38, 28 rows, 38.4 / 53.7 against 41.0 / 54.1; 75x1296x15x16, 25 rows,
     // 34.1 / 44.6 against 34.2 / 39.5; 27x272x37x40, 12 rows, 23.7 / 31.5 against 22.7 / 22.9).

@@ -372,3 +372,19 @@ def test_rows_between_the_steps(dtype, rounds, ragged):
         res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
         assert _paths() == (2, 2)
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(N=8, C=28, H=23, W=23, mode=BS, n_s=2), (2, 2)),          # 237 KB, streaming's accesses 64 bits
+    (dict(N=5, C=28, H=23, W=23, mode=BS, n_s=2), (1, 1)),          # 148 KB
+    (dict(N=8, C=29, H=23, W=23, mode=BS, n_s=2), (1, 1)),          # 245 KB, single elements
+    (dict(N=8, C=29, H=23, W=23, mode=FULL), (2, 1)),
+    (dict(N=14, C=29, H=23, W=23, mode=BS, n_s=2), (2, 2)),         # 430 KB
+], ids=str)
+def test_ragged_bf16_rows_of_small_tensors(kw, want):
+    wl = Workload(name="ragged_small", dtype="bf16", layout="nhwc", data_seed=3, sampling_seed=4, layer_id=2, **kw)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] ragged {kw}", flush=True)
+    res = bns.run_workload(wl, inp)
+    assert (bns.bns_get_option("last_path_forward"), bns.bns_get_option("last_path_backward")) == want
+    assert_parity(res, oracle_reference(wl, inp), wl, what=f"ragged {kw}", inp=inp)
