@@ -282,10 +282,12 @@ __device__ __forceinline__ void team_done(const FusedArgs& A, int j, uint32_t st
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
-// The stamp as a wave-uniform (scalar) value; call behind a barrier that follows draw_stamp.
+// The stamp as a wave-uniform (scalar) value; call behind a barrier that follows stamp_accept.
+// (A plain read of LDS, here and in team_collect: through a volatile pointer it is a flat load, and the wait for that one is a wait for
+// every load and store that the wave has in flight.)
 __device__ __forceinline__ uint32_t read_stamp(const FusedArgs& A, const uint32_t* word) {
     if (A.T == 1) return 0u;
-    return uint32_t(__builtin_amdgcn_readfirstlane(int(*static_cast<const volatile uint32_t*>(word))));
+    return uint32_t(__builtin_amdgcn_readfirstlane(int(*word)));
 }
 
 // Polls member `t`'s slot pair until it carries `stamp`; false (and NaN payloads) if the wait ran out.  Once a wait
@@ -343,6 +345,9 @@ __device__ __forceinline__ bool team_collect(const FusedArgs& A, uint32_t* words
     }
     const uint32_t stamp = read_stamp(A, words) + it;
     unsigned long long* base = A.slots + size_t(it & uint32_t(SETS - 1)) * gridDim.x * 2;
+    // (Polls that set out while this member's own words are still on their way are served late: 78x64x20x20 bf16, both directions, 13.8 us
+    // without this wait, 10.2 with it; 34x64x23x20 13.6 and 10.6.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // words[1 + (it & 1)]: set by a thread whose wait ran out in this exchange; thread 0 clears the other one, which
     // the next exchange uses, between the two barriers
     for (int t = threadIdx.x; t < A.T; t += NT) {
@@ -352,7 +357,7 @@ __device__ __forceinline__ bool team_collect(const FusedArgs& A, uint32_t* words
         team_lds[kMaxTeam + t] = pb;
     }
     __syncthreads();
-    const bool ok = static_cast<volatile uint32_t*>(words)[1 + (it & 1u)] == 0u;
+    const bool ok = words[1 + (it & 1u)] == 0u;
     if (threadIdx.x == 0) {
         // In member order.  Eq. 4 reads eight pairs from LDS at a time (130x128x28x28 f32, forward, with the single wait: 25.7 ->
         // 24.3 us); the other kernels lose by it: the registers pass 128, where a compute unit holds one block instead of two

@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             F.save_invstd[c] = r;
             const double al = double(F.momentum);
             // (a wait for a team-mate that ran out leaves NaN statistics in its channel, whose moving averages then stay as they are)
-            const bool arrived = F.T == 1 || static_cast<volatile uint32_t*>(lost)[threadIdx.x] == 0u;
+            const bool arrived = F.T == 1 || lost[threadIdx.x] == 0u;
             if (F.running_mean && arrived) F.running_mean[c] = float((1.0 - al) * double(rm) + al * mean);
             if (F.running_var && arrived) F.running_var[c] = float((1.0 - al) * double(rv) + al * var);
         }
