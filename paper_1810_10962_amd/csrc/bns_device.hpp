@@ -31,6 +31,15 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
     return (__umulhi(n, f.mul) + n) >> f.shift;
 }
 
+// 1 / sqrt(x) in fp64, within two units in the last place: the hardware's estimate (some 23 bits) and one step of third order,
+// x (y (1 + e / 2 + 3 e^2 / 8))^2 = 1 + O(e^3) with e = 1 - x y^2.  x = 0, infinity and NaN keep the estimate (infinity, 0, NaN).
+// A dozen instructions where a square root and a division are some 90, each a few nanoseconds in blocks of 512 threads that all wait
+// for them (64-bit and 32-bit instructions issue at one rate).
+__device__ __forceinline__ double inv_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return x > 0.0 && x < __builtin_inf() ? fma(y * e, fma(e, 0.375, 0.5), y) : y;
+}
+
 // ---------------------------------------------------------------------------
 // Storage types.  bf16 is handled as raw 16-bit patterns: widening is a shift,
 // narrowing is the hardware conversion (round to nearest, ties to even; NaN stays NaN).

@@ -286,14 +286,14 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
         }
 
         // Eq. 3 (every thread computes the same values from the same totals)
-        const double m1 = t1 / A.s;
+        const double m1 = t1 * A.inv_s64;
         double mean = double(pivot) + m1;
-        double var = t2 / A.s - m1 * m1;
+        double var = t2 * A.inv_s64 - m1 * m1;
         if (!(var >= 0.0)) var = (var != var) ? var : 0.0;      // clamp rounding; keep NaN visible
         if constexpr (MIXED) {
-            const double mv = u1 / A.s_v;
+            const double mv = u1 * A.inv_s_v;
             const double e_v = double(pivot_v) + mv;
-            double var_v = u2 / A.s_v - mv * mv;
+            double var_v = u2 * A.inv_s_v - mv * mv;
             if (!(var_v >= 0.0)) var_v = (var_v != var_v) ? var_v : 0.0;
             if (j == 0 && threadIdx.x == 0) {
                 A.mean_parts[c] = float(e_v);
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
             var = bm * var_v + (1.0 - bm) * var;                // Eq. 4, X = Var
         }
         const float mu = float(mean);
-        const float r = float(1.0 / sqrt(var + double(A.eps)));
+        const float r = float(inv_sqrt(var + double(A.eps)));
         if (j == 0 && threadIdx.x == 0) {
             A.save_mean[c] = mu;
             A.save_invstd[c] = r;
@@ -1150,23 +1150,25 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.eps = eps;
     A.momentum = momentum;
     const bns_box& b = ip.shared;
-    A.s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
+    const double points = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
     A.s_cnt = uint32_t(b.n_cnt) * uint32_t(b.h_cnt) * uint32_t(b.w_cnt);
     A.n_v = 0;
     A.mix_beta = A.w_v = A.w_s = 0.f;
-    A.s_v = 1.0;
+    A.inv_s_v = 1.0;
     A.mean_parts = nullptr;
     if (mix) {
         A.n_v = mix->n_v;
         A.mix_beta = mix->mix_beta;
-        A.s_v = double(mix->n_v) * double(d.HW);
-        A.w_v = float(double(mix->mix_beta) / A.s_v);
-        A.w_s = float((1.0 - double(mix->mix_beta)) / A.s);
+        const double virtual_points = double(mix->n_v) * double(d.HW);
+        A.inv_s_v = 1.0 / virtual_points;
+        A.w_v = float(double(mix->mix_beta) / virtual_points);
+        A.w_s = float((1.0 - double(mix->mix_beta)) / points);
         A.mean_parts = mix->mean_parts;
     }
     A.patch_div = make_fastdiv(uint32_t(b.h_cnt) * uint32_t(b.w_cnt));
     A.pw_div = make_fastdiv(uint32_t(b.w_cnt));
-    A.inv_s = float(1.0 / A.s);
+    A.inv_s64 = 1.0 / points;
+    A.inv_s = float(A.inv_s64);
 
     const int grid = A.num_teams * bestT;
     if (size_t(A.num_teams) * slots_per_team > slot_bytes) return hipErrorNotSupported;

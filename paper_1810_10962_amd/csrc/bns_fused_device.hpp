@@ -163,7 +163,7 @@ struct FusedArgs {
     // sampled real set; mean_parts = [E_v per channel][E_s per channel] (forward: written; backward: read)
     int32_t n_v;
     float mix_beta, w_v, w_s;       // backward weights: mix_beta / s_v and (1 - mix_beta) / s_s
-    double s_v;                     // n_v * HW
+    double inv_s_v;                 // 1 / (n_v * HW)
     float* mean_parts;
     FastDiv patch_div, pw_div;   // h_cnt * w_cnt and w_cnt of S: sampled element q -> (n, ph, pw)
     uint32_t stamp_seed;    // start of the stamp sequence if the workspace holds no launch counter yet
@@ -171,7 +171,7 @@ struct FusedArgs {
     uint32_t spin_limit;    // polls before a missing team-mate is given up on
     int32_t mute;           // 1: members do not publish (host-forced give-up, for tests of that path)
     float eps, momentum, inv_s;
-    double s;       // |S| per channel
+    double inv_s64; // 1 / (|S| per channel)
 };
 
 // Block-wide sum of (a, b) over NT threads; result returned to every thread.

@@ -52,7 +52,7 @@ struct GroupArgs {
     int32_t TY;             // rows taken at a time: threads / column vectors of a group
     int32_t n_v;            // Eq. 4: samples of the virtual set
     float mix_beta, w_s, w_v, eps, momentum;
-    double s, s_v;
+    double inv_s64, inv_s_v;    // 1 / points of S, of the virtual set
 };
 
 // 128-bit (64-bit) accesses at element alignment: planes of an odd number of elements start anywhere.
@@ -163,7 +163,7 @@ __device__ __forceinline__ void channel_totals(const GroupArgs& A, int channels,
 
 // Waves per SIMD that the registers have to allow: K vectors of one (forward) or two tensors, and what the elements need.
 constexpr int group_waves(int nt, int vectors, bool mixed) {
-    return vectors >= 16 || (mixed && vectors >= 8) ? (nt == 256 ? 3 : 2) : 4;
+    return vectors >= 16 || (mixed && vectors >= (nt == 256 ? 4 : 8)) ? (nt == 256 ? 3 : 2) : 4;
 }
 
 template <typename T, int V, int K, int NT, bool MIXED>
@@ -246,14 +246,14 @@ __global__ __launch_bounds__(NT, group_waves(NT, K, MIXED)) void grouped_forward
     if constexpr (MIXED) channel_totals<V, NT>(A, me.channels, part + NT, u1, u2);
     if (leads) {                                                // Eq. 3, Eq. 4, Eq. 8: one thread per channel
         const int c = me.c0 + t;
-        const double m1 = s1 / A.s;
+        const double m1 = s1 * A.inv_s64;
         double mean = double(pivot) + m1;
-        double var = s2 / A.s - m1 * m1;
+        double var = s2 * A.inv_s64 - m1 * m1;
         if (!(var >= 0.0)) var = (var != var) ? var : 0.0;      // clamp rounding; keep NaN visible
         if constexpr (MIXED) {
-            const double mv = u1 / A.s_v;
+            const double mv = u1 * A.inv_s_v;
             const double e_v = double(pivot_v) + mv;
-            double var_v = u2 / A.s_v - mv * mv;
+            double var_v = u2 * A.inv_s_v - mv * mv;
             if (!(var_v >= 0.0)) var_v = (var_v != var_v) ? var_v : 0.0;
             A.mean_parts[c] = float(e_v);
             A.mean_parts[A.C + c] = float(mean);
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(NT, group_waves(NT, K, MIXED)) void grouped_forward
             var = bm * var_v + (1.0 - bm) * var;
         }
         const float mu = float(mean);
-        const float r = float(1.0 / sqrt(var + double(A.eps)));
+        const float r = float(inv_sqrt(var + double(A.eps)));
         A.save_mean[c] = mu;
         A.save_invstd[c] = r;
         const double al = double(A.momentum);
@@ -508,12 +508,14 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     A.G = best_g;
     A.TY = gv.nt / int(lanes);
     const bns_box& b = ip.shared;
-    A.s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
+    const double points = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
     A.n_v = mix ? mix->n_v : 0;
-    A.s_v = mix ? double(mix->n_v) * double(d.HW) : 1.0;
+    const double virtual_points = mix ? double(mix->n_v) * double(d.HW) : 1.0;
+    A.inv_s64 = 1.0 / points;
+    A.inv_s_v = 1.0 / virtual_points;
     A.mix_beta = mix ? mix->mix_beta : 0.f;
-    A.w_s = mix ? float((1.0 - double(mix->mix_beta)) / A.s) : float(1.0 / A.s);
-    A.w_v = mix ? float(double(mix->mix_beta) / A.s_v) : 0.f;
+    A.w_s = mix ? float((1.0 - double(mix->mix_beta)) / points) : float(1.0 / points);
+    A.w_v = mix ? float(double(mix->mix_beta) / virtual_points) : 0.f;
     A.eps = eps;
     A.momentum = momentum;
     const dim3 grid(uint32_t((d.C + best_g - 1) / best_g));

@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kOneBlock) void stats_one_block_kernel(
     double var = t2 / s - m1 * m1;
     if (var < 0.0) var = 0.0;
     save_mean[c] = float(mean);
-    save_invstd[c] = float(1.0 / sqrt(var + double(eps)));
+    save_invstd[c] = float(inv_sqrt(var + double(eps)));
     const double a = double(momentum);
     if (running_mean) running_mean[c] = float((1.0 - a) * double(running_mean[c]) + a * mean);
     if (running_var) running_var[c] = float((1.0 - a) * double(running_var[c]) + a * var);
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kBlock) void stats_finalize_kernel(
     double var = s2 / s - m1 * m1;
     if (var < 0.0) var = 0.0;
     save_mean[c] = float(mean);
-    save_invstd[c] = float(1.0 / sqrt(var + double(eps)));
+    save_invstd[c] = float(inv_sqrt(var + double(eps)));
     const double a = double(momentum);
     if (running_mean) running_mean[c] = float((1.0 - a) * rm + a * mean);
     if (running_var) running_var[c] = float((1.0 - a) * rv + a * var);
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kBlock) void stats_finalize_mixed_kernel(
     const double mean = bm * e_v + (1.0 - bm) * e_s;            // Eq. 4, X = E
     const double var = bm * var_v + (1.0 - bm) * var_s;         // Eq. 4, X = Var
     save_mean[c] = float(mean);
-    save_invstd[c] = float(1.0 / sqrt(var + double(eps)));
+    save_invstd[c] = float(inv_sqrt(var + double(eps)));
     mean_parts[c] = float(e_v);
     mean_parts[C + c] = float(e_s);
     const double al = double(momentum);

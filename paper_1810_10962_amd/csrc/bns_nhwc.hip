@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kBlock) void nhwc_stats_finalize_kernel(
     double var = s2 / s - m1 * m1;      // biased (1/s), Eq. 3
     if (var < 0.0) var = 0.0;
     save_mean[c] = float(mean);
-    save_invstd[c] = float(1.0 / sqrt(var + double(eps)));
+    save_invstd[c] = float(inv_sqrt(var + double(eps)));
     const double al = double(momentum);                       // Eq. 8
     if (running_mean) running_mean[c] = float((1.0 - al) * double(running_mean[c]) + al * mean);
     if (running_var) running_var[c] = float((1.0 - al) * double(running_var[c]) + al * var);
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void nhwc_stats_finalize_mixed_kernel(
     const double mean = bm * e_v + (1.0 - bm) * e_s;            // Eq. 4, X = E
     const double var = bm * var_v + (1.0 - bm) * var_s;         // Eq. 4, X = Var
     save_mean[c] = float(mean);
-    save_invstd[c] = float(1.0 / sqrt(var + double(eps)));
+    save_invstd[c] = float(inv_sqrt(var + double(eps)));
     mean_parts[c] = float(e_v);
     mean_parts[C + c] = float(e_s);
     const double al = double(momentum);                         // Eq. 8

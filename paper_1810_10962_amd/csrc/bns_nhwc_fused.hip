@@ -536,14 +536,14 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             rm = w.z;
             rv = w.w;
         }
-        const double m1 = s1 / F.s;
+        const double m1 = s1 * F.inv_s64;
         double mean = double(piv[threadIdx.x]) + m1;
-        double var = s2 / F.s - m1 * m1;
+        double var = s2 * F.inv_s64 - m1 * m1;
         if (!(var >= 0.0)) var = (var != var) ? var : 0.0;  // clamp rounding; keep NaN visible
         if constexpr (MIXED) {
-            const double mv = u1 / F.s_v;
+            const double mv = u1 * F.inv_s_v;
             const double e_v = double(piv[kRowMaxTile + threadIdx.x]) + mv;
-            double var_v = u2 / F.s_v - mv * mv;
+            double var_v = u2 * F.inv_s_v - mv * mv;
             if (!(var_v >= 0.0)) var_v = (var_v != var_v) ? var_v : 0.0;
             if (l.j == 0) {
                 F.mean_parts[c] = float(e_v);
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             var = bm * var_v + (1.0 - bm) * var;
         }
         const float mu = float(mean);
-        const float r = float(1.0 / sqrt(var + double(F.eps)));
+        const float r = float(inv_sqrt(var + double(F.eps)));
         if (l.j == 0) {
             F.save_mean[c] = mu;
             F.save_invstd[c] = r;
@@ -1089,17 +1089,19 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     A.mute_channel = g_tuning.test_mute_channel;
     F.eps = eps;
     F.momentum = momentum;
-    F.s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
-    F.inv_s = float(1.0 / F.s);
-    F.s_v = 1.0;
+    const double points = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
+    F.inv_s64 = 1.0 / points;
+    F.inv_s = float(F.inv_s64);
+    F.inv_s_v = 1.0;
     A.virtual_rows = 0;
     if (mix) {
         A.virtual_rows = uint32_t(mix->n_v) * uint32_t(d.HW);
         F.n_v = mix->n_v;
         F.mix_beta = mix->mix_beta;
-        F.s_v = double(mix->n_v) * double(d.HW);
-        F.w_v = float(double(mix->mix_beta) / F.s_v);
-        F.w_s = float((1.0 - double(mix->mix_beta)) / F.s);
+        const double virtual_points = double(mix->n_v) * double(d.HW);
+        F.inv_s_v = 1.0 / virtual_points;
+        F.w_v = float(double(mix->mix_beta) / virtual_points);
+        F.w_s = float((1.0 - double(mix->mix_beta)) / points);
         F.mean_parts = mix->mean_parts;
     }
     A.S = make_rowset(d, b);

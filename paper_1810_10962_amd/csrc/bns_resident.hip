@@ -257,12 +257,12 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_forward_kernel(Reside
         block_total(d1, d2, red);
         team_publish(F, read_stamp(F, words), team * F.T, j, it, float(d1), float(d2));
         const bool arrived = gather(F, words, team * F.T, it, d1, d2, team_lds, bc);
-        const double m1 = d1 / F.s;
+        const double m1 = d1 * F.inv_s64;
         const double mean = double(pivot) + m1;
-        double var = d2 / F.s - m1 * m1;
+        double var = d2 * F.inv_s64 - m1 * m1;
         if (!(var >= 0.0)) var = (var != var) ? var : 0.0;  // clamp rounding; keep NaN visible
         const float mu = float(mean);
-        const float r = float(1.0 / sqrt(var + double(F.eps)));
+        const float r = float(inv_sqrt(var + double(F.eps)));
         if (j == 0 && threadIdx.x == 0) {
             F.save_mean[c] = mu;
             F.save_invstd[c] = r;
@@ -560,16 +560,18 @@ hipError_t launch_resident(const Dims& d, const IndexParams& ip, bool backward, 
     F.mute = g_tuning.test_mute_exchange;
     F.eps = eps;
     F.momentum = momentum;
-    F.s = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
-    F.inv_s = float(1.0 / F.s);
-    F.s_v = 1.0;
+    const double points = double(b.n_cnt) * double(b.h_cnt) * double(b.w_cnt);
+    F.inv_s64 = 1.0 / points;
+    F.inv_s = float(F.inv_s64);
+    F.inv_s_v = 1.0;
     A.v_len = 0;
     if (mix) {
         F.n_v = mix->n_v;
         F.mix_beta = mix->mix_beta;
-        F.s_v = double(mix->n_v) * double(d.HW);
-        F.w_v = float(double(mix->mix_beta) / F.s_v);
-        F.w_s = float((1.0 - double(mix->mix_beta)) / F.s);
+        const double virtual_points = double(mix->n_v) * double(d.HW);
+        F.inv_s_v = 1.0 / virtual_points;
+        F.w_v = float(double(mix->mix_beta) / virtual_points);
+        F.w_s = float((1.0 - double(mix->mix_beta)) / points);
         F.mean_parts = mix->mean_parts;
         A.v_len = uint32_t(uint64_t(mix->n_v) * stride);
     }
