@@ -27,8 +27,8 @@ inline FastDiv make_fastdiv(uint32_t d) {  // host; d >= 1
     return f;
 }
 
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
-    return (__umulhi(n, f.mul) + n) >> f.shift;
+__host__ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
+    return (uint32_t((uint64_t(n) * f.mul) >> 32) + n) >> f.shift;
 }
 
 // 1 / sqrt(x) in fp64, within two units in the last place: the hardware's estimate (some 23 bits) and one step of third order,

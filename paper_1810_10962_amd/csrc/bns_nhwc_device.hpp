@@ -34,7 +34,7 @@ __device__ __forceinline__ float coarse(float p) { return __uint_as_float(__floa
 // averaging out.  So the rows of one unrolled iteration are added in fp32 and each group's sum goes
 // into an fp64 accumulator (one fp64 add per group and channel: far below the fp64 rate).
 
-__device__ __forceinline__ uint32_t sampled_row(const RowSet& s, uint32_t i) {
+__host__ __device__ __forceinline__ uint32_t sampled_row(const RowSet& s, uint32_t i) {
     const uint32_t n = fdiv(i, s.patch_div);
     const uint32_t r = i - n * s.patch_div.d;
     const uint32_t ph = fdiv(r, s.pw_div);
