@@ -54,12 +54,13 @@ namespace {
 // 7x7 patch + 2 virtual samples: forward 34 -> 29.7 us, a few registers spilled included).
 template <typename T, int V, int KMAX, int NT, int PATCH, bool MIXED>
 __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
+    touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
     __shared__ float red[2 * (NT / kWave)];
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ double bc[2];
     __shared__ uint32_t words[3];                           // launch stamp, flags of the exchanges
-    const int team = blockIdx.x / A.T;
+    const int team = int(fdiv(blockIdx.x, A.team_div));
     if (team >= A.num_teams) return;                       // blocks beyond the last whole team
     const int j = blockIdx.x - team * A.T;
     const uint32_t hwv = A.hwv_div.d;
@@ -342,12 +343,13 @@ __global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) voi
 // every element), vectors that touch the box to the sampled real set (w_s, centre E_s, masked by the box).
 template <typename T, int V, int KMAX, int NT, bool KEEPX, bool MIXED>
 __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void fused_backward_kernel(FusedArgs A) {
+    touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
     __shared__ float red[2 * (NT / kWave)];
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ double bc[2];
     __shared__ uint32_t words[3];                           // launch stamp, flags of the exchanges
-    const int team = blockIdx.x / A.T;
+    const int team = int(fdiv(blockIdx.x, A.team_div));
     if (team >= A.num_teams) return;
     const int j = blockIdx.x - team * A.T;
     const uint32_t hwv = A.hwv_div.d;
@@ -1134,6 +1136,7 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     A.c0 = c0;
     A.cg = cg;
     A.T = bestT;
+    A.team_div = make_fastdiv(uint32_t(bestT));
     A.num_teams = best_blocks / bestT;
     if (A.num_teams > cg) A.num_teams = cg;
     // A team of one exchanges nothing and needs no slots.  The others: two sets of a pair per block, four in the forward pass

@@ -157,6 +157,7 @@ struct FusedArgs {
     int32_t C, W, HW;
     int32_t c0, cg;
     int32_t T, num_teams;
+    FastDiv team_div;           // blocks of a team (T; not in the N x H x W x C kernels)
     uint32_t tot;   // vectors per channel: N * HW / V
     uint32_t s_cnt; // |S| per channel
     // "VDN + sampling" (Eq. 4), the MIXED flavours: samples [0, n_v) are the virtual set, `ip` describes the

@@ -268,7 +268,8 @@ __global__ __launch_bounds__(NT, 4) void fused_backward_pipe_kernel(FusedArgs A)
     __shared__ float red[2 * (NT / kWave)];
     __shared__ float team_lds[2 * kPipeMaxTeam];
     __shared__ uint32_t stamp_word[3];
-    const int team = blockIdx.x / A.T;                     // the grid is exactly num_teams * T blocks
+    touch_arguments<FusedArgs>();
+    const int team = int(fdiv(blockIdx.x, A.team_div));                     // the grid is exactly num_teams * T blocks
     const int j = blockIdx.x - team * A.T;
     const P p(A, j);
 

@@ -168,6 +168,7 @@ constexpr int group_waves(int nt, int vectors, bool mixed) {
 
 template <typename T, int V, int K, int NT, bool MIXED>
 __global__ __launch_bounds__(NT, group_waves(NT, K, MIXED)) void grouped_forward_kernel(GroupArgs A) {
+    touch_arguments<GroupArgs>();
     typedef ElemVec<T, V> EV;
     __shared__ float4 part[(MIXED ? 2 : 1) * NT];
     __shared__ float4 consts[kGroupMaxChannels];
@@ -297,6 +298,7 @@ __global__ __launch_bounds__(NT, group_waves(NT, K, MIXED)) void grouped_forward
 
 template <typename T, int V, int K, int NT, bool MIXED>
 __global__ __launch_bounds__(NT, group_waves(NT, 2 * K, MIXED)) void grouped_backward_kernel(GroupArgs A) {
+    touch_arguments<GroupArgs>();
     typedef ElemVec<T, V> EV;
     __shared__ float4 part[NT];
     __shared__ float4 consts[(MIXED ? 2 : 1) * kGroupMaxChannels];

@@ -322,6 +322,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
     __shared__ float piv[(MIXED ? 2 : 1) * kRowMaxTile];
     __shared__ float4 consts[kRowMaxTile];
     __shared__ uint32_t words[3], lost[kRowMaxTile];
+    touch_arguments<RowArgs>();
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
     const T* x = static_cast<const T*>(F.x);
@@ -655,6 +656,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
     __shared__ pair_t part[kRowThreads];
     __shared__ float4 consts[(MIXED ? 2 : 1) * kRowMaxTile];
     __shared__ uint32_t words[3];
+    touch_arguments<RowArgs>();
     const FusedArgs& F = A.f;
     const RowLane l = row_lane<V>(A);
     const T* x = static_cast<const T*>(F.x);

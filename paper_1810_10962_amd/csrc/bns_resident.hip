@@ -205,9 +205,10 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_forward_kernel(Reside
     __shared__ double red[2 * kResWaves], bc[2];
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ uint32_t words[3];
+    touch_arguments<ResidentArgs>();
     const FusedArgs& F = A.f;
     Walker<T, V, PATCH> at(A);
-    const int team = int(blockIdx.x) / F.T, j = int(blockIdx.x) - team * F.T;
+    const int team = int(fdiv(blockIdx.x, F.team_div)), j = int(blockIdx.x) - team * F.T;
     const T* x = static_cast<const T*>(F.x);
     T* y = static_cast<T*>(F.out);
     const unsigned long long state = stamp_request(F);
@@ -299,9 +300,10 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_backward_kernel(Resid
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ float consts[2][2];
     __shared__ uint32_t words[3];
+    touch_arguments<ResidentArgs>();
     const FusedArgs& F = A.f;
     Walker<T, V, PATCH> at(A);
-    const int team = int(blockIdx.x) / F.T, j = int(blockIdx.x) - team * F.T;
+    const int team = int(fdiv(blockIdx.x, F.team_div)), j = int(blockIdx.x) - team * F.T;
     const T* x = static_cast<const T*>(F.x);
     const T* dy = static_cast<const T*>(F.dy);
     T* dx = static_cast<T*>(F.out);
@@ -551,6 +553,7 @@ hipError_t launch_resident(const Dims& d, const IndexParams& ip, bool backward, 
     F.HW = d.HW;
     F.cg = d.C;
     F.T = int32_t(T);
+    F.team_div = make_fastdiv(uint32_t(T));
     F.num_teams = int32_t(teams);
     F.tot = uint32_t(tot);
     F.stamp_advance = uint32_t(rounds) + 1u;

@@ -69,6 +69,52 @@ def test_rows_per_thread(rounds, dtype):
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{rounds} rows per thread {dtype} {mkw}", inp=inp)
 
 
+@pytest.mark.parametrize("C_,lanes,members", [
+    (8, 2, 33),                 # 64 threads per channel, one member each, as many as there are rows of 256
+    (32, 8, 15),                # 16 threads per channel: one member each, no multiple of eight
+    (128, 32, 31),              # four threads per channel: eight members each, all polled at once
+    (128, 32, 33),              # nine each: five at a time
+    (128, 32, 70),              # eighteen each: six at a time
+], ids=str)
+def test_members_of_a_tile(C_, lanes, members):
+    """Blocks that share a tile's rows: how many of them a thread polls, and what is left over."""
+    rows = members * 2 * (512 // lanes) - 5                 # two rows per thread
+    for i, mkw in enumerate((dict(mode=FULL), dict(mode=FS, patch_h=1, patch_w=5, n_v=1))):
+        wl = Workload(name="members", N=3, C=C_, H=1, W=rows // 3, dtype="f32", layout="nhwc", data_seed=70 + i, sampling_seed=3,
+                      layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch, {members} members {wl.shape} {mkw}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": lanes}, lambda: bns.run_workload(wl, inp))
+        assert _paths() == (2, 2)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"{members} members {mkw}", inp=inp)
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("path", [0, 1], ids=["default", "streaming"])
+def test_inverse_deviation_at_its_ends(layout, path):
+    """1 / sqrt(Var + eps): a constant channel without and with eps, a spread near the ends of fp32, an infinity."""
+    N, C_, H, W = 4, 8, 9, 9
+    dev, scale = torch.device("cuda:0"), [0.0, 0.0, 1e-18, 1e18, 1.0, 3e-5, 1e4, 1.0]
+    z = torch.randn(N, C_, H, W, generator=torch.Generator().manual_seed(7), dtype=torch.float64)
+    x = (z * torch.tensor(scale, dtype=torch.float64)[None, :, None, None]).float()
+    x[0, 7, 0, 0] = float("inf")
+    stored = (x.permute(0, 2, 3, 1) if layout == "nhwc" else x).contiguous().to(dev)
+    shape, spec = bns.make_shape(N, C_, H, W, "f32", layout), bns.make_spec(FULL)
+    out = lambda: torch.empty(C_, device=dev)               # noqa: E731
+    ws = torch.zeros(bns.bns_workspace_bytes(shape, spec), dtype=torch.uint8, device=dev)
+    for eps in (0.0, 1e-5):
+        mean, invstd = out(), out()
+        _with({"path": path}, lambda: bns.bns_forward(shape, spec, 1, stored, torch.ones(C_, device=dev), torch.zeros(C_, device=dev),
+                                                      eps, 0.1, torch.empty_like(stored), mean, invstd, None, None, ws))
+        got, d = invstd.cpu().double(), x.double()
+        want = 1.0 / torch.sqrt(d.var(dim=(0, 2, 3), unbiased=False) + float(np.float32(eps)))
+        print(f"[gpu-case] inverse deviation {layout} path {path} eps {eps}: {got.tolist()}", flush=True)
+        assert torch.equal(got[:2], want[:2].float().double())                  # (infinity without eps)
+        # a single-precision sum of 324 squares is off by no more than 324 * 2^-24, its square root by half of that
+        assert ((got - want) / want)[2:7].abs().max() < 324 * 2.0 ** -24
+        assert torch.isnan(got[7])
+
+
 @pytest.mark.parametrize("shape,dtype,want", [
     ((13, 137, 7, 7), "bf16", (3, 1)),          # ragged rows, 175 KB: not in waiting kernels
     ((30, 137, 12, 12), "bf16", (2, 2)),        # the same rows, 1.2 MB
