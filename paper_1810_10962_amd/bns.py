@@ -1,4 +1,5 @@
-"""ctypes binding of libbns.so: same names as include/bns.h, argument marshalling only.
+"""Binding of libbns.so: same names as include/bns.h, argument marshalling only (by ctypes; the calls that every layer and step
+makes through the extension _bnscall).
 
 Tensors are torch tensors on the GPU (PyTorch supplies device memory and streams);
 their ``data_ptr()`` and the current HIP stream are handed to the C ABI.  Every step of
@@ -8,6 +9,7 @@ library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 import re
 
@@ -15,6 +17,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbns.so")
+CALL_PATH = os.path.join(_HERE, "_bnscall.so")      # csrc/bns_call.cpp
 HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "bns.h")
 
 BNS_OK, BNS_EINVAL, BNS_EUNSUPPORTED, BNS_EWORKSPACE, BNS_EDEVICE = range(5)
@@ -45,7 +48,7 @@ class BnsError(RuntimeError):
         super().__init__(f"{where}: {msg}")
 
 
-_lib = None
+_lib = _call = None
 _P = C.c_void_p
 _SHP, _SPC = C.POINTER(bns_shape), C.POINTER(bns_spec)
 _PROTOS = {
@@ -81,9 +84,10 @@ def load(reload: bool = False):
     global _lib
     if _lib is not None and not reload:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(f"{LIB_PATH} not found: build it with `python __graft_entry__.py` "
-                          "(there is no CPU fallback)")
+    for path in (LIB_PATH, CALL_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} not found: build it with `python __graft_entry__.py` "
+                              "(there is no CPU fallback)")
     # PyTorch ships a HIP runtime of its own.  The device memory and streams this binding hands to the library
     # come from it, so it has to be the one runtime in the process: loaded before libbns.so, whose dependency
     # on libamdhip64 then resolves to it.  (The other order puts two runtimes side by side; launches then fail
@@ -94,7 +98,13 @@ def load(reload: bool = False):
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
-    _lib = lib
+    global _call
+    spec = importlib.util.spec_from_file_location("_bnscall", CALL_PATH)
+    call = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(call)
+    call.bind(bns_shape, bns_spec, *(C.cast(getattr(lib, "bns_" + name), C.c_void_p).value
+                                     for name in ("forward", "backward", "forward_mixed", "backward_mixed", "inference")))
+    _lib, _call = lib, call
     # The current stream of a device as an integer: torch's own accessor where it has one, a tenth of the time of
     # building a Stream object (1.2 us of a call whose kernels take 4).
     global _raw_stream
@@ -124,8 +134,8 @@ def missing_symbols():
 # marshalling helpers
 # --------------------------------------------------------------------------------------
 # The prototypes in _PROTOS convert Python integers and floats themselves, so the calls below hand over plain values:
-# building a ctypes object for each argument took half of the 8.5 us that a call took on the host (now 4.7 us, 4 of them
-# in the library and the launch).
+# building a ctypes object for each argument took half of the 8.5 us that a call took on the host, ctypes itself another
+# 1.5 of 5.1 in the calls that now go through _bnscall, which adds 0.8 to the library and the launch.
 _raw_stream = None
 
 
@@ -189,19 +199,23 @@ def bns_workspace_bytes(shape: bns_shape, spec: bns_spec) -> int:
     return int(load().bns_workspace_bytes(C.byref(shape), C.byref(spec)))
 
 
+def _calls():
+    if _call is None:
+        load()
+    return _call
+
+
 def bns_forward(shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
                 running_mean, running_var, workspace):
-    _check(load().bns_forward(C.byref(shape), C.byref(spec), seed, _ptr(x), _ptr(gamma), _ptr(beta),
-                              eps, momentum, _ptr(y), _ptr(save_mean), _ptr(save_invstd),
-                              _ptr(running_mean), _ptr(running_var), _ptr(workspace),
-                              workspace.nbytes, _stream(x)), "bns_forward")
+    status = _calls().forward(shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
+                              running_mean, running_var, workspace, workspace.nbytes, _stream(x))
+    _check(status, "bns_forward")
 
 
 def bns_backward(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, workspace):
-    _check(load().bns_backward(C.byref(shape), C.byref(spec), seed, _ptr(x), _ptr(dy), _ptr(gamma),
-                               _ptr(save_mean), _ptr(save_invstd), _ptr(dx), _ptr(dgamma), _ptr(dbeta),
-                               _ptr(workspace), workspace.nbytes,
-                               _stream(x)), "bns_backward")
+    status = _calls().backward(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, workspace,
+                               workspace.nbytes, _stream(x))
+    _check(status, "bns_backward")
 
 
 def bns_backward_builtin_workspace(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta):
@@ -261,26 +275,22 @@ def bns_sample_index_mixed(shape: bns_shape, spec: bns_spec, seed: int, n_v: int
 
 def bns_forward_mixed(shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
                       save_mean_parts, running_mean, running_var, workspace):
-    _check(load().bns_forward_mixed(C.byref(shape), C.byref(spec), seed, n_v,
-                                    mix_beta, _ptr(x), _ptr(gamma), _ptr(beta), eps,
-                                    momentum, _ptr(y), _ptr(save_mean), _ptr(save_invstd),
-                                    _ptr(save_mean_parts), _ptr(running_mean), _ptr(running_var), _ptr(workspace),
-                                    workspace.nbytes, _stream(x)),
-           "bns_forward_mixed")
+    status = _calls().forward_mixed(shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y, save_mean,
+                                    save_invstd, save_mean_parts, running_mean, running_var, workspace,
+                                    workspace.nbytes, _stream(x))
+    _check(status, "bns_forward_mixed")
 
 
 def bns_backward_mixed(shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean, save_invstd, save_mean_parts,
                        dx, dgamma, dbeta, workspace):
-    _check(load().bns_backward_mixed(C.byref(shape), C.byref(spec), seed, n_v,
-                                     mix_beta, _ptr(x), _ptr(dy), _ptr(gamma), _ptr(save_mean),
-                                     _ptr(save_invstd), _ptr(save_mean_parts), _ptr(dx), _ptr(dgamma), _ptr(dbeta),
-                                     _ptr(workspace), workspace.nbytes,
-                                     _stream(x)), "bns_backward_mixed")
+    status = _calls().backward_mixed(shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean, save_invstd,
+                                     save_mean_parts, dx, dgamma, dbeta, workspace, workspace.nbytes, _stream(x))
+    _check(status, "bns_backward_mixed")
 
 
 def bns_inference(shape, x, gamma, beta, running_mean, running_var, eps, y):
-    _check(load().bns_inference(C.byref(shape), _ptr(x), _ptr(gamma), _ptr(beta), _ptr(running_mean),
-                                _ptr(running_var), eps, _ptr(y), _stream(x)), "bns_inference")
+    status = _calls().inference(shape, x, gamma, beta, running_mean, running_var, eps, y, _stream(x))
+    _check(status, "bns_inference")
 
 
 def bns_moving_average_weight(iteration: int, alpha: float) -> float:
