@@ -16,6 +16,7 @@ struct RowSet {                 // the rows of S: sampled row i -> (n, ph, pw) -
     uint32_t rows;              // n_cnt * h_cnt * w_cnt
     uint32_t pivot_rows;        // min(kPivotRows, rows)
     float inv_pivot_rows;
+    double inv_rows;            // 1 / rows
     bool contiguous;            // sampled row i = sampled row 0 + i
 };
 
@@ -67,6 +68,7 @@ inline RowSet make_rowset(const Dims& d, const bns_box& b) {
     s.rows = uint32_t(b.n_cnt) * uint32_t(b.h_cnt) * uint32_t(b.w_cnt);
     s.pivot_rows = s.rows < uint32_t(kPivotRows) ? s.rows : uint32_t(kPivotRows);
     s.inv_pivot_rows = 1.0f / float(s.pivot_rows);
+    s.inv_rows = 1.0 / double(s.rows);
     s.contiguous = (b.w_cnt == d.W && (b.h_cnt == d.H || b.n_cnt == 1)) || (b.n_cnt == 1 && b.h_cnt == 1);
     return s;
 }
