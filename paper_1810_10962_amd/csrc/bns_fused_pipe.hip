@@ -22,32 +22,12 @@ namespace {
 
 constexpr int kPipeMaxTeam = 128;   // members of a team of the pipelined kernel (its exchange buffer is sized for this)
 
-// Sum over the 64 lanes of a wave, returned as a wave-uniform value.  Inclusive scan with data-parallel-primitive
-// moves (shifts of 1, 2, 4, 8 lanes inside each row of 16, then the last lane of row 0 / row 2 broadcast into the
-// next row, then lane 31 into the upper half), after which lane 63 holds the total.  Unlike a butterfly of
-// cross-lane shuffles this needs no lane-index registers, which matter in a kernel that lives on its register
-// budget; the order of the additions is fixed, so results are reproducible.
-__device__ __forceinline__ float wave_total(float v) {
-    auto shifted = [](float x, auto ctrl, auto row_mask) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
-                                                                    decltype(row_mask)::value, 0xf, true));
-    };
-    using std::integral_constant;
-    v += shifted(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr:1
-    v += shifted(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});   // row_shr:2
-    v += shifted(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});   // row_shr:4
-    v += shifted(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});   // row_shr:8
-    v += shifted(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1, 3
-    v += shifted(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2, 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
 // Block-wide sum of (a, b) over NT threads, returned to every thread: one value per wave through LDS, added in
 // wave order by every thread.
 template <int NT>
 __device__ __forceinline__ void block_total2(float& a, float& b, float* red) {
-    a = wave_total(a);
-    b = wave_total(b);
+    a = wave_sum(a);
+    b = wave_sum(b);
     constexpr int nw = NT / kWave;
     if (nw > 1) {
         const int wave = threadIdx.x / kWave;
