@@ -53,7 +53,7 @@ namespace {
 // registers; the compiler is told so, because left alone it takes 150 and the second block is gone (130x128x28x28,
 // 7x7 patch + 2 virtual samples: forward 34 -> 29.7 us, a few registers spilled included).
 template <typename T, int V, int KMAX, int NT, int PATCH, bool MIXED>
-__global__ __launch_bounds__(NT, (MIXED && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
+__global__ __launch_bounds__(NT, ((MIXED || PATCH == 1) && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
     touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
     __shared__ float red[2 * (NT / kWave)];
@@ -803,19 +803,19 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     DeviceInfo& di = *dip;
     if (!di.coop || di.cus <= 0) return hipErrorNotSupported;
 
-    // Planes that are no whole number of vectors: element-aligned vectors, except in channels of up to 2048 elements, which
+    // Planes that are no whole number of vectors: element-aligned vectors, except backward in channels of up to 2048 elements, which
     // hardly fill the threads of a block with one element each.  What a vector costs there -- its offset within the plane, the
-    // elements it shares -- is more than the accesses it saves: medians over the tensors of a sweep, vectors against elements,
-    // 0.88 of the speed backward (30x16x9x9 bf16, a patch, 7.2 against 5.6 us) and 0.97 forward (4x226x5x5 bf16 5.2 against 4.5 us);
-    // forward with a patch, whose elements are read on their own, 1.03.  Eq. 4 has no kernels with one element per access.
+    // elements it shares -- is more than the accesses it saves: over the tensors of a sweep, vectors against elements,
+    // 0.98 of the speed (30x16x9x9 bf16, a patch, 7.2 against 5.6 us); forward it is not, 1.11 (76 tensors; 5x1920x13x13 f32 14.5 -> 5.7).
+    // Eq. 4 has no kernels with one element per access.
     // Whole planes in fp32 with more channels than (512, 8) blocks of vectors fit at once: up to 4096 elements, whose (512, 8) blocks
-    // of elements need fewer registers (2x1188x43x42 backward 14.2 against 19.1 us, 8x656x21x21 forward 8.5 against 9.4; where those do
-    // not fit at once either, forward, vectors: 11x1549x17x17 12.1 against 27.6).
+    // of elements need fewer registers (2x1188x43x42 backward 14.2 against 19.1 us).
     const int64_t channel = int64_t(d.N) * d.HW;
     const bool whole = ip.shared.h_cnt * ip.shared.w_cnt == d.HW;
-    const bool crowded = d.dtype == BNS_F32 && whole && cg > 2 * di.cus && (backward || cg <= 3 * di.cus);
-    const bool odd = fused_odd(d) && (mix || opt_variant != 0 || (!backward && !whole) || channel > (crowded ? 4096 : 2048));
+    const bool crowded = d.dtype == BNS_F32 && whole && cg > 2 * di.cus;
+    const bool odd = fused_odd(d) && (mix || opt_variant != 0 || !backward || channel > (crowded ? 4096 : 2048));
     const int vec = odd ? stream_vec(d) : d.vec;
+    const bool wide = vec == (d.dtype == BNS_F32 ? 4 : 8);
     const uint32_t hwv = uint32_t((d.HW + vec - 1) / vec);
     const uint32_t tot = uint32_t(d.N) * hwv;
     const int combo = combo_index(d, odd);
@@ -826,7 +826,13 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     //  * a team of T blocks needs T * nt * kmax >= vectors per channel; T is then widened so that
     //    every block has work, and nudged (up to 2x) to the T that minimises rounds x vectors per
     //    thread, i.e. that leaves no half-empty last round;
-    //  * candidate A = fewest rounds, then no exchange (T = 1), then the smallest variant;
+    //  * candidate A = fewest rounds, then no exchange (T = 1), then teams of (512, 8) blocks if there is one for every second compute
+    //    unit, then the smallest variant.  Small blocks make large teams: over 1400 drawn layers, each with every variant, teams
+    //    of (64, 1), (128, 2), (256, 4) and (512, 8) blocks in one round took 1.7, 1.45, 1.24 and 1.06 of the time of the fastest kernel forward, 1.6,
+    //    1.5, 1.35 and 1.12 backward (10x96x70x70 f32 10.1 / 12.4 -> 9.7 / 10.3 us, 34x64x23x20 bf16 9.7 / 10.2 -> 6.9 / 7.5).  With fewer
+    //    (512, 8) blocks most of the device has nothing to do: 9x16x64x64 bf16 5.9 / 7.5 against 6.6 / 11.0.  Teams of small blocks, more
+    //    than four of them to a compute unit, count as twice the rounds: 48x816x10x10 bf16, 1632 of 256 threads, 23.3 us against 7.8;
+    //    backward, a block of 32 or 50 vectors per thread that holds its channel comes behind such teams, too;
     //  * backward, and forward with S = everything: (512 threads, 16 vectors), two blocks per
     //    compute unit, beats the bigger variants even when it needs more rounds (two teams per
     //    unit overlap one team's exchange and stores with the other's loads), so A is capped there;
@@ -849,7 +855,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         }
         out->v = -1;
         if (bpc < 0) return hipSuccess;
-        const long blocks = long(di.cus) * bpc;
+        // Forward, patch elements on their own, 128-bit vectors: teams are sized as if a unit took one of these blocks, since what a second one brings is lost
+        // on the larger teams (6x204x33x33 f32 8.9 against 6.1 us, 19x174x57x57 bf16 18.1 against 16.0, 3x256x86x84 f32 12.6 against 10.0).
+        const long blocks = long(di.cus) * (kind == 2 && wide && (v == 4 || (v == 3 && odd)) ? 1 : bpc);
         const int32_t tag = 1 + ((kind * 8 + combo) * 32 + v);
         TeamChoice& known = choice_slot(di, tag, tot, cg);
         if (known.tag == tag && known.tot == tot && known.cg == cg) {
@@ -904,7 +912,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
             const hipError_t pe = plan_for(v, &p);
             if (pe != hipSuccess) return pe;
             if (p.v < 0) continue;
-            const long key = p.rounds * 100000 + (p.T == 1 ? 0 : p.T <= 64 ? 1 : p.T) * 8 + v;
+            const long together = std::min<long>(p.blocks / p.T, cg) * p.T;
+            const bool roomy = kVariants[v].nt == 512 && kVariants[v].kmax == 8 && 2 * together >= di.cus;
+            const bool crowd = p.T > 1 && kVariants[v].nt < 512 && together > 4 * di.cus;
+            const long key = p.rounds * (crowd ? 2 : 1) * 100000 + (p.T == 1 && !(backward && v > 4) ? 0 : p.T == 1 ? 2 : roomy ? 1 : p.T <= 64 ? 2 : 1 + p.T) * 8 + v;
             if (out->v < 0 || key < best_key) {
                 *out = p;
                 best_key = key;
@@ -972,7 +983,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         // 64x1024x16x16 20.5 against 15.0.)
         const bool filled = chosen.v >= 0 && chosen.T == 1 && everything && d.vec == 8 &&
                             8 * uint64_t(tot) >= 7 * uint64_t(kVariants[chosen.v].nt) * uint64_t(kVariants[chosen.v].kmax);
-        if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1)) {
+        // Three and more channels to a compute unit in more than 16 MB: so many small planes are better read as runs (1.4 in the mean of 9
+        // drawn layers; 106x1552x6x6 f32, all 1552 blocks of 256 threads in flight, 20.3 against 13.4 us).
+        const bool many = cg > 2 * di.cus && size_t(d.N) * d.C * d.HW * (d.dtype == BNS_F32 ? 4 : 2) > 16000000;
+        if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1 || many)) {
             const hipError_t ge = grouped();
             if (ge != hipErrorNotSupported) return ge;
         }
@@ -1092,7 +1106,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
                 if ((e = pipe_plan(pipe_alternative_variant(d), &alt)) != hipSuccess) return e;
                 if (alt.kernel && (!pp.kernel || alt.cost < pp.cost)) pp = alt;
             }
-            if (pp.kernel && (pp.rounds < 3 || patch_bf16)) pp.kernel = nullptr;
+            // A channel of fewer than 800 vectors leaves half of such a block idle: of 13 drawn layers the other kernels were ahead on
+            // all (5x1808x4x4 bf16 10.2 against 3.9 us, 10x1808x20x20 bf16 16.5 against 11.7), of 17 with 864 to 3000 on four.
+            if (pp.kernel && (pp.rounds < 3 || patch_bf16 || tot < 800u)) pp.kernel = nullptr;
         }
         if (pp.kernel) {
             pipe_kernel = pp.kernel;

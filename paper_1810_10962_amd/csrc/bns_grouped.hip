@@ -492,8 +492,25 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     if (best_v < 0) return hipErrorNotSupported;
     const int best_g = int(G);
     // A run of more than half a block's threads leaves the others without work (3x700x33x33 f32: 273 of 512 threads, forward
-    // 11.4 us against 8.6 with one element per access).
-    if (opt == 0 && (G * d.HW + V - 1) / V > 256) return hipErrorNotSupported;
+    // 11.4 us against 8.6 with one element per access).  With three and more channels in a run the other kernels have more blocks than
+    // the device holds at once, and this is the faster side backward up to 16 MB (1.2 in the mean of 62 drawn layers, 4x852x17x17 f32 5.8
+    // against 21.6) and forward where planes are whole vectors (asked only when those take several rounds: 1.5 in the mean of 23,
+    // 10x832x28x28 f32 11.0 against 20.1).
+    const int64_t bytes = int64_t(d.N) * d.C * d.HW * (V == 8 ? 2 : 4);
+    const bool crowded = G >= 3 && (backward ? bytes < 16000000 : d.vec > 1);
+    if (opt == 0 && (G * d.HW + V - 1) / V > 256 && !crowded) return hipErrorNotSupported;
+    // Forward, planes that are no whole vectors: a group of fewer than 1536 vectors leaves most of its 512 threads one row or none, and the
+    // kernels of bns_fused.hip, a small block per channel, take 1 / 1.13 (140 layers) and 1 / 1.21 (84) of the time: 62x200x7x7 f32 5.3 against 4.4.
+    // (A patch costs those more: 12x1349x11x9 f32, 1188 vectors, 8.6 against 11.0.)
+    const bool patch = ip.shared.h_cnt != d.H || ip.shared.w_cnt != d.W;
+    // (In more than four channels to a compute unit those no longer fit at once: 26x1632x7x7 f32, 1274 vectors, 7.5 against 8.9.)
+    if (opt == 0 && !backward && d.vec == 1 && d.C <= 4 * cus && int64_t(d.N) * ((G * d.HW + V - 1) / V) < (patch ? 1024 : 1536)) return hipErrorNotSupported;
+    // Backward: a channel of up to 64 vectors fits one wave of its own (1.18 and 1.26 times as fast, 53 and 48 layers, none slower: 2x528x10x10
+    // bf16 5.2 against 3.6; beyond 1.2 MB it is, 12x1952x7x5 bf16 6.2 against 8.5), one of more than 1024 fills a block of 512 threads, which pays
+    // in small tensors (1.05 and 1.10, 68 and 46 layers).
+    const int64_t vectors = int64_t(d.N) * ((d.HW + V - 1) / V);
+    if (opt == 0 && backward && ((vectors <= 64 && bytes <= 1200000) || (vectors > 1024 && bytes <= (d.vec > 1 ? 4000000 : 1800000))))
+        return hipErrorNotSupported;
     // Few channels would fill only part of the device with large blocks; the kernels of bns_fused.hip share a channel (backward, us:
     // 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12 bf16 8.5 against 8.9, 102x64x23x23 bf16 11.0 against 19.3).
     const int blocks = (d.C + best_g - 1) / best_g;
@@ -513,7 +530,6 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // Calls that take 5 us whatever they do: working out the columns costs more there than it saves (forward, us: 8x224x5x5 f32
     // 4.8 against 5.4, 37x96x9x9 bf16 5.7 against 6.3; backward, 6x144x7x7 bf16 5.0 against 5.4).  Just above the lines the median gain is
     // nil: forward, 1.0 to 1.3 MB, 1.00 (30 tensors), backward, bf16, 0.3 to 0.5 MB, 1.06 (66); fp32 below 0.1 MB 1.03 (54).
-    const int64_t bytes = int64_t(d.N) * d.C * d.HW * (V == 8 ? 2 : 4);
     if (opt == 0 && bytes < (backward ? (V == 8 ? 300000 : 0) : 1000000) && !mix) return hipErrorNotSupported;
     const GroupVariant gv = kGroupVariants[best_v];
     const uint32_t lanes = uint32_t((long(best_g) * d.HW + V - 1) / V);

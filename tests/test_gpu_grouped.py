@@ -81,6 +81,33 @@ def test_what_lies_outside_s_does_not_reach_the_statistics(dtype):
         assert np.allclose(got[k][ok], want[k][ok], rtol=tol, atol=tol), k
 
 
+@pytest.mark.parametrize("shape,dtype,mode,want", [
+    ((62, 200, 7, 7), "f32", FULL, (False, True)),         # forward: 806 vectors in a group
+    ((120, 200, 7, 7), "f32", FULL, (True, True)),         # 1560
+    ((12, 600, 11, 9), "f32", FS, (False, True)),          # a patch: 900 vectors in three channels
+    ((14, 600, 11, 9), "f32", FS, (True, True)),           # 1050
+    ((2, 528, 10, 10), "bf16", BS, (False, False)),        # backward: 26 vectors to a channel, one wave each
+    ((8, 528, 10, 10), "bf16", BS, (False, True)),         # 104
+    ((21, 200, 14, 14), "f32", BS, (False, False)),        # 1029 vectors to a channel in 3.3 MB
+    ((26, 200, 14, 14), "f32", BS, (False, True)),         # in 4.1 MB
+    ((4, 852, 17, 17), "f32", NS, (False, True)),          # 289 lanes, but four channels: backward only
+    ((34, 64, 23, 20), "bf16", FULL, (False, False)),      # teams of 512 threads instead of 61 blocks of 64
+    ((9, 16, 40, 40), "bf16", FULL, (False, False)),       # too few channels for them
+    ((6, 130, 33, 33), "f32", FS, (False, False)),         # one block of 512 threads to a channel
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_default_choice_on_both_sides_of_its_lines(shape, dtype, mode, want):
+    """want: whether forward and backward take groups of channels."""
+    N, C_, H, W = shape
+    kw = dict(patch_h=max(1, H // 2), patch_w=max(1, W // 2)) if mode == FS else dict(n_s=1) if mode in (BS, NS) else {}
+    wl = Workload(name="grouped_lines", N=N, C=C_, H=H, W=W, dtype=dtype, mode=mode, data_seed=45, sampling_seed=9, layer_id=3, **kw)
+    inp = workloads.make_inputs(wl)
+    print(f"[gpu-case] grouped or not by default, {shape} {dtype} {mode}", flush=True)
+    res = bns.run_workload(wl, inp)
+    took = bns.bns_get_option("last_fused_forward"), bns.bns_get_option("last_fused_backward")
+    assert (took[0] == 3, took[1] == 4) == want, took
+    assert_parity(res, oracle_reference(wl, inp), wl, what=f"grouped or not {shape} {dtype} {mode}", inp=inp)
+
+
 def test_default_choice_where_the_other_kernels_take_several_rounds():
     """Forward, planes of whole vectors: the planner turns to groups of channels when a channel per block means several
     rounds, and keeps to the other kernels when the groups would, too."""
