@@ -301,18 +301,21 @@ __device__ __forceinline__ typename RawVec<T, V>::raw_t row_load(const T* p) {
     if (NT) return __builtin_nontemporal_load(reinterpret_cast<const elem_t*>(p));
     return *reinterpret_cast<const elem_t*>(p);
 }
-template <typename T, int V>
+// SHARED: part of the lines is written by two blocks.  Stores with the non-temporal hint send their part of a line on to the memory; plain ones
+// wait for the other part in the L2 (see shares_lines).
+template <typename T, int V, bool SHARED>
 __device__ __forceinline__ void row_store(T* p, typename RawVec<T, V>::raw_t r) {
     typedef typename RawVec<T, V>::raw_t raw_t;
     typedef raw_t elem_t __attribute__((aligned(sizeof(T))));
-    __builtin_nontemporal_store(r, reinterpret_cast<elem_t*>(p));
+    if (SHARED) *reinterpret_cast<elem_t*>(p) = r;
+    else __builtin_nontemporal_store(r, reinterpret_cast<elem_t*>(p));
 }
 
 // Forward: Eq. 3 (Eq. 4 if MIXED), Eq. 8, Eq. 1.  A thread keeps K rows in registers and L in LDS; rows beyond are read again.
 // Beyond 16 rows loads are unconditional (past the end the last row is read) and run kAhead rows ahead of the sums: a condition around a load
 // makes every later wait one for all loads, and a thread that issues all of them first finds most of its rows there before it
 // adds the first one up.  FIRST: all loads come first all the same (see rows_first).
-template <typename T, int V, int K, int L, bool MIXED, bool FIRST>
+template <typename T, int V, int K, int L, bool MIXED, bool FIRST, bool SHARED>
 __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowArgs A) {
     typedef RawVec<T, V> RV;
     typedef typename RV::raw_t raw_t;
@@ -609,7 +612,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
             RV::unpack(w, f);
 #pragma unroll
             for (int e = 0; e < V; ++e) f[e] = fmaf(f[e] - mu[e], sc[e], sh[e]);
-            if (at.row < A.M) row_store<T, V>(at_byte(y, at.off), RV::pack(f));
+            if (at.row < A.M) row_store<T, V, SHARED>(at_byte(y, at.off), RV::pack(f));
         };
         Walk w = walk_from(0);
 #pragma unroll
@@ -647,7 +650,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_forward_kernel(RowA
 
 // Backward: the sums of Eq. 5, Eq. 6.  dy stays in registers (K rows) and LDS (L rows); x of the rows of S is read again (KEEPX:
 // stays, too).  Loads as in the forward kernel.
-template <typename T, int V, int K, int L, bool KEEPX, bool MIXED>
+template <typename T, int V, int K, int L, bool KEEPX, bool MIXED, bool SHARED>
 __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(RowArgs A) {
     typedef RawVec<T, V> RV;
     typedef typename RV::raw_t raw_t;
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
 #pragma unroll
                 for (int e = 0; e < V; ++e) f[e] *= ar[e];
             }
-            if (at.row < A.M) row_store<T, V>(at_byte(dx, at.off), RV::pack(f));
+            if (at.row < A.M) row_store<T, V, SHARED>(at_byte(dx, at.off), RV::pack(f));
         };
         auto sampled_here = [&](uint32_t row) { return row < A.M && ((MIXED && row < A.virtual_rows) || in_set(A, 0, row)); };
         Walk w = walk_from(0);
@@ -935,25 +938,31 @@ __global__ __launch_bounds__(kRowThreads, 2) void nhwc_fused_backward_kernel(Row
 // 8.7 streaming; 28x64x6x6 f32, 8 rows: forward 8.1 against 11.9; backward 52x349x4x4 f32, 7 rows, 12.7 against 10.5).
 constexpr int row_solo(int V, bool backward) { return V == 8 ? (backward ? 4 : 5) : (backward ? 4 : 8); }
 
-template <typename T, int V, int I, bool MIXED, bool FIRST>
+template <typename T, int V, int I, bool MIXED, bool FIRST, bool SHARED>
 const void* row_forward() {
     constexpr RowsHeld h = rows_held(V, false, MIXED, I);
-    return reinterpret_cast<const void*>(&nhwc_fused_forward_kernel<T, V, h.regs, FIRST ? 0 : h.park, MIXED, FIRST && (h.regs > kRowKeepX)>);
+    return reinterpret_cast<const void*>(
+        &nhwc_fused_forward_kernel<T, V, h.regs, FIRST ? 0 : h.park, MIXED, FIRST && (h.regs > kRowKeepX), SHARED>);
 }
-template <typename T, int V, int I, bool MIXED>
+template <typename T, int V, int I, bool MIXED, bool SHARED>
 const void* row_backward() {
     constexpr RowsHeld h = rows_held(V, true, MIXED, I);
-    return reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, h.regs, h.park, (h.regs <= kRowKeepX), MIXED>);
+    return reinterpret_cast<const void*>(&nhwc_fused_backward_kernel<T, V, h.regs, h.park, (h.regs <= kRowKeepX), MIXED, SHARED>);
 }
 
 template <typename T, int V>
-const void* row_kernel(int variant, bool backward, bool mixed, bool first) {
+const void* row_kernel(int variant, bool backward, bool mixed, bool first, bool shared) {
+    constexpr bool kTiles = V > 1;                          // (fewer channels than a vector are one tile)
 #define BNS_ROW_CASE(I)                                                                             \
     case I:                                                                                         \
-        return backward ? (mixed ? row_backward<T, V, I, true>() : row_backward<T, V, I, false>())   \
-               : mixed  ? row_forward<T, V, I, true, false>()                                        \
-               : first  ? row_forward<T, V, I, false, (V > 1)>()                                     \
-                        : row_forward<T, V, I, false, false>();
+        return backward ? (mixed    ? row_backward<T, V, I, true, false>()                           \
+                           : shared ? row_backward<T, V, I, false, kTiles>()                         \
+                                    : row_backward<T, V, I, false, false>())                         \
+               : mixed  ? row_forward<T, V, I, true, false, false>()                                 \
+               : shared ? (first ? row_forward<T, V, I, false, kTiles, kTiles>()                     \
+                                 : row_forward<T, V, I, false, false, kTiles>())                     \
+               : first  ? row_forward<T, V, I, false, kTiles, false>()                               \
+                        : row_forward<T, V, I, false, false, false>();
     switch (variant) {
         BNS_ROW_CASE(0)
         BNS_ROW_CASE(1)
@@ -1007,11 +1016,13 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
         // the memory's queues; 1024 pairs are polled in one go (25x382x8x8 bf16 forward, 8 members x 72 channels 9.2, 13 x 128 10.6).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
         // Two rows per thread and no fewer: against four, over 22 drawn layers of up to 4 MB, 1.04 of the speed forward and 1.09 backward, three
-        // 1.02 and 1.04; one 1.03 and 1.09, but 0.89 / 0.92 at 54x144x10x13 bf16.  Larger tensors fill the device with more.
+        // 1.02 and 1.04; one 1.03 and 1.09, but 0.89 / 0.92 at 54x144x10x13 bf16.  Four where more members would make a block read more
+        // than 4096 pairs of sums: 16x48x55x55 bf16, a patch, 256 members 13.7 / 13.7 us, 143 11.6 / 11.9.
         double best = 0.0;
         for (int lanes = want > 0 ? want : 8; lanes <= (want > 0 ? want : 16); lanes += aligned ? 8 : 1) {
             const int tx = lanes_for(lanes), g = groups_for(tx), count = (CV + tx - 1) / tx;
-            const int t = std::min((g + 1) / 2, std::max(1, cus / count));
+            const int two = (g + 1) / 2, few = opt == 1 ? two : std::min(two, 4096 / (tx * V));
+            const int t = std::min(std::max((g + 3) / 4, few), std::max(1, cus / count));
             // what a narrower tile, idle lanes, threads or compute units cost is a share of the time at the memory
             const double use = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads * std::min(1.0, double(count * t) / cus);
             const double moved = double(bytes) * (backward ? 3 : 2), pairs = double(t) * tx * V / 4096.0;
@@ -1156,11 +1167,12 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     A.pitch = uint32_t(d.C) * (d.dtype == BNS_F32 ? 4u : 2u);
     A.keep_x = bytes <= kKeepBytes;
     const bool mixed = mix != nullptr, first = rows_first(rounds, V, backward, mixed, long(A.pitch));
+    const bool shared = shares_lines(tiles, long(A.pitch), long(bytes), backward);
     const int variant = row_variant(rounds, V, backward, mixed);
-    const void* kernel = V == 8               ? row_kernel<bf16_t, 8>(variant, backward, mixed, first)
-                         : V == 4             ? row_kernel<float, 4>(variant, backward, mixed, first)
-                         : d.dtype == BNS_F32 ? row_kernel<float, 1>(variant, backward, mixed, first)
-                                              : row_kernel<bf16_t, 1>(variant, backward, mixed, first);
+    const void* kernel = V == 8               ? row_kernel<bf16_t, 8>(variant, backward, mixed, first, shared)
+                         : V == 4             ? row_kernel<float, 4>(variant, backward, mixed, first, shared)
+                         : d.dtype == BNS_F32 ? row_kernel<float, 1>(variant, backward, mixed, first, shared)
+                                              : row_kernel<bf16_t, 1>(variant, backward, mixed, first, shared);
     *solo = T == 1;
     void* params[] = {&A};
     return launch_waiting(kernel, dim3(uint32_t(tiles) * uint32_t(T)), dim3(kRowThreads), params, T > 1, may_create_event, st);

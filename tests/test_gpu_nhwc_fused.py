@@ -89,6 +89,28 @@ def test_members_of_a_tile(C_, lanes, members):
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{members} members {mkw}", inp=inp)
 
 
+@pytest.mark.parametrize("dtype,C_,rounds", [
+    ("f32", 1250, 3), ("f32", 1250, 13),        # both directions without the hint, x kept and not
+    ("f32", 1250, 19), ("f32", 1252, 45),       # forward: all loads first; rows read twice, whole vectors
+    ("bf16", 2484, 3), ("bf16", 2489, 13), ("bf16", 2489, 20), ("bf16", 2489, 41),     # 41: rows in LDS
+    ("bf16", 2496, 5),                          # rows on 64 bytes: with the hint
+], ids=str)
+def test_lines_shared_between_tiles(dtype, C_, rounds):
+    """Rows that begin on no 64 bytes, in several tiles: blocks of two tiles write parts of one line, with plain stores."""
+    V = 4 if dtype == "f32" else 8
+    tiles = -(-(-(-C_ // V)) // 8)
+    members = torch.cuda.get_device_properties(0).multi_processor_count // tiles
+    rows = 64 * members * (rounds - 1) + 41
+    for i, mkw in enumerate((dict(mode=BS, n_s=1), dict(mode=FS, patch_h=1, patch_w=9))):
+        wl = Workload(name="lines", N=3, C=C_, H=1, W=rows // 3, dtype=dtype, layout="nhwc", data_seed=90 + i, sampling_seed=4,
+                      layer_id=i, **mkw)
+        inp = workloads.make_inputs(wl)
+        print(f"[gpu-case] nhwc single launch, shared lines, {rounds} rows per thread {wl.shape} {dtype} {mkw}", flush=True)
+        res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": 8}, lambda: bns.run_workload(wl, inp))
+        assert _paths() == (2, 2)
+        assert_parity(res, oracle_reference(wl, inp), wl, what=f"shared lines, {rounds} rows {dtype} {mkw}", inp=inp)
+
+
 @pytest.mark.parametrize("layout", ["nchw", "nhwc"])
 @pytest.mark.parametrize("path", [0, 1], ids=["default", "streaming"])
 def test_inverse_deviation_at_its_ends(layout, path):
