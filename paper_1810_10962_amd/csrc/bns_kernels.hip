@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kBlock) void stats_finalize_kernel(
         s1 = double(p.a);
         s2 = double(p.b);
     }
-    // loads that lane 0 needs, issued before the shuffles
+    // loads that lane 0 needs, issued before the sums over the wave
     const bns_box b = box_of_channel(ip, c);
     double pivot = 0.0, rm = 0.0, rv = 0.0;
     if (lane == 0) {
