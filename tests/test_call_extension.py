@@ -1,8 +1,11 @@
 """The extension that marshals the calls of every step (csrc/bns_call.cpp): what the library's functions receive, argument by
-argument, against the values that the binding was given; what it refuses; the exceptions of bad calls."""
+argument, against the values that the binding was given; what is accepted and what is refused, and how, as by ctypes, which the extension
+leaves unusual arguments to."""
 import ctypes as C
 import inspect
+import types
 
+import numpy as np
 import pytest
 
 from paper_1810_10962_amd import bns
@@ -20,9 +23,10 @@ class Tensor:
         return self.address
 
 
-@pytest.fixture
-def received(monkeypatch):
-    """Calls received by stand-ins for the five functions, which answer with the status in `received.status`."""
+@pytest.fixture(params=["extension", "ctypes"])
+def received(request, monkeypatch):
+    """Calls received by stand-ins for the five functions, which answer with the status in `received.status`: through the extension, and
+    with everything left to ctypes."""
     class Calls(list):
         status = 0
     calls = Calls()
@@ -39,8 +43,13 @@ def received(monkeypatch):
     bns.load()
     keep = [stand_in(n) for n in NAMES]
     bns._call.bind(bns.bns_shape, bns.bns_spec, *(C.cast(f, C.c_void_p).value for f in keep))
+    monkeypatch.setattr(bns, "_lib", types.SimpleNamespace(bns_status_string=bns._lib.bns_status_string,
+                                                            **{"bns_" + n: f for n, f in zip(NAMES, keep)}))
+    if request.param == "ctypes":
+        monkeypatch.setattr(bns, "_call", types.SimpleNamespace(**{n: lambda *args: None for n in NAMES}))
     monkeypatch.setattr(bns, "_stream", lambda t: 0x7fff12345678)
     yield calls
+    monkeypatch.undo()
     bns.load(reload=True)
 
 
@@ -81,19 +90,48 @@ def test_arguments_reach_the_library(received, name):
     assert e.value.status == bns.BNS_EWORKSPACE
 
 
+class AsParameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_what_ctypes_converts_is_accepted(received, name):
+    given, _ = _arguments(name)
+    f32 = C.c_float(0.1).value
+    values = {"seed": [(C.c_uint64(2 ** 64 - 3), 2 ** 64 - 3), (AsParameter(7), 7), (True, 1), (np.int64(9), 9)],
+              "n_v": [(C.c_int32(-2), -2), (AsParameter(C.c_int32(3)), 3), (2 ** 32 + 1, 1)],
+              "eps": [(C.c_float(0.1), f32), (AsParameter(0.1), f32), (np.float32(0.1), f32), (np.float64(0.1), f32), (1e300, float("inf"))],
+              "momentum": [(C.c_float(0.1), f32)], "mix_beta": [(C.c_float(0.1), f32)],
+              "x": [(Tensor(None), None), (Tensor(C.c_void_p(4096)), 4096), (Tensor(-16), 2 ** 64 - 16)], "beta": [(None, None)]}
+    for p, pairs in values.items():
+        for i, (value, want) in enumerate(pairs if p in given else []):
+            received.clear()
+            getattr(bns, "bns_" + name)(**{**given, p: value})
+            assert received[0][1][list(given).index(p)] == want, (p, i)
+
+
 @pytest.mark.parametrize("name", NAMES)
 def test_refused_arguments(received, name):
     given, _ = _arguments(name)
-    wrong = {"shape": [None, SPEC, b"0" * 24], "spec": [None, SHAPE], "seed": [1.0, "1", None], "n_v": [2.0, None],
-             "eps": ["1", None], "momentum": [None], "mix_beta": [None], "x": [17, "x"], "y": [object()], "dx": [3.5],
-             "workspace": [None]}
+    bad = C.ArgumentError                                   # (which is no TypeError)
+    wrong = {"shape": [(None, TypeError), (SPEC, bad), (b"0" * 24, TypeError)], "spec": [(None, TypeError), (SHAPE, bad)],
+             "seed": [(1.0, bad), ("1", bad), (None, bad), (C.c_int64(1), bad)], "n_v": [(2.0, bad), (None, bad)],
+             "eps": [("1", bad), (None, bad), (C.c_double(1.0), bad)], "momentum": [(None, bad)], "mix_beta": [(None, bad)],
+             "x": [(17, AttributeError), ("x", AttributeError), (Tensor(1.5), bad)], "y": [(object(), AttributeError)],
+             "dx": [(3.5, AttributeError)], "workspace": [(None, AttributeError)]}
     for p, values in wrong.items():
-        for v in values if p in given else []:
-            with pytest.raises((TypeError, AttributeError)):
-                getattr(bns, "bns_" + name)(**{**given, p: v})
+        for value, kind in values if p in given else []:
+            with pytest.raises(Exception) as e:
+                getattr(bns, "bns_" + name)(**{**given, p: value})
+            assert e.type is kind, (p, value, e.type)
     assert received == []
-    with pytest.raises(TypeError):
-        getattr(bns._call, name)(SHAPE)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_the_extension_leaves_other_numbers_of_arguments_alone(name):
+    bns.load()
+    assert getattr(bns._call, name)(SHAPE) is None
 
 
 class Broken(Tensor):
