@@ -1,5 +1,5 @@
 """Binding of libbns.so: same names as include/bns.h, argument marshalling only (by ctypes; the calls that every layer and step
-makes through the extension _bnscall, where the arguments are plain).
+makes through the extension _bnscall, where there is one for this interpreter and the arguments are plain).
 
 Tensors are torch tensors on the GPU (PyTorch supplies device memory and streams);
 their ``data_ptr()`` and the current HIP stream are handed to the C ABI.  Every step of
@@ -9,6 +9,7 @@ library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
 import importlib.util
 import os
 import re
@@ -17,7 +18,8 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbns.so")
-CALL_PATH = os.path.join(_HERE, "_bnscall.so")      # csrc/bns_call.cpp
+# csrc/bns_call.cpp.  The suffix names the interpreter that it was built for; another one does not find it and marshals through ctypes.
+CALL_PATH = os.path.join(_HERE, "_bnscall" + importlib.machinery.EXTENSION_SUFFIXES[0])
 HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "bns.h")
 
 BNS_OK, BNS_EINVAL, BNS_EUNSUPPORTED, BNS_EWORKSPACE, BNS_EDEVICE = range(5)
@@ -79,15 +81,25 @@ _PROTOS = {
 }
 
 
+_EVERY_STEP = ("forward", "backward", "forward_mixed", "backward_mixed", "inference")
+
+
+class _NoExtension:
+    """What _bnscall is to an interpreter that has none: every call is left to ctypes."""
+
+
+for _name in _EVERY_STEP:
+    setattr(_NoExtension, _name, staticmethod(lambda *args: None))
+
+
 def load(reload: bool = False):
     """Load libbns.so (built by ``__graft_entry__.build()``); raises if it is not there."""
     global _lib
     if _lib is not None and not reload:
         return _lib
-    for path in (LIB_PATH, CALL_PATH):
-        if not os.path.exists(path):
-            raise ImportError(f"{path} not found: build it with `python __graft_entry__.py` "
-                              "(there is no CPU fallback)")
+    if not os.path.exists(LIB_PATH):
+        raise ImportError(f"{LIB_PATH} not found: build it with `python __graft_entry__.py` "
+                          "(there is no CPU fallback)")
     # PyTorch ships a HIP runtime of its own.  The device memory and streams this binding hands to the library
     # come from it, so it has to be the one runtime in the process: loaded before libbns.so, whose dependency
     # on libamdhip64 then resolves to it.  (The other order puts two runtimes side by side; launches then fail
@@ -98,17 +110,17 @@ def load(reload: bool = False):
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
-    global _call
-    spec = importlib.util.spec_from_file_location("_bnscall", CALL_PATH)
-    call = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(call)
-    call.bind(bns_shape, bns_spec, *(C.cast(getattr(lib, "bns_" + name), C.c_void_p).value
-                                     for name in ("forward", "backward", "forward_mixed", "backward_mixed", "inference")))
-    _lib, _call = lib, call
+    global _call, _raw_stream
+    call = _NoExtension
+    if os.path.exists(CALL_PATH):
+        spec = importlib.util.spec_from_file_location("_bnscall", CALL_PATH)
+        call = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(call)
+        call.bind(bns_shape, bns_spec, *(C.cast(getattr(lib, "bns_" + name), C.c_void_p).value for name in _EVERY_STEP))
     # The current stream of a device as an integer: torch's own accessor where it has one, a tenth of the time of
     # building a Stream object (1.2 us of a call whose kernels take 4).
-    global _raw_stream
     _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _lib, _call = lib, call
     return lib
 
 

@@ -2,7 +2,11 @@
 argument, against the values that the binding was given; what is accepted and what is refused, and how, as by ctypes, which the extension
 leaves unusual arguments to."""
 import ctypes as C
+import importlib.machinery
 import inspect
+import os
+import subprocess
+import sys
 import types
 
 import numpy as np
@@ -144,3 +148,23 @@ def test_exceptions_of_a_tensor_pass_through(received):
     with pytest.raises(RuntimeError, match="no storage"):
         bns.bns_inference(**{**given, "gamma": Broken(0)})
     assert received == []
+
+
+def test_another_interpreter_marshals_through_ctypes():
+    """The extension carries the interpreter's tag; one that finds none of its own loads the library all the same."""
+    assert os.path.basename(bns.CALL_PATH) == "_bnscall" + importlib.machinery.EXTENSION_SUFFIXES[0]
+    assert "cpython-3" in bns.CALL_PATH
+    code = ("import importlib.machinery as m; m.EXTENSION_SUFFIXES[0] = '.cpython-399-none.so'\n"
+            "from paper_1810_10962_amd import bns\n"
+            "assert bns.bns_status_string(1) and bns.bns_moving_average_weight(1, 0.5) == 1.0\n"
+            "assert bns._call.__name__ == '_NoExtension'\n"
+            "class T:\n"
+            "    nbytes = 0\n"
+            "    def data_ptr(self): return None\n"
+            "bns._stream = lambda t: 0\n"
+            "try: bns.bns_inference(bns.make_shape(2, 3, 4, 5), T(), T(), T(), T(), T(), 1e-5, T())\n"
+            "except bns.BnsError as e: assert e.status == bns.BNS_EINVAL\n"
+            "else: raise SystemExit('null pointers were taken')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
