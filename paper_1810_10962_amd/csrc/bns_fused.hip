@@ -56,7 +56,7 @@ template <typename T, int V, int KMAX, int NT, int PATCH, bool MIXED>
 __global__ __launch_bounds__(NT, ((MIXED || PATCH == 1) && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
     touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
-    __shared__ float red[2 * (NT / kWave)];
+    __shared__ double __attribute__((aligned(16))) red[2 * (NT / kWave)];
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ double bc[2];
     __shared__ uint32_t words[3];                           // launch stamp, flags of the exchanges
@@ -260,30 +260,24 @@ __global__ __launch_bounds__(NT, ((MIXED || PATCH == 1) && NT == 512 && KMAX <= 
             }
         }
         if (!kStampFirst && it == 0) stamp_accept(A, stamp_request(A), words);
-        double d1, d2;                                          // (planes with element-aligned vectors only)
-        if constexpr (Odd<T>::value) block_allsum2_wide<NT>(s1, s2, red, d1, d2);
-        else block_allsum2<NT>(s1, s2, red);
+        double d1, d2;
+        block_allsum2<NT>(s1, s2, red, A.T == 1, d1, d2);
         if (NT == kWave) __syncthreads();                       // (one wave: block_allsum2 has no barrier of its own)
         double t1, t2, u1 = 0.0, u2 = 0.0;
         bool arrived;
         if constexpr (MIXED) {
             // both pairs are published before either is waited for: one wait for the team instead of two
             // (130x128x28x28 f32, 7x7 patch + 2 virtual samples: 27.3 -> 25.7 us)
-            team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it, s1, s2);
+            team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it, float(d1), float(d2));
             __syncthreads();                                    // red[] is read by every thread of the first sum
             double w1, w2;
-            if constexpr (Odd<T>::value) block_allsum2_wide<NT>(v1, v2, red, w1, w2);
-            else block_allsum2<NT>(v1, v2, red);
-            team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it + 1u, v1, v2);
-            arrived = team_collect<NT, 4>(A, words, team * A.T, 2u * it, s1, s2, t1, t2, team_lds, bc);
+            block_allsum2<NT>(v1, v2, red, A.T == 1, w1, w2);
+            team_publish<4>(A, read_stamp(A, words), team * A.T, j, 2u * it + 1u, float(w1), float(w2));
+            arrived = team_collect<NT, 4>(A, words, team * A.T, 2u * it, d1, d2, t1, t2, team_lds, bc);
             __syncthreads();                                    // bc[] is read by every thread
-            arrived &= team_collect<NT, 4>(A, words, team * A.T, 2u * it + 1u, v1, v2, u1, u2, team_lds, bc);
+            arrived &= team_collect<NT, 4>(A, words, team * A.T, 2u * it + 1u, w1, w2, u1, u2, team_lds, bc);
         } else {
-            arrived = team_allsum2<NT>(A, words, team * A.T, j, it, s1, s2, t1, t2, team_lds, bc);
-        }
-        if (Odd<T>::value && !MIXED && A.T == 1) {            // (Eq. 4: no registers for them)
-            t1 = d1;
-            t2 = d2;
+            arrived = team_allsum2<NT>(A, words, team * A.T, j, it, d1, d2, t1, t2, team_lds, bc);
         }
 
         // Eq. 3 (every thread computes the same values from the same totals)
@@ -345,7 +339,7 @@ template <typename T, int V, int KMAX, int NT, bool KEEPX, bool MIXED>
 __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void fused_backward_kernel(FusedArgs A) {
     touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
-    __shared__ float red[2 * (NT / kWave)];
+    __shared__ double __attribute__((aligned(16))) red[2 * (NT / kWave)];
     __shared__ float team_lds[2 * kMaxTeam];
     __shared__ double bc[2];
     __shared__ uint32_t words[3];                           // launch stamp, flags of the exchanges
@@ -445,16 +439,11 @@ __global__ __launch_bounds__(NT, (KEEPX && NT == 512 && KMAX <= 8) ? 4 : 1) void
         }
         }
         if (!kStampFirst && it == 0) stamp_accept(A, stamp_request(A), words);
-        double d1, d2;                                          // (planes with element-aligned vectors only)
-        if constexpr (Odd<T>::value) block_allsum2_wide<NT>(s1, s2, red, d1, d2);
-        else block_allsum2<NT>(s1, s2, red);
+        double d1, d2;
+        block_allsum2<NT>(s1, s2, red, A.T == 1, d1, d2);
         if (NT == kWave) __syncthreads();
         double t1, t2;
-        team_allsum2<NT>(A, words, team * A.T, j, it, s1, s2, t1, t2, team_lds, bc);
-        if (Odd<T>::value && A.T == 1) {
-            t1 = d1;
-            t2 = d2;
-        }
+        team_allsum2<NT>(A, words, team * A.T, j, it, d1, d2, t1, t2, team_lds, bc);
 
         const float dbeta = float(t1);
         const float dgamma = float(t2 * double(r));
@@ -984,8 +973,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         const bool filled = chosen.v >= 0 && chosen.T == 1 && everything && d.vec == 8 &&
                             8 * uint64_t(tot) >= 7 * uint64_t(kVariants[chosen.v].nt) * uint64_t(kVariants[chosen.v].kmax);
         // Three and more channels to a compute unit in more than 16 MB: so many small planes are better read as runs (1.4 in the mean of 9
-        // drawn layers; 106x1552x6x6 f32, all 1552 blocks of 256 threads in flight, 20.3 against 13.4 us).
-        const bool many = cg > 2 * di.cus && size_t(d.N) * d.C * d.HW * (d.dtype == BNS_F32 ? 4 : 2) > 16000000;
+        // drawn layers; 106x1552x6x6 f32, all 1552 blocks of 256 threads in flight, 20.3 against 13.4 us).  More than six from 8 MB on (1.1 to 2.0 by
+        // type and mode, 18 layers, two below 1: 26x1584x12x12 bf16 9.5 against 7.8; with four to six 0.85 to 0.92, 24 layers).
+        const size_t tensor = size_t(d.N) * d.C * d.HW * (d.dtype == BNS_F32 ? 4 : 2);
+        const bool many = (cg > 2 * di.cus && tensor > 16000000) || (cg > 6 * di.cus && tensor > 8000000);
         if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1 || many)) {
             const hipError_t ge = grouped();
             if (ge != hipErrorNotSupported) return ge;

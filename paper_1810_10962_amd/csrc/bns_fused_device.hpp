@@ -175,60 +175,50 @@ struct FusedArgs {
     double inv_s64; // 1 / (|S| per channel)
 };
 
-// Block-wide sum of (a, b) over NT threads; result returned to every thread.
-template <int NT>
-__device__ __forceinline__ void block_allsum2(float& a, float& b, float* red) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    constexpr int nw = NT / kWave;
-    if (nw > 1) {
-        const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-        __syncthreads();                       // red[] may still be read from the previous use
-        if (lane == 0) {
-            red[wave] = a;
-            red[nw + wave] = b;
-        }
-        __syncthreads();
-        float sa = red[0], sb = red[nw];
-#pragma unroll
-        for (int w = 1; w < nw; ++w) {
-            sa += red[w];
-            sb += red[nw + w];
-        }
-        a = sa;
-        b = sb;
-    }
+// Sums of a and of b over the 64 lanes of a wave (all of them active): lane 31 gets that of a, lane 63 that of b.  The halves of the wave
+// change places, so that one chain of moves adds both; pairs of lanes in fp32, the rest in fp64.
+__device__ __forceinline__ double wave_sum2(float a, float b) {
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    double d = double(__uint_as_float(w[0]) + __uint_as_float(w[1]));   // lanes 0 to 31: of a, the others: of b
+    d += dpp_or_zero<0x111, 0xf>(d);    // row_shr:1
+    d += dpp_or_zero<0x112, 0xf>(d);    // row_shr:2
+    d += dpp_or_zero<0x114, 0xf>(d);    // row_shr:4
+    d += dpp_or_zero<0x118, 0xf>(d);    // row_shr:8
+    d += dpp_or_zero<0x142, 0xa>(d);    // row_bcast:15 into rows 1, 3
+    return d;
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+    typedef int pair_t __attribute__((ext_vector_type(2)));
+    pair_t w = __builtin_bit_cast(pair_t, x);
+    w.x = __builtin_amdgcn_readlane(w.x, lane);
+    w.y = __builtin_amdgcn_readlane(w.y, lane);
+    return __builtin_bit_cast(double, w);
 }
 
-// The same with the waves' sums added in fp64; (a, b) = the totals rounded to fp32, (da, db) = as they are.  For planes that are no
-// whole number of vectors: vectors let fewer and larger blocks share a channel than single elements did, so fewer sums meet in
-// the fp64 sum over the team, and the fp32 chain over the waves was felt (error of the mean against 64 bits: 3x16x91x91, a
-// 45x45 patch, 2.8e-8 with single elements, 6.0e-8 with fp32 here, 3.7e-8 now; 9x848x23x23, Batch Sampling, 1.5e-7, 1.2e-7,
-// 5.1e-8; at most 2 % of the time).
+// Block-wide sum of (a, b) over NT threads in fp64; the result is returned to every thread if `all`, else to the first wave.
+// (With fp32 across lanes and waves the few blocks of 512 threads that share a channel lose what many small ones, whose sums meet in fp64,
+// do not: error of the mean against 64 bits, 3x69x72x72 f32 3.4e-8 with teams of 64 threads, 8.7e-8 with (512, 8), 5.4e-8 now; 9x320x11x11 f32
+// 1.1e-7, now 3.4e-8; over 690 drawn layers 0.6 times as large.  The halved chain of moves pays for it: both directions 1.00 of the speed.)
 template <int NT>
-__device__ __forceinline__ void block_allsum2_wide(float& a, float& b, float* red, double& da, double& db) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    da = double(a);
-    db = double(b);
-    constexpr int nw = NT / kWave;
-    if (nw > 1) {
-        const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-        __syncthreads();                       // red[] may still be read from the previous use
-        if (lane == 0) {
-            red[wave] = a;
-            red[nw + wave] = b;
-        }
-        __syncthreads();
-        da = double(red[0]);
-        db = double(red[nw]);
+__device__ __forceinline__ void block_allsum2(float a, float b, double* red, bool all, double& da, double& db) {
+    const double d = wave_sum2(a, b);
+    if (NT == kWave) {
+        da = lane_value(d, 31);
+        db = lane_value(d, 63);
+        return;
+    }
+    typedef double pair_t __attribute__((ext_vector_type(2)));
+    __syncthreads();                           // red[] may still be read from the previous use
+    if (threadIdx.x % 32 == 31) red[threadIdx.x / 32] = d;
+    __syncthreads();
+    da = db = 0.0;
+    if (!all && threadIdx.x >= kWave) return;
+    const pair_t* pairs = reinterpret_cast<const pair_t*>(red);
 #pragma unroll
-        for (int w = 1; w < nw; ++w) {
-            da += double(red[w]);
-            db += double(red[nw + w]);
-        }
-        a = float(da);
-        b = float(db);
+    for (int w = 0; w < NT / kWave; ++w) {
+        const pair_t p = pairs[w];
+        da += p.x;
+        db += p.y;
     }
 }
 
@@ -337,11 +327,11 @@ __device__ __forceinline__ void team_publish(const FusedArgs& A, uint32_t stamp0
 // team_collect: waits for every member's pair and returns the team totals to every thread.  False if a wait ran
 // out (the totals are then NaN).
 template <int NT, int SETS = 2>
-__device__ __forceinline__ bool team_collect(const FusedArgs& A, uint32_t* words, int team_first_block, uint32_t it, float a,
-                                             float b, double& ta, double& tb, float* team_lds, double* bc) {
+__device__ __forceinline__ bool team_collect(const FusedArgs& A, uint32_t* words, int team_first_block, uint32_t it, double a,
+                                             double b, double& ta, double& tb, float* team_lds, double* bc) {
     if (A.T == 1) {
-        ta = double(a);
-        tb = double(b);
+        ta = a;
+        tb = b;
         return true;
     }
     const uint32_t stamp = read_stamp(A, words) + it;
@@ -396,9 +386,9 @@ __device__ __forceinline__ bool team_collect(const FusedArgs& A, uint32_t* words
 
 template <int NT>
 __device__ __forceinline__ bool team_allsum2(const FusedArgs& A, uint32_t* words, int team_first_block, int j, uint32_t it,
-                                             float a, float b, double& ta, double& tb, float* team_lds,
+                                             double a, double b, double& ta, double& tb, float* team_lds,
                                              double* bc) {
-    team_publish(A, read_stamp(A, words), team_first_block, j, it, a, b);
+    team_publish(A, read_stamp(A, words), team_first_block, j, it, float(a), float(b));
     return team_collect<NT>(A, words, team_first_block, it, a, b, ta, tb, team_lds, bc);
 }
 
