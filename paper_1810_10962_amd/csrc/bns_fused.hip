@@ -51,9 +51,11 @@ namespace {
 // from the registers), a second exchange, and the blend of the two (E, Var) pairs.
 // Eq. 4 at (512 threads, up to 16 vectors) runs two blocks per compute unit, i.e. four waves per SIMD and at most 128
 // registers; the compiler is told so, because left alone it takes 150 and the second block is gone (130x128x28x28,
-// 7x7 patch + 2 virtual samples: forward 34 -> 29.7 us, a few registers spilled included).
+// 7x7 patch + 2 virtual samples: forward 34 -> 29.7 us, a few registers spilled included).  The same for a patch whose elements are read
+// on their own: the planner puts a second block on a unit where one per unit does not hold all channels in one round (3x400x104x104 f32,
+// 400 blocks, streaming 25.4 -> 17.7 us; 15x416x48x50 bf16 27.2 -> 22.2), but not with element-aligned vectors, which are left alone.
 template <typename T, int V, int KMAX, int NT, int PATCH, bool MIXED>
-__global__ __launch_bounds__(NT, ((MIXED || PATCH == 1) && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
+__global__ __launch_bounds__(NT, ((MIXED || (PATCH == 1 && !Odd<T>::value)) && NT == 512 && KMAX <= 16) ? 4 : 1) void fused_forward_kernel(FusedArgs A) {
     touch_arguments<FusedArgs>();
     typedef RawVec<T, V> RV;
     __shared__ double __attribute__((aligned(16))) red[2 * (NT / kWave)];
@@ -844,9 +846,14 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         }
         out->v = -1;
         if (bpc < 0) return hipSuccess;
-        // Forward, patch elements on their own, 128-bit vectors: teams are sized as if a unit took one of these blocks, since what a second one brings is lost
-        // on the larger teams (6x204x33x33 f32 8.9 against 6.1 us, 19x174x57x57 bf16 18.1 against 16.0, 3x256x86x84 f32 12.6 against 10.0).
-        const long blocks = long(di.cus) * (kind == 2 && wide && (v == 4 || (v == 3 && odd)) ? 1 : bpc);
+        const long chunks = long((tot + va.nt - 1) / va.nt);                // nt-vector chunks per channel
+        const long Tmin = (chunks + va.kmax - 1) / va.kmax;                 // members needed for one channel
+        // Forward, patch elements on their own, 128-bit vectors: as long as one block per unit holds all channels, teams are sized as if a unit took no
+        // more, since what a second one brings is lost on the larger teams (6x204x33x33 f32 8.9 against 6.1 us, 19x174x57x57 bf16 18.1 against 16.0,
+        // 3x256x86x84 f32 12.6 against 10.0).  Element-aligned vectors never take more: where one does not hold all, the other kernels are as often
+        // ahead (68x176x43x43 bf16 29.0 against 43.7, 17x192x33x33 f32 7.9 against 10.0; 39x144x43x43 f32 26.5 against 21.9), unless a channel needs them.
+        const bool one = kind == 2 && wide && (odd ? (v == 3 || v == 4) && Tmin <= di.cus : v == 4 && long(cg) * Tmin <= di.cus);
+        const long blocks = long(di.cus) * (one ? 1 : bpc);
         const int32_t tag = 1 + ((kind * 8 + combo) * 32 + v);
         TeamChoice& known = choice_slot(di, tag, tot, cg);
         if (known.tag == tag && known.tot == tot && known.cg == cg) {
@@ -861,8 +868,6 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         known.tot = tot;
         known.cg = cg;
         known.T = 0;
-        const long chunks = long((tot + va.nt - 1) / va.nt);                // nt-vector chunks per channel
-        const long Tmin = (chunks + va.kmax - 1) / va.kmax;                 // members needed for one channel
         if (Tmin > blocks || Tmin > kMaxTeam) return hipSuccess;
         long bestT = 0, best_cost = 0, best_rounds = 0;
         // widen only while every thread still keeps >= 4 vectors: below that the exchange costs more
@@ -977,7 +982,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
         // type and mode, 18 layers, two below 1: 26x1584x12x12 bf16 9.5 against 7.8; with four to six 0.85 to 0.92, 24 layers).
         const size_t tensor = size_t(d.N) * d.C * d.HW * (d.dtype == BNS_F32 ? 4 : 2);
         const bool many = (cg > 2 * di.cus && tensor > 16000000) || (cg > 6 * di.cus && tensor > 8000000);
-        if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1 || many)) {
+        // ... and where a patch takes two blocks per unit (52x384x20x20 f32 18.9 against 12.0 us).
+        const bool second = kind == 2 && wide && !odd && chosen.v == kTwoPerUnit && long(cg) * chosen.T > di.cus;
+        if (groups && !backward && !filled && (chosen.v < 0 || chosen.rounds > 1 || many || second)) {
             const hipError_t ge = grouped();
             if (ge != hipErrorNotSupported) return ge;
         }
