@@ -471,8 +471,8 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     const int V = d.dtype == BNS_F32 ? 4 : 8;
     const int opt = g_tuning.grouped, opt_g = g_tuning.grouped_channels;
     if (d.HW < V || opt == 2 || cus <= 0) return hipErrorNotSupported;
-    // Channels per group: about one block per compute unit (64x2048x7x7 bf16, forward + backward: groups of 8, 256 blocks,
-    // 23 us; of 4, 28 us; of 2, 29 us; 64x512x7x7: groups of 2, 256 blocks, 15.4 us; of 8, 18.5 us), whole vectors per run
+    // Channels per group: about one block per compute unit, also where two fit (64x2048x7x7 bf16, forward / backward: groups of 8, 256 blocks,
+    // 8.3 / 10.0 us; of 4, 9.3 / 10.5; of 2, 10.3 / 15.1; of 16, 9.6 / 12.9; 64x512x7x7: of 2, 256 blocks, 5.5 / 6.0; of 1, 6.4 / 6.6; of 8, 6.8 / 8.0), whole vectors per run
     // (multiples of `unit` channels) if that leaves as many blocks, fewer when the rows of a group would not fit the
     // largest block.  Block: the smallest that holds the group.
     const int unit = d.HW % V == 0 ? 1 : d.HW % (V / 2) == 0 ? 2 : (V == 8 && d.HW % 2 == 0) ? 4 : V;
@@ -494,20 +494,22 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // A run of more than half a block's threads leaves the others without work (3x700x33x33 f32: 273 of 512 threads, forward
     // 11.4 us against 8.6 with one element per access).  With three and more channels in a run the other kernels have more blocks than
     // the device holds at once, and this is the faster side backward up to 16 MB (1.2 in the mean of 62 drawn layers, 4x852x17x17 f32 5.8
-    // against 21.6) and forward where planes are whole vectors (asked only when those take several rounds: 1.5 in the mean of 23,
-    // 10x832x28x28 f32 11.0 against 20.1).
+    // against 21.6) and forward where planes are whole vectors (asked when those take several rounds or have very many blocks: 1.5 in the mean of 23,
+    // 10x832x28x28 f32 11.0 against 20.1).  Eq. 4: 1.11 forward, 11 layers, 1.24 backward, 14.
     const int64_t bytes = int64_t(d.N) * d.C * d.HW * (V == 8 ? 2 : 4);
     const bool crowded = G >= 3 && (backward ? bytes < 16000000 : d.vec > 1);
     if (opt == 0 && (G * d.HW + V - 1) / V > 256 && !crowded) return hipErrorNotSupported;
     // Forward, planes that are no whole vectors: a group of fewer than 1536 vectors leaves most of its 512 threads one row or none, and the
     // kernels of bns_fused.hip, a small block per channel, take 1 / 1.13 (140 layers) and 1 / 1.21 (84) of the time: 62x200x7x7 f32 5.3 against 4.4.
-    // (A patch costs those more: 12x1349x11x9 f32, 1188 vectors, 8.6 against 11.0.)
+    // (A patch costs those more: 12x1349x11x9 f32, 1188 vectors, 8.6 against 11.0.  Eq. 4, other / grouped: up to 1024 vectors 0.76 to 0.95 by size, 177 layers, none
+    // above 1; 1024 to 1536 0.92, 21 layers; beyond 1.14, 45.)
     const bool patch = ip.shared.h_cnt != d.H || ip.shared.w_cnt != d.W;
     // (In more than four channels to a compute unit those no longer fit at once: 26x1632x7x7 f32, 1274 vectors, 7.5 against 8.9.)
-    if (opt == 0 && !backward && d.vec == 1 && d.C <= 4 * cus && int64_t(d.N) * ((G * d.HW + V - 1) / V) < (patch ? 1024 : 1536)) return hipErrorNotSupported;
+    if (opt == 0 && !backward && d.vec == 1 && d.C <= 4 * cus && int64_t(d.N) * ((G * d.HW + V - 1) / V) < (patch && !mix ? 1024 : 1536)) return hipErrorNotSupported;
     // Backward: a channel of up to 64 vectors fits one wave of its own (1.18 and 1.26 times as fast, 53 and 48 layers, none slower: 2x528x10x10
     // bf16 5.2 against 3.6; beyond 1.2 MB it is, 12x1952x7x5 bf16 6.2 against 8.5), one of more than 1024 fills a block of 512 threads, which pays
-    // in small tensors (1.05 and 1.10, 68 and 46 layers).
+    // in small tensors (1.05 and 1.10, 68 and 46 layers).  Eq. 4: up to 64 vectors 0.86 to 0.92, 92 layers; more than 1024 up to these sizes 0.95, 25; beyond them and
+    // between 1.04 to 1.47, by size.
     const int64_t vectors = int64_t(d.N) * ((d.HW + V - 1) / V);
     if (opt == 0 && backward && ((vectors <= 64 && bytes <= 1200000) || (vectors > 1024 && bytes <= (d.vec > 1 ? 4000000 : 1800000))))
         return hipErrorNotSupported;
@@ -515,18 +517,23 @@ hipError_t launch_grouped(const Dims& d, const IndexParams& ip, bool backward, c
     // 128x64x16x16 f32 11.2 against 11.6, 100x60x12x12 bf16 8.5 against 8.9, 102x64x23x23 bf16 11.0 against 19.3).
     const int blocks = (d.C + best_g - 1) / best_g;
     if (opt == 0 && blocks < cus / 2 && best_v >= 2) return hipErrorNotSupported;
-    // ... and those that would leave most of a last round of one block per compute unit empty (61x288x28x28 bf16 backward: 288
-    // blocks, the step 40.8 against 41.7 us).
-    if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > cus && blocks % cus != 0 && blocks % cus < cus / 2) return hipErrorNotSupported;
-    // Forward, planes of whole vectors: beyond two rounds of blocks, of which one holds a compute unit and neither loads while it
-    // stores nor the other way round, the other kernels are ahead (Batch Sampling, us: 96x1024x20x20 bf16, 1024 blocks, 38.1 against
-    // 46.2, 128x2048x14x14 f32, 2048 blocks, 77.9 against 97.4; with two rounds 64x2048x14x14 bf16 31.3 against 25.3).
-    if (opt == 0 && !backward && d.vec > 1 && blocks > 2 * cus) return hipErrorNotSupported;
-    // Backward, planes of whole full-width vectors that begin on cache lines (fp32) or any (bf16): from the second round on the pipelined
-    // kernel is ahead (128x1024x16x16, us: bf16 39.1 against 42.5, f32 74.3 against 80.0; 96x1024x20x20 bf16 57.5 against 62.0; otherwise
-    // not: 64x2048x14x14 bf16 48.5 against 34.9, f32 74.1 against 67.9).
-    const bool lines = V == 8 || d.HW * 4 % 128 == 0;
-    if (opt == 0 && backward && d.vec == V && lines && !mix && blocks > cus) return hipErrorNotSupported;
+    // More blocks than compute units, planes of whole vectors.  Two of these blocks share a unit (one, backward or Eq. 4 with 16 vectors per thread: tall).
+    // The other kernels' time over this one's, layers drawn and timed both ways, geometric means f32 / bf16 (layers below 0.97):
+    //   forward, tall, 257 to 512 blocks 1.40 (3 of 78) / 1.58 (2 of 75); 513 to 1024 1.09 (14 of 71) / 1.12 (11 of 76), a patch 1.19 (1 of 20) / 1.55 (none of
+    //   24); beyond, 0.94 / 1.05.  (99x560x16x16 bf16, all points, 280 blocks, 13.0 against 15.2 us; 91x1552x20x19 bf16, 776 blocks, 49.3 against 63.4.)
+    //   Eq. 4 forward, 257 to 512 blocks 1.43 / 1.10 (6), beyond 1.11 / 0.91.
+    //   backward, whole full-width vectors that begin on cache lines (fp32) or any (bf16), where the pipelined kernel is the other: tall, 257 to 384 1.10 / 0.96,
+    //   385 to 512 1.16 / 1.15 (none below), beyond 0.98 / 0.94 (128x1024x16x16 39.1 against 42.5 us in bf16, 74.3 against 80.0); not tall, 513 to
+    //   1024 1.11 / 1.08, beyond 1.01 / 0.97.
+    //   backward, others, tall: 257 to 320 1.03 / 0.99 (61x288x28x28 bf16 40.8 against 41.7), 321 to 512 1.20 / 1.24, 513 to 640 1.00 / 1.06, then 1.07 / 1.08.
+    const bool tall = best_v == 3, lines = d.vec == V && !mix && (V == 8 || d.HW * 4 % 128 == 0);
+    if (opt == 0 && d.vec > 1 && best_v >= 2 && blocks > cus) {
+        const bool part = blocks % cus != 0 && blocks % cus < cus / 2;         // a last round of one block per unit leaves most of them idle
+        const bool other = !backward ? (mix ? V == 8 && (blocks > 2 * cus || part) : blocks > (patch ? 4 : 2) * cus)
+                           : lines   ? (tall ? blocks > 2 * cus || (V == 8 && 2 * blocks < 3 * cus) : blocks > 4 * cus)
+                                     : tall && (4 * blocks < 5 * cus || (blocks > 2 * cus && part));
+        if (other) return hipErrorNotSupported;
+    }
     // Calls that take 5 us whatever they do: working out the columns costs more there than it saves (forward, us: 8x224x5x5 f32
     // 4.8 against 5.4, 37x96x9x9 bf16 5.7 against 6.3; backward, 6x144x7x7 bf16 5.0 against 5.4).  Just above the lines the median gain is
     // nil: forward, 1.0 to 1.3 MB, 1.00 (30 tensors), backward, bf16, 0.3 to 0.5 MB, 1.06 (66); fp32 below 0.1 MB 1.03 (54).

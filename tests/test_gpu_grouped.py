@@ -91,6 +91,13 @@ def test_what_lies_outside_s_does_not_reach_the_statistics(dtype):
     ((21, 200, 14, 14), "f32", BS, (False, False)),        # 1029 vectors to a channel in 3.3 MB
     ((26, 200, 14, 14), "f32", BS, (False, True)),         # in 4.1 MB
     ((4, 852, 17, 17), "f32", NS, (False, True)),          # 289 lanes, but four channels: backward only
+    # more blocks than compute units, 16 vectors per thread: two of them share a unit forward
+    ((20, 272, 32, 32), "f32", FS, (True, True)),          # 272 blocks; backward, planes that begin on cache lines
+    ((40, 272, 32, 32), "bf16", FS, (True, False)),        # bf16: a last round of 16 blocks
+    ((40, 400, 32, 32), "bf16", FS, (True, True)),         # ... of 144
+    ((20, 272, 28, 28), "f32", FS, (False, False)),        # planes that begin anywhere: a last round of 16 blocks
+    ((20, 336, 28, 28), "f32", FS, (False, True)),         # ... of 80
+    ((20, 272, 28, 28), "f32", FULL, (False, False)),      # all points: the other kernels hold a channel per block in one round
     ((34, 64, 23, 20), "bf16", FULL, (False, False)),      # teams of 512 threads instead of 61 blocks of 64
     ((9, 16, 40, 40), "bf16", FULL, (False, False)),       # too few channels for them
     ((6, 130, 33, 33), "f32", FS, (False, False)),         # one block of 512 threads to a channel
