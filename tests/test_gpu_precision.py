@@ -43,3 +43,36 @@ def test_sums_across_lanes_and_waves_are_not_rounded(shape, dtype, mkw, threads,
     assert mean < ROUNDING * inside
     # dy, whose sums every point takes part in, and the rounding of the result
     assert dbeta < ROUNDING * np.sqrt(1.0 + inside ** 2)
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("kernels,options", [("single launch", {"grouped": 2, "nhwc_fused": 1}), ("grouped", {"grouped": 1}),
+                                             ("streaming", {"path": 1, "nhwc_fused": 2})], ids=["single_launch", "grouped", "streaming"])
+def test_inverse_square_root(layout, kernels, options):
+    """Bit for bit the value in 64 bits, rounded once: an fp64 result two units off lies on the other side of an fp32 rounding boundary
+    once in 2^28 values, the hardware's estimate of 23 bits in every second one."""
+    N, C_, H, W = 4, 16, 12, 12
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(94)
+    x = torch.tensor(rng.integers(1, 16, C_).astype(np.float32) / 8, device=dev)    # (few bits: the mean of some rows is exact, too)
+    x = (x if layout == "nhwc" else x[:, None, None]).expand((N, H, W, C_) if layout == "nhwc" else (N, C_, H, W)).contiguous()
+    shape, spec = bns.make_shape(N, C_, H, W, "f32", layout), bns.make_spec(FULL)
+    one, zero, y = torch.ones(C_, device=dev), torch.zeros(C_, device=dev), torch.empty_like(x)
+    ws = torch.zeros(bns.bns_workspace_bytes(shape, spec), dtype=torch.uint8, device=dev)
+    values = np.ldexp(rng.uniform(1.0, 4.0, 400), 2 * rng.integers(-62, 62, 400)).astype(np.float32)    # every mantissa, odd and even powers
+    mean, got = torch.empty(C_, device=dev), torch.empty(len(values), C_, device=dev)
+    print(f"[gpu-case] inverse square root {layout} {kernels}", flush=True)
+    try:
+        for k, v in options.items():
+            bns.bns_set_option(k, v)
+        for i, eps in enumerate(values):
+            bns.bns_forward(shape, spec, 1, x, one, zero, float(eps), 0.1, y, mean, got[i], None, None, ws)
+        took = bns.bns_get_option("last_path_forward"), bns.bns_get_option("last_fused_forward")
+    finally:
+        for k in options:
+            bns.bns_set_option(k, 0)
+    assert (took[0] == 1) == (kernels == "streaming")
+    if layout == "nchw" and kernels != "streaming":
+        assert (took[1] == 3) == (kernels == "grouped")
+    want = (1.0 / np.sqrt(values.astype(np.float64))).astype(np.float32)
+    assert np.array_equal(got.cpu().numpy(), np.repeat(want[:, None], C_, 1))
