@@ -361,7 +361,9 @@ bns_status bns_set_option(const char* name, int32_t value);
  * between the reduction kernel and a kernel for the rows of S ("nhwc_split_dx", "nhwc_split_ordered"); "last_fused_backward": which fused backward kernel that was
  * (1 plain, 2 x kept in registers, 3 pipelined, 4 groups of channels, 5 one block per compute unit); "last_fused_forward": 3 if groups of
  * channels, 4 if one block per compute unit,
- * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "launch_count": kernels launched by the library since it was
+ * 2 if the fused forward kernel took the statistics of a patch from the registers (see "fused_patch_mask"), else 1; "last_team_forward" /
+ * "last_team_backward": blocks that shared a channel, or a column tile of N x H x W x C, in this thread's last single-launch call, "last_variant_forward" /
+ * "last_variant_backward": the block size that it took, as in "fused_variant" (0: kernels that are not chosen by it); "launch_count": kernels launched by the library since it was
  * loaded, modulo 2^31 (benchmarks report launches per call from its differences).
  * -1 for an unknown name. */
 int32_t bns_get_option(const char* name);

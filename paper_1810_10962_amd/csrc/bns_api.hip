@@ -15,6 +15,8 @@ using namespace bns;
 std::atomic<uint32_t> bns::g_launch_count{0};
 thread_local int32_t bns::t_last_fused_backward = 0;
 thread_local int32_t bns::t_last_fused_forward = 0;
+thread_local int32_t bns::t_last_team[2] = {0, 0};
+thread_local int32_t bns::t_last_variant[2] = {0, 0};
 
 // Built-in scratch memory of bns_backward_builtin_workspace (see there).
 // N x C x H x W: 3840 channels; N x H x W x C: 4 MiB of partial sums behind the slots.
@@ -667,6 +669,10 @@ int32_t bns_get_option(const char* name) {
     if (!strcmp(name, "last_path_backward")) return t_last_path_backward;
     if (!strcmp(name, "last_fused_backward")) return t_last_fused_backward;
     if (!strcmp(name, "last_fused_forward")) return t_last_fused_forward;
+    if (!strcmp(name, "last_team_forward")) return t_last_team[0];
+    if (!strcmp(name, "last_team_backward")) return t_last_team[1];
+    if (!strcmp(name, "last_variant_forward")) return t_last_variant[0];
+    if (!strcmp(name, "last_variant_backward")) return t_last_variant[1];
     if (!strcmp(name, "launch_count")) return int32_t(g_launch_count.load() & 0x7fffffffu);
     for (const TuningEntry& t : kTuningTable)
         if (!strcmp(name, t.name)) {

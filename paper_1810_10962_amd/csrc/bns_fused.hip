@@ -776,7 +776,11 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     if (e != hipSuccess) return e;
     auto grouped = [&]() {
         const hipError_t ge = launch_grouped(d, ip, backward, io, eps, momentum, st, cus, mix);
-        if (ge == hipSuccess) (backward ? t_last_fused_backward : t_last_fused_forward) = backward ? 4 : 3;
+        if (ge == hipSuccess) {
+            (backward ? t_last_fused_backward : t_last_fused_forward) = backward ? 4 : 3;
+            t_last_team[backward] = 1;
+            t_last_variant[backward] = 0;
+        }
         return ge;
     };
     if (groups && (backward || d.vec == 1 || g_tuning.grouped != 0)) {
@@ -1215,6 +1219,8 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     if ((e = chain_behind_last(di, st, may_create_event, &chain)) != hipSuccess) return e;
     g_launch_count.fetch_add(1, std::memory_order_relaxed);
     if (backward) t_last_fused_backward = pipe_kernel ? 3 : (kind & 2) ? 2 : 1;
+    t_last_team[backward] = bestT;
+    t_last_variant[backward] = pipe_kernel ? 0 : best + 1;
     e = opt_coop ? hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(launch_nt), params, 0, st)
                             : hipLaunchKernel(kernel, dim3(grid), dim3(launch_nt), params, 0, st);
     if (e == hipSuccess && chain) chain_launched(di, st);

@@ -31,6 +31,10 @@ extern thread_local int32_t t_last_fused_backward;
 // Which flavour the calling thread's last fused forward call took: 1 plain or patch elements read on their own,
 // 2 patch statistics from the registers, 3 groups of channels, 4 one block per compute unit.
 extern thread_local int32_t t_last_fused_forward;
+// Blocks that shared a channel or a column tile in the calling thread's last single-launch forward / backward call.
+extern thread_local int32_t t_last_team[2];
+// ... and the block size of the kernels of bns_fused.hip that they took, as in "fused_variant"; 0: other kernels.
+extern thread_local int32_t t_last_variant[2];
 
 // Streaming kernels: planes that are no whole number of full-width vectors but hold at least one (see f32_odd in
 // bns_device.hpp), and the elements per access the streaming kernels take.

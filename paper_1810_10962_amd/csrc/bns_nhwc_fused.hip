@@ -37,7 +37,6 @@ namespace {
 
 constexpr int kRowThreads = 512;
 constexpr int kRowMaxTile = 128;        // channels of a column tile
-constexpr int kRowPoll = 8;             // team-mates that a thread polls at a time, at most
 constexpr int kRowBatch = 8;            // rows that are not kept: read again this many at a time
 
 struct RowArgs {
@@ -1015,14 +1014,10 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
         // forward, 8 lanes 61.9, 16 lanes 48.0); idle compute units cost less than their share, since small tensors do not fill
         // the memory's queues; 1024 pairs are polled in one go (25x382x8x8 bf16 forward, 8 members x 72 channels 9.2, 13 x 128 10.6).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
-        // Two rows per thread and no fewer: against four, over 22 drawn layers of up to 4 MB, 1.04 of the speed forward and 1.09 backward, three
-        // 1.02 and 1.04; one 1.03 and 1.09, but 0.89 / 0.92 at 54x144x10x13 bf16.  Four where more members would make a block read more
-        // than 4096 pairs of sums: 16x48x55x55 bf16, a patch, 256 members 13.7 / 13.7 us, 143 11.6 / 11.9.
         double best = 0.0;
         for (int lanes = want > 0 ? want : 8; lanes <= (want > 0 ? want : 16); lanes += aligned ? 8 : 1) {
             const int tx = lanes_for(lanes), g = groups_for(tx), count = (CV + tx - 1) / tx;
-            const int two = (g + 1) / 2, few = opt == 1 ? two : std::min(two, 4096 / (tx * V));
-            const int t = std::min(std::max((g + 3) / 4, few), std::max(1, cus / count));
+            const int t = tile_members(g, tx * V, cus / count);
             // what a narrower tile, idle lanes, threads or compute units cost is a share of the time at the memory
             const double use = double(CV) / double(count * tx) * double(kRowThreads / tx * tx) / kRowThreads * std::min(1.0, double(count * t) / cus);
             const double moved = double(bytes) * (backward ? 3 : 2), pairs = double(t) * tx * V / 4096.0;
@@ -1153,11 +1148,11 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     A.ct_div = make_fastdiv(uint32_t(TX * V));
     A.tiles_div = make_fastdiv(uint32_t(tiles));
     A.eights = T / 8 * 8 * tiles;
-    // Threads that share a channel: as many as there are, for the members no more than leaves each of them the same number.
-    const int threads = kRowThreads / (TX * V), each = (T + threads - 1) / threads, turns = (each + kRowPoll - 1) / kRowPoll;
+    const int threads = kRowThreads / (TX * V);             // that share a channel
+    const TileExchange exchange = tile_exchange(T, threads);
     A.sum_groups = std::min(threads, kSumGroups);
-    A.member_groups = (T + each - 1) / each;
-    A.polled = (each + turns - 1) / turns;
+    A.member_groups = exchange.groups;
+    A.polled = exchange.polled;
     for (int i = 0; i < kPivotRows; ++i)
         A.pivot_off[i] = sampled_row(A.S, std::min(uint32_t(i), A.S.pivot_rows - 1u)) * uint32_t(bytes / M);
     A.M = M;
@@ -1174,6 +1169,8 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
                          : d.dtype == BNS_F32 ? row_kernel<float, 1>(variant, backward, mixed, first, shared)
                                               : row_kernel<bf16_t, 1>(variant, backward, mixed, first, shared);
     *solo = T == 1;
+    t_last_team[backward] = T;
+    t_last_variant[backward] = 0;
     void* params[] = {&A};
     return launch_waiting(kernel, dim3(uint32_t(tiles) * uint32_t(T)), dim3(kRowThreads), params, T > 1, may_create_event, st);
 }

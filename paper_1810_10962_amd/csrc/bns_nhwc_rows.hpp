@@ -49,6 +49,27 @@ constexpr bool rows_first(int rounds, int V, bool backward, bool mixed, long pit
     return !backward && !mixed && V > 1 && rounds > kRowKeepX && pitch % 64 != 0 && (V == 4 || rounds <= rows_in_registers(V, false, false, false));
 }
 
+// Blocks that share the rows of a column tile: two rows per thread and no fewer (against four, over 22 drawn layers of up to 4 MB, 1.04 of the speed
+// forward and 1.09 backward, three 1.02 and 1.04; one 1.03 and 1.09, but 0.89 / 0.92 at 54x144x10x13 bf16); four where more members would make a
+// block read more than 4096 pairs of sums (16x48x55x55 bf16, a patch, 256 members 13.7 / 13.7 us, 143 11.6 / 11.9).  groups: rows of the
+// tile over the rows that a block takes at a time; channels of the tile; most: what the device holds.
+constexpr int tile_members(int groups, int channels, int most) {
+    const int two = (groups + 1) / 2, four = (groups + 3) / 4, pairs = 4096 / channels;
+    const int few = two < pairs ? two : pairs, want = four > few ? four : few;
+    return most < 1 ? 1 : want < most ? want : most;
+}
+
+// How the threads that share a channel (at most `threads` of them) add up the sums of T members: as many as leave each of them the same
+// number, which it polls in as few turns of up to kRowPoll as that takes.
+constexpr int kRowPoll = 8;
+struct TileExchange {
+    int groups, polled;     // threads, members that a thread polls at a time
+};
+constexpr TileExchange tile_exchange(int T, int threads) {
+    const int each = (T + threads - 1) / threads, turns = (each + kRowPoll - 1) / kRowPoll;
+    return TileExchange{(T + each - 1) / each, (each + turns - 1) / turns};
+}
+
 // Whether stores leave the non-temporal hint out: lines that two tiles share are then put together in the L2.  With the hint against without,
 // forward, 90 drawn layers of several tiles whose rows begin on no 64 bytes, f32 / bf16: 1.05 / 1.02 from 2 to 8 MB, 1.10 / 1.09 to 30 MB, 1.37 / 1.53
 // beyond, one layer below 0.97 (us: 23x150x104x104 bf16 68.8 / 37.9, 6x252x109x106 f32 49.8 / 33.5, 50x150x19x19 f32 11.5 / 10.5).  One tile

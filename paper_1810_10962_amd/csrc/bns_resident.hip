@@ -586,6 +586,8 @@ hipError_t launch_resident(const Dims& d, const IndexParams& ip, bool backward, 
     A.s_lo = uint32_t(uint64_t(b.n0) * stride);
     A.s_len = uint32_t(uint64_t(b.n_cnt) * stride);
     (backward ? t_last_fused_backward : t_last_fused_forward) = backward ? 5 : 4;
+    t_last_team[backward] = F.T;
+    t_last_variant[backward] = 0;
     void* params[] = {&A};
     return launch_waiting(kernel, dim3(uint32_t(teams * T)), dim3(kResThreads), params, T > 1, may_create_event, st);
 }

@@ -4,6 +4,8 @@
 //   rules_harness rule   reads "N C H W dtype mode n_s patch_h patch_w n_v per_channel backward" lines and prints "<kernel> <T> <rounds>":
 //                           0 other kernels, 1 all registers for one tensor, 2 x beside dy
 //   rules_harness sweep  random layers: what a taken plan must hold to, whatever the rule
+//   rules_harness tiles  "<groups> <channels> <most> <members>" and, for every number of members and of threads, how they add the sums up:
+//                           "<members> <threads> <threads at work> <polled at a time>"
 //   rules_harness rows   "<V> <backward> <mixed> <rounds> <regs> <park>" for every number of rows per thread
 #include <stdio.h>
 #include <stdlib.h>
@@ -97,11 +99,24 @@ int rows() {
                 }
     return 0;
 }
+
+int tiles() {
+    for (int channels : {4, 8, 32, 52, 64, 128})
+        for (int most : {0, 1, 7, 64, 256})
+            for (int groups = 1; groups <= 1100; groups += groups < 600 ? 1 : 37) printf("m %d %d %d %d\n", groups, channels, most, tile_members(groups, channels, most));
+    for (int threads = 4; threads <= 512; ++threads)
+        for (int T = 1; T <= 256; ++T) {
+            const TileExchange x = tile_exchange(T, threads);
+            printf("x %d %d %d %d\n", T, threads, x.groups, x.polled);
+        }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
     if (argc != 2) return 2;
     if (!strcmp(argv[1], "rule")) return rule();
     if (!strcmp(argv[1], "sweep")) return sweep();
+    if (!strcmp(argv[1], "tiles")) return tiles();
     return !strcmp(argv[1], "rows") ? rows() : 2;
 }

@@ -98,9 +98,9 @@ def test_what_lies_outside_s_does_not_reach_the_statistics(dtype):
     ((20, 272, 28, 28), "f32", FS, (False, False)),        # planes that begin anywhere: a last round of 16 blocks
     ((20, 336, 28, 28), "f32", FS, (False, True)),         # ... of 80
     ((20, 272, 28, 28), "f32", FULL, (False, False)),      # all points: the other kernels hold a channel per block in one round
-    ((34, 64, 23, 20), "bf16", FULL, (False, False)),      # teams of 512 threads instead of 61 blocks of 64
-    ((9, 16, 40, 40), "bf16", FULL, (False, False)),       # too few channels for them
-    ((6, 130, 33, 33), "f32", FS, (False, False)),         # one block of 512 threads to a channel
+    ((34, 64, 23, 20), "bf16", FULL, (False, False)),      # few channels
+    ((9, 16, 40, 40), "bf16", FULL, (False, False)),
+    ((6, 130, 33, 33), "f32", FS, (False, False)),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_default_choice_on_both_sides_of_its_lines(shape, dtype, mode, want):
     """want: whether forward and backward take groups of channels."""

@@ -78,7 +78,7 @@ def test_rows_per_thread(rounds, dtype):
 ], ids=str)
 def test_members_of_a_tile(C_, lanes, members):
     """Blocks that share a tile's rows: how many of them a thread polls, and what is left over."""
-    rows = members * 2 * (512 // lanes) - 5                 # two rows per thread
+    rows = members * (2 if members * C_ <= 4096 else 4) * (512 // lanes) - 5        # rows per thread, by the pairs of sums that a block reads
     for i, mkw in enumerate((dict(mode=FULL), dict(mode=FS, patch_h=1, patch_w=5, n_v=1))):
         wl = Workload(name="members", N=3, C=C_, H=1, W=rows // 3, dtype="f32", layout="nhwc", data_seed=70 + i, sampling_seed=3,
                       layer_id=i, **mkw)
@@ -86,6 +86,7 @@ def test_members_of_a_tile(C_, lanes, members):
         print(f"[gpu-case] nhwc single launch, {members} members {wl.shape} {mkw}", flush=True)
         res = _with({"nhwc_fused": 1, "nhwc_fused_lanes": lanes}, lambda: bns.run_workload(wl, inp))
         assert _paths() == (2, 2)
+        assert (bns.bns_get_option("last_team_forward"), bns.bns_get_option("last_team_backward")) == (members, members)
         assert_parity(res, oracle_reference(wl, inp), wl, what=f"{members} members {mkw}", inp=inp)
 
 

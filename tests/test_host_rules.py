@@ -49,6 +49,28 @@ def test_a_thread_walks_over_few_rows_that_it_does_not_have(harness):
                 assert regs + park - rows < park
 
 
+def test_members_of_a_tile_and_the_sums_they_read(harness):
+    """No more members than the device holds, two rows per thread at least, 4096 pairs of sums at most unless that left more than four rows; every member's
+    sums are added by one thread of those that share a channel, none of which has nothing to do, eight at a time at most."""
+    seen = {"two": 0, "pairs": 0, "four": 0}
+    for line in _run(harness, "tiles").splitlines():
+        kind, *v = line.split()
+        if kind == "m":
+            groups, channels, most, members = map(int, v)
+            two, four, pairs = -(-groups // 2), -(-groups // 4), 4096 // channels
+            assert members == max(1, min(most, max(four, min(two, pairs))))
+            if 1 < members < most:
+                seen["two" if two <= pairs else "pairs" if pairs > four else "four"] += 1
+            continue
+        members, threads, groups, polled = map(int, v)
+        each = -(-members // groups)
+        assert 1 <= groups <= min(threads, members) and 1 <= polled <= 8
+        assert (each - 1) * groups < members                # the last turn is not empty for the first thread
+        assert groups == -(-members // -(-members // threads))
+        assert -(-each // polled) == -(-each // 8) and polled == -(-each // -(-each // 8))
+    assert min(seen.values()) > 100, seen
+
+
 # One block per compute unit on 256 units: layers on both sides of each line, with what other kernels and these took (us).
 # N, C, H, W, dtype, mode, n_s, patch_h, patch_w, n_v, backward, kernel (0 other, 1 dy (x) alone on chip, 2 x beside dy)
 FULL, BS, FS = 0, 2, 3
