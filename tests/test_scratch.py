@@ -59,12 +59,12 @@ def test_only_the_kernels_that_the_build_allows_use_scratch_memory():
 
 
 def test_a_kernel_that_is_not_listed_or_needs_more_is_reported():
-    listed = "_ZN3bns12_GLOBAL__N_123grouped_backward_kernelINS_6bf16_tELi8ELi4ELi256ELb0EEEvNS0_9GroupArgsE"
-    other = listed.replace("Li256", "Li512")
+    listed = "_ZN3bns12_GLOBAL__N_126fused_backward_pipe_kernelINS_6bf16_tELi8ELi5ELi512EEEvNS0_9FusedArgsE"
+    other = listed.replace("Li5E", "Li4E")
     remark = "x.hip:1:1: remark: {} [-Rpass-analysis=kernel-resource-usage]"
     report = "\n".join([remark.format("Function Name: " + listed), "source", "^", remark.format("    ScratchSize [bytes/lane]: 16"),
                         remark.format("Function Name: " + other), "source", "^", remark.format("    ScratchSize [bytes/lane]: 4"), "a warning"])
     lines, spilled = entry._split_resource_remarks(report)
     assert lines == ["a warning"] and spilled == {listed: 16, other: 4}
     assert entry.unexpected_scratch(spilled) == {other: 4}
-    assert entry.unexpected_scratch({listed: 24}) == {listed: 24}
+    assert entry.unexpected_scratch({listed: 60}) == {listed: 60}
