@@ -217,7 +217,7 @@ def _calls():
     return _call
 
 
-def _by_ctypes(name, args):
+def _by_ctypes(name, *args):
     """A call of every step whose arguments the extension left alone: structures, tensors and a stream as in _PROTOS."""
     types = _PROTOS[name][1]
     plain = [C.byref(a) if t in (_SHP, _SPC) else _ptr(a) if t is _P else a for a, t in zip(args[:-1], types)]
@@ -226,17 +226,21 @@ def _by_ctypes(name, args):
 
 def bns_forward(shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
                 running_mean, running_var, workspace):
-    args = (shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean, save_invstd, running_mean,
-            running_var, workspace, workspace.nbytes, _stream(x))
-    status = _calls().forward(*args)
-    _check(_by_ctypes("bns_forward", args) if status is None else status, "bns_forward")
+    status = _calls().forward(shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
+                              running_mean, running_var, workspace, workspace.nbytes, _stream(x))
+    if status is None:
+        status = _by_ctypes("bns_forward", shape, spec, seed, x, gamma, beta, eps, momentum, y, save_mean,
+                            save_invstd, running_mean, running_var, workspace, workspace.nbytes, _stream(x))
+    _check(status, "bns_forward")
 
 
 def bns_backward(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, workspace):
-    args = (shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, workspace,
-            workspace.nbytes, _stream(x))
-    status = _calls().backward(*args)
-    _check(_by_ctypes("bns_backward", args) if status is None else status, "bns_backward")
+    status = _calls().backward(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta, workspace,
+                               workspace.nbytes, _stream(x))
+    if status is None:
+        status = _by_ctypes("bns_backward", shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma,
+                            dbeta, workspace, workspace.nbytes, _stream(x))
+    _check(status, "bns_backward")
 
 
 def bns_backward_builtin_workspace(shape, spec, seed, x, dy, gamma, save_mean, save_invstd, dx, dgamma, dbeta):
@@ -296,24 +300,31 @@ def bns_sample_index_mixed(shape: bns_shape, spec: bns_spec, seed: int, n_v: int
 
 def bns_forward_mixed(shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
                       save_mean_parts, running_mean, running_var, workspace):
-    args = (shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y, save_mean, save_invstd,
-            save_mean_parts, running_mean, running_var, workspace, workspace.nbytes, _stream(x))
-    status = _calls().forward_mixed(*args)
-    _check(_by_ctypes("bns_forward_mixed", args) if status is None else status, "bns_forward_mixed")
+    status = _calls().forward_mixed(shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y, save_mean,
+                                    save_invstd, save_mean_parts, running_mean, running_var, workspace,
+                                    workspace.nbytes, _stream(x))
+    if status is None:
+        status = _by_ctypes("bns_forward_mixed", shape, spec, seed, n_v, mix_beta, x, gamma, beta, eps, momentum, y,
+                            save_mean, save_invstd, save_mean_parts, running_mean, running_var, workspace,
+                            workspace.nbytes, _stream(x))
+    _check(status, "bns_forward_mixed")
 
 
 def bns_backward_mixed(shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean, save_invstd, save_mean_parts,
                        dx, dgamma, dbeta, workspace):
-    args = (shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean, save_invstd, save_mean_parts, dx, dgamma,
-            dbeta, workspace, workspace.nbytes, _stream(x))
-    status = _calls().backward_mixed(*args)
-    _check(_by_ctypes("bns_backward_mixed", args) if status is None else status, "bns_backward_mixed")
+    status = _calls().backward_mixed(shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean, save_invstd,
+                                     save_mean_parts, dx, dgamma, dbeta, workspace, workspace.nbytes, _stream(x))
+    if status is None:
+        status = _by_ctypes("bns_backward_mixed", shape, spec, seed, n_v, mix_beta, x, dy, gamma, save_mean,
+                            save_invstd, save_mean_parts, dx, dgamma, dbeta, workspace, workspace.nbytes, _stream(x))
+    _check(status, "bns_backward_mixed")
 
 
 def bns_inference(shape, x, gamma, beta, running_mean, running_var, eps, y):
-    args = (shape, x, gamma, beta, running_mean, running_var, eps, y, _stream(x))
-    status = _calls().inference(*args)
-    _check(_by_ctypes("bns_inference", args) if status is None else status, "bns_inference")
+    status = _calls().inference(shape, x, gamma, beta, running_mean, running_var, eps, y, _stream(x))
+    if status is None:
+        status = _by_ctypes("bns_inference", shape, x, gamma, beta, running_mean, running_var, eps, y, _stream(x))
+    _check(status, "bns_inference")
 
 
 def bns_moving_average_weight(iteration: int, alpha: float) -> float:
