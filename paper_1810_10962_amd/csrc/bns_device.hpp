@@ -243,9 +243,9 @@ __device__ __forceinline__ float load_scalar<bf16_t>(const bf16_t* p) { return b
 // LDS, then the first wave adds the four in index order.
 // ---------------------------------------------------------------------------
 // Inclusive scan with data-parallel-primitive moves (shifts of 1, 2, 4, 8 lanes inside each row of 16, then the last lane of row 0 / row 2
-// broadcast into the next row, then lane 31 into the upper half), after which lane 63 holds the total: the same balanced tree as a
-// butterfly of cross-lane shuffles, which go through LDS and need lane-index registers (64x2048x7x7 bf16, the sums of a group of channels
-// 0.8 -> 0.5 us).
+// broadcast into the next row, then lane 31 into the upper half), after which lane 63 holds the total: a balanced tree, neighbours
+// first.  A butterfly of cross-lane shuffles is one, too (distant lanes first, so its bits differ), but goes through LDS and needs lane-index registers
+// (64x2048x7x7 bf16, the sums of a group of channels 0.8 -> 0.5 us).
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_or_zero(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, true));

@@ -765,11 +765,10 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     const int opt_masked = g_tuning.fused_patch_mask;
     // Small planes: a block per group of channels (bns_grouped.hip), unless a kernel of this file or a part of the
     // tensor is asked for.  Backward whenever a group fits a block, forward when planes are no whole number of vectors.
-    // Measured, us, against the kernels of this file: 64x2048x7x7 bf16 38.5 -> 10.6 and 26.3 -> 12.3 (forward, backward);
-    // 64x1024x14x14 f32 backward 39.3 -> 32.9, bf16 20.8 -> 13.5 and 25.5 -> 18.0; 32x512x13x13 f32 9.6 -> 9.0 and
-    // 13.8 -> 10.1.  Forward with whole vectors is 0.4 us slower at 128x64x8x8 and 8x512x14x14, 4 us at 64x512x28x28 bf16
-    // (a channel in one block of 50 vectors per thread), and faster only where this file's kernels need several rounds
-    // (64x1024x14x14 f32: 25.0 -> 21.0): see below.
+    // Measured, us, against the other kernels: 64x2048x7x7 bf16 14.3 -> 8.7 and 22.3 -> 10.4 (forward, backward), f32 22.3 -> 12.3 and 33.0 -> 15.7;
+    // 64x1024x14x14 f32 24.7 -> 21.8 and 38.3 -> 32.8, bf16 17.2 -> 12.1 and 24.5 -> 16.6; 32x512x13x13 f32 backward 9.7 -> 8.7.  Forward it is 0.5 us slower
+    // at 128x64x8x8 and 8x512x14x14 and 0.8 at 32x512x13x13; faster only where this file's kernels need several rounds or have very many
+    // blocks: see below.
     const bool groups = cg == d.C && opt_variant == 0 && opt_keep_x == 0 && opt_pipe == 0 && opt_masked == 0;
     int cus = 0;                                        // (asked for before the lock is taken: device_units takes it, too)
     hipError_t e = device_units(&cus);
@@ -928,9 +927,9 @@ hipError_t launch_fused(const Dims& d, const IndexParams& ip, bool backward, con
     // Backward: x is kept, whatever S is, and (512, 8) is the kernel (us, against the rule above: 14x16x103x102 f32 11.0 against
     // 13.8, 2x100x39x39 f32 5.7 against 7.3), except that a (256, 4) block that holds its channel is taken when the (512, 8) blocks need
     // several rounds (3x1024x29x29 bf16 9.9 against 11.0).
-    // 400 tensors drawn afresh, groups of channels and one-element kernels as chosen, against one-element kernels throughout: forward
-    // 1.33 times the speed (geometric mean), 9 more than 3 % slower (worst 74x16x9x9 f32 7.6 against 6.9), backward 1.33, 15 (worst
-    // 17x528x15x14 f32 12.1 against 10.7); the two together never more than 6 % slower.
+    // 400 tensors drawn afresh, groups of channels and, in channels of up to 2048 elements, one-element kernels (then in both directions, now backward
+    // only) as chosen, against one-element kernels throughout: forward 1.33 times the speed (geometric mean), 9 more than 3 % slower (worst 74x16x9x9
+    // f32 7.6 against 6.9), backward 1.33, 15 (worst 17x528x15x14 f32 12.1 against 10.7); the two together never more than 6 % slower.
     auto odd_plan = [&](Plan* out) -> hipError_t {
         hipError_t pe;
         Plan p;

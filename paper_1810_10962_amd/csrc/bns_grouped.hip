@@ -16,8 +16,8 @@
 // the run (the elements it shares with the vector before it are left out of the sums and stored twice with the same bits).
 //
 // Bound by memory: one read of each input, one write of the output, and by what a launch of one round costs (load, two
-// block barriers, store).  64x2048x7x7, Batch Sampling, us forward / backward: bf16 8.8 / 10.3 (2.9 / 3.7 TB/s; with shuffles and divisions 9.95 / 11.4) against
-// 38.5 / 26.3 with one element per access, f32 13.7 / 17.0 (3.8 / 4.5 TB/s) against 34.0 / 34.4.
+// block barriers, store).  64x2048x7x7, Batch Sampling, us forward / backward: bf16 8.7 / 10.4 (2.9 / 3.7 TB/s; with shuffles and divisions 9.95 / 11.4) against
+// 14.3 / 22.3 with the other kernels, f32 12.3 / 15.7 (4.2 / 4.9 TB/s) against 22.3 / 33.0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

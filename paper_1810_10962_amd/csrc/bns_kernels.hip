@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kOneBlock) void stats_one_block_kernel(
     if (running_var) running_var[c] = float((1.0 - a) * double(running_var[c]) + a * var);
 }
 
-// One wave per channel: lane k holds split k, fp64 butterfly (a fixed pattern, so the
+// One wave per channel: lane k holds split k, a tree in fp64 (a fixed pattern, so the
 // rounding order never changes), then lane 0 applies Eq. 3 and Eq. 8.  splits <= 64.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void stats_finalize_kernel(

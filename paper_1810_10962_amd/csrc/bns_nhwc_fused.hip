@@ -1010,7 +1010,8 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
         // reads (128x64x32x32 f32 forward: 128 members x 32 channels 17.6, 256 x 64 20.8; 50x150x19x19 f32: 85 x 52 13.5 / 14.9, 51 x
         // 32 12.5 / 13.9).  The times below are estimates, us, of what depends on the width.  Rows that begin on no 64 bytes: fitted to
         // 1800 passes over tensors of 0.2 to 130 MB, each timed with two to five widths; over 4100 further ones, with all of them, the tile it picks takes
-        // 1.02 of the time of the best, 117 times more than 1.1, at most 1.42 (prices as for aligned rows, over the 1800: 1.03, 1.5).  A line shared between tiles costs as much as 115 bytes of one's own (13x293x67x67 f32
+        // 1.02 of the time of the best, 117 times more than 1.1, at most 1.42 (prices as for aligned rows, over the 1800: 1.03, 1.5).  That was with the non-temporal hint on all stores; without it on
+        // shared lines (shares_lines), 98 layers with nine widths each: 1.01 of the best in both directions, none more than 1.08.  A line shared between tiles costs as much as 115 bytes of one's own (13x293x67x67 f32
         // forward, 8 lanes 61.9, 16 lanes 48.0); idle compute units cost less than their share, since small tensors do not fill
         // the memory's queues; 1024 pairs are polled in one go (25x382x8x8 bf16 forward, 8 members x 72 channels 9.2, 13 x 128 10.6).
         const bool aligned = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 == 0;
@@ -1063,10 +1064,15 @@ hipError_t launch_nhwc_fused(const Dims& d, const IndexParams& ip, bool backward
     // Rows that begin on no 64 bytes are slower the second time, too: 91x92x56x56 f32, a patch, 53 rows, backward 76.5 against 100.6
     // full BN forward, 56 rows, 57.8 against 73.9 (where streaming has to take narrower accesses for want of whole vectors, this is
     // still the faster).
+    // (Since those are stored without the hint: 850 layers of 4 to 190 MB, streaming over this kernel, forward / backward.  Whole vectors, part of the rows, f32
+    // 1.22 / 1.11 at 21 to 36 rows, 1.05 / 0.97 at 41 to 50, 0.89 / 0.91 at 51 to 64, 0.79 / 0.88 to 82: the line holds; bf16 1.14 / 1.06 at 21 to 36, but 1.36 / 1.08
+    // at 41 to 50, six layers, which stay with streaming.)
     const bool split_lines = size_t(d.C) * (d.dtype == BNS_F32 ? 4 : 2) % 64 != 0 && d.C % V == 0;
     // Where streaming takes single elements the line lies further out: Eq. 4 backward 112x407x25x25 f32, 58 rows, 177.2 against 115.1, 19x659x53x53 bf16, 70 rows,
     // 157.5 against 82.3; backward with idle lanes 32x393x40x40 f32 116.2 against 76.8, 16x431x1xW bf16, 66 to 81 rows, twice the time; bf16 rows of
-    // whole vectors 1.02 (66 rows) to 1.05 (81) the other way, 132 and 660 channels (64-bit accesses) forward, a patch, 44 to 60 rows, 1.1.
+    // whole vectors 1.02 (66 rows) to 1.05 (81) the other way, 132 and 660 channels (64-bit accesses) forward, a patch, 44 to 60 rows, 1.1.  (Without the hint this kernel is ahead in f32 up to the last rows timed: streaming over
+    // it 1.6 at 50 to 64 rows, 1.46 to 82, 1.34 to 130 forward, 1.5 to 1.6 backward, Eq. 4 forward 1.3 to 1.65 at 36 to 82; the lines below, drawn with it, still give
+    // such layers to streaming forward: 33x209x67x67 f32 109.5 against 74.4 us.)
     const bool single = d.C % 4 != 0;
     const int limit = !backward && everything && !mix                         ? (idle && !single ? regs + regs * 2 / 5 : split_lines ? regs : 256)
                       : (idle && !single) || split_lines                      ? regs

@@ -75,7 +75,12 @@ constexpr TileExchange tile_exchange(int T, int threads) {
 // beyond, one layer below 0.97 (us: 23x150x104x104 bf16 68.8 / 37.9, 6x252x109x106 f32 49.8 / 33.5, 50x150x19x19 f32 11.5 / 10.5).  One tile
 // that holds whole rows 0.88 (43x16x103x102 bf16) to 0.97, rows on 64 bytes 0.90 (8 to 30 MB).  Backward 1.03 to 1.06 up to 30 MB where vectors,
 // too, begin anywhere (39 layers, none below 0.98; 50x150x19x19 f32 13.7 / 12.6, 26x293x32x30 f32 25.9 / 22.4), 0.98 where they begin on 16
-// bytes; beyond 30 MB either way (71x162x45x45 bf16 52.7 / 41.9, 20x478x52x52 f32, a patch, 84 / 94).
+// bytes; beyond 30 MB either way (71x162x45x45 bf16 52.7 / 41.9, 20x478x52x52 f32, a patch, 84 / 94).  Forward, what is written then lies in the
+// memory-side cache in the place of what was read: backward on its own is as fast as before (600 layers, 1.00 beyond 30 MB), right after
+// forward on the same tensors it finds less of x there (f32 of 70 MB and more: the two together 1.00, at worst 0.94, 3x1023x90x90 152 / 162).  Tiles are
+// 128 to 256 bytes wide, most of their lines are shared, and a hint for the others would change little.
+// Not for Eq. 4, whose kernels have no such flavour: 250 layers, forward 1.05 (none below 0.97), backward 1.00 (22 below), which another
+// 36 kernels (1.4 MB) were not spent on.
 constexpr bool shares_lines(int tiles, long pitch, long bytes, bool backward) {
     return tiles > 1 && (backward ? pitch % 16 != 0 && bytes < 30000000 : pitch % 64 != 0);
 }
