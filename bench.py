@@ -18,6 +18,7 @@ counters), and `roofline` prices the dominant kernel by the bytes that kernel ha
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
 import sys
@@ -43,6 +44,17 @@ def load_traffic():
             return json.load(f)
     except (OSError, ValueError):
         return {"bytes_per_launch": {}, "measured_at_commit": None}
+
+
+def kernel_sources_digest():
+    """SHA-256 of the library's sources without comments and blank space: the traffic table carries that of the kernels it was measured with."""
+    h = hashlib.sha256()
+    csrc = os.path.join(ROOT, "paper_1810_10962_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        if name.startswith("bns_") and name.endswith((".hip", ".hpp")):
+            with open(os.path.join(csrc, name)) as f:
+                h.update((name + "".join("".join(line.split("//")[0].split()) for line in f)).encode())
+    return h.hexdigest()
 
 
 def default_path_kernels(wl, dirs, bns):
@@ -335,7 +347,7 @@ def main():
                     frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                     achieved_by_counters=round(traffic / dom_s / 1e9, 1) if traffic else None,
                     frac_by_counters=round(traffic / dom_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                    stale=traffic is None, counters_measured_at_commit=traffic_table.get("measured_at_commit_of", {}).get(
+                    stale=traffic is None or traffic_table.get("kernel_sources_sha256") != kernel_sources_digest(), counters_measured_at_commit=traffic_table.get("measured_at_commit_of", {}).get(
                         wl.name, traffic_table.get("measured_at_commit")),
                     algorithmic_bytes_per_launch=int(dom_bytes), algorithmic_bytes_note=dom_note,
                     effective_two_pass={"bytes_per_launch": int(two_pass_bytes),

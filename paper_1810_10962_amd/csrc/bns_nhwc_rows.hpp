@@ -72,7 +72,8 @@ constexpr TileExchange tile_exchange(int T, int threads) {
 
 // Whether stores leave the non-temporal hint out: lines that two tiles share are then put together in the L2.  With the hint against without,
 // forward, 90 drawn layers of several tiles whose rows begin on no 64 bytes, f32 / bf16: 1.05 / 1.02 from 2 to 8 MB, 1.10 / 1.09 to 30 MB, 1.37 / 1.53
-// beyond, one layer below 0.97 (us: 23x150x104x104 bf16 68.8 / 37.9, 6x252x109x106 f32 49.8 / 33.5, 50x150x19x19 f32 11.5 / 10.5).  One tile
+// beyond, one layer below 0.97 (us: 23x150x104x104 bf16 68.8 / 37.9, 6x252x109x106 f32 49.8 / 33.5, 50x150x19x19 f32 11.5 / 10.5, whose written
+// bytes by counters went from 1.28 times the least to 1.03, backward from 1.33).  One tile
 // that holds whole rows 0.88 (43x16x103x102 bf16) to 0.97, rows on 64 bytes 0.90 (8 to 30 MB).  Backward 1.03 to 1.06 up to 30 MB where vectors,
 // too, begin anywhere (39 layers, none below 0.98; 50x150x19x19 f32 13.7 / 12.6, 26x293x32x30 f32 25.9 / 22.4), 0.98 where they begin on 16
 // bytes; beyond 30 MB either way (71x162x45x45 bf16 52.7 / 41.9, 20x478x52x52 f32, a patch, 84 / 94).  Forward, what is written then lies in the
